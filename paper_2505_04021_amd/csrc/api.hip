@@ -1637,10 +1637,10 @@ int prefill_attention(int model, int batch, const void *q, const int32_t *q_lens
     if (batch == 0) return PKV_OK;
     if (!q || !q_lens || !ctx_lens || !out) return PKV_E_ARG;
     if (((uintptr_t)q & 15) || ((uintptr_t)out & 15)) return PKV_E_ARG;
-    // A wave takes as many consecutive query tokens as fit the 16 MFMA columns with the g heads of a
-    // kv head; a work-group takes PKV_PREFILL_TILES such tiles and shares the K and V it fetches.
-    const int tile = 16 / m->g > 0 ? 16 / m->g : 1;
-    const int group = PKV_PREFILL_TILES * tile;
+    // A wave takes as many consecutive query tokens as fit its 32 MFMA columns with the g heads of a
+    // kv head; the waves of a work-group take consecutive tiles and share the K and V they fetch.
+    const int tile = PKV_PREFILL_COLS / PKV_PREFILL_WAVES / m->g;
+    const int group = PKV_PREFILL_WAVES * tile;
     std::vector<int4> rows;
     int64_t first = 0, n_groups = 0;
     for (int s = 0; s < batch; ++s) {
@@ -1694,7 +1694,7 @@ int prefill_attention(int model, int batch, const void *q, const int32_t *q_lens
     d.cols = tile * m->g;
     d.scale_log2 = (float)(1.4426950408889634 / sqrt((double)m->D));
     if (any_split) {
-        const size_t need = rows.size() * m->Hkv * (PKV_PREFILL_TILES * 16) * (size_t)(m->D + 4);
+        const size_t need = rows.size() * m->Hkv * PKV_PREFILL_COLS * (size_t)(m->D + 4);
         if (need > m->pf_ws_floats) {
             HIP_TRY(hipStreamSynchronize(g_stream));
             (void)hipFree(m->pf_ws);

@@ -34,49 +34,11 @@
 //   e4m3 K: 16-byte unit (j2, G, t)  = K[t][8(8j2+G)+0..7] , K[t][8(8j2+4+G)+0..7]
 //   e4m3 V: 16-byte unit (jq, G, dl) = V[4G..4G+3][64jq+16u+dl], u = 0..3
 //   e4m3 blocks start with a 128-byte header: fp32 sK[Hkv], fp32 sV[Hkv].
-#include "pkv_internal.h"
+#include "mfma_util.h"
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ u32x4 mk4(uint32_t a, uint32_t b, uint32_t c, uint32_t d) { return u32x4{a, b, c, d}; }
-__device__ __forceinline__ u32x2 mk2(uint32_t a, uint32_t b) { return u32x2{a, b}; }
-
-constexpr int T = 16;   // tokens per block the kernels are built for
-
-// Wave-uniform reads of data this kernel never writes (block tables, context
-// lengths, the work plan, e4m3 scales): going through the constant address space
-// makes them scalar loads, which are counted apart from the vector loads of K and V
-// and so never force the KV pipeline to drain.
-#define PKV_CONST(T_, p_) ((const T_ __attribute__((address_space(4))) *)(p_))
-
-__device__ __forceinline__ uint32_t pack_bf16_trunc(float lo, float hi) {
-    // two fp32 -> packed bf16 by taking the upper halves (exact for values that
-    // already fit bf16)
-    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
-}
-
-__device__ __forceinline__ uint32_t pack_bf16_rne(float lo, float hi) {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    f32x2 v = {lo, hi};
-    bf16x2 b = __builtin_convertvector(v, bf16x2);
-    return *reinterpret_cast<uint32_t *>(&b);
-}
-
-// 4 e4m3 codes in one word -> 4 bf16 in two words (exact): gfx950's packed conversion with a
-// scale of one, two codes per instruction (checked against the fp32 route on all 2^16 code pairs)
-__device__ __forceinline__ u32x2 fp8x4_to_bf16x4(uint32_t w) {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    bf16x2 a = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, false);
-    bf16x2 b = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, true);
-    return mk2(*reinterpret_cast<uint32_t *>(&a), *reinterpret_cast<uint32_t *>(&b));
-}
+constexpr int T = PKV_T;
 
 template <int D, int DT>
 struct Tile {
@@ -221,17 +183,6 @@ __device__ __forceinline__ u32x2 v_half(const PageRegs<D, DT> &r, int jt) {
     return fp8x4_to_bf16x4(w);
 }
 
-// Probabilities reach the matrix unit as bf16: as hi + lo (16 significant bits, two products)
-// wherever the second product is free or the cache is bf16.  The exception is prefill (bound by
-// arithmetic, not by memory) on an e4m3 cache: its values carry 4 significant bits, one bf16
-// probability (8 bits, error 2^-9) is already 32 times finer than the V it multiplies, and the
-// second product is left out (measured error then ~4e-3 of a row's largest output against a bar of
-// 2e-2; 16 % less time).
-template <int DT, bool PREFILL>
-__device__ __forceinline__ constexpr bool p_has_lo() {
-    return DT == PKV_BF16 || !PREFILL;
-}
-
 // bf16 hi + lo of four probabilities: 16 significant bits reach the matrix unit
 __device__ __forceinline__ void split_p(const float *p, u32x2 &hi, u32x2 &lo) {
     const uint32_t h01 = pack_bf16_rne(p[0], p[1]), h23 = pack_bf16_rne(p[2], p[3]);
@@ -241,32 +192,15 @@ __device__ __forceinline__ void split_p(const float *p, u32x2 &hi, u32x2 &lo) {
     lo = mk2(pack_bf16_rne(l0, l1), pack_bf16_rne(l2, l3));
 }
 
-// Largest of three in one instruction.  Written out because the compiler puts a quieting instruction in
-// front of every matrix-unit result that it takes a maximum of.
-__device__ __forceinline__ float max3(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
-// How far (in powers of two) a column's maximum may run ahead of the reference point of its
-// exponentials before a softmax step moves that point and rescales the column's sums.  The reference
-// point need not be the true maximum, only near it: results are the same up to rounding (probabilities
-// up to 2^kRescaleSlack instead of 1, numerator and denominator alike), and the 32 multiplications of a
-// rescale become rare.
-constexpr float kRescaleSlack = 8.f;
-
 // One online-softmax step over the 32 tokens of a page pair.  valid_a is 1..16,
-// valid_b 0..16 (0: the pair has no second page; its registers hold zeros).
-// TAIL: 0 = whether the pair needs masks is decided at run time inside (one code path with
-// selects: right for the memory-bound decode kernel), 1 = the caller knows it needs none,
-// 2 = the caller knows it needs them (the prefill kernel branches, its bound is vector ALU work).
-template <int D, int DT, bool CAUSAL, int TAIL = 0>
+// valid_b 0..16 (0: the pair has no second page; its registers hold zeros).  Whether the
+// pair needs masks is decided at run time inside (one code path with selects: the kernel is
+// bound by memory).
+template <int D, int DT>
 __device__ __forceinline__ void process_pair(State<D, DT> &st, const PairRegs<D, DT> &r, const bf16x8 *qf,
-                                             float scale_log2, int valid_a, int valid_b, int G, int lim_a = 0,
-                                             bool causal = false) {
+                                             float scale_log2, int valid_a, int valid_b, int G) {
     using TL = Tile<D, DT>;
-    const bool tail = TAIL == 1 ? false : (TAIL == 2 ? true : (valid_a < T || valid_b < T || (CAUSAL && causal)));
+    const bool tail = valid_a < T || valid_b < T;
     f32x4 sa = qk_page<D, DT>(r.a, qf);
     f32x4 sb = qk_page<D, DT>(r.b, qf);
     const float sca = DT == PKV_E4M3 ? scale_log2 * r.a.sk : scale_log2;
@@ -277,10 +211,8 @@ __device__ __forceinline__ void process_pair(State<D, DT> &st, const PairRegs<D,
         s[i] = sa[i] * sca;
         s[4 + i] = sb[i] * scb;
         if (tail) {                                        // select, so a NaN logit of a dead token cannot leak
-            const int la = CAUSAL && lim_a < valid_a ? lim_a : valid_a;
-            const int lb = CAUSAL && lim_a - T < valid_b ? lim_a - T : valid_b;
-            if (4 * G + i >= la) s[i] = -INFINITY;
-            if (4 * G + i >= lb) s[4 + i] = -INFINITY;
+            if (4 * G + i >= valid_a) s[i] = -INFINITY;
+            if (4 * G + i >= valid_b) s[4 + i] = -INFINITY;
         }
     }
     float mx = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
@@ -289,18 +221,15 @@ __device__ __forceinline__ void process_pair(State<D, DT> &st, const PairRegs<D,
     // wave-uniform: the reference point of the exponentials moves, and the sums are rescaled, only when some
     // column's maximum has run ahead of it by more than kRescaleSlack (probabilities stay below 2^kRescaleSlack)
     if (__any(m_new > st.m + kRescaleSlack)) {
-        // a column that has seen no token yet (prefill tiles only) has m = -inf on both sides
-        const float alpha = CAUSAL && TAIL != 1 && m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(st.m - m_new);
+        const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
         st.l *= alpha;
 #pragma unroll
         for (int jt = 0; jt < TL::NV; ++jt) st.acc[jt] *= alpha;
         st.m = m_new;
     }
     float p[8];
-    // (a pair without masks leaves every column with a finite maximum)
-    const float m_ref = CAUSAL && TAIL != 1 && st.m == -INFINITY ? 0.f : st.m;     // then every s is -inf and every p is 0
 #pragma unroll
-    for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - m_ref);
+    for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - st.m);
     st.l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
     if (DT == PKV_E4M3) {
 #pragma unroll
@@ -331,119 +260,7 @@ __device__ __forceinline__ void process_pair(State<D, DT> &st, const PairRegs<D,
         u32x4 vv = tail ? mk4(va.x & ma01, va.y & ma23, vb.x & mb01, vb.y & mb23) : mk4(va.x, va.y, vb.x, vb.y);
         const bf16x8 av = *reinterpret_cast<bf16x8 *>(&vv);
         st.acc[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, phv, st.acc[jt], 0, 0, 0);
-        if (p_has_lo<DT, CAUSAL>()) st.acc[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, plv, st.acc[jt], 0, 0, 0);
-    }
-}
-
-// The two halves of process_pair for a pair that needs no masks, for callers that work on
-// several tiles of queries at once (prefill): with the halves of all tiles in one straight
-// line of code the scheduler can overlap the matrix instructions of one tile with the
-// softmax arithmetic of another.
-template <int D, int DT>
-__device__ __forceinline__ void pair_qk(const PairRegs<D, DT> &r, const bf16x8 *qf, f32x4 &sa, f32x4 &sb) {
-    sa = qk_page<D, DT>(r.a, qf);
-    sb = qk_page<D, DT>(r.b, qf);
-}
-
-// The same for two tiles of queries at once (bf16 caches): four independent accumulation chains (two
-// pages x two tiles), written round-robin so that no matrix instruction waits for the one before it.
-template <int D>
-__device__ __forceinline__ void pair_qk2(const PairRegs<D, PKV_BF16> &r, const bf16x8 *q0, const bf16x8 *q1, f32x4 *sa, f32x4 *sb) {
-    using TL = Tile<D, PKV_BF16>;
-    f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, b0 = a0, a1 = a0, b1 = a0;
-#pragma unroll
-    for (int j = 0; j < TL::NK; ++j) {
-        u32x4 ka = r.a.k[j], kb = r.b.k[j];
-        const bf16x8 kav = *reinterpret_cast<bf16x8 *>(&ka), kbv = *reinterpret_cast<bf16x8 *>(&kb);
-        a0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kav, q0[j], a0, 0, 0, 0);
-        b0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kbv, q0[j], b0, 0, 0, 0);
-        a1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kav, q1[j], a1, 0, 0, 0);
-        b1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kbv, q1[j], b1, 0, 0, 0);
-    }
-    sa[0] = a0; sb[0] = b0; sa[1] = a1; sb[1] = b1;
-}
-
-template <int D, int DT>
-__device__ __forceinline__ void pair_softmax(State<D, DT> &st, const PairRegs<D, DT> &r, f32x4 sa, f32x4 sb, float scale_log2,
-                                             bf16x8 &phv, bf16x8 &plv) {
-    using TL = Tile<D, DT>;
-    const float sca = DT == PKV_E4M3 ? scale_log2 * r.a.sk : scale_log2;
-    const float scb = DT == PKV_E4M3 ? scale_log2 * r.b.sk : scale_log2;
-    float s[8];
-    float mx;
-    if (DT == PKV_E4M3) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            s[i] = sa[i] * sca;
-            s[4 + i] = sb[i] * scb;
-        }
-        mx = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
-    } else {
-        // one positive scale for all: the maximum is taken on the raw scores and scaled once, and the
-        // scale of each score is folded into the argument of its exponential below
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            s[i] = sa[i];
-            s[4 + i] = sb[i];
-        }
-        mx = scale_log2 * max3(max3(s[0], s[1], s[2]), max3(s[3], s[4], s[5]), max3(s[6], s[7], s[0]));
-    }
-    // The reference point of the exponentials need not be the true maximum, only near it: it moves (and
-    // the sums are rescaled) when some column's maximum has grown by more than kRescaleSlack, so that
-    // probabilities stay below 2^kRescaleSlack.  Wave-uniform.
-    mx = rows_max(mx);
-    const float m_new = fmaxf(st.m, mx);
-    if (__any(m_new > st.m + kRescaleSlack)) {
-        const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
-        st.l *= alpha;
-#pragma unroll
-        for (int jt = 0; jt < TL::NV; ++jt) st.acc[jt] *= alpha;
-        st.m = m_new;
-    }
-    float p[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-        p[i] = __builtin_amdgcn_exp2f(DT == PKV_E4M3 ? s[i] - st.m : __builtin_fmaf(s[i], scale_log2, -st.m));
-    st.l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-    if (DT == PKV_E4M3) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            p[i] *= r.a.sv;
-            p[4 + i] *= r.b.sv;
-        }
-    }
-    u32x2 ha, la, hb, lb;
-    split_p(p, ha, la);
-    split_p(p + 4, hb, lb);
-    u32x4 ph = mk4(ha.x, ha.y, hb.x, hb.y), pl = mk4(la.x, la.y, lb.x, lb.y);
-    phv = *reinterpret_cast<bf16x8 *>(&ph);
-    plv = *reinterpret_cast<bf16x8 *>(&pl);
-}
-
-template <int D, int DT>
-__device__ __forceinline__ void pair_accumulate(State<D, DT> &st, const PairRegs<D, DT> &r, bf16x8 phv, bf16x8 plv) {
-    using TL = Tile<D, DT>;
-#pragma unroll
-    for (int jt = 0; jt < TL::NV; ++jt) {
-        const u32x2 va = v_half<D, DT>(r.a, jt), vb = v_half<D, DT>(r.b, jt);
-        u32x4 vv = mk4(va.x, va.y, vb.x, vb.y);
-        const bf16x8 av = *reinterpret_cast<bf16x8 *>(&vv);
-        st.acc[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, phv, st.acc[jt], 0, 0, 0);
-        if (p_has_lo<DT, true>()) st.acc[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, plv, st.acc[jt], 0, 0, 0);
-    }
-}
-
-// The same with the operands of the accumulation already assembled (bf16 tiles read from LDS in
-// halves: vop[jt] = the V half of page a and the V half of page b for output tile jt).
-template <int D, int DT>
-__device__ __forceinline__ void pair_accumulate_ops(State<D, DT> &st, const u32x4 *vop, bf16x8 phv, bf16x8 plv) {
-    using TL = Tile<D, DT>;
-#pragma unroll
-    for (int jt = 0; jt < TL::NV; ++jt) {
-        u32x4 vv = vop[jt];
-        const bf16x8 av = *reinterpret_cast<bf16x8 *>(&vv);
-        st.acc[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, phv, st.acc[jt], 0, 0, 0);
-        if (p_has_lo<DT, true>()) st.acc[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, plv, st.acc[jt], 0, 0, 0);
+        st.acc[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, plv, st.acc[jt], 0, 0, 0);
     }
 }
 
@@ -924,7 +741,7 @@ __device__ __forceinline__ void attn_wave(const AttnDesc &d, const AttnTune &w, 
                     const int pa = cur.pb + i;                                  // absolute page of the pair's first half
                     const int va = pa == cur.n_pages - 1 ? last_valid : T;
                     const int vb = i + 1 < n_live ? (pa + 1 == cur.n_pages - 1 ? last_valid : T) : 0;
-                    process_pair<D, DT, false>(st, ring[r], qf, d.scale_log2, va, vb, G);
+                    process_pair<D, DT>(st, ring[r], qf, d.scale_log2, va, vb, G);
                     prio_done += 2;
                 }
             }
@@ -1064,403 +881,6 @@ __global__ void k_clear_words(uint32_t *p, size_t n) {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
 }
 
-// ---------------------------------------------------------------------------------
-// Chunked prefill: causal attention of a group of consecutive query tokens against the
-// paged cache (paper Sec. 5.2).  One work-group of four waves per (group, kv head).  Every
-// wave owns two tiles of query tokens (a tile = 16 MFMA columns = tokens x the g heads of
-// the kv head); the K and V tiles of a page pair are fetched once per work-group, one tile
-// per wave, and passed through LDS in the very byte order they have in the block, so each
-// wave reads its MFMA operands back with conflict-free LDS loads and uses each for both of
-// its tiles.  Eight tiles share each byte fetched, against one in the decode kernel.
-// `vmap` lists the groups like the rows of a decode launch, with up to 8 tiles of tokens
-// each.  A group of few tokens in front of a long context may come as several work-groups,
-// each with a part of the context; those leave partials that k_prefill_merge joins.
-// NL x 1 KiB from the pool straight into LDS: lane l's 16 bytes at src + 1024 j land at
-// dst + 1024 j + 16 l (the hardware adds the lane's offset to the LDS base held in M0).
-// Written as assembly so that the compiler neither drains all loads in flight before the
-// next one that targets the same LDS array, nor before LDS reads of another buffer; the
-// waits are counted by hand where the data is needed (s_waitcnt vmcnt).
-template <int NL>
-__device__ __forceinline__ void lds_fill(const uint8_t *src, uint8_t *dst) {
-    // wave-uniform by construction (the wave's tile of the buffer); tell the compiler so
-    const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t *)dst);
-    if (NL == 1)
-        asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(base) : "memory", "m0");
-    else if (NL == 2)
-        asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %0, off offset:1024" ::"v"(src),
-                     "s"(base)
-                     : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off\n\tglobal_load_lds_dwordx4 %0, off offset:1024\n\t"
-                     "global_load_lds_dwordx4 %0, off offset:2048\n\tglobal_load_lds_dwordx4 %0, off offset:3072" ::"v"(src),
-                     "s"(base)
-                     : "memory", "m0");
-    static_assert(NL == 1 || NL == 2 || NL == 4, "tile sizes of 1, 2 or 4 KiB");
-}
-
-constexpr int PF_WAVES = 4;
-constexpr int PF_TILES = 2;     // tiles of query tokens per wave: each operand read from LDS serves both
-constexpr int PF_BUFS = 4;      // page pairs resident in LDS: one in use, three travelling
-static_assert(PF_WAVES * PF_TILES == PKV_PREFILL_TILES, "host and kernel must agree on the group size");
-
-template <int D, int DT>
-__device__ __forceinline__ void prefill_group(const AttnDesc &d, uint8_t *lds0, uint8_t *lds1, uint8_t *lds2, uint8_t *lds3) {
-    using TL = Tile<D, DT>;
-    constexpr int NT = PF_TILES;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int G = lane >> 4, n = lane & 15;
-    const int group = blockIdx.x / d.Hkv, kvh = blockIdx.x - group * d.Hkv;
-    RowInfo gi = row_info_uniform(d, group);
-    // a group of few query tokens in front of a long context comes as several work-groups, each with a
-    // part of the context; they leave partial results that k_prefill_merge joins
-    const int split = (gi.ntok >> 8) & 0xfff, n_split = gi.ntok >> 20;
-    gi.ntok &= 0xff;
-    const int tile_tok = d.cols / d.g;                      // query tokens per tile
-    const Column col = column_of(d, n);
-    // tokens the group's last query sees, never beyond what the row holds
-    int L = PKV_CONST(int32_t, d.ctx_lens)[gi.seq] - gi.back;
-    const int cap = PKV_CONST(int32_t, d.row_len)[gi.seq] * T;
-    L = L < 0 ? 0 : (L > cap ? cap : L);
-    L = __builtin_amdgcn_readfirstlane(L);
-    const int n_pages = (L + T - 1) / T, n_pairs = (n_pages + 1) >> 1;
-    const int last_valid = L - (n_pages - 1) * T;
-    const int causal_from = L - (gi.ntok - 1);              // first token some column of the group may not see
-    // the pairs this work-group walks
-    const int per_split = n_split > 1 ? (n_pairs + n_split - 1) / n_split : n_pairs;
-    const int p_begin = n_split > 1 ? (split * per_split < n_pairs ? split * per_split : n_pairs) : 0;
-    const int p_end = p_begin + per_split < n_pairs ? p_begin + per_split : n_pairs;
-
-    // this wave's tiles of the group: tile u covers the group's tokens [(w * NT + u) * tile_tok, ...)
-    RowInfo ri[NT];
-    bool col_live[NT];
-    int col_lim[NT], tile_lim[NT];
-    bf16x8 qf[NT][TL::NK];
-    State<D, DT> st[NT];
-#pragma unroll
-    for (int u = 0; u < NT; ++u) {
-        const int t0 = (w * NT + u) * tile_tok;
-        ri[u].seq = gi.seq;
-        ri[u].q0 = gi.q0 + t0;
-        ri[u].back = 0;
-        ri[u].ntok = gi.ntok - t0;
-        ri[u].ntok = ri[u].ntok < 0 ? 0 : (ri[u].ntok > tile_tok ? tile_tok : ri[u].ntok);
-        col_live[u] = n < d.cols && col.tok < ri[u].ntok;
-        // the group's last token sees L; token i of the group sees L - (gi.ntok - 1 - i)
-        col_lim[u] = col_live[u] ? L - (gi.ntok - 1 - (t0 + col.tok)) : L;
-        tile_lim[u] = L - (gi.ntok - 1 - (t0 + ri[u].ntok - 1));      // what the tile's last token sees
-        load_q<D>(qf[u], d, ri[u], kvh, lane, col);
-#pragma unroll
-        for (int jt = 0; jt < TL::NV; ++jt) st[u].acc[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        st[u].m = -INFINITY;
-        st[u].l = 0.f;
-    }
-
-    const int32_t *row = d.table + (size_t)gi.seq * d.row_stride;
-    uint32_t bad = 0;
-
-    // A pair travels from the pool straight into LDS (no staging registers), NBUF - 1 pairs ahead
-    // of the one being worked on.  wave 0: K of page a, wave 1: V of page a, wave 2: K of page b,
-    // wave 3: V of page b.  Every request issues exactly NL loads per lane (a page past the end is
-    // replaced by the last one, and masked later), so the number of loads in flight tells which
-    // pairs have landed.
-    // The block id of a request is read through the scalar cache one request early (next_id), so
-    // that the dependent chain table -> address -> load never waits inside a step.
-    auto table_id = [&](int pair) {
-        int page = 2 * pair + (w >> 1);
-        page = page < n_pages ? page : n_pages - 1;
-        page = page > 0 ? page : 0;
-        const int last = d.row_stride - 1;
-        // wave-uniform, and said to be: the id then comes through the scalar cache.  As a vector load
-        // it would share the counter of the requests in flight, and waiting for it would drain them all.
-        page = __builtin_amdgcn_readfirstlane(page < last ? page : last);
-        return (uint32_t)PKV_CONST(int32_t, row)[page];
-    };
-    uint32_t next_id = table_id(p_begin);
-    auto fetch = [&](int pair, uint8_t *buf) {
-        uint32_t id = (uint32_t)__builtin_amdgcn_readfirstlane((int)next_id);
-        next_id = table_id(pair + 1);
-        const bool ok = id < d.max_block_id;
-        if (!ok) {
-            bad |= 1u;
-            id = 0;
-        }
-        const uint32_t f = fastdiv_div(id, d.slots_div);
-        const uint32_t sl = id - f * d.slots_div.d;
-        const uint8_t *blk = d.pool_base + (uint64_t)f * d.frame_bytes + (uint64_t)sl * d.block_bytes +
-                             (DT == PKV_E4M3 ? PKV_FP8_HEADER : 0);
-        // an id outside the pool is never dereferenced: the same number of loads goes to a zeroed spare tile
-        const uint8_t *src = (ok ? blk + ((size_t)kvh * 2 + (w & 1)) * TL::TILE_BYTES : reinterpret_cast<const uint8_t *>(d.safe)) + lane * 16;
-        lds_fill<TL::NL>(src, buf + (size_t)w * TL::TILE_BYTES);
-    };
-    // wait until the loads of all but the `ahead` most recent requests have landed
-    auto landed = [&](int ahead) {
-        if (ahead >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * TL::NL) : "memory");
-        else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(TL::NL) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    };
-    // Operand registers of the pair being worked on.  The K tiles are read from LDS one step
-    // ahead, right after the scores of the current pair have been issued (the registers are free
-    // from then on), so that a step starts its matrix work without waiting for LDS; the V tiles
-    // are read at the same point and arrive while the softmax arithmetic runs.
-    PairRegs<D, DT> r;
-    r.a.sk = r.a.sv = r.b.sk = r.b.sv = 1.f;
-    // wave-uniform: does any token of pair p lie before what tile u sees
-    auto sees = [&](int u, int p) { return ri[u].ntok > 0 && 2 * p * T < tile_lim[u]; };
-    auto any_sees = [&](int p) {
-        bool a = false;
-#pragma unroll
-        for (int u = 0; u < NT; ++u) a |= sees(u, p);
-        return a && p < p_end;
-    };
-    auto read_k = [&](const uint8_t *buf) {
-        const uint8_t *src = buf + lane * 16;
-#pragma unroll
-        for (int j = 0; j < TL::NL; ++j) {
-            r.a.k[j] = *reinterpret_cast<const u32x4 *>(src + 0 * TL::TILE_BYTES + j * 1024);
-            r.b.k[j] = *reinterpret_cast<const u32x4 *>(src + 2 * TL::TILE_BYTES + j * 1024);
-        }
-    };
-    // bf16: the two pages' halves of an accumulation operand are read side by side into the four
-    // registers of that operand (8-byte reads), so that no register moves are needed to join them
-    u32x4 vop[DT == PKV_BF16 ? TL::NV : 1];
-    // bf16: one LDS instruction per operand (ds_read2st64_b64: two 8-byte reads, 512-byte strides, into
-    // four consecutive registers).  Left to itself the compiler fetches 16 bytes at a time and shuffles
-    // the halves into place with 32 register moves per step.  The reads are issued here and waited for
-    // in read_v_wait (the compiler does not count them; LDS returns in order, so its own waits stay safe).
-    auto read_v = [&](const uint8_t *buf) {
-        if constexpr (DT == PKV_BF16) {
-            const uint32_t at = (uint32_t)(size_t)(__attribute__((address_space(3))) const uint8_t *)buf + (uint32_t)lane * 16u;
-#pragma unroll
-            for (int jt = 0; jt < TL::NV; ++jt) {
-                constexpr int T512 = TL::TILE_BYTES / 512;
-                const int o0 = T512 + 2 * (jt >> 1), o1 = 3 * T512 + 2 * (jt >> 1);
-                const uint32_t a = at + (jt & 1) * 8u;
-                asm volatile("ds_read2st64_b64 %0, %1 offset0:%2 offset1:%3" : "=v"(vop[jt]) : "v"(a), "n"(o0), "n"(o1) : "memory");
-            }
-        } else {
-            const uint8_t *src = buf + lane * 16;
-#pragma unroll
-            for (int j = 0; j < TL::NL; ++j) {
-                r.a.v[j] = *reinterpret_cast<const u32x4 *>(src + 1 * TL::TILE_BYTES + j * 1024);
-                r.b.v[j] = *reinterpret_cast<const u32x4 *>(src + 3 * TL::TILE_BYTES + j * 1024);
-            }
-        }
-    };
-    auto read_v_wait = [&]() {
-        if constexpr (DT == PKV_BF16) {
-            static_assert(DT != PKV_BF16 || TL::NV == 8 || TL::NV == 4, "operand tiles of head dims 128 and 64");
-            if constexpr (TL::NV == 8)
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(vop[0]), "+v"(vop[1]), "+v"(vop[2]), "+v"(vop[3]), "+v"(vop[TL::NV - 4]),
-                             "+v"(vop[TL::NV - 3]), "+v"(vop[TL::NV - 2]), "+v"(vop[TL::NV - 1])::"memory");
-            else
-                asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(vop[0]), "+v"(vop[1]), "+v"(vop[2]), "+v"(vop[3])::"memory");
-        }
-    };
-    // the per-page form of the V tiles that the masked path works on
-    auto v_per_page = [&]() {
-        if (DT == PKV_BF16) {
-#pragma unroll
-            for (int j = 0; j < TL::NL; ++j) {
-                const u32x4 e = vop[DT == PKV_BF16 ? 2 * j : 0], o = vop[DT == PKV_BF16 ? 2 * j + 1 : 0];
-                r.a.v[j] = mk4(e.x, e.y, o.x, o.y);
-                r.b.v[j] = mk4(e.z, e.w, o.z, o.w);
-            }
-        }
-    };
-    // step p works on pair p (K already in registers, V in buf), reads the K tiles of pair p + 1
-    // from buf_next, and sends the pair NBUF - 1 ahead into the buffer that pair p - 1 occupied
-    auto step = [&](int p, const uint8_t *buf, const uint8_t *buf_next, uint8_t *refill) {
-        const int pa = 2 * p;
-        bool mine[NT];
-        bool any_mine = false, all_mine = true;
-#pragma unroll
-        for (int u = 0; u < NT; ++u) {
-            mine[u] = sees(u, p);
-            any_mine |= mine[u];
-            all_mine &= mine[u];
-        }
-        const bool next_mine = any_sees(p + 1);
-        const int va = pa == n_pages - 1 ? last_valid : T;
-        const int vb = pa + 1 < n_pages ? (pa + 1 == n_pages - 1 ? last_valid : T) : 0;
-        const bool pair_tail = va < T || vb < T || (pa + 2) * T > causal_from;       // wave-uniform
-        const bool fast = all_mine && !pair_tail;
-        // The step's meeting point.  Before it, the wave's own requests for every pair up to p + 1 have
-        // landed (the one for p + 2 may still travel); behind it, every wave's have, and every wave has
-        // finished with pair p - 1: pair p + 1's K tiles may be read, and the buffer of pair p - 1 takes
-        // the pair NBUF - 1 ahead.  A step needs neither for its score matrices (their K operands were
-        // read a step ago), so on the common path the waves meet behind those: a wave that is ahead works
-        // instead of waiting, and the requests, which would otherwise queue up behind each other where all
-        // waves of a CU arrive together, are issued while the matrix instructions run.
-        auto meet = [&]() {
-            const int newest = p + PF_BUFS - 2 < p_end - 1 ? p + PF_BUFS - 2 : p_end - 1;
-            landed(newest - (p + 1));
-            __builtin_amdgcn_s_barrier();
-        };
-        if (!fast) meet();
-        if (!fast && p + PF_BUFS - 1 < p_end) fetch(p + PF_BUFS - 1, refill);
-        if (DT == PKV_E4M3 && any_mine) {
-            const int last = d.row_stride - 1;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int page = pa + h;
-                uint32_t id = (uint32_t)__builtin_amdgcn_readfirstlane(PKV_CONST(int32_t, row)[page < last ? page : last]);
-                // past the end of the context, or an id outside the pool: no header is read
-                const bool live = page < n_pages && id < d.max_block_id;
-                if (!live) id = 0;
-                const uint32_t f = fastdiv_div(id, d.slots_div);
-                const uint32_t sl = id - f * d.slots_div.d;
-                const float *hdr = live ? reinterpret_cast<const float *>(d.pool_base + (uint64_t)f * d.frame_bytes +
-                                                                          (uint64_t)sl * d.block_bytes)
-                                        : reinterpret_cast<const float *>(d.safe);
-                float sk = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(PKV_CONST(float, hdr)[kvh])));
-                float sv = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(PKV_CONST(float, hdr)[d.Hkv + kvh])));
-                if (!live) sk = sv = 0.f;
-                if (h == 0) { r.a.sk = sk; r.a.sv = sv; } else { r.b.sk = sk; r.b.sv = sv; }
-            }
-        }
-        if (fast) {
-            // the common case in one straight line: the score matrices of every tile, the operand
-            // reads, the softmax of every tile, the accumulation of every tile
-            f32x4 sa[NT], sb[NT];
-            bf16x8 phv[NT], plv[NT];
-            if constexpr (DT == PKV_BF16 && NT == 2) {
-                pair_qk2<D>(r, qf[0], qf[1], sa, sb);
-            } else {
-#pragma unroll
-                for (int u = 0; u < NT; ++u) pair_qk<D, DT>(r, qf[u], sa[u], sb[u]);
-            }
-            __builtin_amdgcn_sched_barrier(0);        // the K registers are rewritten below: not before their last use is issued
-            meet();
-            read_v(buf);
-            if (next_mine) read_k(buf_next);
-            if (p + PF_BUFS - 1 < p_end) fetch(p + PF_BUFS - 1, refill);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < NT; ++u) pair_softmax<D, DT>(st[u], r, sa[u], sb[u], d.scale_log2, phv[u], plv[u]);
-            read_v_wait();
-#pragma unroll
-            for (int u = 0; u < NT; ++u) {
-                if (DT == PKV_BF16) pair_accumulate_ops<D, DT>(st[u], vop, phv[u], plv[u]);
-                else pair_accumulate<D, DT>(st[u], r, phv[u], plv[u]);
-            }
-        } else {
-            if (any_mine) {
-                read_v(buf);
-                read_v_wait();
-                v_per_page();
-            }
-#pragma unroll
-            for (int u = 0; u < NT; ++u)
-                if (mine[u]) {
-                    if (pair_tail)
-                        process_pair<D, DT, true, 2>(st[u], r, qf[u], d.scale_log2, va, vb, G, col_lim[u] - pa * T, true);
-                    else
-                        process_pair<D, DT, true, 1>(st[u], r, qf[u], d.scale_log2, va, vb, G);
-                }
-            __builtin_amdgcn_sched_barrier(0);
-            if (next_mine) read_k(buf_next);
-        }
-    };
-
-    // prologue: the first NBUF - 1 pairs are requested, the first two must have landed
-    const int my_pairs = p_end - p_begin;
-    if (my_pairs > 0) fetch(p_begin, lds0);
-    if (my_pairs > 1) fetch(p_begin + 1, lds1);
-    if (my_pairs > 2) fetch(p_begin + 2, lds2);
-    landed((my_pairs < PF_BUFS - 1 ? my_pairs : PF_BUFS - 1) - 2);
-    __builtin_amdgcn_s_barrier();
-    // The queries were fetched with ordinary loads, which the compiler waits for where they are
-    // first used.  That must not be inside the loop: the wait it would place there (it knows of
-    // no other load) would drain the pair requests in flight in every step.  Use them here.
-#pragma unroll
-    for (int u = 0; u < NT; ++u)
-#pragma unroll
-        for (int j = 0; j < TL::NK; ++j) asm volatile("" ::"v"(qf[u][j]));
-    if (any_sees(p_begin)) read_k(lds0);
-    for (int p = p_begin; p < p_end; p += PF_BUFS) {
-        step(p, lds0, lds1, lds3);
-        if (p + 1 < p_end) step(p + 1, lds1, lds2, lds0);
-        if (p + 2 < p_end) step(p + 2, lds2, lds3, lds1);
-        if (p + 3 < p_end) step(p + 3, lds3, lds0, lds2);
-    }
-
-#pragma unroll
-    for (int u = 0; u < NT; ++u) {
-        float l = st[u].l;
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
-        if (n_split > 1) {
-            // a part of the context: the unnormalised sums, the maximum and the denominator of every column
-            float *part = d.ws + (((size_t)group * d.Hkv + kvh) * (PKV_PREFILL_TILES * 16) + (w * NT + u) * 16 + n) * (D + 4);
-#pragma unroll
-            for (int jt = 0; jt < TL::NV; ++jt) *reinterpret_cast<f32x4 *>(part + 16 * jt + 4 * G) = st[u].acc[jt];
-            if (G == 0) {
-                part[D] = st[u].m;
-                part[D + 1] = l;
-            }
-        } else if (col_live[u]) {
-            float *out_row = d.out + ((size_t)(ri[u].q0 + col.tok) * d.Hq + kvh * d.g + col.head) * D;
-            const float inv = l > 0.f ? 1.0f / l : 0.f;          // no visible token: the row is defined as zero
-#pragma unroll
-            for (int jt = 0; jt < TL::NV; ++jt)
-                *reinterpret_cast<f32x4 *>(out_row + 16 * jt + 4 * G) = st[u].acc[jt] * inv;
-        }
-    }
-    if (bad && lane == 0) atomicOr(d.err, 1u);
-}
-
-// Joins the parts of a group whose context was walked by several work-groups of k_prefill: one
-// work-group per (first part of such a group, kv head, tile of 16 columns); the parts are consecutive
-// rows of d.vmap.  out = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i with M = max_i m_i, per column.
-__global__ __launch_bounds__(256) void k_prefill_merge(const AttnDesc d) {
-    const int tile = blockIdx.x % PKV_PREFILL_TILES, rk = blockIdx.x / PKV_PREFILL_TILES;
-    const int row = rk / d.Hkv, kvh = rk - row * d.Hkv;
-    const int4 e = d.vmap[row];
-    const int split = (e.w >> 8) & 0xfff, n_split = e.w >> 20, ntok = e.w & 0xff;
-    if (n_split <= 1 || split != 0) return;
-    const int D = d.D, tile_tok = d.cols / d.g, stride = D + 4;       // D sums, the maximum, the denominator, two unused (16-byte rows)
-    constexpr int NCOL = PKV_PREFILL_TILES * 16;
-    const int quads = D / 4;
-    for (int i = threadIdx.x; i < 16 * quads; i += blockDim.x) {
-        const int n = i / quads, dq = i - n * quads;
-        const int c = tile * 16 + n;
-        const int tok = n / d.g, head = n - tok * d.g;
-        const int t0 = tile * tile_tok;
-        if (n >= d.cols || t0 + tok >= ntok) continue;            // a column without a query
-        float M = -INFINITY;
-        for (int s = 0; s < n_split; ++s) {
-            const float *part = d.ws + (((size_t)(row + s) * d.Hkv + kvh) * NCOL + c) * stride;
-            M = fmaxf(M, part[D]);
-        }
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        float den = 0.f;
-        for (int s = 0; s < n_split; ++s) {
-            const float *part = d.ws + (((size_t)(row + s) * d.Hkv + kvh) * NCOL + c) * stride;
-            const float m = part[D];
-            const float f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
-            den += f * part[D + 1];
-            // a part that saw no token holds no usable sums (its factor is 0, its sums may be anything finite)
-            if (f > 0.f) acc += *reinterpret_cast<const f32x4 *>(part + 4 * dq) * f;
-        }
-        const float inv = den > 0.f ? 1.0f / den : 0.f;
-        float *out_row = d.out + ((size_t)(e.y + t0 + tok) * d.Hq + kvh * d.g + head) * D;
-        *reinterpret_cast<f32x4 *>(out_row + 4 * dq) = acc * inv;
-    }
-}
-
-__global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d) {
-    // one array per buffer: distinct objects, so that a read of one buffer is not taken to depend
-    // on the loads still travelling into the others; each holds a pair of the largest tiles (bf16, D = 128)
-    __shared__ __align__(16) uint8_t lds0[4 * T * 128 * 2], lds1[4 * T * 128 * 2], lds2[4 * T * 128 * 2], lds3[4 * T * 128 * 2];
-    if (d.dtype == PKV_BF16) {
-        if (d.D == 128) prefill_group<128, PKV_BF16>(d, lds0, lds1, lds2, lds3);
-        else prefill_group<64, PKV_BF16>(d, lds0, lds1, lds2, lds3);
-    } else {
-        if (d.D == 128) prefill_group<128, PKV_E4M3>(d, lds0, lds1, lds2, lds3);
-        else prefill_group<64, PKV_E4M3>(d, lds0, lds1, lds2, lds3);
-    }
-}
-
 // Read ceilings for comparison.  granule == 0: plain streaming read of the buffer,
 // 16 bytes per lane.  granule > 0 (a power-of-two number of KiB): each wave reads
 // whole granules of that size picked in a scrambled order, which is the access pattern
@@ -1547,14 +967,6 @@ hipError_t pkv_launch_attention_static(const AttnGroup &grp, uint32_t *cnt, size
     const unsigned blocks = (unsigned)((n_cnt + 255) / 256);
     hipLaunchKernelGGL(k_clear_words, dim3(blocks < 64 ? (blocks ? blocks : 1) : 64), dim3(256), 0, s, cnt, n_cnt);
     hipLaunchKernelGGL(k_attention_static, dim3(grp.m[0].n_items), dim3(64), 0, s, grp);
-    return hipGetLastError();
-}
-
-hipError_t pkv_launch_prefill(const AttnDesc &d, int n_groups, bool any_split, hipStream_t s) {
-    if (n_groups == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_prefill, dim3((unsigned)(n_groups * d.Hkv)), dim3(64 * PF_WAVES), 0, s, d);
-    if (any_split)
-        hipLaunchKernelGGL(k_prefill_merge, dim3((unsigned)(n_groups * d.Hkv * PKV_PREFILL_TILES)), dim3(256), 0, s, d);
     return hipGetLastError();
 }
 

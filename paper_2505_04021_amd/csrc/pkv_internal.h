@@ -95,7 +95,8 @@ struct AttnDesc {
     uint32_t max_block_id;      // n_frames * slots
     int32_t batch, row_stride;
     int32_t Hq, Hkv, g, D, dtype;
-    int32_t cols;               // MFMA columns in use per kv head: (query tokens per row) * g, at most 16
+    int32_t cols;               // MFMA columns in use per kv head: (query tokens per row) * g, at most 16 (prefill: of a
+                                // wave's tile, at most 32)
     int32_t item_begin;         // first work item of this model in a grouped launch
     int32_t n_items;            // work items (waves) of this model
     int32_t min_share;          // smallest share of pages a wave may get
@@ -105,7 +106,8 @@ struct AttnDesc {
 };
 
 #define PKV_MAX_GROUP 16
-#define PKV_PREFILL_TILES 8     // tiles of query tokens per prefill work-group (4 waves x 2)
+#define PKV_PREFILL_WAVES 4     // waves of a prefill work-group
+#define PKV_PREFILL_COLS 128    // MFMA columns (query tokens x heads of the kv head) of a prefill work-group, 32 per wave
 
 // How a launch cuts each block of eight consecutive shares among the eight XCDs.
 struct AttnTune {
@@ -143,6 +145,6 @@ hipError_t pkv_launch_attention(const AttnGroup &grp, bool deep, hipStream_t s, 
 // the entry point that allocates nothing: the current device's copy of the library's scratch array
 hipError_t pkv_static_scratch(void **ptr);
 hipError_t pkv_launch_attention_static(const AttnGroup &grp, uint32_t *cnt, size_t n_cnt, hipStream_t s);
-// chunked prefill: d.vmap lists n_groups groups of up to PKV_PREFILL_TILES * (d.cols / d.g) query tokens
+// chunked prefill: d.vmap lists n_groups groups of up to PKV_PREFILL_WAVES * (d.cols / d.g) query tokens
 hipError_t pkv_launch_prefill(const AttnDesc &d, int n_groups, bool any_split, hipStream_t s);
 hipError_t pkv_launch_stream_read(const void *src, size_t bytes, size_t granule_bytes, uint32_t *sink, hipStream_t s);

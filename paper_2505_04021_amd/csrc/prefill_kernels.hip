@@ -1,0 +1,498 @@
+// Chunked prefill over the shared pool (gfx950 / CDNA4): causal attention of a group of consecutive
+// query tokens against the paged cache (paper Sec. 5.2).
+//
+// One work-group of four waves per (group, kv head).  Every wave owns a tile of 32 MFMA columns (query
+// tokens x the g heads of the kv head) and walks the context a page pair (32 tokens) at a time:
+//   scores   S[token][column] = K . q^T          D / 16 products 32x32x16, K as the row operand
+//   output   O^T[d][column] += V^T . P           2 * D / 32 products per half of P (hi, lo)
+// The accumulator layout of the first is the column-operand layout of the second once the eight tokens a
+// lane holds of a page are taken as the eight contraction slots of its lane half, so probabilities never
+// change lanes.  K and V tiles travel from the pool into LDS in the byte order they have in the block
+// (kv_layout.h), one tile of the pair per wave.
+//
+// What bounds it: power, then the latency of a step.  On bf16 caches with 128-wide heads a wave's step is 24
+// products (768 matrix cycles, a third of them the low half of the probabilities) and 138 other vector
+// instructions; two waves per SIMD turn a step over in 2150 cycles each (71 % matrix occupancy) while the chip
+// holds about 1.5 GHz; with all operands zero the same kernel runs 25 % faster, and a plain 8192^3 matrix product
+// loses as much to random data.  Why this shape: 32x32x16 products read half as many operand registers and LDS
+// bytes per flop as 16x16x32, need one lane exchange instead of two per maximum (and that only when the
+// reference point moves), and fill 32 columns better for odd g.  The step is software-pipelined by one pair:
+// scores of pair p + 1 and the V reads of pair p are issued before the softmax of pair p is needed.  The waves
+// meet once in two pairs (every pair: 2 % slower).  8 sequences x (2048 cached + 512 new) of 32/8/128: bf16 236
+// -> 212 us, e4m3 300 -> 180 us; 64-wide heads 183 -> 131 us.
+#include "mfma_util.h"
+
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int PF_WAVES = PKV_PREFILL_WAVES;
+constexpr int PF_COLS = 32;     // MFMA columns per wave
+constexpr int PF_SLOTS = 4;     // page pairs per ring (K and V have a ring each)
+static_assert(PF_WAVES * PF_COLS == PKV_PREFILL_COLS, "host and kernel must agree on the group size");
+
+// Where the reference point of the exponentials starts: finite, so that a column that has seen no token
+// yet needs no special case (its probabilities are exp2(-inf) = 0 and any real maximum replaces it).
+constexpr float PF_M0 = -1e30f;
+
+template <int D, int DT>
+struct PfTile {
+    static constexpr int E = DT == PKV_BF16 ? 2 : 1;
+    static constexpr int BYTES = PKV_T * D * E;            // one K or V tile
+    static constexpr int NL = BYTES / 1024;                // 1 KiB requests per tile
+    static constexpr int NU = BYTES / 512;                 // 16-byte LDS reads per lane for the K operands of a pair
+    static constexpr int NK = D / 16;                      // score products per pair
+    static constexpr int ND = D / 32;                      // tiles of 32 output elements
+};
+
+// NL x 1 KiB from the pool straight into LDS: lane l's 16 bytes at src + 1024 j + 16 l land at dst + 1024 j + 16 l.
+// Written as assembly so that the compiler does not drain all requests in flight before every LDS read;
+// the waits are counted by hand (s_waitcnt vmcnt).  src and dst are wave-uniform.
+template <int NL>
+__device__ __forceinline__ void lds_fill(const uint8_t *src, uint32_t dst, uint32_t lane16) {
+    if (NL == 1)
+        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane16), "s"(src), "s"(dst) : "memory", "m0");
+    else if (NL == 2)
+        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1\n\tglobal_load_lds_dwordx4 %0, %1 offset:1024" ::"v"(lane16),
+                     "s"(src), "s"(dst)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1\n\tglobal_load_lds_dwordx4 %0, %1 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %0, %1 offset:2048\n\tglobal_load_lds_dwordx4 %0, %1 offset:3072" ::"v"(lane16),
+                     "s"(src), "s"(dst)
+                     : "memory", "m0");
+    static_assert(NL == 1 || NL == 2 || NL == 4, "tile sizes of 1, 2 or 4 KiB");
+}
+
+template <int NL>
+__device__ __forceinline__ void wait_requests(int ahead) {      // all but the `ahead` most recent requests have landed
+    if (ahead >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
+    else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+template <int D, int DT>
+__global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d) {
+    using TL = PfTile<D, DT>;
+    constexpr int SLOT = 2 * TL::BYTES;                    // the K (or V) tiles of a pair
+    __shared__ __align__(16) uint8_t ring[2 * PF_SLOTS * SLOT];   // K slots, then V slots
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int h = lane >> 5, n = lane & 31, c16 = lane & 15, hi16 = (lane >> 4) & 1;
+    const int group = blockIdx.x / d.Hkv, kvh = blockIdx.x - group * d.Hkv;
+
+    const int32_t *vm = reinterpret_cast<const int32_t *>(d.vmap + group);
+    const int seq = PKV_CONST(int32_t, vm)[0], q0 = PKV_CONST(int32_t, vm)[1], back = PKV_CONST(int32_t, vm)[2];
+    const int packed = PKV_CONST(int32_t, vm)[3];
+    // a group of few query tokens in front of a long context comes as several work-groups, each with a
+    // part of the context; they leave partial results that k_prefill_merge joins
+    const int ntok = packed & 0xff, split = (packed >> 8) & 0xfff, n_split = packed >> 20;
+    const int tile_tok = d.cols / d.g;                     // query tokens per wave
+    const int tok = n / d.g, head = n - tok * d.g;         // this lane's column
+    // tokens the group's last query sees, never beyond what the row holds
+    int L = PKV_CONST(int32_t, d.ctx_lens)[seq] - back;
+    const int cap = PKV_CONST(int32_t, d.row_len)[seq] * PKV_T;
+    L = L < 0 ? 0 : (L > cap ? cap : L);
+    const int n_pages = (L + PKV_T - 1) / PKV_T, n_pairs = (n_pages + 1) >> 1;
+    // the pairs this work-group walks
+    const int per = n_split > 1 ? (n_pairs + n_split - 1) / n_split : n_pairs;
+    const int p_begin = n_split > 1 ? (split * per < n_pairs ? split * per : n_pairs) : 0;
+    const int p_end = p_begin + per < n_pairs ? p_begin + per : n_pairs;
+    const int np = p_end - p_begin;
+    // pairs below it hold only tokens that every column sees
+    const int causal_from = L - (ntok - 1);
+    const int p_plain = causal_from > 0 ? causal_from >> 5 : 0;
+
+    // this wave's tile: the group's tokens [w * tile_tok, ...)
+    const int t0 = w * tile_tok;
+    int my_tok = ntok - t0;
+    my_tok = my_tok < 0 ? 0 : (my_tok > tile_tok ? tile_tok : my_tok);
+    const bool col_live = n < d.cols && tok < my_tok;
+    const int col_lim = col_live ? L - (ntok - 1 - (t0 + tok)) : L;          // tokens this column sees
+    const int tile_lim = my_tok > 0 ? L - (ntok - t0 - my_tok) : 0;          // tokens some column of the tile sees
+
+    // q as the column operand: lane (h, n) holds q[column n][16 kk + 8 h .. + 7]
+    u32x4 qf[TL::NK];
+    {
+        const uint16_t *qrow = d.q + ((size_t)(q0 + t0 + tok) * d.Hq + kvh * d.g + head) * D + 8 * h;
+#pragma unroll
+        for (int kk = 0; kk < TL::NK; ++kk) {
+            qf[kk] = mk4(0, 0, 0, 0);
+            if (col_live) qf[kk] = *reinterpret_cast<const u32x4 *>(qrow + 16 * kk);
+        }
+    }
+
+    f32x16 acc[TL::ND];
+#pragma unroll
+    for (int dt = 0; dt < TL::ND; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[dt][i] = 0.f;
+    float m = PF_M0, l = 0.f;
+
+    // ---- requests.  Wave 0: K of page a, wave 1: V of page a, wave 2: K of page b, wave 3: V of page b.
+    // The addresses of 64 pairs are worked out at a time, one pair per lane, and handed out by lane reads;
+    // e4m3: so are the scales of both pages of 64 pairs.
+    const int32_t *row = d.table + (size_t)seq * d.row_stride;
+    const bool is_v = w & 1;
+    uint32_t bad = 0;
+    const uint32_t lane16 = lane * 16;
+    const uint32_t lds_tile = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t *)ring + (is_v ? PF_SLOTS * SLOT : 0) +
+                              (w >> 1) * TL::BYTES;
+    auto block_of = [&](int page, bool &ok) __attribute__((always_inline)) {
+        page = page < n_pages ? page : n_pages - 1;        // past the end: the last page again (masked later)
+        page = page < d.row_stride ? page : d.row_stride - 1;
+        uint32_t id = (uint32_t)row[page];
+        ok = id < d.max_block_id;
+        if (!ok) id = 0;
+        const uint32_t f = fastdiv_div(id, d.slots_div);
+        const uint32_t sl = id - f * d.slots_div.d;
+        return d.pool_base + (uint64_t)f * d.frame_bytes + (uint64_t)sl * d.block_bytes;
+    };
+    uint32_t addr_lo = 0, addr_hi = 0;
+    int addr_win = 0;
+    auto load_addr = [&](int p) __attribute__((always_inline)) {
+        addr_win = p;
+        bool ok;
+        const uint8_t *blk = block_of(2 * (p + lane) + (w >> 1), ok);
+        // an id outside the pool is never dereferenced: a zeroed spare tile stands in
+        bad |= ok ? 0u : 1u;
+        const uint8_t *src = ok ? blk + (DT == PKV_E4M3 ? PKV_FP8_HEADER : 0) + ((size_t)kvh * 2 + (is_v ? 1 : 0)) * TL::BYTES
+                                : reinterpret_cast<const uint8_t *>(d.safe);
+        addr_lo = (uint32_t)(uintptr_t)src;
+        addr_hi = (uint32_t)((uintptr_t)src >> 32);
+        asm volatile("" ::"v"(addr_lo), "v"(addr_hi));     // waited for here, not where they are used
+    };
+    auto fetch = [&](int r) __attribute__((always_inline)) {                              // request this wave's tile of pair p_begin + r
+        const int p = p_begin + r;
+        if (p - addr_win >= 64) load_addr(p);
+        const int at = p - addr_win;
+        const uint64_t src = (uint32_t)__builtin_amdgcn_readlane((int)addr_lo, at) |
+                             ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)addr_hi, at) << 32);
+        lds_fill<TL::NL>(reinterpret_cast<const uint8_t *>(src), lds_tile + (uint32_t)(r & (PF_SLOTS - 1)) * SLOT, lane16);
+    };
+    float w_ska = 1.f, w_skb = 1.f, w_sva = 1.f, w_svb = 1.f;
+    int scale_win = -64;
+    float sva = 1.f, svb = 1.f, sva_n = 1.f, svb_n = 1.f, sca = d.scale_log2, scb = d.scale_log2;
+    auto scales = [&](int p) __attribute__((always_inline)) {                             // e4m3: the scales of pair p (K into sca / scb, V into sv*_n)
+        if (DT != PKV_E4M3) return;
+        if (p - scale_win >= 64) {
+            scale_win = p;
+            bool oka, okb;
+            const uint8_t *a = block_of(2 * (p + lane), oka), *b = block_of(2 * (p + lane) + 1, okb);
+            const float *ha = reinterpret_cast<const float *>(oka ? a : reinterpret_cast<const uint8_t *>(d.safe));
+            const float *hb = reinterpret_cast<const float *>(okb ? b : reinterpret_cast<const uint8_t *>(d.safe));
+            w_ska = ha[kvh]; w_sva = ha[d.Hkv + kvh];
+            w_skb = hb[kvh]; w_svb = hb[d.Hkv + kvh];
+            asm volatile("" ::"v"(w_ska), "v"(w_sva), "v"(w_skb), "v"(w_svb));
+        }
+        const int at = p - scale_win;
+        auto lane_of = [&](float x) __attribute__((always_inline)) { return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), at)); };
+        sca = lane_of(w_ska) * d.scale_log2;
+        scb = lane_of(w_skb) * d.scale_log2;
+        sva_n = lane_of(w_sva);
+        svb_n = lane_of(w_svb);
+    };
+
+    // ---- operands.  K: lane (h, n) reads token n & 15 of page n >> 4, units h and h + 2, ... (512 bytes apart)
+    u32x4 kr[TL::NU];
+    const uint8_t *k_lane = ring + hi16 * TL::BYTES + h * 256 + c16 * 16;
+    auto read_k = [&](int r) __attribute__((always_inline)) {
+        const uint8_t *src = k_lane + (r & (PF_SLOTS - 1)) * SLOT;
+#pragma unroll
+        for (int u = 0; u < TL::NU; ++u) kr[u] = *reinterpret_cast<const u32x4 *>(src + u * 512);
+    };
+    // V: output element 32 dt + n of tokens 4h..4h+3 and 8+4h..8+4h+3 of a page (lane row groups h and 2 + h)
+    constexpr int VW = DT == PKV_BF16 ? 2 : 1;             // words per token group
+    uint32_t vr[TL::ND][2][2 * VW];
+    const uint8_t *v_lane = ring + PF_SLOTS * SLOT + h * 256 + c16 * 16 + hi16 * 4 * VW;
+    auto read_v = [&](int r) __attribute__((always_inline)) {
+        const uint8_t *src = v_lane + (r & (PF_SLOTS - 1)) * SLOT;
+#pragma unroll
+        for (int dt = 0; dt < TL::ND; ++dt)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const uint8_t *at = src + k * TL::BYTES + (DT == PKV_BF16 ? dt * 1024 : (dt >> 1) * 1024 + (dt & 1) * 8);
+                if constexpr (DT == PKV_BF16) {
+                    const u32x2 a = *reinterpret_cast<const u32x2 *>(at), b = *reinterpret_cast<const u32x2 *>(at + 512);
+                    vr[dt][k][0] = a.x; vr[dt][k][1] = a.y; vr[dt][k][2] = b.x; vr[dt][k][3] = b.y;
+                } else {
+                    vr[dt][k][0] = *reinterpret_cast<const uint32_t *>(at);
+                    vr[dt][k][1] = *reinterpret_cast<const uint32_t *>(at + 512);
+                }
+            }
+    };
+    auto k_op = [&](int kk) __attribute__((always_inline)) {
+        if constexpr (DT == PKV_BF16) return as_bf16x8(kr[kk]);
+        else {
+            const u32x4 u = kr[2 * (kk >> 2) + (kk & 1)];
+            const u32x2 a = fp8x4_to_bf16x4((kk & 2) ? u.z : u.x), b = fp8x4_to_bf16x4((kk & 2) ? u.w : u.y);
+            return as_bf16x8(mk4(a.x, a.y, b.x, b.y));
+        }
+    };
+    auto v_op = [&](int dt, int k) __attribute__((always_inline)) {
+        if constexpr (DT == PKV_BF16) return as_bf16x8(mk4(vr[dt][k][0], vr[dt][k][1], vr[dt][k][2], vr[dt][k][3]));
+        else {
+            const u32x2 a = fp8x4_to_bf16x4(vr[dt][k][0]), b = fp8x4_to_bf16x4(vr[dt][k][1]);
+            return as_bf16x8(mk4(a.x, a.y, b.x, b.y));
+        }
+    };
+    // tokens past the context may hold anything (even NaN): blank their V (their probabilities are 0)
+    auto blank_v = [&](int p) __attribute__((always_inline)) {
+        const int left = L - 32 * p - 4 * h;               // tokens of the pair before the end, from this half's first
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int v = left - 16 * k - 8 * q;       // live tokens of this group of four
+                if constexpr (DT == PKV_BF16) {
+                    const uint32_t m01 = v >= 2 ? 0xffffffffu : (v == 1 ? 0x0000ffffu : 0u);
+                    const uint32_t m23 = v >= 4 ? 0xffffffffu : (v == 3 ? 0x0000ffffu : 0u);
+#pragma unroll
+                    for (int dt = 0; dt < TL::ND; ++dt) {
+                        vr[dt][k][2 * q] &= m01;
+                        vr[dt][k][2 * q + 1] &= m23;
+                    }
+                } else {
+                    const uint32_t mm = v >= 4 ? 0xffffffffu : (v <= 0 ? 0u : (1u << (8 * v)) - 1u);
+#pragma unroll
+                    for (int dt = 0; dt < TL::ND; ++dt) vr[dt][k][q] &= mm;
+                }
+            }
+    };
+
+    // ---- one pair's softmax, in two parts.  Arguments: t = score * scale - m (log2 domain) against the reference
+    // point m as it stands.  m need not be the column's maximum, only near it: it moves, and the sums are
+    // rescaled, when some argument exceeds kRescaleSlack, so that probabilities stay below 2^kRescaleSlack.
+    f32x16 s, t;
+    auto args = [&](int p, bool masked) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) t[i] = __builtin_fmaf(s[i], i < 8 ? sca : scb, -m);
+        if (masked) {
+            const int rel = col_lim - 32 * p - 4 * h;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const float x = t[i];
+                t[i] = 16 * (i >> 3) + 8 * ((i >> 2) & 1) + (i & 3) < rel ? x : -INFINITY;
+            }
+        }
+    };
+    auto settle = [&](int p, bool masked) __attribute__((always_inline)) {
+        float mx = fmaxf(fmaxf(t[0], t[1]), t[2]);
+#pragma unroll
+        for (int i = 3; i < 15; i += 2) mx = fmaxf(fmaxf(mx, t[i]), t[i + 1]);
+        mx = fmaxf(mx, t[15]);
+        if (__builtin_expect(__any(mx > kRescaleSlack), 0)) {
+            // the column's maximum from the scores themselves (t is inexact when m is far off)
+            const int rel = col_lim - 32 * p - 4 * h;
+            float top = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const float x = s[i] * (i < 8 ? sca : scb);
+                const bool dead = masked && 16 * (i >> 3) + 8 * ((i >> 2) & 1) + (i & 3) >= rel;
+                top = fmaxf(top, dead ? -INFINITY : x);
+            }
+            top = halves_max(top);
+            const float m_new = fmaxf(m, top);
+            const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+            l *= alpha;
+#pragma unroll
+            for (int dt = 0; dt < TL::ND; ++dt) acc[dt] *= alpha;
+            m = m_new;
+            args(p, masked);
+        }
+    };
+    auto scores = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < TL::NK; ++kk)
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_op(kk), as_bf16x8(qf[kk]), s, 0, 0, 0);
+    };
+    u32x4 ph[2], pl[2];
+    f32x16 pr;
+    auto probabilities = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) pr[i] = __builtin_amdgcn_exp2f(t[i]);
+        l += (((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]))) +
+             (((pr[8] + pr[9]) + (pr[10] + pr[11])) + ((pr[12] + pr[13]) + (pr[14] + pr[15])));
+        if (DT == PKV_E4M3) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) pr[i] *= i < 8 ? sva : svb;
+        }
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ph[k][e] = pack_bf16_rne(pr[8 * k + 2 * e], pr[8 * k + 2 * e + 1]);
+    };
+    auto low_halves = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                pl[k][e] = pack_bf16_rne(pr[8 * k + 2 * e] - __uint_as_float(ph[k][e] << 16),
+                                         pr[8 * k + 2 * e + 1] - __uint_as_float(ph[k][e] & 0xffff0000u));
+    };
+    auto accumulate = [&](const u32x4 *p) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int dt = 0; dt < TL::ND; ++dt)
+                acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_op(dt, k), as_bf16x8(p[k]), acc[dt], 0, 0, 0);
+    };
+
+    // the meeting point of the steps r and r + 1 (r even), in the middle of step r: all requests under way have
+    // landed; behind it K of pairs r + 2, r + 3 and V of pairs r + 1, r + 2 are visible to all waves, and the slots
+    // of K r, r + 1 and V r - 1, r take the pairs PF_SLOTS ahead of them
+    auto meet = [&](int r) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        const int next = r + PF_SLOTS - (is_v ? 1 : 0);
+        if (next < np) fetch(next);
+        if (next + 1 < np) fetch(next + 1);
+    };
+
+    if (np > 0) {
+        load_addr(p_begin);
+        const int ahead = is_v ? PF_SLOTS - 1 : PF_SLOTS, first = ahead < np ? ahead : np;
+        for (int r = 0; r < first; ++r) fetch(r);
+        wait_requests<TL::NL>(first - 2);                  // K 0, K 1 and V 0, V 1
+        __builtin_amdgcn_s_barrier();
+        const bool live = my_tok > 0;
+        if (live) read_k(0);
+        if (live) {
+            scales(p_begin);
+            scores();
+            sva = sva_n; svb = svb_n;
+            if (np > 1) read_k(1);
+            const bool masked = p_begin >= p_plain;
+            args(p_begin, masked);
+            settle(p_begin, masked);
+        }
+        int r = 0;
+        if (live) {
+            // pairs without masks: straight-line steps
+            for (; r + 1 < np && p_begin + r + 1 < p_plain; ++r) {
+                read_v(r);
+                scales(p_begin + r + 1);
+                scores();
+                probabilities();
+                if (!(r & 1)) meet(r);
+                if (r + 2 < np) read_k(r + 2);
+                sva = sva_n; svb = svb_n;
+                accumulate(ph);
+                if (DT == PKV_BF16) {
+                    low_halves();
+                    accumulate(pl);
+                }
+                args(p_begin + r + 1, false);
+                settle(p_begin + r + 1, false);
+            }
+        }
+        for (; r < np; ++r) {
+            const int p = p_begin + r;
+            const bool now = live && 32 * p < tile_lim, next = live && r + 1 < np && 32 * (p + 1) < tile_lim;
+            if (now) {
+                read_v(r);
+                probabilities();
+            }
+            if (next) {
+                scales(p + 1);
+                scores();
+            }
+            if (r + 1 < np && !(r & 1)) meet(r);
+            if (next && r + 2 < np) read_k(r + 2);
+            if (now) {
+                if (32 * (p + 1) > L) blank_v(p);
+                accumulate(ph);
+                if (DT == PKV_BF16) {
+                    low_halves();
+                    accumulate(pl);
+                }
+            }
+            if (next) {
+                sva = sva_n; svb = svb_n;
+                const bool masked = p + 1 >= p_plain;
+                args(p + 1, masked);
+                settle(p + 1, masked);
+            }
+        }
+    }
+
+    l += __shfl_xor(l, 32);
+    if (n_split > 1) {
+        // a part of the context: the unnormalised sums, the reference point and the denominator of every column
+        float *part = d.ws + (((size_t)group * d.Hkv + kvh) * PKV_PREFILL_COLS + w * PF_COLS + n) * (D + 4);
+#pragma unroll
+        for (int dt = 0; dt < TL::ND; ++dt)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                *reinterpret_cast<f32x4 *>(part + 32 * dt + 8 * j + 4 * h) =
+                    f32x4{acc[dt][4 * j], acc[dt][4 * j + 1], acc[dt][4 * j + 2], acc[dt][4 * j + 3]};
+        if (h == 0) {
+            part[D] = m;
+            part[D + 1] = l;
+        }
+    } else if (col_live) {
+        float *out_row = d.out + ((size_t)(q0 + t0 + tok) * d.Hq + kvh * d.g + head) * D;
+        const float inv = l > 0.f ? 1.0f / l : 0.f;        // no visible token: the row is defined as zero
+#pragma unroll
+        for (int dt = 0; dt < TL::ND; ++dt)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                *reinterpret_cast<f32x4 *>(out_row + 32 * dt + 8 * j + 4 * h) =
+                    f32x4{acc[dt][4 * j], acc[dt][4 * j + 1], acc[dt][4 * j + 2], acc[dt][4 * j + 3]} * inv;
+    }
+    if (__any(bad != 0) && lane == 0) atomicOr(d.err, 1u);
+}
+
+// Joins the parts of a group whose context was walked by several work-groups of k_prefill: one
+// work-group per (first part of such a group, kv head, wave tile of 32 columns); the parts are consecutive
+// rows of d.vmap.  out = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i with M = max_i m_i, per column.
+__global__ __launch_bounds__(256) void k_prefill_merge(const AttnDesc d) {
+    const int tile = blockIdx.x % PF_WAVES, rk = blockIdx.x / PF_WAVES;
+    const int row = rk / d.Hkv, kvh = rk - row * d.Hkv;
+    const int4 e = d.vmap[row];
+    const int split = (e.w >> 8) & 0xfff, n_split = e.w >> 20, ntok = e.w & 0xff;
+    if (n_split <= 1 || split != 0) return;
+    const int D = d.D, tile_tok = d.cols / d.g, stride = D + 4;       // D sums, the reference point, the denominator, two unused (16-byte rows)
+    const int quads = D / 4;
+    for (int i = threadIdx.x; i < PF_COLS * quads; i += blockDim.x) {
+        const int n = i / quads, dq = i - n * quads;
+        const int c = tile * PF_COLS + n;
+        const int tok = n / d.g, head = n - tok * d.g;
+        const int t0 = tile * tile_tok;
+        if (n >= d.cols || t0 + tok >= ntok) continue;            // a column without a query
+        float M = PF_M0;
+        for (int s = 0; s < n_split; ++s) {
+            const float *part = d.ws + (((size_t)(row + s) * d.Hkv + kvh) * PKV_PREFILL_COLS + c) * stride;
+            M = fmaxf(M, part[D]);
+        }
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        float den = 0.f;
+        for (int s = 0; s < n_split; ++s) {
+            const float *part = d.ws + (((size_t)(row + s) * d.Hkv + kvh) * PKV_PREFILL_COLS + c) * stride;
+            const float f = __builtin_amdgcn_exp2f(part[D] - M);
+            den += f * part[D + 1];
+            acc += *reinterpret_cast<const f32x4 *>(part + 4 * dq) * f;
+        }
+        const float inv = den > 0.f ? 1.0f / den : 0.f;
+        float *out_row = d.out + ((size_t)(e.y + t0 + tok) * d.Hq + kvh * d.g + head) * D;
+        *reinterpret_cast<f32x4 *>(out_row + 4 * dq) = acc * inv;
+    }
+}
+
+}  // namespace
+
+hipError_t pkv_launch_prefill(const AttnDesc &d, int n_groups, bool any_split, hipStream_t s) {
+    if (n_groups == 0) return hipSuccess;
+    const dim3 grid((unsigned)(n_groups * d.Hkv)), wg(64 * PF_WAVES);
+    if (d.dtype == PKV_BF16) {
+        if (d.D == 128) hipLaunchKernelGGL((k_prefill<128, PKV_BF16>), grid, wg, 0, s, d);
+        else hipLaunchKernelGGL((k_prefill<64, PKV_BF16>), grid, wg, 0, s, d);
+    } else {
+        if (d.D == 128) hipLaunchKernelGGL((k_prefill<128, PKV_E4M3>), grid, wg, 0, s, d);
+        else hipLaunchKernelGGL((k_prefill<64, PKV_E4M3>), grid, wg, 0, s, d);
+    }
+    if (any_split) hipLaunchKernelGGL(k_prefill_merge, dim3((unsigned)(n_groups * d.Hkv * PF_WAVES)), dim3(256), 0, s, d);
+    return hipGetLastError();
+}

@@ -1,0 +1,30 @@
+"""Prefill at the edges of its tiles: query counts around a wave's tile and a work-group's group (32 // g and
+4 * (32 // g) tokens), contexts around page pairs, the rings of pairs in flight and the 64 pairs (2048 tokens) whose
+addresses are worked out at a time, against the oracle.  Bars as for all prefill tests (bf16 2e-3, e4m3 2e-2)."""
+import pytest
+
+from parity import TOL, row_rel_err
+from test_gpu_prefill import BF16, E4M3, Twin, gpu  # noqa: F401  (fixture)
+from workloads import gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("g,hkv,d,dtype", [(1, 2, 128, BF16), (3, 1, 64, BF16), (4, 2, 128, E4M3), (5, 1, 128, BF16), (7, 2, 64, E4M3),
+                                           (8, 1, 128, BF16), (16, 1, 64, BF16), (16, 1, 128, E4M3)])
+@pytest.mark.parametrize("long", [False, True])
+def test_prefill_tile_edges(gpu, oracle, g, hkv, d, dtype, long):  # noqa: F811
+    tile = 32 // g
+    if long:        # few queries in front of long contexts: parts of the context, more than one window of addresses
+        cases = [(2048, 1), (2049, tile), (2081, tile + 1), (2300, 3)]
+    else:
+        cases = [(1, 1), (16, min(16, tile)), (31, min(31, tile + 1)), (33, 2), (64, min(64, 4 * tile)), (4 * tile + 65, 4 * tile + 1),
+                 (97, 5), (129, 97), (161, 160), (200, 0), (5, 5)]
+    ctx, qlen = [c for c, _ in cases], [q for _, q in cases]
+    t = Twin(gpu, oracle, g * hkv, hkv, d, dtype, ctx, max_blocks=160)
+    q = gen.queries((31, d, g), sum(qlen), g * hkv, d)
+    rc_o, out_o = oracle.prefill_attention(t.models[1], q, qlen, ctx)
+    rc_g, out_g = gpu.prefill_attention(t.models[0], q, qlen, ctx)
+    assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
+    assert row_rel_err(out_g, out_o) <= TOL[dtype]
+    t.close()
