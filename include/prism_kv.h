@@ -238,8 +238,7 @@ int kv_append(int model, int batch, const void *k_new, const void *v_new, const 
  * [head_dim]), at the indices ctx_lens[s] - q_lens[s] .. ctx_lens[s] - 1.  The result is that
  * of kv_append applied token by token in order (so a cache filled in chunks equals one
  * filled a token at a time, e4m3 codes and scales included).  q_lens: HOST int32 [batch];
- * ctx_lens: dev int32 [batch].  Returns sum q_lens.  Enqueues only (plus a small
- * host-to-device copy of the chunk list); errors as kv_append. */
+ * ctx_lens: dev int32 [batch].  Returns sum q_lens.  Enqueues only; errors as kv_append. */
 int kv_append_chunk(int model, int batch, const void *k_new, const void *v_new, const int32_t *q_lens,
                     const int32_t *ctx_lens);
 
@@ -301,11 +300,10 @@ int decode_attention_multi(int n_models, const int *models, const int *batches,
  * out: dev fp32 [sum q_lens][q_heads][head_dim].  q_lens: HOST int32 [batch] (the caller's
  * scheduler chose the chunk sizes); ctx_lens: dev int32 [batch].  The library's table is
  * used.  A sequence whose ctx_lens is below its q_lens gets zero rows for the queries
- * that would stand before position 0.  Enqueues only (a small host-to-device copy of the
- * row plan included); a call with few query tokens in front of long contexts splits the
- * contexts over several work-groups and then keeps partial results in a per-model buffer
- * that the library allocates, or enlarges after waiting for the stream, when it is first
- * needed. */
+ * that would stand before position 0.  Enqueues only; a call with few query tokens in
+ * front of long contexts splits the contexts over several work-groups and then keeps
+ * partial results in a per-model buffer that the library allocates, or enlarges after
+ * waiting for the stream, when it is first needed. */
 int prefill_attention(int model, int batch, const void *q, const int32_t *q_lens,
                       const int32_t *ctx_lens, float *out);
 

@@ -85,8 +85,6 @@ struct Model {
     size_t ws_floats = 0;
     uint32_t *cnt = nullptr;                // arrival counters, zero between launches
     size_t cnt_cap = 0;
-    int4 *vmap = nullptr;                   // device: the rows (query tiles) of the last prefill launch
-    size_t vmap_cap = 0;
     float *pf_ws = nullptr;                 // device: partial results of prefill groups whose context is split
     size_t pf_ws_floats = 0;
 };
@@ -252,9 +250,6 @@ void free_model_dev(Model &m) {
     (void)hipFree(m.dev.row_len); (void)hipFree(m.dev.counters);
     uc_release(m.ws);
     uc_release(m.cnt);
-    (void)hipFree(m.vmap);
-    m.vmap = nullptr;
-    m.vmap_cap = 0;
     (void)hipFree(m.pf_ws);
     m.pf_ws = nullptr;
     m.pf_ws_floats = 0;
@@ -354,10 +349,8 @@ void plan_launch(const LaunchLoad &l) {
 }
 
 // Everything of a launch descriptor except its split-K workspace.
-// cols: MFMA columns per kv head (0 = g: one query token per row); units_hint: upper bound of the
-// page units of the launch when the rows are not whole sequences (0 = derive from the blocks in use)
 void fill_desc_core(AttnDesc &d, Model &m, int batch, const void *q, const int32_t *table, int row_stride,
-                    const int32_t *ctx_lens, float *out, double share_of_launch, int cols = 0, double units_hint = 0.0) {
+                    const int32_t *ctx_lens, float *out, double share_of_launch) {
     Pool &p = g_pools[m.pool];
     const bool own = table == nullptr;
     d.pool_base = p.base + (size_t)m.layer * m.layer_bytes;      // the layer's part of every block
@@ -375,8 +368,7 @@ void fill_desc_core(AttnDesc &d, Model &m, int batch, const void *q, const int32
     d.max_block_id = (uint32_t)(p.n_frames * m.slots);
     d.batch = batch;
     d.Hq = m.Hq; d.Hkv = m.Hkv; d.g = m.g; d.D = m.D; d.dtype = m.dtype;
-    d.vmap = nullptr;
-    d.cols = cols > 0 ? cols : m.g;
+    d.cols = m.g;
     d.item_begin = 0;
     d.scale_log2 = (float)(1.4426950408889634 / sqrt((double)m.D));
     if (g_min_share > 0) {
@@ -388,9 +380,7 @@ void fill_desc_core(AttnDesc &d, Model &m, int batch, const void *q, const int32
     }
     d.seg_cost = g_seg_cost >= 0 ? g_seg_cost : kDefaultSegCost;
     // no more items than there can be shares of min_share pages (an empty row counts as one page)
-    const double units = units_hint > 0.0 ? units_hint
-                                          : ((own ? (double)m.used_blocks : (double)batch * d.row_stride) +
-                                             (double)batch * (d.seg_cost + 1)) * m.Hkv;
+    const double units = ((own ? (double)m.used_blocks : (double)batch * d.row_stride) + (double)batch * (d.seg_cost + 1)) * m.Hkv;
     double items = g_plan_items * share_of_launch;
     if (items > units / d.min_share) items = units / d.min_share;
     d.n_items = items < 1.0 ? 1 : (int)items;                // never more than the slots in total
@@ -426,8 +416,8 @@ int ensure_workspace(Model &m, size_t need_floats, size_t n_cnt, size_t slack = 
 }
 
 int fill_desc(AttnDesc &d, Model &m, int batch, const void *q, const int32_t *table, int row_stride,
-              const int32_t *ctx_lens, float *out, double share_of_launch, int cols = 0, double units_hint = 0.0) {
-    fill_desc_core(d, m, batch, q, table, row_stride, ctx_lens, out, share_of_launch, cols, units_hint);
+              const int32_t *ctx_lens, float *out, double share_of_launch) {
+    fill_desc_core(d, m, batch, q, table, row_stride, ctx_lens, out, share_of_launch);
     const int rc = ensure_workspace(m, ws_floats_for(m, d.n_items, d.cols), (size_t)batch * m.Hkv);
     if (rc) return rc;
     d.ws = m.ws;
@@ -1488,6 +1478,30 @@ int kv_read(int model, int seq, int tok_begin, int n_tok, void *k_out, void *v_o
     return n_tok;
 }
 
+// Collects the ChunkPlan of one launch after the other.
+struct PlanBuilder {
+    ChunkPlan p;
+    uint32_t row = 0, unit = 0;
+    PlanBuilder() { p.n_seqs = p.seq0 = 0; }
+    bool full() const { return p.n_seqs == PKV_PLAN_SEQS; }
+    void add(uint32_t rows, uint32_t units, uint32_t parts) {
+        p.s[p.n_seqs].unit = unit;
+        p.s[p.n_seqs].row = row | parts << PKV_PLAN_PART_SHIFT;
+        ++p.n_seqs;
+        row += rows;
+        unit += units;
+    }
+    ChunkPlan take(int next_seq) {               // the plan so far; the next one begins at sequence next_seq
+        p.s[p.n_seqs].unit = unit;
+        p.s[p.n_seqs].row = row;
+        const ChunkPlan done = p;
+        p.n_seqs = 0;
+        p.seq0 = next_seq;
+        unit = 0;
+        return done;
+    }
+};
+
 int kv_append_chunk(int model, int batch, const void *k_new, const void *v_new, const int32_t *q_lens,
                     const int32_t *ctx_lens) {
     Model *m = get_model(model);
@@ -1495,37 +1509,28 @@ int kv_append_chunk(int model, int batch, const void *k_new, const void *v_new, 
     if (batch < 0 || batch > m->dev.max_seqs) return PKV_E_RANGE;
     if (batch == 0) return 0;
     if (!k_new || !v_new || !q_lens || !ctx_lens) return PKV_E_ARG;
-    // one entry per (sequence, j-th page its chunk may touch): a chunk of n tokens that starts
-    // anywhere in a page touches at most ceil(n / T) + 1 pages
-    Pool &p = g_pools[m->pool];
-    std::vector<int4> rows;
-    int64_t first = 0;
+    int64_t total = 0;
     for (int s = 0; s < batch; ++s) {
         if (q_lens[s] < 0) return PKV_E_ARG;
-        if (q_lens[s] > 0)
-            for (int j = 0; j < (q_lens[s] + p.T - 1) / p.T + 1; ++j)
-                rows.push_back(make_int4((int)first, q_lens[s], s, j));
-        first += q_lens[s];
-        if (first > (int64_t)1 << 24) return PKV_E_RANGE;
+        total += q_lens[s];
+        if (total > (int64_t)1 << 24) return PKV_E_RANGE;
     }
-    if (first == 0) return 0;
-    if (rows.size() > m->vmap_cap) {
-        HIP_TRY(hipStreamSynchronize(g_stream));
-        (void)hipFree(m->vmap);
-        m->vmap = nullptr;
-        m->vmap_cap = 0;
-        HIP_TRY(hipMalloc((void **)&m->vmap, rows.size() * 2 * sizeof(int4)));
-        m->vmap_cap = rows.size() * 2;
-    }
-    // pageable source: the copy has read `rows` when the call returns, and runs in stream order
-    HIP_TRY(hipMemcpyAsync(m->vmap, rows.data(), rows.size() * sizeof(int4), hipMemcpyHostToDevice, g_stream));
+    const int T = g_pools[m->pool].T;
     AttnDesc d{};
     fill_addressing(d, *m);
-    d.batch = (int)rows.size();
+    d.batch = batch;
     d.ctx_lens = ctx_lens;
-    d.vmap = m->vmap;
-    HIP_TRY(pkv_launch_kv_append(d, k_new, v_new, g_stream));
-    return (int)first;
+    // one unit per (sequence, j-th page its chunk may touch): a chunk of n tokens that starts
+    // anywhere in a page touches at most ceil(n / T) + 1 pages
+    PlanBuilder plan;
+    for (int s = 0; s < batch; ++s) {
+        if (plan.full()) {
+            HIP_TRY(pkv_launch_kv_append_chunk(d, plan.take(s), k_new, v_new, g_stream));
+        }
+        plan.add((uint32_t)q_lens[s], q_lens[s] > 0 ? (uint32_t)((q_lens[s] + T - 1) / T + 1) : 0u, 0u);
+    }
+    HIP_TRY(pkv_launch_kv_append_chunk(d, plan.take(batch), k_new, v_new, g_stream));
+    return (int)total;
 }
 
 int kv_append(int model, int batch, const void *k_new, const void *v_new, const int32_t *ctx_lens) {
@@ -1630,6 +1635,66 @@ int decode_attention_static(int model, int batch, const void *q, const int32_t *
     return PKV_OK;
 }
 
+constexpr int kMinPartPairs = 8;        // no part shorter than this
+constexpr double kFillGroups = 1024.0;  // work-groups from which on nothing is cut
+
+// Parts a sequence's groups are cut into when a part should hold about part_pairs page pairs (0: never cut).
+static int prefill_parts(const Model &m, int seq, double part_pairs) {
+    if (part_pairs <= 0.0) return 1;
+    const int pairs = (m.row_len[seq] + 1) / 2;
+    int n = (int)(pairs / part_pairs + 0.5);
+    if (n > pairs / kMinPartPairs) n = pairs / kMinPartPairs;
+    if (n > PKV_PLAN_MAX_PARTS) n = PKV_PLAN_MAX_PARTS;
+    return n < 1 ? 1 : n;
+}
+
+// Few groups in front of long contexts would leave part of the chip idle: then a group comes as several
+// work-groups, each with a part of the context, and a second kernel joins their partial results.  The host
+// estimates both (it knows the blocks a row holds, not its context length) and takes the cheapest of a dozen part
+// lengths.  Time of the main kernel in microseconds, fitted to measurements with 32/8 heads: a pair takes a
+// work-group alone on its CU t1 and two of them share a CU at t2 a pair each; every work-group costs kGroupPairs
+// pairs besides its own.  The parts' partial sums are written and read once, at about 3.5 TB/s.  Cutting up to 1024
+// work-groups whatever that costs, as before, took 135 us for 4 x (2048 + 512) tokens (112 uncut), 55 for 4 x (32 + 512)
+// (29 uncut), 103 for 8 x (4032 + 64) (65 with the cuts chosen here).
+static double prefill_part_pairs(const Model &m, int batch, const int32_t *q_lens, int group) {
+    const double t1 = m.D == 128 ? 0.85 : 0.60, t2 = m.D == 128 ? (m.dtype == PKV_BF16 ? 0.70 : 0.58) : 0.40;
+    constexpr double kGroupPairs = 4.0, kCUs = 256.0, kMergeUs = 5.0, kPartBytesPerUs = 3.5e6;
+    int longest = 0;
+    double plain = 0.0;
+    for (int s = 0; s < batch; ++s)
+        if (q_lens[s] > 0) {
+            plain += (q_lens[s] + group - 1) / group;
+            longest = longest > m.row_len[s] ? longest : m.row_len[s];
+        }
+    longest = (longest + 1) / 2;
+    if (plain * m.Hkv >= kFillGroups || longest < 2 * kMinPartPairs) return 0.0;
+    static const int kCuts[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
+    double best = 0.0, best_us = 1e30;
+    for (int cuts : kCuts) {
+        const double part = cuts > 1 ? (double)longest / cuts : 0.0;
+        if (cuts > 1 && part < kMinPartPairs) break;
+        double units = 0.0, work = 0.0, top = 0.0, parts_written = 0.0;
+        for (int s = 0; s < batch; ++s) {
+            if (q_lens[s] == 0) continue;
+            const int n = prefill_parts(m, s, part);
+            const double u = (double)((q_lens[s] + group - 1) / group) * n * m.Hkv;
+            const double len = (double)((m.row_len[s] + 1) / 2) / n + kGroupPairs;
+            units += u;
+            work += u * len;
+            top = top > len ? top : len;
+            if (n > 1) parts_written += u;
+        }
+        const double alone = top * t1, shared = top * 2.0 * t2, even = work / kCUs * t2;
+        double us = units <= kCUs ? alone : (even > shared ? even + 0.25 * shared : shared);
+        if (parts_written > 0.0) us += kMergeUs + parts_written * (PKV_PREFILL_COLS * (m.D + 4) * 4 * 2) / kPartBytesPerUs;
+        if (us < best_us) {
+            best_us = us;
+            best = part;
+        }
+    }
+    return best;
+}
+
 int prefill_attention(int model, int batch, const void *q, const int32_t *q_lens, const int32_t *ctx_lens, float *out) {
     Model *m = get_model(model);
     if (!m) return PKV_E_HANDLE;
@@ -1641,72 +1706,51 @@ int prefill_attention(int model, int batch, const void *q, const int32_t *q_lens
     // kv head; the waves of a work-group take consecutive tiles and share the K and V they fetch.
     const int tile = PKV_PREFILL_COLS / PKV_PREFILL_WAVES / m->g;
     const int group = PKV_PREFILL_WAVES * tile;
-    std::vector<int4> rows;
-    int64_t first = 0, n_groups = 0;
+    int64_t total = 0;
     for (int s = 0; s < batch; ++s) {
         if (q_lens[s] < 0) return PKV_E_ARG;
-        n_groups += (q_lens[s] + group - 1) / group;
-        first += q_lens[s];
-        if (first > (int64_t)1 << 24) return PKV_E_RANGE;
+        total += q_lens[s];
+        if (total > (int64_t)1 << 24) return PKV_E_RANGE;
     }
-    if (n_groups == 0) return PKV_OK;
-    // Few groups in front of long contexts would leave most of the chip idle: then every group comes
-    // as several work-groups, each with a part of the context of at least kMinSplitPairs page pairs
-    // (as far as the host can tell: it knows the blocks a row holds, not its context length).
-    constexpr int kFillWorkGroups = 1024, kMinSplitPairs = 8, kMaxSplit = 64;
-    const int64_t plain = n_groups * m->Hkv;
-    const int want_split = plain >= kFillWorkGroups ? 1 : (int)((kFillWorkGroups + plain - 1) / plain);
-    bool any_split = false;
-    first = 0;
-    for (int s = 0; s < batch; ++s) {
-        const int est_pairs = (m->row_len[s] + 1) / 2;
-        int n_split = want_split;
-        if (n_split > est_pairs / kMinSplitPairs) n_split = est_pairs / kMinSplitPairs;
-        if (n_split > kMaxSplit) n_split = kMaxSplit;
-        if (n_split < 2) n_split = 0;
-        // longest groups of a sequence first: they take the most pages
-        for (int t0 = ((q_lens[s] - 1) / group) * group; q_lens[s] > 0 && t0 >= 0; t0 -= group) {
-            const int n = q_lens[s] - t0 < group ? q_lens[s] - t0 : group;
-            if (n_split == 0) rows.push_back(make_int4(s, (int)(first + t0), q_lens[s] - (t0 + n), n));
-            for (int k = 0; k < n_split; ++k)
-                rows.push_back(make_int4(s, (int)(first + t0), q_lens[s] - (t0 + n), n | (k << 8) | (n_split << 20)));
-            any_split |= n_split > 0;
-        }
-        first += q_lens[s];
-    }
-    if (rows.size() > m->vmap_cap) {
-        HIP_TRY(hipStreamSynchronize(g_stream));
-        (void)hipFree(m->vmap);
-        m->vmap = nullptr;
-        m->vmap_cap = 0;
-        HIP_TRY(hipMalloc((void **)&m->vmap, rows.size() * 2 * sizeof(int4)));
-        m->vmap_cap = rows.size() * 2;
-    }
-    // pageable source: the copy has read `rows` when the call returns, and runs in stream order
-    HIP_TRY(hipMemcpyAsync(m->vmap, rows.data(), rows.size() * sizeof(int4), hipMemcpyHostToDevice, g_stream));
+    if (total == 0) return PKV_OK;
+    const double part_pairs = prefill_part_pairs(*m, batch, q_lens, group);
     AttnDesc d{};
     fill_addressing(d, *m);
     d.q = (const uint16_t *)q;
     d.ctx_lens = ctx_lens;
     d.out = out;
     d.batch = batch;
-    d.vmap = m->vmap;
     d.cols = tile * m->g;
     d.scale_log2 = (float)(1.4426950408889634 / sqrt((double)m->D));
-    if (any_split) {
-        const size_t need = rows.size() * m->Hkv * PKV_PREFILL_COLS * (size_t)(m->D + 4);
-        if (need > m->pf_ws_floats) {
-            HIP_TRY(hipStreamSynchronize(g_stream));
-            (void)hipFree(m->pf_ws);
-            m->pf_ws = nullptr;
-            m->pf_ws_floats = 0;
-            HIP_TRY(hipMalloc((void **)&m->pf_ws, need * sizeof(float)));
-            m->pf_ws_floats = need;
+    int split_groups = 0;
+    auto launch = [&](const ChunkPlan &plan) -> int {
+        if (split_groups > 0) {
+            const size_t need = (size_t)plan.s[plan.n_seqs].unit * m->Hkv * PKV_PREFILL_COLS * (size_t)(m->D + 4);
+            if (need > m->pf_ws_floats) {
+                HIP_TRY(hipStreamSynchronize(g_stream));
+                (void)hipFree(m->pf_ws);
+                m->pf_ws = nullptr;
+                m->pf_ws_floats = 0;
+                HIP_TRY(hipMalloc((void **)&m->pf_ws, need * sizeof(float)));
+                m->pf_ws_floats = need;
+            }
+            d.ws = m->pf_ws;
         }
-        d.ws = m->pf_ws;
+        HIP_TRY(pkv_launch_prefill(d, plan, split_groups, g_stream));
+        split_groups = 0;
+        return PKV_OK;
+    };
+    PlanBuilder plan;
+    for (int s = 0; s < batch; ++s) {
+        if (plan.full()) {
+            const int rc = launch(plan.take(s));
+            if (rc) return rc;
+        }
+        const int parts = prefill_parts(*m, s, part_pairs), groups = (q_lens[s] + group - 1) / group;
+        plan.add((uint32_t)q_lens[s], (uint32_t)(groups * parts), (uint32_t)parts);
+        if (parts > 1 && groups > split_groups) split_groups = groups;
     }
-    HIP_TRY(pkv_launch_prefill(d, (int)rows.size(), any_split, g_stream));
-    return PKV_OK;
+    return launch(plan.take(batch));
 }
 
 int decode_attention(int model, const void *q, const int32_t *block_table, const int32_t *ctx_lens, float *out) {

@@ -65,6 +65,9 @@ struct PairIds {
 
 __device__ __forceinline__ PairIds fetch_ids(const AttnDesc &d, const int32_t *row, int page) {
     const int last = d.row_stride - 1;
+    // wave-uniform, and said to be: the ids come through the scalar cache (a vector load would wait for all K and V in flight)
+    row = reinterpret_cast<const int32_t *>((uint32_t)__builtin_amdgcn_readfirstlane((int)(uintptr_t)row) |
+                                            (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)((uintptr_t)row >> 32)) << 32);
     const int ia = page < last ? page : last, ib = page + 1 < last ? page + 1 : last;
     PairIds ids;
     ids.a = (uint32_t)__builtin_amdgcn_readfirstlane(PKV_CONST(int32_t, row)[ia]);
@@ -286,23 +289,6 @@ struct Ring {
 constexpr int FLIGHT_KIB_1WAVE = 8;
 constexpr int MAX_PIECES = 64;   // pieces of one (sequence, kv head) the merge stages in LDS
 
-// A row of a launch.  In a decode step it is a sequence with its one new query token.  In a
-// prefill launch it is a tile of consecutive query tokens of a sequence's chunk (as many as
-// fit the 16 MFMA columns together with the g heads of a kv head): `seq` is the sequence,
-// `q0` the first of the tile's rows in the packed q and out arrays, `ntok` their number,
-// and `back` how many chunk tokens follow the tile, so that the tile's last token sees
-// ctx_lens[seq] - back tokens.
-struct RowInfo {
-    int seq, q0, back, ntok;
-};
-
-__device__ __forceinline__ RowInfo row_info_uniform(const AttnDesc &d, int row) {
-    if (!d.vmap) return RowInfo{row, row, 0, 1};
-    const int32_t *v = reinterpret_cast<const int32_t *>(d.vmap + row);
-    return RowInfo{__builtin_amdgcn_readfirstlane(PKV_CONST(int32_t, v)[0]), __builtin_amdgcn_readfirstlane(PKV_CONST(int32_t, v)[1]),
-                   __builtin_amdgcn_readfirstlane(PKV_CONST(int32_t, v)[2]), __builtin_amdgcn_readfirstlane(PKV_CONST(int32_t, v)[3])};
-}
-
 __device__ __forceinline__ int ctx_clamped(const AttnDesc &d, int seq) {
     int L = PKV_CONST(int32_t, d.ctx_lens)[seq];
     const int cap = (d.row_len ? PKV_CONST(int32_t, d.row_len)[seq] : d.row_stride) * T;
@@ -360,22 +346,19 @@ __device__ __forceinline__ Piece piece_next(const Piece &c, const AttnDesc &d, u
     return nx;
 }
 
-// Which (query token of the row, head of the kv head's group) an MFMA column stands for.
-struct Column {
-    int tok, head;      // column n = tok * g + head
-};
-
-__device__ __forceinline__ Column column_of(const AttnDesc &d, int n) {
-    const int tok = n / d.g;
-    return Column{tok, n - tok * d.g};
+// Whether MFMA column n is a query head at all.  Worked out anew for every piece: known to be the same throughout,
+// the compiler splits the streaming loop on it and loses count of the loads in flight (full waits inside the loop).
+__device__ __forceinline__ bool column_live(const AttnDesc &d, int n) {
+    asm volatile("" : "+v"(n));
+    return n < d.g;
 }
 
-// q as the B operand: lane (G, n) holds q[column n][8(4j+G) .. +7] for each k-step j
+// q as the B operand (column n: head n of the kv head's group): lane (G, n) holds q[column n][8(4j+G) .. +7] for each k-step j
 template <int D>
-__device__ __forceinline__ void load_q(bf16x8 *qf, const AttnDesc &d, const RowInfo &ri, int kvh, int lane, Column col) {
+__device__ __forceinline__ void load_q(bf16x8 *qf, const AttnDesc &d, int seq, int kvh, int lane) {
     const int G = lane >> 4, n = lane & 15;
-    const uint16_t *qrow = d.q + ((size_t)(ri.q0 + col.tok) * d.Hq + kvh * d.g + col.head) * D;
-    const bool live = n < d.cols && col.tok < ri.ntok;
+    const uint16_t *qrow = d.q + ((size_t)seq * d.Hq + kvh * d.g + n) * D;
+    const bool live = column_live(d, n);
 #pragma unroll
     for (int j = 0; j < D / 32; ++j) {
         u32x4 v = mk4(0, 0, 0, 0);
@@ -403,9 +386,8 @@ __device__ __forceinline__ void merge_rows(const AttnDesc &d, const Pending &pd,
                                            const float *base, int n_pc) {
     constexpr int D4 = D / 4;
     constexpr int PB = 32 / EPL;                      // pieces per trip
-    const int g = d.cols, pf = partial_floats(g, D);  // g: columns (query token, head) of a partial
+    const int g = d.g, pf = partial_floats(g, D);
     const int E = g * D4;
-    const RowInfo ri = row_info_uniform(d, pd.seq);
     int hn[EPL], x[EPL];
 #pragma unroll
     for (int k = 0; k < EPL; ++k) {
@@ -464,17 +446,15 @@ __device__ __forceinline__ void merge_rows(const AttnDesc &d, const Pending &pd,
     }
 #pragma unroll
     for (int k = 0; k < EPL; ++k) {
-        const Column col = column_of(d, hn[k]);
-        if (lane + 64 * k < E && col.tok < ri.ntok)
-            *reinterpret_cast<f32x4 *>(d.out + ((size_t)(ri.q0 + col.tok) * d.Hq + pd.kvh * d.g + col.head) * D + 4 * x[k]) =
-                num[k] * (1.0f / den[k]);
+        if (lane + 64 * k < E)
+            *reinterpret_cast<f32x4 *>(d.out + ((size_t)pd.seq * d.Hq + pd.kvh * g + hn[k]) * D + 4 * x[k]) = num[k] * (1.0f / den[k]);
     }
     __builtin_amdgcn_wave_barrier();
 }
 
 template <int D>
 __device__ __forceinline__ void merge_segment(const AttnDesc &d, const Pending &pd, int lane, float *s_m, float *s_l) {
-    const int g = d.cols, pf = partial_floats(g, D);
+    const int g = d.g, pf = partial_floats(g, D);
     const int n_pc = (int)(pd.k1 - pd.k0) + 1;
     const float *base = d.ws + (size_t)(2 * pd.k0) * pf;
     const int groups = (g * (D / 4) + 63) / 64;       // element groups per lane
@@ -535,8 +515,7 @@ __device__ __forceinline__ void attn_wave(const AttnDesc &d, const AttnTune &w, 
     const int lane = threadIdx.x;
     __builtin_amdgcn_s_setprio(3);      // from the first instruction: a wave still setting up must not wait behind streaming ones
     const int G = lane >> 4, n = lane & 15;
-    const int g = d.cols, Hkv = d.Hkv, B = d.batch;   // g: columns in use, (query tokens of a row) x (heads of a kv head)
-    const Column col = column_of(d, n);
+    const int g = d.g, Hkv = d.Hkv, B = d.batch;
     const uint64_t t_begin = w.stat ? wall_clock64() : 0;
 
     // --- planned pages per sequence, prefix sums across the wave.  Batches of up to
@@ -661,9 +640,8 @@ __device__ __forceinline__ void attn_wave(const AttnDesc &d, const AttnTune &w, 
     constexpr int RING = Ring<D, DT, FLIGHT_KIB>::N;
     PairRegs<D, DT> ring[RING];
     PairIds pre;                            // block ids of the next pair to be requested
-    RowInfo ri_c = row_info_uniform(d, cur.seq);       // the row of the piece being worked on
     {
-        const int32_t *row = d.table + (size_t)ri_c.seq * d.row_stride;
+        const int32_t *row = d.table + (size_t)cur.seq * d.row_stride;
         const int live_n = cur.n_pages > 0 ? cur.pe - cur.pb : 0;
 #pragma unroll
         for (int r = 0; r < RING - 1; ++r)
@@ -672,7 +650,7 @@ __device__ __forceinline__ void attn_wave(const AttnDesc &d, const AttnTune &w, 
         pre = fetch_ids(d, row, cur.pb + 2 * (RING - 1));
     }
     bf16x8 qf[TL::NK], qn[TL::NK];
-    load_q<D>(qf, d, ri_c, cur.kvh, lane, col);
+    load_q<D>(qf, d, cur.seq, cur.kvh, lane);
 
     State<D, DT> st;
     // Instruction issue favours the older wave of a SIMD, and at two waves per SIMD the
@@ -684,18 +662,17 @@ __device__ __forceinline__ void attn_wave(const AttnDesc &d, const AttnTune &w, 
     int prio_lvl = 0;
     while (cur.valid) {
         const Piece nxt = piece_next(cur, d, gbeg, gend);
-        const RowInfo ri_n = nxt.valid ? row_info_uniform(d, nxt.seq) : ri_c;
+        const int seq_n = __builtin_amdgcn_readfirstlane(nxt.valid ? nxt.seq : cur.seq);
         // q of the next piece travels while this piece streams (of this piece again if there is no next)
-        load_q<D>(qn, d, ri_n, nxt.valid ? nxt.kvh : cur.kvh, lane, col);
+        load_q<D>(qn, d, seq_n, nxt.valid ? nxt.kvh : cur.kvh, lane);
 #pragma unroll
         for (int jt = 0; jt < TL::NV; ++jt) st.acc[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
         st.m = -INFINITY;
         st.l = 0.f;
 
-        const int32_t *row_c = d.table + (size_t)ri_c.seq * d.row_stride;
-        const int32_t *row_n = d.table + (size_t)ri_n.seq * d.row_stride;
-        // whether this lane's column is a query of the row at all
-        const bool col_live = n < g && col.tok < ri_c.ntok;
+        const int32_t *row_c = d.table + (size_t)__builtin_amdgcn_readfirstlane(cur.seq) * d.row_stride;
+        const int32_t *row_n = d.table + (size_t)seq_n * d.row_stride;
+        const bool col_live = column_live(d, n);
         const int n_live = cur.n_pages > 0 ? cur.pe - cur.pb : 0;       // pages to read and process
         const int n_next = (nxt.valid && nxt.n_pages > 0) ? nxt.pe - nxt.pb : 0;
         const int n_pairs = n_live > 0 ? (n_live + 1) >> 1 : 1;         // an empty segment still takes a turn
@@ -748,7 +725,7 @@ __device__ __forceinline__ void attn_wave(const AttnDesc &d, const AttnTune &w, 
         }
 
         // --- the piece is done: finish the segment or park a partial
-        float *out_row = d.out + ((size_t)(ri_c.q0 + col.tok) * d.Hq + cur.kvh * d.g + col.head) * D;
+        float *out_row = d.out + ((size_t)cur.seq * d.Hq + cur.kvh * g + n) * D;
         if (cur.n_pages == 0) {                  // empty context: the row is defined as zero
             if (cur.pb == 0 && col_live) {
 #pragma unroll
@@ -796,7 +773,6 @@ __device__ __forceinline__ void attn_wave(const AttnDesc &d, const AttnTune &w, 
             }
         }
         cur = nxt;
-        ri_c = ri_n;
 #pragma unroll
         for (int j = 0; j < TL::NK; ++j) qf[j] = qn[j];
     }

@@ -223,34 +223,20 @@ __device__ __forceinline__ void append_rows_e4m3(uint8_t *tile, float *scale_p, 
         }
 }
 
-// kv_append: one wave per (sequence, kv head).  Without a chunk list it writes the token with
-// index ctx_lens[seq] - 1 from row `seq` of k_new / v_new (bf16 [batch][Hkv][D]).  With one
-// (d.vmap: per unit {first row of the sequence's new tokens, their number, sequence, which of the
-// pages they touch}) it writes the sequence's new tokens at indices ctx_lens[seq] - tokens ..
-// ctx_lens[seq] - 1 from consecutive rows, each exactly as a single append would (the e4m3 scale
-// rule is sequential within a block by definition).
+// Decode step: one wave per (sequence, kv head) writes the token with index ctx_lens[seq] - 1 from row `seq` of
+// k_new / v_new (bf16 [batch][Hkv][D]).  Chunk: the sequence's new tokens, at indices ctx_lens[seq] - tokens ..
+// ctx_lens[seq] - 1, come from consecutive rows, each written exactly as a single append would; one wave per
+// (sequence, kv head, j-th page the chunk touches).  Where the chunk starts is known only here (ctx_lens is
+// device data), so the plan has one page more than the chunk can touch and a wave whose page holds none of the
+// chunk leaves.  Tokens of one page go in order (the e4m3 scale rule is sequential within a block by definition);
+// pages do not depend on each other (a block's scale starts afresh at its first slot).
 // A context length outside what the row holds is skipped and reported through the device
 // error flags (bit 1).
 template <int DT>
-__global__ __launch_bounds__(64) void k_kv_append(AttnDesc d, const uint16_t *k_new, const uint16_t *v_new) {
+__device__ __forceinline__ void append_unit(const AttnDesc &d, const uint16_t *k_new, const uint16_t *v_new, int h, int seq,
+                                            int first_row, int n_new, int j) {
     const int lane = threadIdx.x;
-    const int unit = blockIdx.x / d.Hkv, h = blockIdx.x - unit * d.Hkv;
     const int D = d.D;
-    // decode step: one wave per (sequence, kv head), one token.  Chunk: one wave per (sequence, kv
-    // head, j-th page the chunk touches); where the chunk starts is known only here (ctx_lens is
-    // device data), so the host lists one page more than the chunk can touch and a wave whose page
-    // holds none of the chunk leaves.  Tokens of one page go in order (the e4m3 scale of a block
-    // runs over its tokens); pages do not depend on each other (a block's scale starts afresh at
-    // its first slot).
-    int seq = unit, first_row = unit, n_new = 1, j = 0;
-    if (d.vmap) {
-        const int4 e = d.vmap[unit];
-        first_row = e.x;
-        n_new = e.y;
-        seq = e.z;
-        j = e.w;
-        if (n_new == 0) return;
-    }
     const int ctx = d.ctx_lens[seq];
     const int cap = d.row_len[seq] * PKV_T;
     if (ctx < n_new || ctx < 1 || ctx > cap) {
@@ -341,6 +327,20 @@ __global__ __launch_bounds__(64) void k_kv_append(AttnDesc d, const uint16_t *k_
     }
 }
 
+template <int DT>
+__global__ __launch_bounds__(64) void k_kv_append(const AttnDesc d, const uint16_t *k_new, const uint16_t *v_new) {
+    const int seq = blockIdx.x / d.Hkv, h = blockIdx.x - seq * d.Hkv;
+    append_unit<DT>(d, k_new, v_new, h, seq, seq, 1, 0);
+}
+
+template <int DT>
+__global__ __launch_bounds__(64) void k_kv_append_chunk(const AttnDesc d, const ChunkPlan plan, const uint16_t *k_new,
+                                                        const uint16_t *v_new) {
+    const int unit = blockIdx.x / d.Hkv, h = blockIdx.x - unit * d.Hkv;
+    const PlanUnit pu = plan_find(plan, (uint32_t)unit);
+    append_unit<DT>(d, k_new, v_new, h, pu.seq, pu.row, pu.rows, pu.unit);
+}
+
 }  // namespace
 
 hipError_t pkv_launch_kv_write(const AttnDesc &d, int seq, int tok_begin, int n_tok, const void *k, const void *v,
@@ -382,6 +382,18 @@ hipError_t pkv_launch_kv_append(const AttnDesc &d, const void *k_new, const void
                            (const uint16_t *)v_new);
     else
         hipLaunchKernelGGL(k_kv_append<PKV_E4M3>, dim3(blocks), dim3(64), 0, s, d, (const uint16_t *)k_new,
+                           (const uint16_t *)v_new);
+    return hipGetLastError();
+}
+
+hipError_t pkv_launch_kv_append_chunk(const AttnDesc &d, const ChunkPlan &plan, const void *k_new, const void *v_new, hipStream_t s) {
+    const unsigned blocks = plan.s[plan.n_seqs].unit * (unsigned)d.Hkv;
+    if (blocks == 0) return hipSuccess;
+    if (d.dtype == PKV_BF16)
+        hipLaunchKernelGGL(k_kv_append_chunk<PKV_BF16>, dim3(blocks), dim3(64), 0, s, d, plan, (const uint16_t *)k_new,
+                           (const uint16_t *)v_new);
+    else
+        hipLaunchKernelGGL(k_kv_append_chunk<PKV_E4M3>, dim3(blocks), dim3(64), 0, s, d, plan, (const uint16_t *)k_new,
                            (const uint16_t *)v_new);
     return hipGetLastError();
 }

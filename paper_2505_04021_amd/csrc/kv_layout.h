@@ -38,3 +38,36 @@ __device__ __forceinline__ uint8_t *block_ptr(const AttnDesc &d, uint32_t id) {
     const uint32_t s = id - f * d.slots_div.d;
     return const_cast<uint8_t *>(d.pool_base) + (uint64_t)f * d.frame_bytes + (uint64_t)s * d.block_bytes;
 }
+
+// The unit u of a chunk launch: which sequence it belongs to (counted from plan.seq0), its number among that
+// sequence's units, the sequence's first packed row, its rows and the parts of the context its groups come in.
+struct PlanUnit {
+    int seq, unit, row, rows, parts;
+};
+
+// One read of the plan for all 64 lanes and no further memory trip: the sequence is the last one that begins at
+// or before u (sequences without units share their start with the next one).
+__device__ __forceinline__ PlanUnit plan_find(const ChunkPlan &plan, uint32_t u) {
+    static_assert(PKV_PLAN_SEQS + 1 == 128, "two entries per lane");
+    const int lane = threadIdx.x & 63, n = plan.n_seqs;
+    uint32_t unit[2], row[2];
+    int at = -1;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int i = lane + 64 * k;
+        unit[k] = plan.s[i].unit;
+        row[k] = plan.s[i].row;
+        at += __popcll(__ballot(i < n && unit[k] <= u));
+    }
+    auto pick = [&](const uint32_t *x, int i) {
+        return (uint32_t)(i < 64 ? __builtin_amdgcn_readlane((int)x[0], i & 63) : __builtin_amdgcn_readlane((int)x[1], i & 63));
+    };
+    PlanUnit r;
+    const uint32_t first = pick(row, at);
+    r.seq = plan.seq0 + at;
+    r.unit = (int)(u - pick(unit, at));
+    r.row = (int)(first & PKV_PLAN_ROWS);
+    r.rows = (int)(pick(row, at + 1) & PKV_PLAN_ROWS) - r.row;
+    r.parts = (int)(first >> PKV_PLAN_PART_SHIFT);
+    return r;
+}

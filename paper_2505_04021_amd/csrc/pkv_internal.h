@@ -82,9 +82,6 @@ struct AttnDesc {
     const int32_t *table;       // [B][row_stride]
     const int32_t *ctx_lens;    // [B]
     const int32_t *row_len;     // library table: [max_seqs] blocks reserved per row; NULL for a caller's table
-    const int4 *vmap;           // prefill launches: [groups] {sequence, first q/out row, chunk tokens after the
-                                // group, tokens in the group}; chunk append: [units] {first new row of the
-                                // sequence, its new tokens, sequence, which of the pages the chunk touches}
     float *out;                 // [B][Hq][D]
     float *ws;                  // split-K partials: two per work item (uncached memory)
     uint32_t *cnt;              // [B][Hkv] arrival counters of the split-K merge, zero between launches
@@ -95,14 +92,28 @@ struct AttnDesc {
     uint32_t max_block_id;      // n_frames * slots
     int32_t batch, row_stride;
     int32_t Hq, Hkv, g, D, dtype;
-    int32_t cols;               // MFMA columns in use per kv head: (query tokens per row) * g, at most 16 (prefill: of a
-                                // wave's tile, at most 32)
+    int32_t cols;               // prefill: MFMA columns in use of a wave's tile, (query tokens) * g, at most 32
     int32_t item_begin;         // first work item of this model in a grouped launch
     int32_t n_items;            // work items (waves) of this model
     int32_t min_share;          // smallest share of pages a wave may get
     int32_t weighted;           // items come in whole blocks of eight aligned with the XCDs
     int32_t seg_cost;           // what a segment costs besides its pages, in pages (for the split only)
     float scale_log2;           // log2(e) / sqrt(D)
+};
+
+// How a chunk call (prefill_attention, kv_append_chunk) falls into units of work, as far as the host decides it: per
+// sequence where its units and its packed rows begin.  It travels in the kernel's arguments, so a call copies
+// nothing to the device and needs no buffer; a call of more sequences is several launches.
+#define PKV_PLAN_SEQS 127
+#define PKV_PLAN_PART_SHIFT 25       // of `row`: parts of the context per group above, first packed row (at most 2^24) below
+#define PKV_PLAN_ROWS 0x1ffffffu
+#define PKV_PLAN_MAX_PARTS 64
+struct ChunkPlan {
+    int32_t n_seqs, seq0;                 // sequences seq0 .. seq0 + n_seqs - 1
+    struct {
+        uint32_t unit;                    // its first unit
+        uint32_t row;                     // its first packed row | parts of the context per group << PKV_PLAN_PART_SHIFT
+    } s[PKV_PLAN_SEQS + 1];               // [n_seqs]: the totals
 };
 
 #define PKV_MAX_GROUP 16
@@ -140,11 +151,14 @@ hipError_t pkv_launch_kv_read(const AttnDesc &d, int seq, int tok_begin, int n_t
                               hipStream_t s);
 // d.batch sequences, d.ctx_lens / d.row_len / d.table as for attention
 hipError_t pkv_launch_kv_append(const AttnDesc &d, const void *k_new, const void *v_new, hipStream_t s);
+// plan: per sequence one unit for every page its new tokens may touch
+hipError_t pkv_launch_kv_append_chunk(const AttnDesc &d, const ChunkPlan &plan, const void *k_new, const void *v_new, hipStream_t s);
 // ev: NULL or two events recorded before and after the attention kernel
 hipError_t pkv_launch_attention(const AttnGroup &grp, bool deep, hipStream_t s, hipEvent_t *ev);
 // the entry point that allocates nothing: the current device's copy of the library's scratch array
 hipError_t pkv_static_scratch(void **ptr);
 hipError_t pkv_launch_attention_static(const AttnGroup &grp, uint32_t *cnt, size_t n_cnt, hipStream_t s);
-// chunked prefill: d.vmap lists n_groups groups of up to PKV_PREFILL_WAVES * (d.cols / d.g) query tokens
-hipError_t pkv_launch_prefill(const AttnDesc &d, int n_groups, bool any_split, hipStream_t s);
+// chunked prefill: a unit is a group of up to PKV_PREFILL_WAVES * (d.cols / d.g) query tokens, or one of the parts
+// of its context; split_groups: most groups of a sequence whose groups come in parts (0: none does)
+hipError_t pkv_launch_prefill(const AttnDesc &d, const ChunkPlan &plan, int split_groups, hipStream_t s);
 hipError_t pkv_launch_stream_read(const void *src, size_t bytes, size_t granule_bytes, uint32_t *sink, hipStream_t s);

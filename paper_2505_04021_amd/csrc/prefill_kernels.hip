@@ -71,8 +71,29 @@ __device__ __forceinline__ void wait_requests(int ahead) {      // all but the `
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// One unit of the launch: the query tokens of a group (rows q0 .. q0 + ntok - 1 of the packed q and out, followed by
+// `back` more of the sequence's chunk) and which of `parts` parts of the context it walks.
+struct GroupInfo {
+    int seq, q0, ntok, back, part, parts;
+};
+
+__device__ __forceinline__ GroupInfo group_info(const AttnDesc &d, const ChunkPlan &plan, int unit) {
+    const PlanUnit pu = plan_find(plan, (uint32_t)unit);
+    const int size = PF_WAVES * (d.cols / d.g), groups = (pu.rows + size - 1) / size;
+    const int rank = pu.parts > 1 ? pu.unit / pu.parts : pu.unit;
+    const int t0 = (groups - 1 - rank) * size;
+    GroupInfo g;
+    g.seq = pu.seq;
+    g.q0 = pu.row + t0;
+    g.ntok = pu.rows - t0 < size ? pu.rows - t0 : size;
+    g.back = pu.rows - t0 - g.ntok;
+    g.parts = pu.parts;
+    g.part = pu.unit - rank * pu.parts;
+    return g;
+}
+
 template <int D, int DT>
-__global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d) {
+__global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, const ChunkPlan plan) {
     using TL = PfTile<D, DT>;
     constexpr int SLOT = 2 * TL::BYTES;                    // the K (or V) tiles of a pair
     __shared__ __align__(16) uint8_t ring[2 * PF_SLOTS * SLOT];   // K slots, then V slots
@@ -81,16 +102,18 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d) 
     const int h = lane >> 5, n = lane & 31, c16 = lane & 15, hi16 = (lane >> 4) & 1;
     const int group = blockIdx.x / d.Hkv, kvh = blockIdx.x - group * d.Hkv;
 
-    const int32_t *vm = reinterpret_cast<const int32_t *>(d.vmap + group);
-    const int seq = PKV_CONST(int32_t, vm)[0], q0 = PKV_CONST(int32_t, vm)[1], back = PKV_CONST(int32_t, vm)[2];
-    const int packed = PKV_CONST(int32_t, vm)[3];
-    // a group of few query tokens in front of a long context comes as several work-groups, each with a
-    // part of the context; they leave partial results that k_prefill_merge joins
-    const int ntok = packed & 0xff, split = (packed >> 8) & 0xfff, n_split = packed >> 20;
+    // groups of a sequence come longest context first; a group of few query tokens in front of a long context comes
+    // as several work-groups, each with a part of the context, that leave partial results for k_prefill_merge
+    const GroupInfo gi = group_info(d, plan, group);
+    const int seq = gi.seq, q0 = gi.q0, ntok = gi.ntok, split = gi.part, n_split = gi.parts;
     const int tile_tok = d.cols / d.g;                     // query tokens per wave
     const int tok = n / d.g, head = n - tok * d.g;         // this lane's column
+    // the block ids of the first 64 pairs are asked for along with the context length, not behind it
+    const int32_t *row = d.table + (size_t)seq * d.row_stride;
+    auto table_id = [&](int page) __attribute__((always_inline)) { return (uint32_t)row[page < d.row_stride ? page : d.row_stride - 1]; };
+    const uint32_t first_id = table_id(2 * lane + (w >> 1));
     // tokens the group's last query sees, never beyond what the row holds
-    int L = PKV_CONST(int32_t, d.ctx_lens)[seq] - back;
+    int L = PKV_CONST(int32_t, d.ctx_lens)[seq] - gi.back;
     const int cap = PKV_CONST(int32_t, d.row_len)[seq] * PKV_T;
     L = L < 0 ? 0 : (L > cap ? cap : L);
     const int n_pages = (L + PKV_T - 1) / PKV_T, n_pairs = (n_pages + 1) >> 1;
@@ -132,32 +155,28 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d) 
     // ---- requests.  Wave 0: K of page a, wave 1: V of page a, wave 2: K of page b, wave 3: V of page b.
     // The addresses of 64 pairs are worked out at a time, one pair per lane, and handed out by lane reads;
     // e4m3: so are the scales of both pages of 64 pairs.
-    const int32_t *row = d.table + (size_t)seq * d.row_stride;
     const bool is_v = w & 1;
     uint32_t bad = 0;
     const uint32_t lane16 = lane * 16;
     const uint32_t lds_tile = (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t *)ring + (is_v ? PF_SLOTS * SLOT : 0) +
                               (w >> 1) * TL::BYTES;
-    auto block_of = [&](int page, bool &ok) __attribute__((always_inline)) {
-        page = page < n_pages ? page : n_pages - 1;        // past the end: the last page again (masked later)
-        page = page < d.row_stride ? page : d.row_stride - 1;
-        uint32_t id = (uint32_t)row[page];
-        ok = id < d.max_block_id;
-        if (!ok) id = 0;
+    // a page past the end of the context, or an id outside the pool, is never dereferenced: zeros stand in
+    auto block_of = [&](int page, uint32_t id, uint64_t offset) __attribute__((always_inline)) {
+        const bool in_pool = id < d.max_block_id;
+        const bool live = page < n_pages;
+        bad |= live && !in_pool ? 1u : 0u;
         const uint32_t f = fastdiv_div(id, d.slots_div);
         const uint32_t sl = id - f * d.slots_div.d;
-        return d.pool_base + (uint64_t)f * d.frame_bytes + (uint64_t)sl * d.block_bytes;
+        const uint8_t *blk = d.pool_base + (uint64_t)f * d.frame_bytes + (uint64_t)sl * d.block_bytes + offset;
+        return live && in_pool ? blk : reinterpret_cast<const uint8_t *>(d.safe);
     };
+    const uint64_t tile_offset = (DT == PKV_E4M3 ? PKV_FP8_HEADER : 0) + ((uint64_t)kvh * 2 + (is_v ? 1 : 0)) * TL::BYTES;
     uint32_t addr_lo = 0, addr_hi = 0;
     int addr_win = 0;
     auto load_addr = [&](int p) __attribute__((always_inline)) {
         addr_win = p;
-        bool ok;
-        const uint8_t *blk = block_of(2 * (p + lane) + (w >> 1), ok);
-        // an id outside the pool is never dereferenced: a zeroed spare tile stands in
-        bad |= ok ? 0u : 1u;
-        const uint8_t *src = ok ? blk + (DT == PKV_E4M3 ? PKV_FP8_HEADER : 0) + ((size_t)kvh * 2 + (is_v ? 1 : 0)) * TL::BYTES
-                                : reinterpret_cast<const uint8_t *>(d.safe);
+        const int page = 2 * (p + lane) + (w >> 1);
+        const uint8_t *src = block_of(page, p == 0 ? first_id : table_id(page), tile_offset);
         addr_lo = (uint32_t)(uintptr_t)src;
         addr_hi = (uint32_t)((uintptr_t)src >> 32);
         asm volatile("" ::"v"(addr_lo), "v"(addr_hi));     // waited for here, not where they are used
@@ -177,10 +196,10 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d) 
         if (DT != PKV_E4M3) return;
         if (p - scale_win >= 64) {
             scale_win = p;
-            bool oka, okb;
-            const uint8_t *a = block_of(2 * (p + lane), oka), *b = block_of(2 * (p + lane) + 1, okb);
-            const float *ha = reinterpret_cast<const float *>(oka ? a : reinterpret_cast<const uint8_t *>(d.safe));
-            const float *hb = reinterpret_cast<const float *>(okb ? b : reinterpret_cast<const uint8_t *>(d.safe));
+            const int page = 2 * (p + lane);
+            const uint32_t ida = table_id(page), idb = table_id(page + 1);
+            const float *ha = reinterpret_cast<const float *>(block_of(page, ida, 0));
+            const float *hb = reinterpret_cast<const float *>(block_of(page + 1, idb, 0));
             w_ska = ha[kvh]; w_sva = ha[d.Hkv + kvh];
             w_skb = hb[kvh]; w_svb = hb[d.Hkv + kvh];
             asm volatile("" ::"v"(w_ska), "v"(w_sva), "v"(w_skb), "v"(w_svb));
@@ -445,54 +464,79 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d) 
     if (__any(bad != 0) && lane == 0) atomicOr(d.err, 1u);
 }
 
-// Joins the parts of a group whose context was walked by several work-groups of k_prefill: one
-// work-group per (first part of such a group, kv head, wave tile of 32 columns); the parts are consecutive
-// rows of d.vmap.  out = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i with M = max_i m_i, per column.
-__global__ __launch_bounds__(256) void k_prefill_merge(const AttnDesc d) {
-    const int tile = blockIdx.x % PF_WAVES, rk = blockIdx.x / PF_WAVES;
-    const int row = rk / d.Hkv, kvh = rk - row * d.Hkv;
-    const int4 e = d.vmap[row];
-    const int split = (e.w >> 8) & 0xfff, n_split = e.w >> 20, ntok = e.w & 0xff;
-    if (n_split <= 1 || split != 0) return;
-    const int D = d.D, tile_tok = d.cols / d.g, stride = D + 4;       // D sums, the reference point, the denominator, two unused (16-byte rows)
-    const int quads = D / 4;
-    for (int i = threadIdx.x; i < PF_COLS * quads; i += blockDim.x) {
-        const int n = i / quads, dq = i - n * quads;
-        const int c = tile * PF_COLS + n;
-        const int tok = n / d.g, head = n - tok * d.g;
-        const int t0 = tile * tile_tok;
-        if (n >= d.cols || t0 + tok >= ntok) continue;            // a column without a query
-        float M = PF_M0;
-        for (int s = 0; s < n_split; ++s) {
-            const float *part = d.ws + (((size_t)(row + s) * d.Hkv + kvh) * PKV_PREFILL_COLS + c) * stride;
-            M = fmaxf(M, part[D]);
-        }
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        float den = 0.f;
-        for (int s = 0; s < n_split; ++s) {
-            const float *part = d.ws + (((size_t)(row + s) * d.Hkv + kvh) * PKV_PREFILL_COLS + c) * stride;
-            const float f = __builtin_amdgcn_exp2f(part[D] - M);
-            den += f * part[D + 1];
-            acc += *reinterpret_cast<const f32x4 *>(part + 4 * dq) * f;
-        }
-        const float inv = den > 0.f ? 1.0f / den : 0.f;
-        float *out_row = d.out + ((size_t)(e.y + t0 + tok) * d.Hq + kvh * d.g + head) * D;
-        *reinterpret_cast<f32x4 *>(out_row + 4 * dq) = acc * inv;
+// Joins the parts of a group whose context was walked by several work-groups of k_prefill (consecutive units):
+// out = sum_i 2^(m_i - M) acc_i / sum_i 2^(m_i - M) l_i with M = max_i m_i, per column.  One work-group per eight
+// columns, 32 lanes a column.  Bound by memory round trips: all maxima and denominators of a column travel at once,
+// its sums eight parts a trip (one part after the other, 32 parts of one group took 80 of a call's 101 us).
+constexpr int MERGE_COLS = 8;
+
+__global__ __launch_bounds__(32 * MERGE_COLS) void k_prefill_merge(const AttnDesc d, const ChunkPlan plan) {
+    __shared__ float s_f[MERGE_COLS][PKV_PLAN_MAX_PARTS];
+    constexpr int BLOCKS = PKV_PREFILL_COLS / MERGE_COLS;
+    const int sub = threadIdx.x & 31, cc = threadIdx.x >> 5;
+    const int x = blockIdx.x / BLOCKS, rank = x / d.Hkv, kvh = x - rank * d.Hkv;
+    const int c = (blockIdx.x - x * BLOCKS) * MERGE_COLS + cc;
+    const uint32_t first = plan.s[blockIdx.y].row;
+    const int parts = (int)(first >> PKV_PLAN_PART_SHIFT), row0 = (int)(first & PKV_PLAN_ROWS);
+    const int rows = (int)(plan.s[blockIdx.y + 1].row & PKV_PLAN_ROWS) - row0;
+    const int tile_tok = d.cols / d.g, size = PF_WAVES * tile_tok, groups = (rows + size - 1) / size;
+    if (parts <= 1 || rank >= groups) return;
+    const int t0 = (groups - 1 - rank) * size;
+    const int n = c & (PF_COLS - 1), tok = t0 + (c / PF_COLS) * tile_tok + n / d.g;      // this column's query token
+    if (__syncthreads_or(n < d.cols && tok < rows) == 0) return;
+    const int D = d.D, stride = D + 4;       // D sums, the reference point, the denominator, two unused (16-byte rows)
+    const size_t step = (size_t)d.Hkv * PKV_PREFILL_COLS * stride;
+    const float *part = d.ws + (((size_t)plan.s[blockIdx.y].unit + (size_t)rank * parts) * d.Hkv + kvh) * PKV_PREFILL_COLS * stride + (size_t)c * stride;
+    float m[2], l[2], M = PF_M0;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int i = sub + 32 * k;
+        m[k] = i < parts ? part[i * step + D] : PF_M0;
+        l[k] = i < parts ? part[i * step + D + 1] : 0.f;
+        M = fmaxf(M, m[k]);
     }
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
+    float den = 0.f;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int i = sub + 32 * k;
+        const float f = i < parts ? __builtin_amdgcn_exp2f(m[k] - M) : 0.f;
+        s_f[cc][i] = f;
+        den += f * l[k];
+    }
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) den += __shfl_xor(den, o);
+    __syncthreads();
+    if (n >= d.cols || tok >= rows || 4 * sub >= D) return;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int i0 = 0; i0 < parts; i0 += 8) {
+        f32x4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const f32x4 *>(part + (i0 + u < parts ? i0 + u : parts - 1) * step + 4 * sub);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (i0 + u < parts) acc += v[u] * s_f[cc][i0 + u];
+    }
+    const float inv = den > 0.f ? 1.0f / den : 0.f;
+    *reinterpret_cast<f32x4 *>(d.out + ((size_t)(row0 + tok) * d.Hq + kvh * d.g + (n - (n / d.g) * d.g)) * D + 4 * sub) = acc * inv;
 }
 
 }  // namespace
 
-hipError_t pkv_launch_prefill(const AttnDesc &d, int n_groups, bool any_split, hipStream_t s) {
-    if (n_groups == 0) return hipSuccess;
-    const dim3 grid((unsigned)(n_groups * d.Hkv)), wg(64 * PF_WAVES);
+hipError_t pkv_launch_prefill(const AttnDesc &d, const ChunkPlan &plan, int split_groups, hipStream_t s) {
+    const uint32_t units = plan.s[plan.n_seqs].unit;
+    if (units == 0) return hipSuccess;
+    const dim3 grid(units * (unsigned)d.Hkv), wg(64 * PF_WAVES);
     if (d.dtype == PKV_BF16) {
-        if (d.D == 128) hipLaunchKernelGGL((k_prefill<128, PKV_BF16>), grid, wg, 0, s, d);
-        else hipLaunchKernelGGL((k_prefill<64, PKV_BF16>), grid, wg, 0, s, d);
+        if (d.D == 128) hipLaunchKernelGGL((k_prefill<128, PKV_BF16>), grid, wg, 0, s, d, plan);
+        else hipLaunchKernelGGL((k_prefill<64, PKV_BF16>), grid, wg, 0, s, d, plan);
     } else {
-        if (d.D == 128) hipLaunchKernelGGL((k_prefill<128, PKV_E4M3>), grid, wg, 0, s, d);
-        else hipLaunchKernelGGL((k_prefill<64, PKV_E4M3>), grid, wg, 0, s, d);
+        if (d.D == 128) hipLaunchKernelGGL((k_prefill<128, PKV_E4M3>), grid, wg, 0, s, d, plan);
+        else hipLaunchKernelGGL((k_prefill<64, PKV_E4M3>), grid, wg, 0, s, d, plan);
     }
-    if (any_split) hipLaunchKernelGGL(k_prefill_merge, dim3((unsigned)(n_groups * d.Hkv * PF_WAVES)), dim3(256), 0, s, d);
+    if (split_groups > 0)
+        hipLaunchKernelGGL(k_prefill_merge, dim3((unsigned)(split_groups * d.Hkv * (PKV_PREFILL_COLS / MERGE_COLS)), (unsigned)plan.n_seqs),
+                           dim3(32 * MERGE_COLS), 0, s, d, plan);
     return hipGetLastError();
 }

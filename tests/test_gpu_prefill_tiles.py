@@ -28,3 +28,22 @@ def test_prefill_tile_edges(gpu, oracle, g, hkv, d, dtype, long):  # noqa: F811
     assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
     assert row_rel_err(out_g, out_o) <= TOL[dtype]
     t.close()
+
+
+@pytest.mark.parametrize("n,dtype", [(127, BF16), (128, E4M3), (131, BF16), (260, E4M3)])
+def test_chunk_of_many_sequences(gpu, oracle, n, dtype):  # noqa: F811
+    """Around 127 sequences, what the plan of one launch holds: a chunk of 0 to 3 tokens for each is appended, then attends."""
+    hq, hkv, d = 4, 1, 64
+    ctx = [3 + (5 * s) % 37 for s in range(n)]
+    qlen = [(s * 7 + 3) % 4 for s in range(n)]
+    t = Twin(gpu, oracle, hq, hkv, d, dtype, ctx, max_blocks=8)
+    g = gen.generator(37, n)
+    k, v = (gen.randn_bf16((sum(qlen), hkv, d), g) for _ in range(2))
+    for be, m in zip(t.be, t.models):
+        assert be.kv_append_chunk(m, k, v, qlen, ctx) == sum(qlen)
+    q = gen.queries((41, n), sum(qlen), hq, d)
+    rc_o, out_o = oracle.prefill_attention(t.models[1], q, qlen, ctx)
+    rc_g, out_g = gpu.prefill_attention(t.models[0], q, qlen, ctx)
+    assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
+    assert row_rel_err(out_g, out_o) <= TOL[dtype]
+    t.close()
