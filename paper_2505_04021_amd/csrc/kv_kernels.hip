@@ -4,44 +4,11 @@
 // Paper: Sec. 4.2, D2 — a growing sequence takes its next token block from the slots of
 // its model's pages; these kernels put K and V of the new tokens into that block, in the
 // operand order the attention kernels read (kv_layout.h).
-#include "kv_layout.h"
+#include "mfma_util.h"
+
+#include <type_traits>
 
 namespace {
-
-// kv_write: logical [n_tok][Hkv][D] -> the in-block operand layouts.
-// One lane per (token, kv head, element); K and V handled together.
-template <int DT>
-__global__ void k_kv_write(AttnDesc d, const int32_t *row, int tok_begin, int n_tok, const uint8_t *k,
-                           const uint8_t *v, const float *ks, const float *vs) {
-    constexpr int E = DT == PKV_BF16 ? 2 : 1;
-    const int D = d.D, Hkv = d.Hkv;
-    const int64_t total = (int64_t)n_tok * Hkv * D;
-    const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (idx >= total) return;
-    const int dd = (int)(idx % D);
-    const int h = (int)((idx / D) % Hkv);
-    const int ti = (int)(idx / ((int64_t)D * Hkv));
-    const int tok = tok_begin + ti;
-    const int page = tok / PKV_T, t = tok % PKV_T;
-    uint8_t *blk = block_ptr(d, (uint32_t)row[page]);
-    if (DT == PKV_E4M3) {
-        if (dd == 0) {
-            const int srow = page - tok_begin / PKV_T;
-            reinterpret_cast<float *>(blk)[h] = ks[(size_t)srow * Hkv + h];
-            reinterpret_cast<float *>(blk)[Hkv + h] = vs[(size_t)srow * Hkv + h];
-        }
-        blk += PKV_FP8_HEADER;
-    }
-    const size_t tile = (size_t)PKV_T * D * E;
-    uint8_t *kt = blk + (size_t)h * 2 * tile, *vt = kt + tile;
-    if (DT == PKV_BF16) {
-        reinterpret_cast<uint16_t *>(kt)[k_elem_off<DT>(t, dd)] = reinterpret_cast<const uint16_t *>(k)[idx];
-        reinterpret_cast<uint16_t *>(vt)[v_elem_off<DT>(t, dd)] = reinterpret_cast<const uint16_t *>(v)[idx];
-    } else {
-        kt[k_elem_off<DT>(t, dd)] = k[idx];
-        vt[v_elem_off<DT>(t, dd)] = v[idx];
-    }
-}
 
 // kv_read: the inverse gather, plus the scale of each token's block.
 template <int DT>
@@ -155,190 +122,401 @@ __device__ __forceinline__ void append_row_e4m3(uint8_t *tile, float *scale_p, i
     }
 }
 
-// Several consecutive K or V rows of one page of an e4m3 model (slots slot0 .. slot0 + n - 1), with the
-// same outcome, bit for bit, as append_row_e4m3 called for each in turn.  What those calls exchange
-// through memory — the block's scale, the codes of the slots before — is held on chip here: the new rows
-// and the codes the page already holds are fetched in one go, the rows are then taken in order (the scale
-// rule is sequential by definition) with the page's codes in LDS, and codes and scale are written once.
-// A lane only ever touches its own columns (lane and lane + 64), so the LDS arrays need no barrier.
-template <bool IS_V>
-__device__ __forceinline__ void append_rows_e4m3(uint8_t *tile, float *scale_p, int slot0, int n, int D, const uint16_t *x_bf16,
-                                                 size_t row_stride, int lane, float (*sx)[128], uint8_t (*sc)[128]) {
-    auto off = [&](int t, int dd) { return IS_V ? v_elem_off<PKV_E4M3>(t, dd) : k_elem_off<PKV_E4M3>(t, dd); };
-    for (int t = 0; t < n; ++t)
+
+// ---- whole pages -----------------------------------------------------------------------------------
+// One wave writes consecutive tokens of one page (slots s0 .. s0 + n - 1) into the K or the V tile of one kv head, in
+// whole 16-byte units.  Lane layout of all of it: token t = lane & 15, column group c = lane >> 4, so that a wave's
+// store is one contiguous KiB.  Bound by memory: every byte of the source is read once and every unit written once
+// (kv_write of 8192 tokens of 8 heads x 128 in bf16, 67 MB: 32 us element by element with 2-byte stores).  A V unit holds four consecutive
+// tokens: the four lanes of a quad hold one token each, and exchange elements by quad broadcasts.
+
+struct PageRows {           // where the tokens come from and go to
+    const uint8_t *src;     // first token's row of this head
+    size_t stride;          // bytes from token to token
+    int s0, n;              // slots written
+    bool aligned;           // src may be read in 16-byte pieces
+};
+
+// N bytes of slot t's row from byte `at`; zeros for a slot that is not written.
+template <int N, int E>
+__device__ __forceinline__ void row_bytes(uint32_t *w, const PageRows &p, int t, int at) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int dd = lane + 64 * i;
-            if (dd < D) sx[slot0 + t][dd] = bf16_bits_to_float(x_bf16[(size_t)t * row_stride + dd]);
+    for (int i = 0; i < N / 4; ++i) w[i] = 0u;
+    if (t < p.s0 || t >= p.s0 + p.n) return;
+    const uint8_t *q = p.src + (size_t)(t - p.s0) * p.stride + at;
+    if (p.aligned) {
+        if constexpr (N == 16) {
+            const u32x4 v = *reinterpret_cast<const u32x4 *>(q);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = v[i];
+        } else if constexpr (N == 8) {
+            const u32x2 v = *reinterpret_cast<const u32x2 *>(q);
+            w[0] = v.x;
+            w[1] = v.y;
+        } else {
+            w[0] = *reinterpret_cast<const uint32_t *>(q);
         }
-    float scale = 1.0f;
-    if (slot0 > 0) {
-        scale = *scale_p;
-        for (int t = 0; t < slot0; ++t)
+    } else {
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int dd = lane + 64 * i;
-                if (dd < D) sc[t][dd] = tile[off(t, dd)];
-            }
-    }
-    int first_changed = slot0;                       // slots below it still hold what memory holds
-    for (int slot = slot0; slot < slot0 + n; ++slot) {
-        float x[2];
-        float amax = 0.f;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int dd = lane + 64 * i;
-            x[i] = dd < D ? sx[slot][dd] : 0.f;
-            amax = fmaxf(amax, fabsf(x[i]));
-        }
-        amax = wave_max(amax);
-        const float cand = __fdiv_rn(amax, 448.0f);
-        if (slot == 0) {
-            scale = amax > 0.f ? cand : 1.0f;
-        } else if (cand > scale) {
-            for (int t = 0; t < slot; ++t)
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int dd = lane + 64 * i;
-                    if (dd < D) {
-                        const float v = __fmul_rn(e4m3_decode(sc[t][dd]), scale);
-                        sc[t][dd] = (uint8_t)e4m3_encode(__fdiv_rn(v, cand));
-                    }
-                }
-            scale = cand;
-            first_changed = 0;
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int dd = lane + 64 * i;
-            if (dd < D) sc[slot][dd] = (uint8_t)e4m3_encode(__fdiv_rn(x[i], scale));
+        for (int i = 0; i < N / E; ++i) {
+            const uint32_t x = E == 2 ? reinterpret_cast<const uint16_t *>(q)[i] : q[i];
+            w[i * E / 4] |= x << (8 * (i * E % 4));
         }
     }
-    if (lane == 0) *scale_p = scale;
-    for (int t = first_changed; t < slot0 + n; ++t)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int dd = lane + 64 * i;
-            if (dd < D) tile[off(t, dd)] = sc[t][dd];
-        }
 }
 
-// Decode step: one wave per (sequence, kv head) writes the token with index ctx_lens[seq] - 1 from row `seq` of
-// k_new / v_new (bf16 [batch][Hkv][D]).  Chunk: the sequence's new tokens, at indices ctx_lens[seq] - tokens ..
-// ctx_lens[seq] - 1, come from consecutive rows, each written exactly as a single append would; one wave per
-// (sequence, kv head, j-th page the chunk touches).  Where the chunk starts is known only here (ctx_lens is
-// device data), so the plan has one page more than the chunk can touch and a wave whose page holds none of the
-// chunk leaves.  Tokens of one page go in order (the e4m3 scale rule is sequential within a block by definition);
-// pages do not depend on each other (a block's scale starts afresh at its first slot).
-// A context length outside what the row holds is skipped and reported through the device
-// error flags (bit 1).
+template <int R>
+__device__ __forceinline__ uint32_t quad_bcast(uint32_t x) {          // lane R of the quad, in all four
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, R * 0x55, 0xf, 0xf, true);
+}
+
+// Four lanes of a quad hold four bytes each (one token's elements d .. d + 3): lane e receives element d + e of all
+// four tokens.  Its own inverse.
+__device__ __forceinline__ uint32_t transpose_bytes(uint32_t w, int e) {
+    const uint32_t lo = 0x0c0c0400u + (uint32_t)e * 0x0101u, hi = 0x04000c0cu + (uint32_t)e * 0x01010000u;
+    return __builtin_amdgcn_perm(quad_bcast<1>(w), quad_bcast<0>(w), lo) | __builtin_amdgcn_perm(quad_bcast<3>(w), quad_bcast<2>(w), hi);
+}
+
+// The same for four 16-bit elements in two words.
+__device__ __forceinline__ u32x2 transpose_halves(uint32_t w0, uint32_t w1, int e) {
+    // (all broadcasts first: a conditional one would run without the lanes it reads from)
+    const uint32_t a0 = quad_bcast<0>(w0), a1 = quad_bcast<1>(w0), a2 = quad_bcast<2>(w0), a3 = quad_bcast<3>(w0);
+    const uint32_t b0 = quad_bcast<0>(w1), b1 = quad_bcast<1>(w1), b2 = quad_bcast<2>(w1), b3 = quad_bcast<3>(w1);
+    const bool up = e & 2;
+    const uint32_t z0 = up ? b0 : a0, z1 = up ? b1 : a1, z2 = up ? b2 : a2, z3 = up ? b3 : a3;
+    const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+    return mk2(__builtin_amdgcn_perm(z1, z0, sel), __builtin_amdgcn_perm(z3, z2, sel));
+}
+
+// Bytes of a V unit's token group that belong to slots first .. last - 1: of the word with one byte per token (e4m3) ...
+__device__ __forceinline__ uint32_t slot_bytes(int group, int first, int last) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) m |= (4 * group + k >= first && 4 * group + k < last) ? 0xffu << (8 * k) : 0u;
+    return m;
+}
+// ... and of the two words with two tokens each (bf16).
+__device__ __forceinline__ u32x2 slot_halves(int group, int first, int last) {
+    uint32_t m[2] = {0, 0};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) m[k >> 1] |= (4 * group + k >= first && 4 * group + k < last) ? 0xffffu << (16 * (k & 1)) : 0u;
+    return mk2(m[0], m[1]);
+}
+
+__device__ __forceinline__ u32x4 blend(u32x4 neu, u32x4 old, u32x4 mask) { return (neu & mask) | (old & ~mask); }
+
+// bf16 values into a bf16 tile
+template <int D, bool IS_V>
+__device__ __forceinline__ void page_bf16(uint8_t *tile, const PageRows &p) {
+    const int lane = threadIdx.x & 63, t = lane & 15, c = lane >> 4, G = t >> 2, e = t & 3;
+    if constexpr (!IS_V) {
+#pragma unroll
+        for (int i = 0; i < D / 32; ++i) {
+            uint32_t w[4];
+            row_bytes<16, 2>(w, p, t, 16 * (4 * i + c));
+            if (t >= p.s0 && t < p.s0 + p.n) *reinterpret_cast<u32x4 *>(tile + ((4 * i + c) * 16 + t) * 16) = mk4(w[0], w[1], w[2], w[3]);
+        }
+    } else {
+        const u32x2 m = slot_halves(G, p.s0, p.s0 + p.n);
+        const bool any = (m.x | m.y) != 0u, whole = (m.x & m.y) == 0xffffffffu;
+#pragma unroll
+        for (int jp = 0; jp < D / 32; ++jp) {
+            uint32_t a[2], b[2];
+            row_bytes<8, 2>(a, p, t, 2 * (32 * jp + 4 * c));
+            row_bytes<8, 2>(b, p, t, 2 * (32 * jp + 16 + 4 * c));
+            const u32x2 ta = transpose_halves(a[0], a[1], e), tb = transpose_halves(b[0], b[1], e);
+            u32x4 *unit = reinterpret_cast<u32x4 *>(tile + ((jp * 4 + G) * 16 + 4 * c + e) * 16);
+            u32x4 v = mk4(ta.x, ta.y, tb.x, tb.y);
+            if (any) {
+                if (!whole) v = blend(v, *unit, mk4(m.x, m.y, m.x, m.y));
+                *unit = v;
+            }
+        }
+    }
+}
+
+// e4m3 codes as they are into an e4m3 tile
+template <int D, bool IS_V>
+__device__ __forceinline__ void page_codes(uint8_t *tile, const PageRows &p) {
+    const int lane = threadIdx.x & 63, t = lane & 15, c = lane >> 4, G = t >> 2, e = t & 3;
+    const uint32_t m = slot_bytes(G, p.s0, p.s0 + p.n);
+#pragma unroll
+    for (int j = 0; j < D / 64; ++j) {
+        uint32_t w[4];
+        if constexpr (!IS_V) {
+            row_bytes<8, 1>(w, p, t, 8 * (8 * j + c));
+            row_bytes<8, 1>(w + 2, p, t, 8 * (8 * j + 4 + c));
+            if (t >= p.s0 && t < p.s0 + p.n) *reinterpret_cast<u32x4 *>(tile + ((j * 4 + c) * 16 + t) * 16) = mk4(w[0], w[1], w[2], w[3]);
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                row_bytes<4, 1>(w + u, p, t, 64 * j + 16 * u + 4 * c);
+                w[u] = transpose_bytes(w[u], e);
+            }
+            u32x4 *unit = reinterpret_cast<u32x4 *>(tile + ((j * 4 + G) * 16 + 4 * c + e) * 16);
+            u32x4 v = mk4(w[0], w[1], w[2], w[3]);
+            if (m) {
+                if (m != 0xffffffffu) v = blend(v, *unit, mk4(m, m, m, m));
+                *unit = v;
+            }
+        }
+    }
+}
+
+// Four values over one scale as e4m3 codes, bit for bit e4m3_encode(v / scale) with the correctly rounded quotient.
+// The quotient is first taken between two products, v * lo and v * hi with lo < 1 / scale < hi (2^-21 either side of
+// v_rcp_f32, which is within 2^-23): where both round to the same code the exact quotient does too (rounding is
+// monotonic; the conversion instruction equals e4m3_encode for every float below 464 in magnitude, checked on all of
+// them).  Where they differ, or the code is a NaN, or the scale is out of the range in which this holds, the division is
+// done: a word in some thousand.
+struct Divisor {
+    float scale, lo, hi;
+    bool plain;             // the scale is small or large: always divide
+};
+__device__ __forceinline__ Divisor divisor(float scale) {
+    const float r = __builtin_amdgcn_rcpf(scale);
+    return Divisor{scale, r * (1.0f - 0x1p-21f), r * (1.0f + 0x1p-21f), !(scale > 0x1p-100f && scale < 0x1p100f)};
+}
+__device__ __forceinline__ uint32_t encode4(float a, float b, float c, float d, const Divisor &s) {
+    int x = __builtin_amdgcn_cvt_pk_fp8_f32(a * s.lo, b * s.lo, 0, false);
+    x = __builtin_amdgcn_cvt_pk_fp8_f32(c * s.lo, d * s.lo, x, true);
+    int y = __builtin_amdgcn_cvt_pk_fp8_f32(a * s.hi, b * s.hi, 0, false);
+    y = __builtin_amdgcn_cvt_pk_fp8_f32(c * s.hi, d * s.hi, y, true);
+    const bool odd = s.plain || x != y || (((x & 0x7f7f7f7f) + 0x01010101) & 0x80808080) != 0;
+    if (__any(odd)) {
+        const uint32_t z = e4m3_encode(__fdiv_rn(a, s.scale)) | e4m3_encode(__fdiv_rn(b, s.scale)) << 8 |
+                           e4m3_encode(__fdiv_rn(c, s.scale)) << 16 | e4m3_encode(__fdiv_rn(d, s.scale)) << 24;
+        return odd ? z : (uint32_t)x;
+    }
+    return (uint32_t)x;
+}
+
+// bf16 values into an e4m3 tile under its running scale, with the outcome, bit for bit, of append_row_e4m3 called for
+// each token in turn.  The scale after a token is the largest amax / 448 so far, so all 16 are known at once from one
+// prefix maximum; a token is encoded under the scale of its own step and then re-encoded at every later step that raises
+// the scale (for 16 like tokens between two and three times).  Bound by the vector instructions of that: 8 x 512 tokens
+// of 8 heads x 128, K and V: 64 us with the tokens one after the other, a wave maximum through LDS and two divisions an
+// element each; 20 us so.
+template <int D, bool IS_V>
+__device__ __forceinline__ void page_quantise(uint8_t *tile, float *scale_p, const PageRows &p) {
+    constexpr int NW = D / 16;                           // words of codes per lane
+    const int lane = threadIdx.x & 63, t = lane & 15, c = lane >> 4, G = t >> 2, e = t & 3;
+    const int s0 = p.s0, end = p.s0 + p.n;
+    uint32_t x[2 * NW];                                  // this lane's values, two per word
+#pragma unroll
+    for (int i = 0; i < D / 64; ++i) {
+        if constexpr (!IS_V) {                           // elements of units (i, c): 8 (8 i + c) .. + 7 and 8 (8 i + 4 + c) .. + 7
+            row_bytes<16, 2>(x + 8 * i, p, t, 16 * (8 * i + c));
+            row_bytes<16, 2>(x + 8 * i + 4, p, t, 16 * (8 * i + 4 + c));
+        } else {                                         // elements 64 i + 16 u + 4 c .. + 3
+#pragma unroll
+            for (int u = 0; u < 4; ++u) row_bytes<8, 2>(x + 8 * i + 2 * u, p, t, 2 * (64 * i + 16 * u + 4 * c));
+        }
+    }
+    // what the tile holds: codes of the slots before, and (V: units hold four tokens) bytes that must stay
+    u32x4 old[D / 64];
+    const bool keeps = s0 > 0 || (IS_V && end < PKV_T);
+    u32x4 *unit = reinterpret_cast<u32x4 *>(tile + (IS_V ? (G * 16 + 4 * c + e) * 16 : (c * 16 + t) * 16));
+    if (keeps) {
+#pragma unroll
+        for (int i = 0; i < D / 64; ++i) old[i] = unit[64 * i];
+    }
+    const float kept_scale = s0 > 0 ? *scale_p : 1.0f;
+    float amax = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2 * NW; ++i)
+        amax = fmaxf(fmaxf(amax, fabsf(__uint_as_float(x[i] << 16))), fabsf(__uint_as_float(x[i] & 0xffff0000u)));
+    amax = rows_max(amax);                               // over the four column groups: lanes t, t + 16, t + 32, t + 48
+    const float cand = __fdiv_rn(amax, 448.0f);
+    // largest candidate up to this token, from the first new one on
+    float top = t >= s0 && t < end ? cand : 0.f;
+    auto up = [&](float v, int ctrl) __attribute__((always_inline)) {
+        int r;
+        switch (ctrl) {                                  // row_shr:n, zeros shifted in
+            case 1: r = __builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x111, 0xf, 0xf, false); break;
+            case 2: r = __builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x112, 0xf, 0xf, false); break;
+            case 4: r = __builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x114, 0xf, 0xf, false); break;
+            default: r = __builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x118, 0xf, 0xf, false); break;
+        }
+        return __uint_as_float((uint32_t)r);
+    };
+    top = fmaxf(top, up(top, 1));
+    top = fmaxf(top, up(top, 2));
+    top = fmaxf(top, up(top, 4));
+    top = fmaxf(top, up(top, 8));
+    auto of_lane = [&](float v, int l) __attribute__((always_inline)) {
+        return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), l));
+    };
+    // slot 0 starts afresh: the scale of its token, 1 if that is all zero; else the scale the block has
+    const float amax0 = of_lane(amax, 0), start = s0 > 0 ? kept_scale : (amax0 > 0.f ? of_lane(cand, 0) : 1.0f);
+    const float scale = top > start ? top : start;       // after this lane's token
+    float before = up(scale, 1);
+    before = t == s0 ? start : before;
+    uint32_t events = (uint32_t)__ballot(t >= s0 && t > 0 && t < end && scale > before) & 0xffffu;
+    const bool raised = events != 0u;
+
+    uint32_t w[NW];
+    const Divisor own = divisor(scale);
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+        w[i] = encode4(__uint_as_float(x[2 * i] << 16), __uint_as_float(x[2 * i] & 0xffff0000u), __uint_as_float(x[2 * i + 1] << 16),
+                       __uint_as_float(x[2 * i + 1] & 0xffff0000u), own);
+    if (s0 > 0) {
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            uint32_t held = old[i / 4][i & 3];
+            if constexpr (IS_V) held = transpose_bytes(held, e);
+            w[i] = t < s0 ? held : w[i];
+        }
+    }
+    while (events) {                                     // wave-uniform; in the order of the tokens
+        const int u = __ffs((int)events) - 1;
+        events &= events - 1u;
+        const float was = of_lane(before, u);
+        const Divisor now = divisor(of_lane(scale, u));
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[i], false), hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[i], true);
+            const uint32_t again = encode4(__fmul_rn(lo[0], was), __fmul_rn(lo[1], was), __fmul_rn(hi[0], was), __fmul_rn(hi[1], was), now);
+            w[i] = t < u ? again : w[i];
+        }
+    }
+    if (lane == 0) *scale_p = of_lane(scale, end - 1);
+    const int first = raised ? 0 : s0;                   // slots below it still hold what memory holds
+    const uint32_t m = slot_bytes(G, first, end);
+#pragma unroll
+    for (int i = 0; i < D / 64; ++i) {
+        if constexpr (!IS_V) {
+            if (t >= first && t < end) unit[64 * i] = mk4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
+        } else {
+            u32x4 v = mk4(transpose_bytes(w[4 * i], e), transpose_bytes(w[4 * i + 1], e), transpose_bytes(w[4 * i + 2], e),
+                          transpose_bytes(w[4 * i + 3], e));
+            if (keeps) v = blend(v, old[i], mk4(m, m, m, m));
+            if (m) unit[64 * i] = v;
+        }
+    }
+}
+
+// One wave's share of a page: the K (which = 0) or V (1) tile of kv head h.  QUANT: bf16 values into an e4m3 block.
+template <int DT, bool QUANT>
+__device__ __forceinline__ void page_tile(const AttnDesc &d, uint8_t *blk, int h, int which, const PageRows &p) {
+    constexpr int E = DT == PKV_BF16 ? 2 : 1;
+    uint8_t *tile = blk + (DT == PKV_E4M3 ? PKV_FP8_HEADER : 0) + ((size_t)h * 2 + which) * PKV_T * d.D * E;
+    auto go = [&](auto dim, auto is_v) __attribute__((always_inline)) {
+        constexpr int D = decltype(dim)::value;
+        constexpr bool IS_V = decltype(is_v)::value;
+        if constexpr (DT == PKV_BF16) page_bf16<D, IS_V>(tile, p);
+        else if constexpr (QUANT) page_quantise<D, IS_V>(tile, reinterpret_cast<float *>(blk) + (IS_V ? d.Hkv : 0) + h, p);
+        else page_codes<D, IS_V>(tile, p);
+    };
+    if (d.D == 128) {
+        if (which) go(std::integral_constant<int, 128>{}, std::true_type{});
+        else go(std::integral_constant<int, 128>{}, std::false_type{});
+    } else {
+        if (which) go(std::integral_constant<int, 64>{}, std::true_type{});
+        else go(std::integral_constant<int, 64>{}, std::false_type{});
+    }
+}
+
+constexpr int PAGE_WAVES = 4;       // waves of a work-group; wave x of the launch: K or V, kv head, page, fastest first
+
+// kv_write: logical [n_tok][Hkv][D] values (bf16) or codes with their scales (e4m3) -> the in-block operand layouts.
 template <int DT>
-__device__ __forceinline__ void append_unit(const AttnDesc &d, const uint16_t *k_new, const uint16_t *v_new, int h, int seq,
-                                            int first_row, int n_new, int j) {
+__global__ __launch_bounds__(64 * PAGE_WAVES) void k_kv_write(const AttnDesc d, const int32_t *row, int tok_begin, int n_tok,
+                                                              const uint8_t *k, const uint8_t *v, const float *ks, const float *vs) {
+    constexpr int E = DT == PKV_BF16 ? 2 : 1;
+    const int x = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * PAGE_WAVES + (threadIdx.x >> 6)));
+    const int which = x & 1, hp = x >> 1, j = hp / d.Hkv, h = hp - j * d.Hkv;
+    const int page = tok_begin / PKV_T + j, end = tok_begin + n_tok;
+    const int lo = page * PKV_T > tok_begin ? page * PKV_T : tok_begin, hi = (page + 1) * PKV_T < end ? (page + 1) * PKV_T : end;
+    if (lo >= hi) return;
+    uint8_t *blk = block_ptr(d, (uint32_t)row[page]);
+    const uint8_t *src = which ? v : k;
+    PageRows p;
+    p.stride = (size_t)d.Hkv * d.D * E;
+    p.src = src + (size_t)(lo - tok_begin) * p.stride + (size_t)h * d.D * E;
+    p.s0 = lo % PKV_T;
+    p.n = hi - lo;
+    p.aligned = (reinterpret_cast<uintptr_t>(src) & 15) == 0;
+    if (DT == PKV_E4M3 && (threadIdx.x & 63) == 0)
+        reinterpret_cast<float *>(blk)[(which ? d.Hkv : 0) + h] = (which ? vs : ks)[(size_t)j * d.Hkv + h];
+    page_tile<DT, false>(d, blk, h, which, p);
+}
+
+// kv_append, the decode step: one wave per (sequence, kv head) writes the token with index ctx_lens[seq] - 1 from row
+// `seq` of k_new / v_new (bf16 [batch][Hkv][D]).  A context length outside what the row holds is skipped and reported
+// through the device error flags (bit 1).
+template <int DT>
+__global__ __launch_bounds__(64) void k_kv_append(const AttnDesc d, const uint16_t *k_new, const uint16_t *v_new) {
     const int lane = threadIdx.x;
+    const int seq = blockIdx.x / d.Hkv, h = blockIdx.x - seq * d.Hkv;
     const int D = d.D;
     const int ctx = d.ctx_lens[seq];
     const int cap = d.row_len[seq] * PKV_T;
-    if (ctx < n_new || ctx < 1 || ctx > cap) {
+    if (ctx < 1 || ctx > cap) {
         if (lane == 0) atomicOr(d.err, 2u);
         return;
     }
-    const int tok0 = ctx - n_new, page_j = tok0 / PKV_T + j;
-    const int lo = tok0 > page_j * PKV_T ? tok0 : page_j * PKV_T;
-    const int hi = ctx < (page_j + 1) * PKV_T ? ctx : (page_j + 1) * PKV_T;
-    if (lo >= hi) return;
-    const uint32_t id = (uint32_t)d.table[(size_t)seq * d.row_stride + page_j];
+    const uint32_t id = (uint32_t)d.table[(size_t)seq * d.row_stride + (ctx - 1) / PKV_T];
     if (id >= d.max_block_id) {
         if (lane == 0) atomicOr(d.err, 1u);
         return;
     }
     uint8_t *blk = block_ptr(d, id);
+    const int slot = (ctx - 1) % PKV_T;
+    const uint16_t *kx = k_new + ((size_t)seq * d.Hkv + h) * D, *vx = v_new + ((size_t)seq * d.Hkv + h) * D;
     if (DT == PKV_BF16) {
-        // the elements of the page's new tokens do not depend on each other: all lanes, all tokens at once
         const size_t tile = (size_t)PKV_T * D * 2;
         uint16_t *kt = reinterpret_cast<uint16_t *>(blk + (size_t)h * 2 * tile);
         uint16_t *vt = reinterpret_cast<uint16_t *>(blk + (size_t)h * 2 * tile + tile);
-        const size_t row0 = ((size_t)(first_row + (lo - tok0)) * d.Hkv + h) * D, stride = (size_t)d.Hkv * D;
-        const int s0 = lo % PKV_T, n = hi - lo;
-        if (n >= 4 && ((reinterpret_cast<uintptr_t>(k_new) | reinterpret_cast<uintptr_t>(v_new)) & 15) == 0) {
-            // Several tokens of a chunk: whole 16-byte units.  A K unit is eight consecutive elements of
-            // one token's row, as in the source; a V unit holds four consecutive tokens of one element
-            // (8 bytes each for elements d and d + 16), gathered from four source rows.  Token groups the
-            // chunk covers only in part go element by element.
-            const int c8 = D >> 3;
-            for (int e = lane; e < n * c8; e += 64) {
-                const int t = e / c8, c = e - t * c8;
-                *reinterpret_cast<uint4 *>(kt + k_elem_off<PKV_BF16>(s0 + t, 8 * c)) =
-                    *reinterpret_cast<const uint4 *>(k_new + row0 + (size_t)t * stride + 8 * c);
-            }
-            for (int e = lane; e < 4 * D; e += 64) {
-                const int G = e / D, dd = e - G * D;
-                const int t_lo = 4 * G - s0;                       // the group's first token, counted from lo
-                if (t_lo >= 0 && t_lo + 4 <= n) {
-                    const uint16_t *src = v_new + row0 + (size_t)t_lo * stride + dd;
-                    const uint32_t a = src[0], b = src[stride], c = src[2 * stride], f = src[3 * stride];
-                    *reinterpret_cast<uint2 *>(vt + v_elem_off<PKV_BF16>(4 * G, dd)) = make_uint2(a | (b << 16), c | (f << 16));
-                } else {
-                    for (int k = 0; k < 4; ++k) {
-                        const int t = t_lo + k;
-                        if (t >= 0 && t < n) vt[v_elem_off<PKV_BF16>(4 * G + k, dd)] = v_new[row0 + (size_t)t * stride + dd];
-                    }
-                }
-            }
-            return;
+        for (int dd = lane; dd < D; dd += 64) {
+            kt[k_elem_off<PKV_BF16>(slot, dd)] = kx[dd];
+            vt[v_elem_off<PKV_BF16>(slot, dd)] = vx[dd];
         }
-        const int n_el = n * D;
-#pragma unroll 4
-        for (int e = lane; e < n_el; e += 64) {
-            const int t = e / D, dd = e - t * D;
-            const size_t src = row0 + (size_t)t * stride + dd;
-            kt[k_elem_off<PKV_BF16>(s0 + t, dd)] = k_new[src];
-            vt[v_elem_off<PKV_BF16>(s0 + t, dd)] = v_new[src];
-        }
-        return;
-    }
-    if (hi - lo > 1) {
-        // several tokens of a chunk in this page: in order, as single appends would, but in one pass
-        __shared__ float sx[PKV_T][128];
-        __shared__ uint8_t sc[PKV_T][128];
+    } else {
         float *hdr = reinterpret_cast<float *>(blk);
         const size_t tile = (size_t)PKV_T * D;
         uint8_t *kt = blk + PKV_FP8_HEADER + (size_t)h * 2 * tile, *vt = kt + tile;
-        const size_t src = ((size_t)(first_row + (lo - tok0)) * d.Hkv + h) * D, stride = (size_t)d.Hkv * D;
-        append_rows_e4m3<false>(kt, hdr + h, lo % PKV_T, hi - lo, D, k_new + src, stride, lane, sx, sc);
-        append_rows_e4m3<true>(vt, hdr + d.Hkv + h, lo % PKV_T, hi - lo, D, v_new + src, stride, lane, sx, sc);
+        append_row_e4m3<false>(kt, hdr + h, slot, D, kx, lane);
+        append_row_e4m3<true>(vt, hdr + d.Hkv + h, slot, D, vx, lane);
+    }
+}
+
+// kv_append_chunk: the sequence's new tokens, at indices ctx_lens[seq] - tokens .. ctx_lens[seq] - 1, come from
+// consecutive rows, each written exactly as a single append would; one wave per (sequence, j-th page the chunk touches,
+// kv head, K or V).  Where the chunk starts is known only here (ctx_lens is device data), so the plan has one page more
+// than the chunk can touch and a wave whose page holds none of the chunk leaves.  Tokens of one page go in order (the
+// e4m3 scale rule is sequential within a block by definition); pages do not depend on each other (a block's scale
+// starts afresh at its first slot).
+template <int DT>
+__global__ __launch_bounds__(64 * PAGE_WAVES) void k_kv_append_chunk(const AttnDesc d, const ChunkPlan plan, const uint16_t *k_new,
+                                                                     const uint16_t *v_new) {
+    const int lane = threadIdx.x & 63;
+    const int x = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * PAGE_WAVES + (threadIdx.x >> 6)));
+    const int which = x & 1, hp = x >> 1, unit = hp / d.Hkv, h = hp - unit * d.Hkv;
+    if ((uint32_t)unit >= plan.s[plan.n_seqs].unit) return;          // the last work-group may have waves to spare
+    const PlanUnit pu = plan_find(plan, (uint32_t)unit);
+    const int ctx = PKV_CONST(int32_t, d.ctx_lens)[pu.seq], cap = PKV_CONST(int32_t, d.row_len)[pu.seq] * PKV_T;
+    if (ctx < pu.rows || ctx < 1 || ctx > cap) {
+        if (lane == 0) atomicOr(d.err, 2u);
         return;
     }
-    for (int tok = lo; tok < hi; ++tok) {
-        const int i = tok - tok0, slot = tok % PKV_T;
-        const uint16_t *kx = k_new + ((size_t)(first_row + i) * d.Hkv + h) * D;
-        const uint16_t *vx = v_new + ((size_t)(first_row + i) * d.Hkv + h) * D;
-        {
-            float *hdr = reinterpret_cast<float *>(blk);
-            const size_t tile = (size_t)PKV_T * D;
-            uint8_t *kt = blk + PKV_FP8_HEADER + (size_t)h * 2 * tile, *vt = kt + tile;
-            append_row_e4m3<false>(kt, hdr + h, slot, D, kx, lane);
-            append_row_e4m3<true>(vt, hdr + d.Hkv + h, slot, D, vx, lane);
-            // the next token of the chunk may read this block's codes and scale (written by other lanes)
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
+    const int tok0 = ctx - pu.rows, page = tok0 / PKV_T + pu.unit;
+    const int lo = tok0 > page * PKV_T ? tok0 : page * PKV_T, hi = ctx < (page + 1) * PKV_T ? ctx : (page + 1) * PKV_T;
+    if (lo >= hi) return;
+    const uint32_t id = (uint32_t)PKV_CONST(int32_t, d.table)[(size_t)pu.seq * d.row_stride + page];
+    if (id >= d.max_block_id) {
+        if (lane == 0) atomicOr(d.err, 1u);
+        return;
     }
-}
-
-template <int DT>
-__global__ __launch_bounds__(64) void k_kv_append(const AttnDesc d, const uint16_t *k_new, const uint16_t *v_new) {
-    const int seq = blockIdx.x / d.Hkv, h = blockIdx.x - seq * d.Hkv;
-    append_unit<DT>(d, k_new, v_new, h, seq, seq, 1, 0);
-}
-
-template <int DT>
-__global__ __launch_bounds__(64) void k_kv_append_chunk(const AttnDesc d, const ChunkPlan plan, const uint16_t *k_new,
-                                                        const uint16_t *v_new) {
-    const int unit = blockIdx.x / d.Hkv, h = blockIdx.x - unit * d.Hkv;
-    const PlanUnit pu = plan_find(plan, (uint32_t)unit);
-    append_unit<DT>(d, k_new, v_new, h, pu.seq, pu.row, pu.rows, pu.unit);
+    const uint16_t *src = which ? v_new : k_new;
+    PageRows p;
+    p.stride = (size_t)d.Hkv * d.D * 2;
+    p.src = reinterpret_cast<const uint8_t *>(src) + (size_t)(pu.row + (lo - tok0)) * p.stride + (size_t)h * d.D * 2;
+    p.s0 = lo % PKV_T;
+    p.n = hi - lo;
+    p.aligned = (reinterpret_cast<uintptr_t>(src) & 15) == 0;
+    page_tile<DT, true>(d, block_ptr(d, id), h, which, p);
 }
 
 }  // namespace
@@ -346,15 +524,15 @@ __global__ __launch_bounds__(64) void k_kv_append_chunk(const AttnDesc d, const 
 hipError_t pkv_launch_kv_write(const AttnDesc &d, int seq, int tok_begin, int n_tok, const void *k, const void *v,
                                const float *ks, const float *vs, int page_tokens, hipStream_t s) {
     (void)page_tokens;
-    const int64_t total = (int64_t)n_tok * d.Hkv * d.D;
-    if (total == 0) return hipSuccess;
+    if (n_tok == 0) return hipSuccess;
     const int32_t *row = d.table + (size_t)seq * d.row_stride;
-    const unsigned blocks = (unsigned)((total + 255) / 256);
+    const int pages = (tok_begin + n_tok - 1) / PKV_T - tok_begin / PKV_T + 1;
+    const unsigned waves = (unsigned)pages * (unsigned)d.Hkv * 2u, blocks = (waves + PAGE_WAVES - 1) / PAGE_WAVES;
     if (d.dtype == PKV_BF16)
-        hipLaunchKernelGGL(k_kv_write<PKV_BF16>, dim3(blocks), dim3(256), 0, s, d, row, tok_begin, n_tok,
+        hipLaunchKernelGGL(k_kv_write<PKV_BF16>, dim3(blocks), dim3(64 * PAGE_WAVES), 0, s, d, row, tok_begin, n_tok,
                            (const uint8_t *)k, (const uint8_t *)v, ks, vs);
     else
-        hipLaunchKernelGGL(k_kv_write<PKV_E4M3>, dim3(blocks), dim3(256), 0, s, d, row, tok_begin, n_tok,
+        hipLaunchKernelGGL(k_kv_write<PKV_E4M3>, dim3(blocks), dim3(64 * PAGE_WAVES), 0, s, d, row, tok_begin, n_tok,
                            (const uint8_t *)k, (const uint8_t *)v, ks, vs);
     return hipGetLastError();
 }
@@ -387,13 +565,13 @@ hipError_t pkv_launch_kv_append(const AttnDesc &d, const void *k_new, const void
 }
 
 hipError_t pkv_launch_kv_append_chunk(const AttnDesc &d, const ChunkPlan &plan, const void *k_new, const void *v_new, hipStream_t s) {
-    const unsigned blocks = plan.s[plan.n_seqs].unit * (unsigned)d.Hkv;
+    const unsigned waves = plan.s[plan.n_seqs].unit * (unsigned)d.Hkv * 2u, blocks = (waves + PAGE_WAVES - 1) / PAGE_WAVES;
     if (blocks == 0) return hipSuccess;
     if (d.dtype == PKV_BF16)
-        hipLaunchKernelGGL(k_kv_append_chunk<PKV_BF16>, dim3(blocks), dim3(64), 0, s, d, plan, (const uint16_t *)k_new,
+        hipLaunchKernelGGL(k_kv_append_chunk<PKV_BF16>, dim3(blocks), dim3(64 * PAGE_WAVES), 0, s, d, plan, (const uint16_t *)k_new,
                            (const uint16_t *)v_new);
     else
-        hipLaunchKernelGGL(k_kv_append_chunk<PKV_E4M3>, dim3(blocks), dim3(64), 0, s, d, plan, (const uint16_t *)k_new,
+        hipLaunchKernelGGL(k_kv_append_chunk<PKV_E4M3>, dim3(blocks), dim3(64 * PAGE_WAVES), 0, s, d, plan, (const uint16_t *)k_new,
                            (const uint16_t *)v_new);
     return hipGetLastError();
 }

@@ -38,6 +38,19 @@ __device__ __forceinline__ u32x2 fp8x4_to_bf16x4(uint32_t w) {
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return *reinterpret_cast<bf16x8 *>(&v); }
 
+// max over the four 16-lane rows of a wave (lanes l, l^16, l^32, l^48), in every lane.
+// v_permlane32_swap exchanges the upper half of its first operand with the lower half of
+// its second, v_permlane16_swap the odd rows of the first with the even rows of the
+// second; fed the same value twice, the two results hold both partners of every lane.
+// No LDS traffic, so the step does not wait on the scalar-load / LDS counter.
+__device__ __forceinline__ float rows_max(float x) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    u2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 // max over the two 32-lane halves of a wave (lanes l and l ^ 32), in every lane: v_permlane32_swap exchanges
 // the upper half of its first operand with the lower half of its second; fed the same value twice, the two
 // results hold both partners of every lane.

@@ -1,0 +1,118 @@
+"""Bulk writes into pages (kv_append_chunk, kv_write) at the edges of a page's token groups, from sources that are not
+16-byte aligned, and with values on which the e4m3 encoding can go wrong; codes, scales and values bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from workloads import gen
+
+pytestmark = pytest.mark.gpu
+
+BF16, E4M3 = 0, 1
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    from paper_2505_04021_amd import PrismKV
+    return PrismKV()
+
+
+def one_sequence(be, tokens, hkv, d, dtype):
+    pool = be.pool_create(8 << 20, 16, 2 << 20)
+    m = be.model_register(pool, 4 * hkv, hkv, d, dtype, 2, 16)
+    assert be.balloon_resize(m, 4) == 4 and be.seq_reserve(m, 0, tokens) >= 0
+    return pool, m
+
+
+def drop(be, pool, m):
+    be.seq_release(m, 0)
+    assert be.balloon_resize(m, 0) == 0 and be.model_unregister(m) == 0 and be.pool_destroy(pool) == 0
+
+
+def hard_values(n, hkv, d, kind, seed):
+    g = gen.generator(47, seed)
+    x = torch.randn((n, hkv, d), generator=g)
+    if kind == "rising":          # every token raises the scale: re-encoding at each step
+        x = x * (1.07 ** torch.arange(n))[:, None, None]
+    elif kind == "integers":      # quotients on and near the code boundaries
+        x = torch.randint(-28, 29, (n, hkv, d), generator=g).float()
+    elif kind == "wide":          # zeros, whole zero tokens, tiny and huge values, scales out of the ordinary range
+        x = x * torch.pow(2.0, torch.randint(-40, 40, (n, 1, 1), generator=g).float())
+        x[::5] = 0.0
+        x[1::7] = x[1::7] * 2.0 ** -95
+        x[:, :, ::9] = -0.0
+    elif kind == "special":       # infinities and NaN
+        x[3::11, :, 5] = float("inf")
+        x[6::13, :, 7] = float("nan")
+    return gen.to_bf16_bits(x)
+
+
+def bits(parts):
+    return [p if p is None or p.dtype != np.float32 else p.view(np.int32) for p in parts]
+
+
+@pytest.mark.parametrize("kind", ["normal", "rising", "integers", "wide", "special"])
+@pytest.mark.parametrize("hkv,d,dtype", [(3, 128, E4M3), (2, 64, E4M3), (3, 64, BF16), (2, 128, BF16)])
+def test_chunk_equals_single_tokens(gpu, kind, hkv, d, dtype):
+    """A row filled in chunks that start and end at every position within a group of four tokens, against the same
+    tokens appended one at a time; sources at every alignment of their elements."""
+    cuts = [0, 1, 3, 16, 21, 22, 32, 39, 44, 64, 78, 79, 130, 131]
+    n = cuts[-1]
+    k, v = hard_values(n, hkv, d, kind, 1), hard_values(n, hkv, d, kind, 2)
+    got = []
+    for chunked in (True, False):
+        pool, m = one_sequence(gpu, n, hkv, d, dtype)
+        for i, (a, b) in enumerate(zip(cuts, cuts[1:])) if chunked else ((0, (t, t + 1)) for t in range(n)):
+            dev = []
+            for x in (k, v):
+                room = torch.zeros((b - a) * hkv * d + 8, dtype=torch.int16, device="cuda")
+                at = room[i % 8:i % 8 + (b - a) * hkv * d]           # 2-byte aligned only
+                at.copy_(torch.from_numpy(x[a:b].view(np.int16).reshape(-1)))
+                dev.append(at)
+            ctx = torch.tensor([b], dtype=torch.int32, device="cuda")
+            if chunked:
+                assert gpu.kv_append_chunk_dev(m, dev[0], dev[1], [b - a], ctx) == b - a
+            else:
+                assert gpu.kv_append_dev(m, dev[0], dev[1], ctx) == 1
+            torch.cuda.synchronize()
+        rc, *parts = gpu.kv_read(m, 0, 0, n)
+        assert rc == n and gpu.device_errors() == 0
+        got.append(bits(parts))
+        drop(gpu, pool, m)
+    for a, b in zip(*got):
+        assert (a is None and b is None) or np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("hkv,d,dtype", [(3, 128, E4M3), (1, 64, E4M3), (3, 64, BF16), (2, 128, BF16)])
+def test_write_then_read(gpu, hkv, d, dtype):
+    """kv_write over ranges that begin and end anywhere in a page, at every byte alignment of the source: what was written
+    reads back, what was there stays."""
+    n = 150
+    pool, m = one_sequence(gpu, n, hkv, d, dtype)
+    et = np.uint16 if dtype == BF16 else np.uint8
+    rng = np.random.RandomState(7)
+    want = [rng.randint(0, 256, (n, hkv, d)).astype(et) for _ in range(2)]
+    scale = [rng.rand(10, hkv).astype(np.float32) + 0.5 for _ in range(2)]
+    tt = torch.int16 if dtype == BF16 else torch.uint8
+
+    def write(a, b, off):
+        dev = []
+        for x in want:
+            room = torch.zeros((b - a) * hkv * d + 16, dtype=tt, device="cuda")
+            at = room[off:off + (b - a) * hkv * d].view(b - a, hkv, d)
+            at.copy_(torch.from_numpy(x[a:b].view(np.int16) if dtype == BF16 else x[a:b]))
+            dev.append(at)
+        sc = [None, None] if dtype == BF16 else [s[a // 16:(b + 15) // 16] for s in scale]
+        assert gpu.kv_write(m, 0, a, dev[0], dev[1], *sc) == b - a
+
+    write(0, n, 0)
+    for i, (a, b) in enumerate([(0, 1), (1, 4), (5, 7), (3, 18), (16, 32), (31, 33), (46, 99), (100, 147), (149, 150), (62, 150)]):
+        for x in want:
+            x[a:b] = rng.randint(0, 256, (b - a, hkv, d)).astype(et)
+        write(a, b, i % 9)
+        rc, k, v, ks, vs = gpu.kv_read(m, 0, 0, n)
+        assert rc == n and np.array_equal(k, want[0]) and np.array_equal(v, want[1])
+        if dtype == E4M3:
+            for s, r in zip(scale, (ks, vs)):
+                assert np.array_equal(r, s[np.arange(n) // 16])
+    drop(gpu, pool, m)
