@@ -286,6 +286,15 @@ constexpr int kDeepMaxItems = 1024, kDeepMinItems = 512, kItemGrain = 256;
 constexpr double kDeepMinUnits = 10240.0;
 constexpr double kMemBytesPerUs = 6.6e6;       // what the memory system delivers to this kernel at its best
 constexpr double kDeepCapacity = 1.3;          // waves' own rate over the memory's, where more waves stop paying
+// Launches of fewer pages than kSmallMaxPages are bound by dependent memory trips and go to a kernel of their own
+// (k_attention_small: a work-group of four waves per part of a row and kv head), whichever form is in force.  Parts of
+// at least 32 pages (four page pairs a wave; 16 and 24 are slower where rows are ragged, 64 in single long rows), longer
+// where the launch has more than 512 of them, what the chip holds at once.  Ordinary or second form -> small kernel, us:
+// 4 short sequences of 8/2/64 9.4 -> 5.2; 32/8/128 bf16: 4 x 256 tokens 9.9 -> 5.6, 64 x 190 18.4 -> 9.5, 4 x 2048
+// 17.5 -> 11.3, 1 x 8192 21.5 -> 12.7, lognormal 8 x 2048 17.0 -> 13.0, 16 x 1024 (11 700 pages) 24.3 -> 23.1, 12 x 2048
+// (12 300) 25.0 -> 27.7, 16 x 2048 (27 100) 44.7 -> 56; e4m3 8 x 2048 22.1 -> 16.8 and, 64-wide, 21.6 -> 11.4.
+constexpr double kSmallMaxPages = 11000.0, kSmallWorkGroups = 512.0;
+constexpr int kSmallMinPart = 32, kSmallMaxParts = 64;
 // Smallest share of a wave, in pages.  It only binds in launches too small to give every wave slot a
 // share; there the last wave of a (sequence, kv head) merges one partial per piece, one after the
 // other, and many small pieces cost more than they gain in parallelism: an eighth of a mean row,
@@ -299,6 +308,8 @@ constexpr int kDefaultSegCost = 6;
 constexpr double kPageCost = 0.8, kDeepPageCost = 1.6;
 int g_plan_items = kDefaultItems;     // items of the launch being prepared, all models together
 int g_last_items = 0;                 // items of the most recent launch
+bool g_small_now = false;             // the launch being prepared is a small one: a work-group per (sequence, kv head) or part of one
+double g_small_pages = 0.0;           // its pages, as far as the host knows
 
 // Time (us) a wave of the second form, alone on its SIMD, spends on one page.
 double deep_page_us(const Model &m) {
@@ -327,11 +338,12 @@ double launch_units(const Model &m, bool own, int batch, int row_stride) {
 // What the host knows of a launch before it is cut: page units, their time in waves of the second form,
 // and the bytes they stand for.
 struct LaunchLoad {
-    double units = 0.0, wave_us = 0.0, bytes = 0.0;
+    double units = 0.0, wave_us = 0.0, bytes = 0.0, pages = 0.0;
     void add(const Model &m, bool own, int batch, int row_stride) {
         const double u = launch_units(m, own, batch, row_stride);
         units += u;
         wave_us += u * deep_page_us(m);
+        pages += (own ? (double)m.used_blocks : (double)batch * row_stride) * m.Hkv;
         bytes += (own ? (double)m.used_blocks : (double)batch * row_stride) * (double)m.layer_bytes;
     }
 };
@@ -345,6 +357,9 @@ void plan_launch(const LaunchLoad &l) {
     n = n < kDeepMinItems ? kDeepMinItems : (n > kDeepMaxItems ? kDeepMaxItems : n);
     if (g_deep_mode >= 0) g_deep_now = g_deep_mode == 1;
     else g_deep_now = g_items == 0 && fits && l.units >= kDeepMinUnits;
+    // (a caller that moves the split gets the kernel whose split it moves)
+    g_small_now = g_deep_mode < 0 && g_items == 0 && g_min_share == 0 && g_seg_cost < 0 && l.pages < kSmallMaxPages;
+    g_small_pages = l.pages;
     g_plan_items = g_items > 0 ? g_items : (g_deep_now ? n : kDefaultItems);
 }
 
@@ -386,6 +401,11 @@ void fill_desc_core(AttnDesc &d, Model &m, int batch, const void *q, const int32
     d.n_items = items < 1.0 ? 1 : (int)items;                // never more than the slots in total
     if (d.n_items >= 8) d.n_items &= ~7;                     // whole blocks of eight: one item per XCD
     d.weighted = d.n_items % 8 == 0 ? 1 : 0;
+    d.max_pages = row_stride;
+    if (own) {
+        d.max_pages = 0;
+        for (int s = 0; s < batch; ++s) d.max_pages = d.max_pages > m.row_len[s] ? d.max_pages : m.row_len[s];
+    }
 }
 
 // floats of split-K partials a launch of n_items work items needs: two partials per item
@@ -550,6 +570,30 @@ static int tune_setup() {
     return PKV_OK;
 }
 
+// Lays a small launch out: pages per part, parts per (sequence, kv head), first work-group of every model.
+static bool plan_small(AttnGroup &grp) {
+    if (!g_small_now) return false;
+    const int grain = 8;                                  // a page pair for every wave of a work-group
+    int size = (int)(g_small_pages / kSmallWorkGroups);
+    size = size < kSmallMinPart ? kSmallMinPart : size;
+    size = (size + grain - 1) / grain * grain;
+    for (int i = 0; i < grp.n; ++i) {
+        AttnDesc &d = grp.m[i];
+        int part = size;
+        if ((d.max_pages + part - 1) / part > kSmallMaxParts) part = ((d.max_pages + kSmallMaxParts - 1) / kSmallMaxParts + grain - 1) / grain * grain;
+        d.part_pages = part;
+        d.parts = d.max_pages > part ? (d.max_pages + part - 1) / part : 1;
+        // partials: one per work-group, in a workspace made for two per work item
+        if ((long)d.batch * d.Hkv * d.parts > 2L * kDefaultItems) return false;
+    }
+    int begin = 0;
+    for (int i = 0; i < grp.n; ++i) {
+        grp.m[i].item_begin = begin;
+        begin += grp.m[i].batch * grp.m[i].Hkv * grp.m[i].parts;
+    }
+    return true;
+}
+
 // One attention launch.  While weight updates are owed, a launch that fills the chip is also measured.
 static int launch_attention(AttnGroup &grp) {
     // copies of the totals that have arrived meanwhile (never waits)
@@ -566,7 +610,7 @@ static int launch_attention(AttnGroup &grp) {
         measure = measure && grp.m[i].weighted;
     }
     g_last_items = items;
-    measure = measure && items >= kMinTuneItems;
+    measure = measure && items >= kMinTuneItems && !g_small_now;
     if (measure && g_tune_left <= 0) measure = ++g_tune_tick % kSlowTuneEvery == 0;
     if (measure) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -576,7 +620,8 @@ static int launch_attention(AttnGroup &grp) {
         if (slot < 0) measure = false;                     // all copies still travelling
     }
     fill_tune(grp.tune, measure);
-    HIP_TRY(pkv_launch_attention(grp, g_deep_now, g_stream, next_events()));
+    const AttnForm form = plan_small(grp) ? AttnForm::small : (g_deep_now ? AttnForm::deep : AttnForm::ordinary);
+    HIP_TRY(pkv_launch_attention(grp, form, g_stream, next_events()));
     if (measure) {
         HIP_TRY(hipMemcpyAsync(g_tune_host + 16 * slot, g_xcd_stat, 16 * sizeof(uint64_t), hipMemcpyDeviceToHost, g_stream));
         HIP_TRY(hipEventRecord(g_tune_ev[slot], g_stream));

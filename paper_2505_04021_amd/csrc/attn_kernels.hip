@@ -840,6 +840,168 @@ __global__ __launch_bounds__(64, 2) void k_attention_static(const AttnGroup grp)
     }
 }
 
+// Small launches: one work-group of SMALL_WAVES waves per part of a (sequence, kv head).
+//
+// Such a launch is bound by the number of dependent memory trips, not by bytes: the kernels above find their share from
+// all context lengths, then its block ids, then the pages, and hand every cut segment over through memory (partial,
+// arrival, partials of the others: three more trips of about 1 us).  Here the block index alone names the segment and
+// the part, so block ids, context length and queries are asked for together and the pages behind them; the waves of
+// the work-group take the part's page pairs in turn and join their sums through LDS.  Only segments longer than
+// `part_pages` pages come in several parts, whose partials the last to arrive joins.  The host sizes the parts
+// (plan_small); a context that has outgrown them (a launch replayed from a graph) gets longer parts here.
+constexpr int SMALL_WAVES = 4;
+
+template <int D, int DT>
+__device__ __forceinline__ void attn_part(const AttnDesc &d, int wg, float *s_acc, float *s_m, float *s_l, uint32_t *s_arrived) {
+    using TL = Tile<D, DT>;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int G = lane >> 4, n = lane & 15, g = d.g;
+    // parts are the slow index: work-groups of rows shorter than the longest, which have nothing to do, start last
+    const int n_segs = d.batch * d.Hkv, part = wg / n_segs, seg = wg - part * n_segs;
+    const int seq = seg / d.Hkv, kvh = seg - seq * d.Hkv;
+    const int32_t *row = d.table + (size_t)seq * d.row_stride;
+    bf16x8 qf[TL::NK];
+    load_q<D>(qf, d, seq, kvh, lane);
+    PairIds ids = fetch_ids(d, row, part * d.part_pages + 2 * w);
+    const int L = __builtin_amdgcn_readfirstlane(ctx_clamped(d, seq));
+    const int n_pages = (L + T - 1) / T;
+    int size = d.part_pages;
+    if (n_pages > d.parts * size) {                       // longer than the host knew
+        size = (n_pages + d.parts - 1) / d.parts;
+        size = (size + 2 * SMALL_WAVES - 1) / (2 * SMALL_WAVES) * (2 * SMALL_WAVES);
+        ids = fetch_ids(d, row, part * size + 2 * w);
+    }
+    const int n_parts = n_pages > size ? (n_pages + size - 1) / size : 1;
+    if (part >= n_parts) return;
+    const int pe = (part + 1) * size < n_pages ? (part + 1) * size : n_pages;
+    const int last_valid = L - (n_pages - 1) * T;
+    uint32_t bad = 0;
+    State<D, DT> st;
+#pragma unroll
+    for (int jt = 0; jt < TL::NV; ++jt) st.acc[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    st.m = -INFINITY;
+    st.l = 0.f;
+    // this wave's pairs: pages p, p + 1 for p = first, first + 2 * SMALL_WAVES, ...; one pair ahead of the one in use
+    constexpr int STEP = 2 * SMALL_WAVES;
+    PairRegs<D, DT> ring[2];
+    int p = part * size + 2 * w;
+    load_pair<D, DT>(ring[0], d, ids, p < pe, p + 1 < pe, kvh, lane, bad);
+    ids = fetch_ids(d, row, p + STEP);
+    while (p < pe) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            load_pair<D, DT>(ring[r ^ 1], d, ids, p + STEP < pe, p + STEP + 1 < pe, kvh, lane, bad);
+            ids = fetch_ids(d, row, p + 2 * STEP);
+            if (p < pe) {
+                const int va = p == n_pages - 1 ? last_valid : T;
+                const int vb = p + 1 < pe ? (p + 1 == n_pages - 1 ? last_valid : T) : 0;
+                process_pair<D, DT>(st, ring[r], qf, d.scale_log2, va, vb, G);
+            }
+            p += STEP;
+        }
+    }
+    float l = st.l;
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (n < g) {
+        float *a = s_acc + (w * g + n) * D;
+#pragma unroll
+        for (int jt = 0; jt < TL::NV; ++jt) *reinterpret_cast<f32x4 *>(a + 16 * jt + 4 * G) = st.acc[jt];
+        if (G == 0) {
+            s_m[w * 16 + n] = st.m;
+            s_l[w * 16 + n] = l;
+        }
+    }
+    if (bad && lane == 0) atomicOr(d.err, 1u);
+    __syncthreads();
+    // the sums of the work-group: lane by lane four output elements of one head
+    const int quads = g * (D / 4), pf = partial_floats(g, D);
+    const bool whole = n_parts == 1;
+    float *mine = d.ws + (size_t)(seg * d.parts + part) * pf;
+    for (int i = threadIdx.x; i < quads; i += 64 * SMALL_WAVES) {
+        const int hn = i / (D / 4), x = i - hn * (D / 4);
+        float M = s_m[hn];
+#pragma unroll
+        for (int v = 1; v < SMALL_WAVES; ++v) M = fmaxf(M, s_m[v * 16 + hn]);
+        float den = 0.f;
+        f32x4 num = {0.f, 0.f, 0.f, 0.f};
+        if (n_pages > 0) {                                // an empty context: the row is defined as zero
+#pragma unroll
+            for (int v = 0; v < SMALL_WAVES; ++v) {
+                const float f = __builtin_amdgcn_exp2f(s_m[v * 16 + hn] - M);
+                den += f * s_l[v * 16 + hn];
+                num += f * *reinterpret_cast<const f32x4 *>(s_acc + (v * g + hn) * D + 4 * x);
+            }
+        }
+        if (whole) {
+            *reinterpret_cast<f32x4 *>(d.out + ((size_t)seq * d.Hq + kvh * g + hn) * D + 4 * x) = n_pages > 0 ? num * (1.0f / den) : num;
+        } else {
+            *reinterpret_cast<f32x4 *>(mine + hn * D + 4 * x) = num;
+            if (x == 0) {
+                mine[g * D + hn] = M;
+                mine[g * D + g + hn] = den;
+            }
+        }
+    }
+    if (whole) return;
+    // Hand-over as in attn_wave: partials and counters are in uncached memory, so the order of a wave's own accesses is
+    // all there is to enforce; every wave's stores have landed when the counter moves.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) *s_arrived = atomicAdd(d.cnt + seg, 1u);
+    __syncthreads();
+    if (*s_arrived != (uint32_t)(n_parts - 1)) return;
+    if (threadIdx.x == 0) d.cnt[seg] = 0u;                // ready for the next launch
+    const float *base = d.ws + (size_t)seg * d.parts * pf;
+    // all maxima and sums travel together with the first eight parts of the accumulators
+    for (int i = threadIdx.x; i < n_parts * g; i += 64 * SMALL_WAVES) {
+        const int c = i / g, hn = i - c * g;
+        s_acc[i] = base[(size_t)c * pf + g * D + hn];
+        s_acc[MAX_PIECES * 16 + i] = base[(size_t)c * pf + g * D + g + hn];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < quads; i += 64 * SMALL_WAVES) {
+        const int hn = i / (D / 4), x = i - hn * (D / 4);
+        float M = -INFINITY, den = 0.f;
+        f32x4 num = {0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < n_parts; ++c) M = fmaxf(M, s_acc[c * g + hn]);
+        for (int c0 = 0; c0 < n_parts; c0 += 8) {
+            f32x4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                v[u] = *reinterpret_cast<const f32x4 *>(base + (size_t)(c0 + u < n_parts ? c0 + u : n_parts - 1) * pf + hn * D + 4 * x);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (c0 + u < n_parts) {
+                    const float f = __builtin_amdgcn_exp2f(s_acc[(c0 + u) * g + hn] - M);
+                    den += f * s_acc[MAX_PIECES * 16 + (c0 + u) * g + hn];
+                    num += f * v[u];
+                }
+        }
+        *reinterpret_cast<f32x4 *>(d.out + ((size_t)seq * d.Hq + kvh * g + hn) * D + 4 * x) = num * (1.0f / den);
+    }
+}
+
+__global__ __launch_bounds__(64 * SMALL_WAVES, 2) void k_attention_small(const AttnGroup grp) {
+    __shared__ __align__(16) float s_acc[SMALL_WAVES * 16 * 128];
+    __shared__ float s_m[SMALL_WAVES * 16], s_l[SMALL_WAVES * 16];
+    __shared__ uint32_t s_arrived;
+    static_assert(2 * MAX_PIECES * 16 <= SMALL_WAVES * 16 * 128, "maxima and sums of all parts fit where the accumulators were");
+    const int gi = blockIdx.x;
+    int mi = 0;
+    for (int i = 1; i < grp.n; ++i)
+        if (gi >= grp.m[i].item_begin) mi = i;
+    const AttnDesc &d = grp.m[mi];
+    const int wg = gi - d.item_begin;
+    if (d.dtype == PKV_BF16) {
+        if (d.D == 128) attn_part<128, PKV_BF16>(d, wg, s_acc, s_m, s_l, &s_arrived);
+        else attn_part<64, PKV_BF16>(d, wg, s_acc, s_m, s_l, &s_arrived);
+    } else {
+        if (d.D == 128) attn_part<128, PKV_E4M3>(d, wg, s_acc, s_m, s_l, &s_arrived);
+        else attn_part<64, PKV_E4M3>(d, wg, s_acc, s_m, s_l, &s_arrived);
+    }
+}
+
 __global__ void k_clear_words(uint32_t *p, size_t n) {
     for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
 }
@@ -882,13 +1044,14 @@ __global__ __launch_bounds__(256) void k_stream_read(const u32x4 *src, size_t n1
 
 }  // namespace
 
-hipError_t pkv_launch_attention(const AttnGroup &grp, bool deep, hipStream_t s, hipEvent_t *ev) {
+hipError_t pkv_launch_attention(const AttnGroup &grp, AttnForm form, hipStream_t s, hipEvent_t *ev) {
     int items = 0;
-    for (int i = 0; i < grp.n; ++i) items += grp.m[i].n_items;
+    for (int i = 0; i < grp.n; ++i) items += form == AttnForm::small ? grp.m[i].batch * grp.m[i].Hkv * grp.m[i].parts : grp.m[i].n_items;
     if (items == 0) return hipSuccess;
     hipError_t e;
     if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
-    if (deep) hipLaunchKernelGGL(k_attention_deep, dim3(items), dim3(64), 0, s, grp);
+    if (form == AttnForm::deep) hipLaunchKernelGGL(k_attention_deep, dim3(items), dim3(64), 0, s, grp);
+    else if (form == AttnForm::small) hipLaunchKernelGGL(k_attention_small, dim3(items), dim3(64 * SMALL_WAVES), 0, s, grp);
     else hipLaunchKernelGGL(k_attention, dim3(items), dim3(64), 0, s, grp);
     e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -98,6 +98,9 @@ struct AttnDesc {
     int32_t min_share;          // smallest share of pages a wave may get
     int32_t weighted;           // items come in whole blocks of eight aligned with the XCDs
     int32_t seg_cost;           // what a segment costs besides its pages, in pages (for the split only)
+    int32_t max_pages;          // longest row, as far as the host knows
+    int32_t parts, part_pages;  // small launches: work-groups per (sequence, kv head), pages of each (item_begin then counts
+                                // work-groups)
     float scale_log2;           // log2(e) / sqrt(D)
 };
 
@@ -154,7 +157,8 @@ hipError_t pkv_launch_kv_append(const AttnDesc &d, const void *k_new, const void
 // plan: per sequence one unit for every page its new tokens may touch
 hipError_t pkv_launch_kv_append_chunk(const AttnDesc &d, const ChunkPlan &plan, const void *k_new, const void *v_new, hipStream_t s);
 // ev: NULL or two events recorded before and after the attention kernel
-hipError_t pkv_launch_attention(const AttnGroup &grp, bool deep, hipStream_t s, hipEvent_t *ev);
+enum class AttnForm { ordinary, deep, small };
+hipError_t pkv_launch_attention(const AttnGroup &grp, AttnForm form, hipStream_t s, hipEvent_t *ev);
 // the entry point that allocates nothing: the current device's copy of the library's scratch array
 hipError_t pkv_static_scratch(void **ptr);
 hipError_t pkv_launch_attention_static(const AttnGroup &grp, uint32_t *cnt, size_t n_cnt, hipStream_t s);

@@ -1,0 +1,62 @@
+"""Small decode launches (a work-group per row and kv head, or per part of 32 pages): rows at the edges of pages, pairs
+and parts against the oracle, and a captured launch whose rows have outgrown the parts it was laid out with."""
+import numpy as np
+import pytest
+import torch
+
+from parity import TOL, row_rel_err
+from test_gpu_prefill import BF16, E4M3, Twin, gpu  # noqa: F401  (fixture)
+from workloads import gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("g,hkv,d,dtype", [(1, 3, 128, BF16), (3, 2, 64, BF16), (4, 2, 128, E4M3), (5, 1, 64, E4M3), (8, 1, 128, BF16),
+                                           (16, 1, 128, E4M3), (16, 2, 64, BF16)])
+def test_small_launch_edges(gpu, oracle, g, hkv, d, dtype):  # noqa: F811
+    ctx = [0, 1, 16, 17, 31, 33, 127, 129, 511, 512, 513, 528, 529, 1024, 1025, 2100]
+    t = Twin(gpu, oracle, g * hkv, hkv, d, dtype, ctx, max_blocks=140)
+    for n in (len(ctx), 5, 1):                       # all rows; short rows only; one empty row
+        q = gen.queries((53, d, g, n), n, g * hkv, d)
+        rc_o, out_o = oracle.decode_attention(t.models[1], q, np.array(ctx[:n], dtype=np.int32))
+        for _ in range(2):                           # the arrival counters are ready again
+            rc_g, out_g = gpu.decode_attention(t.models[0], q, np.array(ctx[:n], dtype=np.int32))
+            assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
+            assert row_rel_err(out_g, out_o) <= TOL[dtype]
+    t.close()
+
+
+def test_rows_outgrow_a_captured_launch(gpu, oracle):  # noqa: F811
+    hq, hkv, d = 8, 2, 128
+    last = [2300, 900, 40, 1500]
+    t = Twin(gpu, oracle, hq, hkv, d, BF16, last, max_blocks=160, poison=False)
+    m = t.models[0]
+    gpu.seq_release_batch(m, np.arange(4, dtype=np.int32))
+    assert gpu.seq_reserve_batch(m, [0, 1, 2, 3], [40] * 4) == 12
+    q = gen.queries((59,), 4, hq, d)
+    qd = torch.from_numpy(q.view(np.int16)).cuda()
+    ctx = torch.tensor([40] * 4, dtype=torch.int32, device="cuda")
+    out = torch.zeros((4, hq, d), dtype=torch.float32, device="cuda")
+    kv = [gen.seq_kv((13, s), c, hkv, d, BF16, 16) for s, c in enumerate(last)]
+    for s in range(4):
+        assert gpu.kv_write(m, s, 0, kv[s]["k"][:40], kv[s]["v"][:40]) == 40
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        gpu.use_current_stream()
+        graph.capture_begin()
+        assert gpu.decode_attention_dev(m, qd, ctx, out) == 0
+        graph.capture_end()
+    torch.cuda.synchronize()
+    gpu.use_current_stream()
+    for step in ([40] * 4, [600, 560, 40, 513], last, [1100, 900, 7, 1025], last):
+        assert gpu.seq_reserve_batch(m, [0, 1, 2, 3], step) >= 0
+        for s in range(4):
+            assert gpu.kv_write(m, s, 0, kv[s]["k"][:step[s]], kv[s]["v"][:step[s]]) == step[s]
+        ctx.copy_(torch.tensor(step, dtype=torch.int32))
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        rc_o, out_o = oracle.decode_attention(t.models[1], q, np.array(step, dtype=np.int32))
+        assert rc_o == 0 and gpu.device_errors() == 0 and row_rel_err(out.cpu().numpy(), out_o) <= TOL[BF16]
+    t.close()
