@@ -67,8 +67,6 @@ __device__ __forceinline__ float e4m3_decode(uint32_t code) {
     return p[0];
 }
 
-__device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
 __device__ __forceinline__ float wave_max(float x) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
@@ -80,14 +78,13 @@ __device__ __forceinline__ float wave_max(float x) {
 // fp32 with IEEE rounding (explicit _rn operations: nothing may be fused or reordered,
 // the codes are compared bit for bit).
 template <bool IS_V>
-__device__ __forceinline__ void append_row_e4m3(uint8_t *tile, float *scale_p, int slot, int D, const uint16_t *x_bf16,
+__device__ __forceinline__ void append_row_e4m3(uint8_t *tile, float *scale_p, int slot, int D, const uint32_t *x_bf16,
                                                 int lane) {
     float x[2];
     float amax = 0.f;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int dd = lane + 64 * i;
-        x[i] = dd < D ? bf16_bits_to_float(x_bf16[dd]) : 0.f;
+    for (int i = 0; i < 2; ++i) {                          // this lane's elements lane, lane + 64 (0 past the head's width)
+        x[i] = __uint_as_float(x_bf16[i] << 16);
         amax = fmaxf(amax, fabsf(x[i]));
     }
     amax = wave_max(amax);
@@ -451,32 +448,42 @@ __global__ __launch_bounds__(64) void k_kv_append(const AttnDesc d, const uint16
     const int lane = threadIdx.x;
     const int seq = blockIdx.x / d.Hkv, h = blockIdx.x - seq * d.Hkv;
     const int D = d.D;
-    const int ctx = d.ctx_lens[seq];
-    const int cap = d.row_len[seq] * PKV_T;
-    if (ctx < 1 || ctx > cap) {
+    // The new token's values are asked for along with the context length: the launch is bound by its dependent memory
+    // trips (context length, block id, the block), not by what it moves.
+    const size_t src = ((size_t)seq * d.Hkv + h) * D + lane;
+    const size_t second = src + (D > 64 ? 64 : 0);         // (no branch: it would wait for the first loads)
+    uint32_t kx[2] = {k_new[src], k_new[second]}, vx[2] = {v_new[src], v_new[second]};
+    asm volatile("" ::: "memory");                         // issued here: the compiler would put them where they are used
+    const int ctx = PKV_CONST(int32_t, d.ctx_lens)[seq];
+    const int cap = PKV_CONST(int32_t, d.row_len)[seq] * PKV_T;
+    if ((ctx < 1) | (ctx > cap)) {
         if (lane == 0) atomicOr(d.err, 2u);
         return;
     }
-    const uint32_t id = (uint32_t)d.table[(size_t)seq * d.row_stride + (ctx - 1) / PKV_T];
+    const uint32_t id = (uint32_t)PKV_CONST(int32_t, d.table)[(size_t)seq * d.row_stride + (ctx - 1) / PKV_T];
     if (id >= d.max_block_id) {
         if (lane == 0) atomicOr(d.err, 1u);
         return;
     }
     uint8_t *blk = block_ptr(d, id);
     const int slot = (ctx - 1) % PKV_T;
-    const uint16_t *kx = k_new + ((size_t)seq * d.Hkv + h) * D, *vx = v_new + ((size_t)seq * d.Hkv + h) * D;
     if (DT == PKV_BF16) {
         const size_t tile = (size_t)PKV_T * D * 2;
         uint16_t *kt = reinterpret_cast<uint16_t *>(blk + (size_t)h * 2 * tile);
         uint16_t *vt = reinterpret_cast<uint16_t *>(blk + (size_t)h * 2 * tile + tile);
-        for (int dd = lane; dd < D; dd += 64) {
-            kt[k_elem_off<PKV_BF16>(slot, dd)] = kx[dd];
-            vt[v_elem_off<PKV_BF16>(slot, dd)] = vx[dd];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int dd = lane + 64 * i;
+            if (dd < D) {
+                kt[k_elem_off<PKV_BF16>(slot, dd)] = (uint16_t)kx[i];
+                vt[v_elem_off<PKV_BF16>(slot, dd)] = (uint16_t)vx[i];
+            }
         }
     } else {
         float *hdr = reinterpret_cast<float *>(blk);
         const size_t tile = (size_t)PKV_T * D;
         uint8_t *kt = blk + PKV_FP8_HEADER + (size_t)h * 2 * tile, *vt = kt + tile;
+        if (D == 64) kx[1] = vx[1] = 0u;
         append_row_e4m3<false>(kt, hdr + h, slot, D, kx, lane);
         append_row_e4m3<true>(vt, hdr + d.Hkv + h, slot, D, vx, lane);
     }
