@@ -1325,7 +1325,9 @@ static int check_reserve_list(const Model &m, int T, int n, const int32_t *seqs,
 static int enqueue_reserve(Model &m, int n, const int32_t *seqs, const int32_t *ctx_lens, bool sticky = false) {
     Pool &p = g_pools[m.pool];
     const int slot = take_ticket();
-    int32_t *ops = ticket_ops(slot);
+    BookList list;
+    const bool is_short = 3 * n <= PKV_BOOK_LIST;
+    int32_t *ops = is_short ? list.v : ticket_ops(slot);
     memcpy(ops, seqs, sizeof(int32_t) * n);
     memcpy(ops + n, ctx_lens, sizeof(int32_t) * n);
     // What an entry's row holds before it, as far as the list alone decides: the largest want among the
@@ -1340,7 +1342,7 @@ static int enqueue_reserve(Model &m, int n, const int32_t *seqs, const int32_t *
         if (want > seen) seen = want;
     }
     for (int i = 0; i < n; ++i) m.list_max[(size_t)seqs[i]] = 0;
-    hipError_t e = pkv_launch_reserve(p.dev, m.dev, n, ops, &g_res[slot], sticky ? g_err : nullptr, g_stream);
+    hipError_t e = pkv_launch_reserve(p.dev, m.dev, n, is_short ? nullptr : ops, list, &g_res[slot], sticky ? g_err : nullptr, g_stream);
     if (e != hipSuccess) g_res[slot].value = fail_hip(e, "seq_reserve_batch launch");
     return slot;
 }
@@ -1397,9 +1399,11 @@ int seq_reserve(int model, int seq, int ctx_len) {
 static int enqueue_release(Model &m, int n, const int32_t *seqs, bool sticky = false) {
     Pool &p = g_pools[m.pool];
     const int slot = take_ticket();
-    int32_t *ops = ticket_ops(slot);
+    BookList list;
+    const bool is_short = n <= PKV_BOOK_LIST;
+    int32_t *ops = is_short ? list.v : ticket_ops(slot);
     memcpy(ops, seqs, sizeof(int32_t) * n);
-    hipError_t e = pkv_launch_release(p.dev, m.dev, n, ops, &g_res[slot], sticky ? g_err : nullptr, g_stream);
+    hipError_t e = pkv_launch_release(p.dev, m.dev, n, is_short ? nullptr : ops, list, &g_res[slot], sticky ? g_err : nullptr, g_stream);
     if (e != hipSuccess) g_res[slot].value = fail_hip(e, "seq_release launch");
     return slot;
 }

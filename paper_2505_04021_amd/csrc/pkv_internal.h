@@ -140,13 +140,19 @@ struct AttnGroup {
 hipError_t pkv_launch_pool_init(const PoolDev &p, const uint32_t *perm_dev, hipStream_t s);
 // Bookkeeping kernels: the result goes to *res (pinned host memory); a refused call also sets bit 2 of *err.
 hipError_t pkv_launch_resize(const PoolDev &p, const ModelDev &m, int64_t target, BookResult *res, uint32_t *err, hipStream_t s);
-// ops: pinned host memory, n sequence ids, n context lengths, then per entry the largest want (blocks) among
+// A call's list: in pinned host memory (ops), or, where it is short, in the kernel's arguments (ops NULL: a read of host
+// memory is the longest trip such a kernel makes).
+#define PKV_BOOK_LIST 192
+struct BookList {
+    int32_t v[PKV_BOOK_LIST];
+};
+// list: n sequence ids, n context lengths, then per entry the largest want (blocks) among
 // the earlier entries of its sequence in the list (n <= PKV_MAX_BATCH_OPS)
-hipError_t pkv_launch_reserve(const PoolDev &p, const ModelDev &m, int n, const int32_t *ops, BookResult *res, uint32_t *err,
-                              hipStream_t s);
-// ops: pinned host memory, n sequence ids (n <= PKV_MAX_SEQS)
-hipError_t pkv_launch_release(const PoolDev &p, const ModelDev &m, int n, const int32_t *ops, BookResult *res, uint32_t *err,
-                              hipStream_t s);
+hipError_t pkv_launch_reserve(const PoolDev &p, const ModelDev &m, int n, const int32_t *ops, const BookList &list, BookResult *res,
+                              uint32_t *err, hipStream_t s);
+// list: n sequence ids (n <= PKV_MAX_SEQS)
+hipError_t pkv_launch_release(const PoolDev &p, const ModelDev &m, int n, const int32_t *ops, const BookList &list, BookResult *res,
+                              uint32_t *err, hipStream_t s);
 
 hipError_t pkv_launch_kv_write(const AttnDesc &d, int seq, int tok_begin, int n_tok, const void *k, const void *v,
                                const float *ks, const float *vs, int page_tokens, hipStream_t s);

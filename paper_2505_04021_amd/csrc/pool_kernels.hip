@@ -29,9 +29,9 @@ __device__ inline int block_excl_scan(int v, int &total, int *s_wave) {
         int o = __shfl_up(inc, d);
         if (lane >= d) inc += o;
     }
-    __syncthreads();                 // protect s_wave from the previous call's readers
+    lds_barrier();                   // protect s_wave from the previous call's readers
     if (lane == 63) s_wave[wave] = inc;
-    __syncthreads();
+    lds_barrier();
     int before = 0, sum = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
@@ -180,15 +180,20 @@ __global__ __launch_bounds__(NT) void k_resize(PoolDev p, ModelDev m, int64_t ta
 // times (the growth rounds of an admission in one call): entry i then needs what its
 // row lacks after the earlier entries, i.e. its want minus the largest want among the
 // earlier entries of the same sequence (and the row's length before the call).
-// ops: host (pinned) memory, n sequence ids, then n context lengths, then for each entry the largest want
+// list (kernel arguments or pinned host memory): n sequence ids, then n context lengths, then for each entry the largest want
 // (in blocks) among the earlier entries of its sequence in this list, 0 if there is none.
-__global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, const int32_t *ops, BookResult *res, uint32_t *err) {
+constexpr int RESERVE_WIN = 8192;       // ranks whose blocks k_reserve collects in LDS at a time
+
+__global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, const int32_t *host_ops, const BookList list,
+                                                BookResult *res, uint32_t *err) {
+    const int32_t *ops = host_ops ? host_ops : list.v;
     __shared__ int s_wave[NW];
     __shared__ int s_cur[PKV_MAX_SEQS];             // row lengths: as the call finds them, then with its wants
     __shared__ int s_start[PKV_MAX_BATCH_OPS + 1];  // first rank of entry i
     __shared__ uint32_t s_ent[PKV_MAX_BATCH_OPS];   // entry i: sequence << 20 | row length before the entry
     __shared__ uint32_t s_free[NT], s_fid[NT];      // placement: free bits of frame j's current word, its frame id
     __shared__ int s_rank[NT];                      // placement: rank of the first free slot of that word
+    __shared__ uint32_t s_blk[RESERVE_WIN];         // placement: the blocks of a window of ranks
     __shared__ int s_fail;
     const int tid = threadIdx.x;
     // Everything the kernel will read is asked for here, before the first answer is needed: the list
@@ -269,8 +274,12 @@ __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, co
     // Placement.  Free slots are ranked in frame-list order, ascending slot inside a frame; rank r goes to
     // the entry e with s_start[e] <= r < s_start[e + 1].  A lane per frame counts the frame's free slots (a
     // prefix sum gives the rank of its first one) and publishes one 32-slot word at a time; then a lane per
-    // (frame, slot) of that word takes over: a free slot knows its rank from the bits below it, finds its
-    // entry by binary search and writes the row.  The frame's lane sets the bits that were taken.
+    // (frame, slot) of that word takes over: a free slot knows its rank from the bits below it and puts its block id
+    // there, in LDS.  The entries then copy their ranks into their rows, `group` lanes each (a search for the entry of
+    // every slot took 4 of this kernel's 13 us).  The frame's lane sets the bits that were taken.
+    int group = 4;
+    while (group < NT && group * 2 * n <= NT) group *= 2;
+    const int sub = tid & (group - 1);
     int running = 0;
     for (int64_t base = 0; base < owned && running < total; base += NT) {
         const int64_t i = base + tid;
@@ -294,46 +303,44 @@ __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, co
         if (i < owned)
             for (int w = 0; w < wpf; ++w) zeros += __popc(~word_of(w) & valid_of(w));
         int chunk_total;
-        int rank0 = running + block_excl_scan(zeros, chunk_total, s_wave);    // rank of this frame's first free slot
+        const int rank0 = running + block_excl_scan(zeros, chunk_total, s_wave);    // rank of this frame's first free slot
         const uint32_t f = i < owned ? (base == 0 ? pre_frame : m.frames[i]) : 0u;
         const int nf = (int)(owned - base < NT ? owned - base : NT);
-        for (int w = 0; w < wpf; ++w) {
-            const bool mine = i < owned && zeros && rank0 < total;
-            const uint32_t word = mine ? word_of(w) : 0u;
-            const uint32_t freeb = mine ? ~word & valid_of(w) : 0u;
-            s_free[tid] = freeb;
-            s_rank[tid] = rank0;
-            s_fid[tid] = f;
-            lds_barrier();
-            for (int idx = tid; idx < nf * 32; idx += NT) {
-                const int j = idx >> 5, bit = idx & 31;
-                const uint32_t fr = s_free[j];
-                if (!((fr >> bit) & 1u)) continue;
-                const int r = s_rank[j] + __popc(fr & ((1u << bit) - 1u));
-                if (r >= total) continue;
-                // last entry with s_start <= r: three pivots a step (their reads travel together), then halves
-                int lo = 0, hi = n;
-                while (hi - lo > 3) {
-                    const int q = (hi - lo) >> 2;
-                    const int m1 = lo + q, m2 = m1 + q, m3 = m2 + q;
-                    const int a1 = s_start[m1], a2 = s_start[m2], a3 = s_start[m3];
-                    if (a3 <= r) lo = m3;
-                    else if (a2 <= r) { lo = m2; hi = m3; }
-                    else if (a1 <= r) { lo = m1; hi = m2; }
-                    else hi = m1;
+        const int pass_end = running + chunk_total < total ? running + chunk_total : total;
+        for (int win0 = running; win0 < pass_end; win0 += RESERVE_WIN) {
+            const int win1 = win0 + RESERVE_WIN < pass_end ? win0 + RESERVE_WIN : pass_end;
+            int rank = rank0;
+            for (int w = 0; w < wpf; ++w) {
+                const uint32_t freeb = i < owned && zeros && rank < win1 ? ~word_of(w) & valid_of(w) : 0u;
+                s_free[tid] = freeb;
+                s_rank[tid] = rank;
+                s_fid[tid] = f;
+                rank += __popc(freeb);
+                lds_barrier();
+                for (int idx = tid; idx < nf * 32; idx += NT) {
+                    const int j = idx >> 5, bit = idx & 31;
+                    const uint32_t fr = s_free[j];
+                    const int r = s_rank[j] + __popc(fr & ((1u << bit) - 1u));
+                    if (((fr >> bit) & 1u) && r >= win0 && r < win1) s_blk[r - win0] = s_fid[j] * (uint32_t)slots + (uint32_t)(32 * w + bit);
                 }
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (s_start[mid] <= r) lo = mid; else hi = mid;
-                }
-                const uint32_t ent = s_ent[lo];
-                m.rows[(int64_t)(ent >> 20) * m.max_blocks + (ent & 0xfffffu) + (r - s_start[lo])] =
-                    (int32_t)(s_fid[j] * (uint32_t)slots + (uint32_t)(32 * w + bit));
+                lds_barrier();
+            }
+            for (int e = tid / group; e < n; e += NT / group) {
+                const int st = s_start[e], en = s_start[e + 1];
+                const int lo = st > win0 ? st : win0, hi = en < win1 ? en : win1;
+                if (lo >= hi) continue;
+                const uint32_t ent = s_ent[e];
+                int32_t *row = m.rows + (int64_t)(ent >> 20) * m.max_blocks + (ent & 0xfffffu);
+                for (int r = lo + sub; r < hi; r += group) row[r - st] = (int32_t)s_blk[r - win0];
             }
             lds_barrier();
-            if (freeb) {
+        }
+        int rank = rank0;
+        if (i < owned && zeros)
+            for (int w = 0; w < wpf && rank < total; ++w) {
+                const uint32_t word = word_of(w), freeb = ~word & valid_of(w);
                 const int c = __popc(freeb);
-                int take = total - rank0;
+                int take = total - rank;
                 take = take > c ? c : take;
                 uint32_t mask = freeb;                   // the lowest `take` free bits
                 if (take < c) {
@@ -344,10 +351,9 @@ __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, co
                         rest &= rest - 1u;
                     }
                 }
-                m.bits[i * wpf + w] = word | mask;
-                rank0 += c;
+                if (mask) m.bits[i * wpf + w] = word | mask;
+                rank += c;
             }
-        }
         running += chunk_total;
     }
     __syncthreads();
@@ -362,26 +368,33 @@ constexpr int RELEASE_WIN = 6144;      // words of a model's slot bitmap that k_
 
 // release (batched): clear the slot bits of every block of the listed rows; the same state as single
 // releases in order (a sequence listed twice is empty the second time).
-// ops: host (pinned) memory, n sequence ids, checked by the host.
-__global__ __launch_bounds__(NT) void k_release(PoolDev p, ModelDev m, int n, const int32_t *ops, BookResult *res, uint32_t *err) {
+// list: n sequence ids, checked by the host; in the kernel's arguments up to PKV_BOOK_LIST words (reading 32 of them from
+// host memory and comparing them pairwise for repetitions took 3 of the kernel's 10.6 us), else in pinned host memory.
+__global__ __launch_bounds__(NT) void k_release(PoolDev p, ModelDev m, int n, const int32_t *host_ops, const BookList list,
+                                                BookResult *res, uint32_t *err) {
+    const int32_t *ops = host_ops ? host_ops : list.v;
     __shared__ int s_wave[NW];
+    __shared__ uint32_t s_seen[PKV_MAX_SEQS / 32];
     __shared__ int s_start[PKV_MAX_SEQS + 1];
     __shared__ int s_seq[PKV_MAX_SEQS];
     __shared__ uint32_t s_win[RELEASE_WIN];
     const int tid = threadIdx.x;
-    for (int i = tid; i < n; i += NT) {
-        const int s_ = ops[i];
-        s_seq[i] = (s_ >= 0 && s_ < m.max_seqs) ? s_ : -1;
-    }
+    for (int i = tid; i < PKV_MAX_SEQS / 32; i += NT) s_seen[i] = 0u;
+    const int64_t words_total = m.counters[0] * m.wpf;
     __syncthreads();
     int total = 0;
     for (int c0 = 0; c0 < n; c0 += NT) {
         const int i = c0 + tid;
         int len = 0;
-        if (i < n && s_seq[i] >= 0) {
-            len = m.row_len[s_seq[i]];
-            for (int j = 0; j < i && len > 0; ++j)       // listed before: already empty
-                if (s_seq[j] == s_seq[i]) len = 0;
+        if (i < n) {
+            int s_ = ops[i];
+            s_ = (s_ >= 0 && s_ < m.max_seqs) ? s_ : -1;
+            // a sequence listed twice is freed once, whichever of its entries does it
+            if (s_ >= 0) {
+                len = m.row_len[s_];
+                if ((atomicOr(&s_seen[s_ >> 5], 1u << (s_ & 31)) >> (s_ & 31)) & 1u) len = 0;
+            }
+            s_seq[i] = s_;
         }
         int chunk_total;
         const int excl = block_excl_scan(len, chunk_total, s_wave);
@@ -398,7 +411,6 @@ __global__ __launch_bounds__(NT) void k_release(PoolDev p, ModelDev m, int n, co
     // then rewritten once by one lane: thirty atomics on the same word in memory cost more than the
     // rest of the kernel.
     constexpr int RELEASE_BATCH = 8;
-    const int64_t words_total = m.counters[0] * m.wpf;
     for (int64_t win0 = 0; win0 < words_total && total > 0; win0 += RELEASE_WIN) {
         for (int i = tid; i < RELEASE_WIN; i += NT) s_win[i] = 0u;
         lds_barrier();
@@ -458,13 +470,13 @@ hipError_t pkv_launch_resize(const PoolDev &p, const ModelDev &m, int64_t target
     hipLaunchKernelGGL(k_resize, dim3(1), dim3(NT), 0, s, p, m, target, res, err);
     return hipGetLastError();
 }
-hipError_t pkv_launch_reserve(const PoolDev &p, const ModelDev &m, int n, const int32_t *ops, BookResult *res, uint32_t *err,
-                              hipStream_t s) {
-    hipLaunchKernelGGL(k_reserve, dim3(1), dim3(NT), 0, s, p, m, n, ops, res, err);
+hipError_t pkv_launch_reserve(const PoolDev &p, const ModelDev &m, int n, const int32_t *ops, const BookList &list, BookResult *res,
+                              uint32_t *err, hipStream_t s) {
+    hipLaunchKernelGGL(k_reserve, dim3(1), dim3(NT), 0, s, p, m, n, ops, list, res, err);
     return hipGetLastError();
 }
-hipError_t pkv_launch_release(const PoolDev &p, const ModelDev &m, int n, const int32_t *ops, BookResult *res, uint32_t *err,
-                              hipStream_t s) {
-    hipLaunchKernelGGL(k_release, dim3(1), dim3(NT), 0, s, p, m, n, ops, res, err);
+hipError_t pkv_launch_release(const PoolDev &p, const ModelDev &m, int n, const int32_t *ops, const BookList &list, BookResult *res,
+                              uint32_t *err, hipStream_t s) {
+    hipLaunchKernelGGL(k_release, dim3(1), dim3(NT), 0, s, p, m, n, ops, list, res, err);
     return hipGetLastError();
 }
