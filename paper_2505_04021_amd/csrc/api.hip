@@ -288,13 +288,15 @@ constexpr double kMemBytesPerUs = 6.6e6;       // what the memory system deliver
 constexpr double kDeepCapacity = 1.3;          // waves' own rate over the memory's, where more waves stop paying
 // Launches of fewer pages than kSmallMaxPages are bound by dependent memory trips and go to a kernel of their own
 // (k_attention_small: a work-group of four waves per part of a row and kv head), whichever form is in force.  Parts of
-// at least 32 pages (four page pairs a wave; 16 and 24 are slower where rows are ragged, 64 in single long rows), longer
-// where the launch has more than 512 of them, what the chip holds at once.  Ordinary or second form -> small kernel, us:
-// 4 short sequences of 8/2/64 9.4 -> 5.2; 32/8/128 bf16: 4 x 256 tokens 9.9 -> 5.6, 64 x 190 18.4 -> 9.5, 4 x 2048
-// 17.5 -> 11.3, 1 x 8192 21.5 -> 12.7, lognormal 8 x 2048 17.0 -> 13.0, 16 x 1024 (11 700 pages) 24.3 -> 23.1, 12 x 2048
-// (12 300) 25.0 -> 27.7, 16 x 2048 (27 100) 44.7 -> 56; e4m3 8 x 2048 22.1 -> 16.8 and, 64-wide, 21.6 -> 11.4.
-constexpr double kSmallMaxPages = 11000.0, kSmallWorkGroups = 512.0;
-constexpr int kSmallMinPart = 32, kSmallMaxParts = 64;
+// 32 pages (four page pairs a wave; with 24 or 48 eight lognormal rows of 2048 take 24-25 us instead of 22), longer where
+// the launch would then have more than the 512 work-groups that the chip holds at once (64 lognormal rows of 300 tokens:
+// 44 us in parts of 32, 26 in parts of 48).  Ordinary or second form -> small kernel, us:
+// 4 short sequences of 8/2/64 9.4 -> 4.7; 32/8/128 bf16: 4 x 256 tokens 9.9 -> 5.6, 64 x 190 18.4 -> 9.5, 4 x 2048
+// 17.3 -> 11.1, 1 x 8192 21.5 -> 12.7, lognormal 8 x 2048 (10 200 pages) 25.8 -> 22.1, 16 x 1024 (11 700) 24.0 -> 23.7,
+// 12 x 2048 (12 300) 25.2 -> 24.5, 16 x 2048 (27 100) 44.5 -> 45.4; e4m3 8 x 2048 22.2 -> 14.0 and, 64-wide, 21.6 -> 11.2.
+constexpr double kSmallMaxPages = 11000.0;
+constexpr long kSmallWorkGroups = 512;
+constexpr int kSmallParts = 6, kSmallPart[kSmallParts] = {32, 48, 64, 96, 128, 256}, kSmallMaxParts = 64;
 // Smallest share of a wave, in pages.  It only binds in launches too small to give every wave slot a
 // share; there the last wave of a (sequence, kv head) merges one partial per piece, one after the
 // other, and many small pieces cost more than they gain in parallelism: an eighth of a mean row,
@@ -309,7 +311,7 @@ constexpr double kPageCost = 0.8, kDeepPageCost = 1.6;
 int g_plan_items = kDefaultItems;     // items of the launch being prepared, all models together
 int g_last_items = 0;                 // items of the most recent launch
 bool g_small_now = false;             // the launch being prepared is a small one: a work-group per (sequence, kv head) or part of one
-double g_small_pages = 0.0;           // its pages, as far as the host knows
+long g_small_wgs[kSmallParts];        // its work-groups with parts of each length, as far as the host knows
 
 // Time (us) a wave of the second form, alone on its SIMD, spends on one page.
 double deep_page_us(const Model &m) {
@@ -359,7 +361,7 @@ void plan_launch(const LaunchLoad &l) {
     else g_deep_now = g_items == 0 && fits && l.units >= kDeepMinUnits;
     // (a caller that moves the split gets the kernel whose split it moves)
     g_small_now = g_deep_mode < 0 && g_items == 0 && g_min_share == 0 && g_seg_cost < 0 && l.pages < kSmallMaxPages;
-    g_small_pages = l.pages;
+    for (int k = 0; k < kSmallParts; ++k) g_small_wgs[k] = 0;
     g_plan_items = g_items > 0 ? g_items : (g_deep_now ? n : kDefaultItems);
 }
 
@@ -401,10 +403,13 @@ void fill_desc_core(AttnDesc &d, Model &m, int batch, const void *q, const int32
     d.n_items = items < 1.0 ? 1 : (int)items;                // never more than the slots in total
     if (d.n_items >= 8) d.n_items &= ~7;                     // whole blocks of eight: one item per XCD
     d.weighted = d.n_items % 8 == 0 ? 1 : 0;
-    d.max_pages = row_stride;
-    if (own) {
-        d.max_pages = 0;
-        for (int s = 0; s < batch; ++s) d.max_pages = d.max_pages > m.row_len[s] ? d.max_pages : m.row_len[s];
+    if (g_small_now) {
+        d.max_pages = own ? 0 : row_stride;
+        for (int s = 0; s < batch; ++s) {
+            const int pages = own ? m.row_len[s] : row_stride;
+            if (pages > d.max_pages) d.max_pages = pages;
+            for (int k = 0; k < kSmallParts; ++k) g_small_wgs[k] += m.Hkv * (pages > kSmallPart[k] ? (pages + kSmallPart[k] - 1) / kSmallPart[k] : 1);
+        }
     }
 }
 
@@ -574,9 +579,9 @@ static int tune_setup() {
 static bool plan_small(AttnGroup &grp) {
     if (!g_small_now) return false;
     const int grain = 8;                                  // a page pair for every wave of a work-group
-    int size = (int)(g_small_pages / kSmallWorkGroups);
-    size = size < kSmallMinPart ? kSmallMinPart : size;
-    size = (size + grain - 1) / grain * grain;
+    int size = PKV_MAX_ROW_BLOCKS;                        // rows enough for the chip: none is cut
+    for (int k = kSmallParts - 1; k >= 0; --k)
+        if (g_small_wgs[k] <= kSmallWorkGroups) size = kSmallPart[k];
     for (int i = 0; i < grp.n; ++i) {
         AttnDesc &d = grp.m[i];
         int part = size;
@@ -1662,7 +1667,7 @@ int decode_attention_static(int model, int batch, const void *q, const int32_t *
     HIP_TRY(pkv_static_scratch(&scratch_ptr));
     AttnGroup grp;
     grp.n = 1;
-    g_deep_now = false;                   // the ordinary kernel form, every cache type
+    g_deep_now = g_small_now = false;     // the ordinary kernel form, every cache type
     g_plan_items = g_items > 0 ? g_items : kDefaultItems;
     AttnDesc &d = grp.m[0];
     fill_desc_core(d, *m, batch, q, block_table, row_stride, ctx_lens, out, 1.0);
