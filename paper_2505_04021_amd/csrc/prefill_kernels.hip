@@ -31,9 +31,10 @@ constexpr int PF_COLS = 32;     // MFMA columns per wave
 constexpr int PF_SLOTS = 4;     // page pairs per ring (K and V have a ring each)
 static_assert(PF_WAVES * PF_COLS == PKV_PREFILL_COLS, "host and kernel must agree on the group size");
 
-// Where the reference point of the exponentials starts: finite, so that a column that has seen no token
-// yet needs no special case (its probabilities are exp2(-inf) = 0 and any real maximum replaces it).
-constexpr float PF_M0 = -1e30f;
+// Where the reference point of the exponentials starts: finite, so that a column that has seen no token yet needs no
+// special case (its probabilities are exp2(-inf) = 0), and the lowest number there is, so that the first visible token's
+// score, whatever it is, lies above it and replaces it.
+constexpr float PF_M0 = -3.402823466e+38f;
 
 template <int D, int DT>
 struct PfTile {

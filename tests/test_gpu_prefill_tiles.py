@@ -1,6 +1,7 @@
 """Prefill at the edges of its tiles: query counts around a wave's tile and a work-group's group (32 // g and
 4 * (32 // g) tokens), contexts around page pairs, the rings of pairs in flight and the 64 pairs (2048 tokens) whose
 addresses are worked out at a time, against the oracle.  Bars as for all prefill tests (bf16 2e-3, e4m3 2e-2)."""
+import numpy as np
 import pytest
 
 from parity import TOL, row_rel_err
@@ -42,6 +43,40 @@ def test_chunk_of_many_sequences(gpu, oracle, n, dtype):  # noqa: F811
     for be, m in zip(t.be, t.models):
         assert be.kv_append_chunk(m, k, v, qlen, ctx) == sum(qlen)
     q = gen.queries((41, n), sum(qlen), hq, d)
+    rc_o, out_o = oracle.prefill_attention(t.models[1], q, qlen, ctx)
+    rc_g, out_g = gpu.prefill_attention(t.models[0], q, qlen, ctx)
+    assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
+    assert row_rel_err(out_g, out_o) <= TOL[dtype]
+    t.close()
+
+
+@pytest.mark.parametrize("dtype", [BF16, E4M3])
+@pytest.mark.parametrize("score", [-1e20, -1e29, -1e33, -1e38])
+def test_prefill_of_very_low_scores(gpu, oracle, dtype, score):  # noqa: F811
+    """Every visible score far below zero, every fifth one (the first token among them) equal to the row's maximum and the
+    others far below that: a row is the mean of the V it gives weight to, as for any other level of the scores.  Fresh
+    prompts, and few queries in front of a context that is cut into parts."""
+    hq, hkv, d = 8, 2, 64
+    cases = [(70, 70), (33, 2), (1, 1), (1500, 3), (2100, 1)]
+    ctx, qlen = [c for c, _ in cases], [n for _, n in cases]
+    t = Twin(gpu, oracle, hq, hkv, d, dtype, ctx, max_blocks=160)
+    size = np.float32(np.sqrt(-score * 8))          # q and k of this size: |q k| / sqrt(64) = |score|
+    for s, c in enumerate(ctx):
+        kv = gen.seq_kv((13, s), c, hkv, d, dtype, 16)
+        low = np.where(np.arange(c) % 5 == 0, -1.0, -2.0)
+        if dtype == BF16:
+            k = np.zeros((c, hkv, d), dtype=np.float32)
+            k[:, :, 0] = low[:, None] * size
+            kv["k"] = (k.view(np.uint32) >> 16).astype(np.uint16)
+        else:
+            kv["k"] = np.zeros((c, hkv, d), dtype=np.uint8)
+            kv["k"][:, :, 0] = np.where(low == -1.0, 0xB8, 0xC0)[:, None]        # the codes of -1 and -2
+            kv["k_scale"] = np.full_like(kv["k_scale"], size)
+        for be, m in zip(t.be, t.models):
+            assert be.kv_write(m, s, 0, kv["k"], kv["v"], kv["k_scale"], kv["v_scale"]) == c
+    q = np.zeros((sum(qlen), hq, d), dtype=np.float32)
+    q[:, :, 0] = size
+    q = (q.view(np.uint32) >> 16).astype(np.uint16)
     rc_o, out_o = oracle.prefill_attention(t.models[1], q, qlen, ctx)
     rc_g, out_g = gpu.prefill_attention(t.models[0], q, qlen, ctx)
     assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
