@@ -35,6 +35,8 @@ static_assert(PF_WAVES * PF_COLS == PKV_PREFILL_COLS, "host and kernel must agre
 // special case (its probabilities are exp2(-inf) = 0), and the lowest number there is, so that the first visible token's
 // score, whatever it is, lies above it and replaces it.
 constexpr float PF_M0 = -3.402823466e+38f;
+// Scores (log2 domain) beyond this are rounded to more than one.
+constexpr float PF_FAR = 0x1p24f;
 
 template <int D, int DT>
 struct PfTile {
@@ -283,10 +285,22 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
     // ---- one pair's softmax, in two parts.  Arguments: t = score * scale - m (log2 domain) against the reference
     // point m as it stands.  m need not be the column's maximum, only near it: it moves, and the sums are
     // rescaled, when some argument exceeds kRescaleSlack, so that probabilities stay below 2^kRescaleSlack.
+    // An argument takes the score before it is rounded, m is a rounded one: where that difference is no longer small
+    // (some |m| beyond PF_FAR), every step is settled (slack -inf), with arguments that take the rounded score too.
     f32x16 s, t;
-    auto args = [&](int p, bool masked) __attribute__((always_inline)) {
+    float slack = kRescaleSlack;                           // wave-uniform
+    auto args = [&](int p, bool masked, bool far = false) __attribute__((always_inline)) {
+        if (far) {
+#pragma clang fp contract(off)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) t[i] = __builtin_fmaf(s[i], i < 8 ? sca : scb, -m);
+            for (int i = 0; i < 16; ++i) {
+                const float x = s[i] * (i < 8 ? sca : scb);
+                t[i] = x - m;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) t[i] = __builtin_fmaf(s[i], i < 8 ? sca : scb, -m);
+        }
         if (masked) {
             const int rel = col_lim - 32 * p - 4 * h;
 #pragma unroll
@@ -301,7 +315,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
 #pragma unroll
         for (int i = 3; i < 15; i += 2) mx = fmaxf(fmaxf(mx, t[i]), t[i + 1]);
         mx = fmaxf(mx, t[15]);
-        if (__builtin_expect(__any(mx > kRescaleSlack), 0)) {
+        if (__builtin_expect(__any(mx > slack), 0)) {
             // the column's maximum from the scores themselves (t is inexact when m is far off)
             const int rel = col_lim - 32 * p - 4 * h;
             float top = -INFINITY;
@@ -318,7 +332,9 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
 #pragma unroll
             for (int dt = 0; dt < TL::ND; ++dt) acc[dt] *= alpha;
             m = m_new;
-            args(p, masked);
+            const bool far = __any(fabsf(m) > PF_FAR && m > PF_M0);
+            slack = far ? -INFINITY : kRescaleSlack;
+            args(p, masked, far);
         }
     };
     auto scores = [&]() __attribute__((always_inline)) {

@@ -51,34 +51,40 @@ def test_chunk_of_many_sequences(gpu, oracle, n, dtype):  # noqa: F811
 
 
 @pytest.mark.parametrize("dtype", [BF16, E4M3])
-@pytest.mark.parametrize("score", [-1e20, -1e29, -1e33, -1e38])
-def test_prefill_of_very_low_scores(gpu, oracle, dtype, score):  # noqa: F811
-    """Every visible score far below zero, every fifth one (the first token among them) equal to the row's maximum and the
+@pytest.mark.parametrize("score", [-1e6, -1e20, -1e29, -1e33, -2e37, 1e6, 1e20, 2e37])
+def test_prefill_of_extreme_scores(gpu, oracle, dtype, score):  # noqa: F811
+    """Every visible score far from zero, every fifth one (the first token among them) equal to the row's maximum and the
     others far below that: a row is the mean of the V it gives weight to, as for any other level of the scores.  Fresh
     prompts, and few queries in front of a context that is cut into parts."""
     hq, hkv, d = 8, 2, 64
     cases = [(70, 70), (33, 2), (1, 1), (1500, 3), (2100, 1)]
     ctx, qlen = [c for c, _ in cases], [n for _, n in cases]
     t = Twin(gpu, oracle, hq, hkv, d, dtype, ctx, max_blocks=160)
-    size = np.float32(np.sqrt(-score * 8))          # q and k of this size: |q k| / sqrt(64) = |score|
-    for s, c in enumerate(ctx):
-        kv = gen.seq_kv((13, s), c, hkv, d, dtype, 16)
-        low = np.where(np.arange(c) % 5 == 0, -1.0, -2.0)
-        if dtype == BF16:
-            k = np.zeros((c, hkv, d), dtype=np.float32)
-            k[:, :, 0] = low[:, None] * size
-            kv["k"] = (k.view(np.uint32) >> 16).astype(np.uint16)
-        else:
-            kv["k"] = np.zeros((c, hkv, d), dtype=np.uint8)
-            kv["k"][:, :, 0] = np.where(low == -1.0, 0xB8, 0xC0)[:, None]        # the codes of -1 and -2
-            kv["k_scale"] = np.full_like(kv["k_scale"], size)
-        for be, m in zip(t.be, t.models):
-            assert be.kv_write(m, s, 0, kv["k"], kv["v"], kv["k_scale"], kv["v_scale"]) == c
-    q = np.zeros((sum(qlen), hq, d), dtype=np.float32)
-    q[:, :, 0] = size
-    q = (q.view(np.uint32) >> 16).astype(np.uint16)
-    rc_o, out_o = oracle.prefill_attention(t.models[1], q, qlen, ctx)
-    rc_g, out_g = gpu.prefill_attention(t.models[0], q, qlen, ctx)
-    assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
-    assert row_rel_err(out_g, out_o) <= TOL[dtype]
-    t.close()
+    try:
+        size = np.float32(np.sqrt(abs(score) * 8))      # q and k of this size: |q k| / sqrt(64) = |score|
+        for s, c in enumerate(ctx):
+            kv = gen.seq_kv((13, s), c, hkv, d, dtype, 16)
+            level = np.where(np.arange(c) % 5 == 0, -1.0, -2.0) if score < 0 else np.where(np.arange(c) % 5 == 0, 2.0, 1.0)
+            if dtype == BF16:
+                k = np.zeros((c, hkv, d), dtype=np.float32)
+                k[:, :, 0] = level[:, None] * size
+                kv["k"] = (k.view(np.uint32) >> 16).astype(np.uint16)
+            else:
+                kv["k"] = np.zeros((c, hkv, d), dtype=np.uint8)
+                kv["k"][:, :, 0] = np.where(abs(level) == 1.0, 0x38, 0x40)[:, None] + (0x80 if score < 0 else 0)
+                kv["k_scale"] = np.full_like(kv["k_scale"], size)
+            for be, m in zip(t.be, t.models):
+                assert be.kv_write(m, s, 0, kv["k"], kv["v"], kv["k_scale"], kv["v_scale"]) == c
+        q = np.zeros((sum(qlen), hq, d), dtype=np.float32)
+        q[:, :, 0] = size
+        q = (q.view(np.uint32) >> 16).astype(np.uint16)
+        rc_o, out_o = oracle.prefill_attention(t.models[1], q, qlen, ctx)
+        rc_g, out_g = gpu.prefill_attention(t.models[0], q, qlen, ctx)
+        assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
+        assert row_rel_err(out_g, out_o) <= TOL[dtype]
+        # the last query of every chunk is a decode step
+        last = np.cumsum(qlen) - 1
+        rc_g, out_g = gpu.decode_attention(t.models[0], q[last], t.ctx)
+        assert rc_g == 0 and row_rel_err(out_g, out_o[last]) <= TOL[dtype]
+    finally:
+        t.close()
