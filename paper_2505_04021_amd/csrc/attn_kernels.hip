@@ -185,8 +185,8 @@ __device__ __forceinline__ void split_p(const float *p, u32x2 &hi, u32x2 &lo) {
 // One online-softmax step over the 32 tokens of a page pair.  valid_a is 1..16,
 // valid_b 0..16 (0: the pair has no second page; its registers hold zeros).  Whether the
 // pair needs masks is decided at run time inside (one code path with selects: the kernel is
-// bound by memory).
-template <int D, int DT>
+// bound by memory).  MAY_BE_EMPTY: logits of -inf may be all that a column has seen so far; they weigh nothing.
+template <int D, int DT, bool MAY_BE_EMPTY = false>
 __device__ __forceinline__ void process_pair(State<D, DT> &st, const PairRegs<D, DT> &r, const bf16x8 *qf,
                                              float scale_log2, int valid_a, int valid_b, int G) {
     using TL = Tile<D, DT>;
@@ -211,15 +211,16 @@ __device__ __forceinline__ void process_pair(State<D, DT> &st, const PairRegs<D,
     // wave-uniform: the reference point of the exponentials moves, and the sums are rescaled, only when some
     // column's maximum has run ahead of it by more than kRescaleSlack (probabilities stay below 2^kRescaleSlack)
     if (__any(m_new > st.m + kRescaleSlack)) {
-        const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
+        const float alpha = MAY_BE_EMPTY && m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(st.m - m_new);
         st.l *= alpha;
 #pragma unroll
         for (int jt = 0; jt < TL::NV; ++jt) st.acc[jt] *= alpha;
         st.m = m_new;
     }
     float p[8];
+    const float m_ref = MAY_BE_EMPTY && st.m == -INFINITY ? 0.f : st.m;      // then every s is -inf and every p is 0
 #pragma unroll
-    for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - st.m);
+    for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - m_ref);
     st.l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
     if (DT == PKV_E4M3) {
 #pragma unroll
@@ -851,6 +852,10 @@ __global__ __launch_bounds__(64, 2) void k_attention_static(const AttnGroup grp)
 // (plan_small); a context that has outgrown them (a launch replayed from a graph) gets longer parts here.
 constexpr int SMALL_WAVES = 4;
 
+// Weight of a partial sum with maximum m beside a joint maximum of M.  A wave or part that has seen nothing but logits of
+// -inf has m = -inf and sums of zero (four waves each begin somewhere in the row, so that is not only the row's own start).
+__device__ __forceinline__ float merge_weight(float m, float M) { return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M); }
+
 template <int D, int DT>
 __device__ __forceinline__ void attn_part(const AttnDesc &d, int wg, float *s_acc, float *s_m, float *s_l, uint32_t *s_arrived) {
     using TL = Tile<D, DT>;
@@ -909,7 +914,7 @@ __device__ __forceinline__ void attn_part(const AttnDesc &d, int wg, float *s_ac
             if (p < pe) {
                 const int va = p == n_pages - 1 ? last_valid : T;
                 const int vb = p + 1 < pe ? (p + 1 == n_pages - 1 ? last_valid : T) : 0;
-                process_pair<D, DT>(st, ring[r], qf, d.scale_log2, va, vb, G);
+                process_pair<D, DT, true>(st, ring[r], qf, d.scale_log2, va, vb, G);
             }
             p += STEP;
         }
@@ -942,7 +947,7 @@ __device__ __forceinline__ void attn_part(const AttnDesc &d, int wg, float *s_ac
         if (n_pages > 0) {                                // an empty context: the row is defined as zero
 #pragma unroll
             for (int v = 0; v < SMALL_WAVES; ++v) {
-                const float f = __builtin_amdgcn_exp2f(s_m[v * 16 + hn] - M);
+                const float f = merge_weight(s_m[v * 16 + hn], M);
                 den += f * s_l[v * 16 + hn];
                 num += f * *reinterpret_cast<const f32x4 *>(s_acc + (v * g + hn) * D + 4 * x);
             }
@@ -987,7 +992,7 @@ __device__ __forceinline__ void attn_part(const AttnDesc &d, int wg, float *s_ac
 #pragma unroll
             for (int u = 0; u < 8; ++u)
                 if (c0 + u < n_parts) {
-                    const float f = __builtin_amdgcn_exp2f(s_acc[(c0 + u) * g + hn] - M);
+                    const float f = merge_weight(s_acc[(c0 + u) * g + hn], M);
                     den += f * s_acc[MAX_PIECES * 16 + (c0 + u) * g + hn];
                     num += f * v[u];
                 }

@@ -60,3 +60,26 @@ def test_rows_outgrow_a_captured_launch(gpu, oracle):  # noqa: F811
         rc_o, out_o = oracle.decode_attention(t.models[1], q, np.array(step, dtype=np.int32))
         assert rc_o == 0 and gpu.device_errors() == 0 and row_rel_err(out.cpu().numpy(), out_o) <= TOL[BF16]
     t.close()
+
+
+@pytest.mark.parametrize("ctx", [[300], [64, 200, 128], [2100, 90]])
+def test_tokens_of_logit_minus_infinity(gpu, oracle, ctx):  # noqa: F811
+    """Keys of -inf in pages 2 to 5, 10, 11 and 64 to 95: those tokens weigh nothing, also where they are all that one wave of
+    a work-group, or one part of a row, gets to see."""
+    hq, hkv, d = 8, 2, 64
+    t = Twin(gpu, oracle, hq, hkv, d, BF16, ctx, max_blocks=140)
+    try:
+        for s, c in enumerate(ctx):
+            kv = gen.seq_kv((13, s), c, hkv, d, BF16, 16)
+            page = np.arange(c) // 16
+            kv["k"][((page >= 2) & (page < 6)) | (page == 10) | (page == 11) | ((page >= 64) & (page < 96)), :, 0] = 0xFF80
+            for be, m in zip(t.be, t.models):
+                assert be.kv_write(m, s, 0, kv["k"], kv["v"]) == c
+        q = gen.queries((61,), len(ctx), hq, d)
+        q[:, :, 0] = 0x3F80                              # a positive factor of the infinite element
+        rc_o, out_o = oracle.decode_attention(t.models[1], q, np.array(ctx, dtype=np.int32))
+        rc_g, out_g = gpu.decode_attention(t.models[0], q, np.array(ctx, dtype=np.int32))
+        assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
+        assert row_rel_err(out_g, out_o) <= TOL[BF16]
+    finally:
+        t.close()
