@@ -185,22 +185,29 @@ __device__ __forceinline__ u32x2 transpose_halves(uint32_t w0, uint32_t w1, int 
     return mk2(__builtin_amdgcn_perm(z1, z0, sel), __builtin_amdgcn_perm(z3, z2, sel));
 }
 
-// Bytes of a V unit's token group that belong to slots first .. last - 1: of the word with one byte per token (e4m3) ...
-__device__ __forceinline__ uint32_t slot_bytes(int group, int first, int last) {
-    uint32_t m = 0;
+// A V unit holds the four tokens of slots 4 * group .. + 3; those of slots first .. last - 1 are stored.  A unit that
+// is written in part is stored by elements and never read back: another call, on another stream, may be writing the other
+// tokens of the group.  e4m3: word u, byte k = token k of element 16 u; bf16: two words, then two words, two tokens each.
+template <int E>
+__device__ __forceinline__ void put_v_unit(uint8_t *unit, u32x4 v, int group, int first, int last) {
+    const int k0 = first - 4 * group, k1 = last - 4 * group;
+    if (k0 <= 0 && k1 >= 4) {
+        *reinterpret_cast<u32x4 *>(unit) = v;
+        return;
+    }
+    if (k0 >= 4 || k1 <= 0) return;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) m |= (4 * group + k >= first && 4 * group + k < last) ? 0xffu << (8 * k) : 0u;
-    return m;
-}
-// ... and of the two words with two tokens each (bf16).
-__device__ __forceinline__ u32x2 slot_halves(int group, int first, int last) {
-    uint32_t m[2] = {0, 0};
+    for (int k = 0; k < 4; ++k)
+        if (k >= k0 && k < k1) {
+            if constexpr (E == 2) {
+                reinterpret_cast<uint16_t *>(unit)[k] = (uint16_t)(v[k >> 1] >> (16 * (k & 1)));
+                reinterpret_cast<uint16_t *>(unit)[4 + k] = (uint16_t)(v[2 + (k >> 1)] >> (16 * (k & 1)));
+            } else {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) m[k >> 1] |= (4 * group + k >= first && 4 * group + k < last) ? 0xffffu << (16 * (k & 1)) : 0u;
-    return mk2(m[0], m[1]);
+                for (int u = 0; u < 4; ++u) unit[4 * u + k] = (uint8_t)(v[u] >> (8 * k));
+            }
+        }
 }
-
-__device__ __forceinline__ u32x4 blend(u32x4 neu, u32x4 old, u32x4 mask) { return (neu & mask) | (old & ~mask); }
 
 // bf16 values into a bf16 tile
 template <int D, bool IS_V>
@@ -214,20 +221,13 @@ __device__ __forceinline__ void page_bf16(uint8_t *tile, const PageRows &p) {
             if (t >= p.s0 && t < p.s0 + p.n) *reinterpret_cast<u32x4 *>(tile + ((4 * i + c) * 16 + t) * 16) = mk4(w[0], w[1], w[2], w[3]);
         }
     } else {
-        const u32x2 m = slot_halves(G, p.s0, p.s0 + p.n);
-        const bool any = (m.x | m.y) != 0u, whole = (m.x & m.y) == 0xffffffffu;
 #pragma unroll
         for (int jp = 0; jp < D / 32; ++jp) {
             uint32_t a[2], b[2];
             row_bytes<8, 2>(a, p, t, 2 * (32 * jp + 4 * c));
             row_bytes<8, 2>(b, p, t, 2 * (32 * jp + 16 + 4 * c));
             const u32x2 ta = transpose_halves(a[0], a[1], e), tb = transpose_halves(b[0], b[1], e);
-            u32x4 *unit = reinterpret_cast<u32x4 *>(tile + ((jp * 4 + G) * 16 + 4 * c + e) * 16);
-            u32x4 v = mk4(ta.x, ta.y, tb.x, tb.y);
-            if (any) {
-                if (!whole) v = blend(v, *unit, mk4(m.x, m.y, m.x, m.y));
-                *unit = v;
-            }
+            put_v_unit<2>(tile + ((jp * 4 + G) * 16 + 4 * c + e) * 16, mk4(ta.x, ta.y, tb.x, tb.y), G, p.s0, p.s0 + p.n);
         }
     }
 }
@@ -236,7 +236,6 @@ __device__ __forceinline__ void page_bf16(uint8_t *tile, const PageRows &p) {
 template <int D, bool IS_V>
 __device__ __forceinline__ void page_codes(uint8_t *tile, const PageRows &p) {
     const int lane = threadIdx.x & 63, t = lane & 15, c = lane >> 4, G = t >> 2, e = t & 3;
-    const uint32_t m = slot_bytes(G, p.s0, p.s0 + p.n);
 #pragma unroll
     for (int j = 0; j < D / 64; ++j) {
         uint32_t w[4];
@@ -250,12 +249,7 @@ __device__ __forceinline__ void page_codes(uint8_t *tile, const PageRows &p) {
                 row_bytes<4, 1>(w + u, p, t, 64 * j + 16 * u + 4 * c);
                 w[u] = transpose_bytes(w[u], e);
             }
-            u32x4 *unit = reinterpret_cast<u32x4 *>(tile + ((j * 4 + G) * 16 + 4 * c + e) * 16);
-            u32x4 v = mk4(w[0], w[1], w[2], w[3]);
-            if (m) {
-                if (m != 0xffffffffu) v = blend(v, *unit, mk4(m, m, m, m));
-                *unit = v;
-            }
+            put_v_unit<1>(tile + ((j * 4 + G) * 16 + 4 * c + e) * 16, mk4(w[0], w[1], w[2], w[3]), G, p.s0, p.s0 + p.n);
         }
     }
 }
@@ -310,11 +304,10 @@ __device__ __forceinline__ void page_quantise(uint8_t *tile, float *scale_p, con
             for (int u = 0; u < 4; ++u) row_bytes<8, 2>(x + 8 * i + 2 * u, p, t, 2 * (64 * i + 16 * u + 4 * c));
         }
     }
-    // what the tile holds: codes of the slots before, and (V: units hold four tokens) bytes that must stay
+    // what the tile holds: codes of the slots before
     u32x4 old[D / 64];
-    const bool keeps = s0 > 0 || (IS_V && end < PKV_T);
     u32x4 *unit = reinterpret_cast<u32x4 *>(tile + (IS_V ? (G * 16 + 4 * c + e) * 16 : (c * 16 + t) * 16));
-    if (keeps) {
+    if (s0 > 0) {
 #pragma unroll
         for (int i = 0; i < D / 64; ++i) old[i] = unit[64 * i];
     }
@@ -380,16 +373,14 @@ __device__ __forceinline__ void page_quantise(uint8_t *tile, float *scale_p, con
     }
     if (lane == 0) *scale_p = of_lane(scale, end - 1);
     const int first = raised ? 0 : s0;                   // slots below it still hold what memory holds
-    const uint32_t m = slot_bytes(G, first, end);
 #pragma unroll
     for (int i = 0; i < D / 64; ++i) {
         if constexpr (!IS_V) {
             if (t >= first && t < end) unit[64 * i] = mk4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
         } else {
-            u32x4 v = mk4(transpose_bytes(w[4 * i], e), transpose_bytes(w[4 * i + 1], e), transpose_bytes(w[4 * i + 2], e),
+            const u32x4 v = mk4(transpose_bytes(w[4 * i], e), transpose_bytes(w[4 * i + 1], e), transpose_bytes(w[4 * i + 2], e),
                           transpose_bytes(w[4 * i + 3], e));
-            if (keeps) v = blend(v, old[i], mk4(m, m, m, m));
-            if (m) unit[64 * i] = v;
+            put_v_unit<1>(reinterpret_cast<uint8_t *>(unit + 64 * i), v, G, first, end);
         }
     }
 }
