@@ -333,7 +333,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
             for (int dt = 0; dt < TL::ND; ++dt) acc[dt] *= alpha;
             m = m_new;
             const bool far = __any(fabsf(m) > PF_FAR && m > PF_M0);
-            slack = far ? -INFINITY : kRescaleSlack;
+            slack = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(far ? -INFINITY : kRescaleSlack)));
             args(p, masked, far);
         }
     };
