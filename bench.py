@@ -27,7 +27,7 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-KERNEL_FORM_NAME = ("k_attention", "k_attention_deep")
+KERNEL_FORM_NAME = ("k_attention", "k_attention_deep", "k_attention_small")
 HBM_PEAK_GBPS = 8000.0      # MI355X datasheet HBM3E bandwidth
 
 
@@ -443,7 +443,7 @@ def bursty_leg(gpu, torch, size, steps, warmup, frame_bytes=0):
     outs = [torch.empty((s.batch, s.q_heads, s.head_dim), dtype=torch.float32, device="cuda") for s in cfg.models]
     ctxs = [torch.zeros(s.batch, dtype=torch.int32, device="cuda") for s in cfg.models]
     staged = [[torch.from_numpy(adm[mi]).pin_memory() if mi in adm else None for mi in range(n)] for _, _, adm, _ in tape]
-    forms = [0, 0]
+    forms = [0] * len(KERNEL_FORM_NAME)
     tickets = []              # (step, ticket) of calls whose result has not been looked at yet
 
     def step(t):
@@ -468,7 +468,7 @@ def bursty_leg(gpu, torch, size, steps, warmup, frame_bytes=0):
         step(t)
     torch.cuda.synchronize()
     gpu.timing_enable(1)
-    forms[0] = forms[1] = 0
+    forms[:] = [0] * len(forms)
     first_timed = LAUNCHES[0]
     t0 = time.perf_counter()
     for t in range(warmup, total):

@@ -44,11 +44,11 @@ int pkv_set_segment_cost(int pages);
  * page units) or its pages are so small that 1024 such waves could not saturate the memory
  * (e4m3 caches with 64-wide heads). */
 int pkv_set_kernel_form(int form);
-/* The form (0 or 1) the most recent decode attention launch of this process was planned for.  With
- * every knob of the split at its default, launches of fewer than 11 000 pages run a kernel of their
- * own, whichever form that is: a work-group per (sequence, kv head), or per part of a long one. */
+/* What the most recent decode attention launch of this process ran as: form 0 or 1, or 2, the kernel of
+ * small launches (a work-group per (sequence, kv head), or per part of a long one), which the library takes
+ * for launches of fewer than 11 000 pages while every knob of the split is at its default. */
 int pkv_last_kernel_form(void);
-/* The work items (waves) that launch was planned for, all its models together. */
+/* The work items (waves; work-groups of four waves in form 2) of that launch, all its models together. */
 int pkv_last_launch_items(void);
 /* Cost model that shares the waves out among the models of a grouped launch: a page
  * costs per_mille/1000 + 0.1 per KiB of its K and V tile (-1 = the default: 800 in kernel

@@ -309,7 +309,8 @@ constexpr int kDefaultSegCost = 6;
 // 95.0 us at 0.8, 92.9 at 1.2, 92.6 at 1.6, 93.4 at 2.0, 94.4 at 2.4, 95.2 at 3.2.
 constexpr double kPageCost = 0.8, kDeepPageCost = 1.6;
 int g_plan_items = kDefaultItems;     // items of the launch being prepared, all models together
-int g_last_items = 0;                 // items of the most recent launch
+AttnForm g_last_form = AttnForm::ordinary;  // what the most recent launch ran as
+int g_last_items = 0;                 // its work items, work-groups of a small launch
 bool g_small_now = false;             // the launch being prepared is a small one: a work-group per (sequence, kv head) or part of one
 long g_small_wgs[kSmallParts];        // its work-groups with parts of each length, as far as the host knows
 
@@ -614,8 +615,14 @@ static int launch_attention(AttnGroup &grp) {
         items += grp.m[i].n_items;
         measure = measure && grp.m[i].weighted;
     }
+    const AttnForm form = plan_small(grp) ? AttnForm::small : (g_deep_now ? AttnForm::deep : AttnForm::ordinary);
+    g_last_form = form;
     g_last_items = items;
-    measure = measure && items >= kMinTuneItems && !g_small_now;
+    if (form == AttnForm::small) {
+        const AttnDesc &last = grp.m[grp.n - 1];
+        g_last_items = last.item_begin + last.batch * last.Hkv * last.parts;
+    }
+    measure = measure && items >= kMinTuneItems && form != AttnForm::small;
     if (measure && g_tune_left <= 0) measure = ++g_tune_tick % kSlowTuneEvery == 0;
     if (measure) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -625,7 +632,6 @@ static int launch_attention(AttnGroup &grp) {
         if (slot < 0) measure = false;                     // all copies still travelling
     }
     fill_tune(grp.tune, measure);
-    const AttnForm form = plan_small(grp) ? AttnForm::small : (g_deep_now ? AttnForm::deep : AttnForm::ordinary);
     HIP_TRY(pkv_launch_attention(grp, form, g_stream, next_events()));
     if (measure) {
         HIP_TRY(hipMemcpyAsync(g_tune_host + 16 * slot, g_xcd_stat, 16 * sizeof(uint64_t), hipMemcpyDeviceToHost, g_stream));
@@ -687,7 +693,7 @@ int pkv_set_kernel_form(int form) {
     return PKV_OK;
 }
 
-int pkv_last_kernel_form(void) { return g_deep_now ? 1 : 0; }
+int pkv_last_kernel_form(void) { return g_last_form == AttnForm::small ? 2 : (g_last_form == AttnForm::deep ? 1 : 0); }
 
 int pkv_last_launch_items(void) { return g_last_items; }
 
@@ -1668,6 +1674,7 @@ int decode_attention_static(int model, int batch, const void *q, const int32_t *
     AttnGroup grp;
     grp.n = 1;
     g_deep_now = g_small_now = false;     // the ordinary kernel form, every cache type
+    g_last_form = AttnForm::ordinary;
     g_plan_items = g_items > 0 ? g_items : kDefaultItems;
     AttnDesc &d = grp.m[0];
     fill_desc_core(d, *m, batch, q, block_table, row_stride, ctx_lens, out, 1.0);

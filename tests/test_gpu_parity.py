@@ -345,9 +345,10 @@ def test_xcd_weights_api_and_tuning(gpu, oracle):
 
 
 def test_kernel_form_choice(gpu):
-    """Which form of the decode kernel a launch gets and how many work items: the ordinary form (2048
-    items at most) for small launches and for pages too small for 1024 lone waves to saturate the
-    memory (e4m3, 64-wide heads); otherwise one wave per SIMD with 512 (bf16, 128-wide heads), 768
+    """What a decode launch runs as and how many work items it has: the kernel of small launches (form 2, a work-group
+    per row and kv head here) below 11 000 pages with every knob of the split at its default; the ordinary form (2048
+    items at most) for pages too small for 1024 lone waves to saturate the memory (e4m3, 64-wide heads) and
+    for small launches whose split a caller moves; otherwise one wave per SIMD with 512 (bf16, 128-wide heads), 768
     (bf16, 64-wide) or 1024 (e4m3, 128-wide) items; either form when forced, with equal results."""
     pool = gpu.pool_create(2 << 30, 16, 2 << 20)
     assert pool >= 0
@@ -372,14 +373,20 @@ def test_kernel_form_choice(gpu):
             assert rc == 0 and np.isfinite(out).all()
             return gpu.last_kernel_form(), gpu.last_launch_items(), out
 
+        assert launch("b128", 4, 256)[:2] == (2, 32)
+        assert gpu.set_split(0, 4) == 0
         assert launch("b128", 4, 256)[:2] == (0, 184)          # 4 x (16 + 7) x 8 = 736 units in shares of 4 pages or more
+        assert gpu.set_split(0, 0) == 0
+        assert launch("b128", 64, 336)[:2] == (2, 512)         # 64 x 21 x 8 = 10 752 pages
+        assert launch("b128", 64, 337)[:2] == (1, 512)         # 64 x 22 x 8 = 11 264 pages
         assert launch("b128", 64, 1600)[:2] == (1, 512)
         assert launch("b128", 64, 400)[:2] == (1, 512)         # 64 x (25 + 7) x 8 = 16384 units
-        assert launch("b128", 64, 190)[0] == 0                 # 64 x (12 + 7) x 8 = 9728 units: small
+        assert launch("b128", 64, 190)[:2] == (2, 512)
         assert launch("b64", 64, 1600)[:2] == (1, 768)
         assert launch("e128", 64, 1600)[:2] == (1, 1024)
         assert launch("e64", 64, 1600)[:2] == (0, 2048)
-        assert launch("e128", 4, 200)[0] == 0
+        assert launch("e128", 4, 200)[:2] == (2, 32)
+        assert launch("e64", 4, 1024)[:2] == (2, 64)           # in two parts of 32 pages
         for key in shapes:                                      # forced either way: same numbers
             f1, n1, out1 = launch(key, 48, 1100, form=1)
             f0, n0, out0 = launch(key, 48, 1100, form=0)
@@ -389,7 +396,7 @@ def test_kernel_form_choice(gpu):
         assert gpu.set_kernel_form(2) == -1 and gpu.set_kernel_form(-2) == -1
         assert gpu.device_errors() == 0
     finally:
-        gpu.set_kernel_form(-1)
+        gpu.set_kernel_form(-1), gpu.set_split(0, 0)
         for m in ms.values():
             gpu.seq_release_batch(m, np.arange(64, dtype=np.int32))
             assert gpu.balloon_resize(m, 0) == 0 and gpu.model_unregister(m) == 0
