@@ -287,16 +287,14 @@ constexpr double kDeepMinUnits = 10240.0;
 constexpr double kMemBytesPerUs = 6.6e6;       // what the memory system delivers to this kernel at its best
 constexpr double kDeepCapacity = 1.3;          // waves' own rate over the memory's, where more waves stop paying
 // Launches of fewer pages than kSmallMaxPages are bound by dependent memory trips and go to a kernel of their own
-// (k_attention_small: a work-group of four waves per part of a row and kv head), whichever form is in force.  Parts of
-// 32 pages (four page pairs a wave; with 24 or 48 eight lognormal rows of 2048 take 24-25 us instead of 22), longer where
-// the launch would then have more than the 512 work-groups that the chip holds at once (64 lognormal rows of 300 tokens:
-// 44 us in parts of 32, 26 in parts of 48).  Ordinary or second form -> small kernel, us:
+// (k_attention_small: a work-group of four waves per part of a row and kv head), whichever form is in force, if plan_small
+// finds a part length that suits their rows.  Ordinary or second form -> small kernel, us:
 // 4 short sequences of 8/2/64 9.4 -> 4.7; 32/8/128 bf16: 4 x 256 tokens 9.9 -> 5.6, 64 x 190 18.4 -> 9.5, 4 x 2048
 // 17.3 -> 11.1, 1 x 8192 21.5 -> 12.7, lognormal 8 x 2048 (10 200 pages) 25.8 -> 22.1, 16 x 1024 (11 700) 24.0 -> 23.7,
 // 12 x 2048 (12 300) 25.2 -> 24.5, 16 x 2048 (27 100) 44.5 -> 45.4; e4m3 8 x 2048 22.2 -> 14.0 and, 64-wide, 21.6 -> 11.2.
 constexpr double kSmallMaxPages = 11000.0;
-constexpr long kSmallWorkGroups = 512;
-constexpr int kSmallParts = 6, kSmallPart[kSmallParts] = {32, 48, 64, 96, 128, 256}, kSmallMaxParts = 64;
+constexpr int kSmallPart[] = {32, 48, 64, 96, 128, 256, PKV_MAX_ROW_BLOCKS}, kSmallMaxParts = 64;
+constexpr long kSmallWorkGroups = 512;         // that the chip holds at once
 // Smallest share of a wave, in pages.  It only binds in launches too small to give every wave slot a
 // share; there the last wave of a (sequence, kv head) merges one partial per piece, one after the
 // other, and many small pieces cost more than they gain in parallelism: an eighth of a mean row,
@@ -312,7 +310,7 @@ int g_plan_items = kDefaultItems;     // items of the launch being prepared, all
 AttnForm g_last_form = AttnForm::ordinary;  // what the most recent launch ran as
 int g_last_items = 0;                 // its work items, work-groups of a small launch
 bool g_small_now = false;             // the launch being prepared is a small one: a work-group per (sequence, kv head) or part of one
-long g_small_wgs[kSmallParts];        // its work-groups with parts of each length, as far as the host knows
+double g_small_pages = 0.0;           // its pages
 
 // Time (us) a wave of the second form, alone on its SIMD, spends on one page.
 double deep_page_us(const Model &m) {
@@ -362,7 +360,7 @@ void plan_launch(const LaunchLoad &l) {
     else g_deep_now = g_items == 0 && fits && l.units >= kDeepMinUnits;
     // (a caller that moves the split gets the kernel whose split it moves)
     g_small_now = g_deep_mode < 0 && g_items == 0 && g_min_share == 0 && g_seg_cost < 0 && l.pages < kSmallMaxPages;
-    for (int k = 0; k < kSmallParts; ++k) g_small_wgs[k] = 0;
+    g_small_pages = l.pages;
     g_plan_items = g_items > 0 ? g_items : (g_deep_now ? n : kDefaultItems);
 }
 
@@ -409,7 +407,6 @@ void fill_desc_core(AttnDesc &d, Model &m, int batch, const void *q, const int32
         for (int s = 0; s < batch; ++s) {
             const int pages = own ? m.row_len[s] : row_stride;
             if (pages > d.max_pages) d.max_pages = pages;
-            for (int k = 0; k < kSmallParts; ++k) g_small_wgs[k] += m.Hkv * (pages > kSmallPart[k] ? (pages + kSmallPart[k] - 1) / kSmallPart[k] : 1);
         }
     }
 }
@@ -576,22 +573,64 @@ static int tune_setup() {
     return PKV_OK;
 }
 
-// Lays a small launch out: pages per part, parts per (sequence, kv head), first work-group of every model.
-static bool plan_small(AttnGroup &grp) {
-    if (!g_small_now) return false;
+// Lays a small launch out with parts of `size` pages: pages per part and parts per (sequence, kv head).  Returns an
+// estimate of what it takes (us) beside what any small launch takes, or a negative number if the partials of some model do
+// not fit.  Every row comes in as many parts as the longest one, so a long row among many short ones means work-groups
+// without pages.
+static double lay_out_small(AttnGroup &grp, int size) {
     const int grain = 8;                                  // a page pair for every wave of a work-group
-    int size = PKV_MAX_ROW_BLOCKS;                        // rows enough for the chip: none is cut
-    for (int k = kSmallParts - 1; k >= 0; --k)
-        if (g_small_wgs[k] <= kSmallWorkGroups) size = kSmallPart[k];
+    long grid = 0;
     for (int i = 0; i < grp.n; ++i) {
         AttnDesc &d = grp.m[i];
         int part = size;
         if ((d.max_pages + part - 1) / part > kSmallMaxParts) part = ((d.max_pages + kSmallMaxParts - 1) / kSmallMaxParts + grain - 1) / grain * grain;
         d.part_pages = part;
         d.parts = d.max_pages > part ? (d.max_pages + part - 1) / part : 1;
-        // partials: one per work-group, in a workspace made for two per work item
-        if ((long)d.batch * d.Hkv * d.parts > 2L * kDefaultItems) return false;
+        grid += (long)d.batch * d.Hkv * d.parts;
     }
+    double walk = 0.0, empty = 0.0;
+    bool cut = false;
+    for (int i = 0; i < grp.n; ++i) {
+        AttnDesc &d = grp.m[i];
+        // Where the kv heads come fastest, the CUs of an XCD are dealt (row, part) in turn, and with an even number of parts
+        // all first parts, which every row has, would fall on the same few CUs: 60 rows of 100 tokens and one of 2000 in
+        // four parts 26.5 us, in five 18.8; 32 lognormal rows of 512 33.4 and 24.6 in parts of 48.
+        if (d.parts > 1 && d.parts < kSmallMaxParts && grid > kSmallWorkGroups && d.Hkv % 8 == 0) d.parts |= 1;
+        // partials: one per work-group, in a workspace made for two per work item
+        const long wgs = (long)d.batch * d.Hkv * d.parts;
+        if (wgs > 2L * kDefaultItems) return -1.0;
+        cut |= d.parts > 1;
+        const double page_kib = d.D * (d.dtype == PKV_BF16 ? 4 : 2) / 64.0;      // K and V of 16 tokens
+        const int pages = d.max_pages < d.part_pages ? d.max_pages : d.part_pages;
+        const double us = (double)((pages + grain - 1) / grain) * (0.5 + 0.07 * page_kib);
+        walk = us > walk ? us : walk;
+        empty += (double)wgs * (d.Hkv % 8 == 0 ? 0.003 : 0.0015);       // (a work-group without pages costs less where these come last)
+    }
+    return walk + (cut ? 2.0 + empty : grid > kSmallWorkGroups ? 0.0035 * grid : 0.0);
+}
+
+// Lays a small launch out with the best of the part lengths.  False where the ordinary forms are the better ones, which
+// deal pages out evenly whatever the rows: a few long rows among many short ones, or very many rows.  Small kernel and
+// ordinary forms, us, 32/8/128 bf16: 63 rows of 128 tokens and one of 8192 75 uncut, 32 to 47 in parts, 25.5; 64 of 64 and one
+// of 17 600 50 to 154, 29; 30 of 256 and one of 8192 26, 24.4; 120 of 50 and one of 1500 20 to 24, 18; 500 of 16 27, 24; but
+// 60 of 100 and one of 2000 18.6, 20.3; 30 of 256 and one of 4096 20.6, 22.6; 20 of 300 and three of 4000 20.1, 29.6;
+// 127 of 16 and one of 1000 12.7, 15.7; 100 lognormal rows of 120 19.5, 23.  What the ordinary forms take grows with the
+// pages, and with the longest row, whose pieces are joined one after the other (one of 60 000, one kv head: 24, 67).
+static bool plan_small(AttnGroup &grp) {
+    if (!g_small_now) return false;
+    int longest = 0, size = 0;
+    double best = 1e30;
+    for (int i = 0; i < grp.n; ++i) longest = longest > grp.m[i].max_pages ? longest : grp.m[i].max_pages;
+    for (int part : kSmallPart) {
+        const double us = lay_out_small(grp, part);
+        if (us >= 0.0 && us < best) {
+            best = us;
+            size = part;
+        }
+        if (part >= longest) break;                       // longer parts change nothing
+    }
+    if (size == 0 || best > fmax(12.0 + 0.5e-3 * g_small_pages, longest / 64.0)) return false;
+    lay_out_small(grp, size);
     int begin = 0;
     for (int i = 0; i < grp.n; ++i) {
         grp.m[i].item_begin = begin;

@@ -83,3 +83,23 @@ def test_tokens_of_logit_minus_infinity(gpu, oracle, ctx):  # noqa: F811
         assert row_rel_err(out_g, out_o) <= TOL[BF16]
     finally:
         t.close()
+
+
+@pytest.mark.parametrize("ctx,small", [([100] * 60 + [2000], True), ([256] * 30 + [4096], True), ([128] * 63 + [8192], False),
+                                       ([8192] + [128] * 63, False), ([64] * 64 + [9600], False), ([16] * 300, True), ([16] * 500, False)])
+def test_rows_of_unlike_length(gpu, oracle, ctx, small):  # noqa: F811
+    """A few long rows among many short ones, and very many rows: whether such a launch is cut into parts of rows or goes to
+    the forms that deal pages out evenly, no row waits for one work-group to walk a long context, and all rows are right."""
+    hq, hkv, d = 8, 8, 64
+    t = Twin(gpu, oracle, hq, hkv, d, BF16, ctx, max_blocks=640)
+    try:
+        q = gen.queries((67, len(ctx)), len(ctx), hq, d)
+        c = np.array(ctx, dtype=np.int32)
+        rc_o, out_o = oracle.decode_attention(t.models[1], q, c)
+        for _ in range(2):
+            rc_g, out_g = gpu.decode_attention(t.models[0], q, c)
+            assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
+            assert (gpu.last_kernel_form() == 2) == small
+            assert row_rel_err(out_g, out_o) <= TOL[BF16]
+    finally:
+        t.close()
