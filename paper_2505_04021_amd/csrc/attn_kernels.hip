@@ -852,8 +852,9 @@ __global__ __launch_bounds__(64, 2) void k_attention_static(const AttnGroup grp)
 // (plan_small); a context that has outgrown them (a launch replayed from a graph) gets longer parts here.
 constexpr int SMALL_WAVES = 4;
 
-// Weight of a partial sum with maximum m beside a joint maximum of M.  A wave or part that has seen nothing but logits of
-// -inf has m = -inf and sums of zero (four waves each begin somewhere in the row, so that is not only the row's own start).
+// Weight of a wave's sums with maximum m beside a joint maximum of M.  A wave that has seen nothing but logits of -inf has
+// m = -inf and sums of zero (four waves each begin somewhere in the row, so that is not only the row's own start); so may
+// have all waves of a part.
 __device__ __forceinline__ float merge_weight(float m, float M) { return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M); }
 
 template <int D, int DT>
@@ -992,7 +993,7 @@ __device__ __forceinline__ void attn_part(const AttnDesc &d, int wg, float *s_ac
 #pragma unroll
             for (int u = 0; u < 8; ++u)
                 if (c0 + u < n_parts) {
-                    const float f = merge_weight(s_acc[(c0 + u) * g + hn], M);
+                    const float f = __builtin_amdgcn_exp2f(s_acc[(c0 + u) * g + hn] - M);
                     den += f * s_acc[MAX_PIECES * 16 + (c0 + u) * g + hn];
                     num += f * v[u];
                 }
