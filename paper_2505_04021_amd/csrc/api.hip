@@ -412,7 +412,7 @@ void fill_desc_core(AttnDesc &d, Model &m, int batch, const void *q, const int32
 }
 
 // floats of split-K partials a launch of n_items work items needs: two partials per item
-size_t ws_floats_for(const Model &m, int n_items, int cols) { return (size_t)2 * n_items * cols * (m.D + 2); }
+size_t ws_floats_for(const Model &m, int n_items, int cols) { return (size_t)2 * n_items * partial_floats(cols, m.D); }
 
 // The model's own workspace.  It is sized at registration for every launch the default settings can
 // produce from the library's table; only a caller's table with more rows than the model has, or a

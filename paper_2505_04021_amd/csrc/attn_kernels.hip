@@ -255,9 +255,6 @@ __device__ __forceinline__ void process_pair(State<D, DT> &st, const PairRegs<D,
     }
 }
 
-// Floats per split-K partial: g rows of D accumulators, then g maxima, then g sums.
-__host__ __device__ inline int partial_floats(int g, int D) { return g * (D + 2); }
-
 constexpr int FLIGHT_KIB_2WAVES = 16;      // bytes in flight per wave, two waves per SIMD
 // Page pairs resident per wave: one in use, the rest in flight.  In the form with two waves per
 // SIMD every shape keeps the same number of bytes in flight (FLIGHT_KIB_2WAVES), small pages

@@ -62,6 +62,13 @@ struct PoolDev {
     int64_t n_frames;
 };
 
+// Floats per split-K partial of decode attention: g rows of D accumulators, then g maxima, then g sums, in whole 16-byte
+// units (the kernels read and write the accumulators in those, and a workspace holds partial after partial).
+__host__ __device__ constexpr int partial_floats(int g, int D) { return (g * (D + 2) + 3) & ~3; }
+static_assert(partial_floats(1, 128) * sizeof(float) % 16 == 0 && partial_floats(3, 64) * sizeof(float) % 16 == 0 &&
+                  partial_floats(16, 128) == 16 * 130 && partial_floats(5, 64) >= 5 * 66,
+              "whole units, nothing lost");
+
 // Device-resident per-model bookkeeping state.
 struct ModelDev {
     uint32_t *frames;      // [n_frames] acquisition order
