@@ -1577,12 +1577,18 @@ int kv_read(int model, int seq, int tok_begin, int n_tok, void *k_out, void *v_o
     return n_tok;
 }
 
-// Collects the ChunkPlan of one launch after the other.
+// Collects the ChunkPlan of one launch after the other; a call of more sequences than a plan holds comes in launches of
+// about equal size.
 struct PlanBuilder {
     ChunkPlan p;
     uint32_t row = 0, unit = 0;
-    PlanBuilder() { p.n_seqs = p.seq0 = 0; }
-    bool full() const { return p.n_seqs == PKV_PLAN_SEQS; }
+    int per_launch;
+    explicit PlanBuilder(int batch) {
+        const int launches = (batch + PKV_PLAN_SEQS - 1) / PKV_PLAN_SEQS;
+        per_launch = (batch + launches - 1) / launches;
+        p.n_seqs = p.seq0 = 0;
+    }
+    bool full() const { return p.n_seqs == per_launch; }
     void add(uint32_t rows, uint32_t units, uint32_t parts) {
         p.s[p.n_seqs].unit = unit;
         p.s[p.n_seqs].row = row | parts << PKV_PLAN_PART_SHIFT;
@@ -1621,7 +1627,7 @@ int kv_append_chunk(int model, int batch, const void *k_new, const void *v_new, 
     d.ctx_lens = ctx_lens;
     // one unit per (sequence, j-th page its chunk may touch): a chunk of n tokens that starts
     // anywhere in a page touches at most ceil(n / T) + 1 pages
-    PlanBuilder plan;
+    PlanBuilder plan(batch);
     for (int s = 0; s < batch; ++s) {
         if (plan.full()) {
             HIP_TRY(pkv_launch_kv_append_chunk(d, plan.take(s), k_new, v_new, g_stream));
@@ -1756,12 +1762,12 @@ static int prefill_parts(const Model &m, int seq, double part_pairs) {
 // pairs besides its own.  The parts' partial sums are written and read once, at about 3.5 TB/s.  Cutting up to 1024
 // work-groups whatever that costs, as before, took 135 us for 4 x (2048 + 512) tokens (112 uncut), 55 for 4 x (32 + 512)
 // (29 uncut), 103 for 8 x (4032 + 64) (65 with the cuts chosen here).
-static double prefill_part_pairs(const Model &m, int batch, const int32_t *q_lens, int group) {
+static double prefill_part_pairs(const Model &m, int seq0, int seq1, const int32_t *q_lens, int group) {
     const double t1 = m.D == 128 ? 0.85 : 0.60, t2 = m.D == 128 ? (m.dtype == PKV_BF16 ? 0.70 : 0.58) : 0.40;
     constexpr double kGroupPairs = 4.0, kCUs = 256.0, kMergeUs = 5.0, kPartBytesPerUs = 3.5e6;
     int longest = 0;
     double plain = 0.0;
-    for (int s = 0; s < batch; ++s)
+    for (int s = seq0; s < seq1; ++s)
         if (q_lens[s] > 0) {
             plain += (q_lens[s] + group - 1) / group;
             longest = longest > m.row_len[s] ? longest : m.row_len[s];
@@ -1774,7 +1780,7 @@ static double prefill_part_pairs(const Model &m, int batch, const int32_t *q_len
         const double part = cuts > 1 ? (double)longest / cuts : 0.0;
         if (cuts > 1 && part < kMinPartPairs) break;
         double units = 0.0, work = 0.0, top = 0.0, parts_written = 0.0;
-        for (int s = 0; s < batch; ++s) {
+        for (int s = seq0; s < seq1; ++s) {
             if (q_lens[s] == 0) continue;
             const int n = prefill_parts(m, s, part);
             const double u = (double)((q_lens[s] + group - 1) / group) * n * m.Hkv;
@@ -1813,7 +1819,6 @@ int prefill_attention(int model, int batch, const void *q, const int32_t *q_lens
         if (total > (int64_t)1 << 24) return PKV_E_RANGE;
     }
     if (total == 0) return PKV_OK;
-    const double part_pairs = prefill_part_pairs(*m, batch, q_lens, group);
     AttnDesc d{};
     fill_addressing(d, *m);
     d.q = (const uint16_t *)q;
@@ -1840,12 +1845,15 @@ int prefill_attention(int model, int batch, const void *q, const int32_t *q_lens
         split_groups = 0;
         return PKV_OK;
     };
-    PlanBuilder plan;
+    PlanBuilder plan(batch);
+    double part_pairs = 0.0;
     for (int s = 0; s < batch; ++s) {
         if (plan.full()) {
             const int rc = launch(plan.take(s));
             if (rc) return rc;
         }
+        if (s % plan.per_launch == 0)
+            part_pairs = prefill_part_pairs(*m, s, s + plan.per_launch < batch ? s + plan.per_launch : batch, q_lens, group);
         const int parts = prefill_parts(*m, s, part_pairs), groups = (q_lens[s] + group - 1) / group;
         plan.add((uint32_t)q_lens[s], (uint32_t)(groups * parts), (uint32_t)parts);
         if (parts > 1 && groups > split_groups) split_groups = groups;

@@ -486,8 +486,8 @@ __global__ __launch_bounds__(64) void k_kv_append(const AttnDesc d, const uint16
 // than the chunk can touch and a wave whose page holds none of the chunk leaves.  Tokens of one page go in order (the
 // e4m3 scale rule is sequential within a block by definition); pages do not depend on each other (a block's scale
 // starts afresh at its first slot).
-template <int DT>
-__global__ __launch_bounds__(64 * PAGE_WAVES) void k_kv_append_chunk(const AttnDesc d, const ChunkPlan plan, const uint16_t *k_new,
+template <int DT, int SEQS>
+__global__ __launch_bounds__(64 * PAGE_WAVES) void k_kv_append_chunk(const AttnDesc d, const PlanOf<SEQS> plan, const uint16_t *k_new,
                                                                      const uint16_t *v_new) {
     const int lane = threadIdx.x & 63;
     const int x = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * PAGE_WAVES + (threadIdx.x >> 6)));
@@ -565,11 +565,14 @@ hipError_t pkv_launch_kv_append(const AttnDesc &d, const void *k_new, const void
 hipError_t pkv_launch_kv_append_chunk(const AttnDesc &d, const ChunkPlan &plan, const void *k_new, const void *v_new, hipStream_t s) {
     const unsigned waves = plan.s[plan.n_seqs].unit * (unsigned)d.Hkv * 2u, blocks = (waves + PAGE_WAVES - 1) / PAGE_WAVES;
     if (blocks == 0) return hipSuccess;
-    if (d.dtype == PKV_BF16)
-        hipLaunchKernelGGL(k_kv_append_chunk<PKV_BF16>, dim3(blocks), dim3(64 * PAGE_WAVES), 0, s, d, plan, (const uint16_t *)k_new,
-                           (const uint16_t *)v_new);
-    else
-        hipLaunchKernelGGL(k_kv_append_chunk<PKV_E4M3>, dim3(blocks), dim3(64 * PAGE_WAVES), 0, s, d, plan, (const uint16_t *)k_new,
-                           (const uint16_t *)v_new);
+    const dim3 grid(blocks), wg(64 * PAGE_WAVES);
+    const uint16_t *k = (const uint16_t *)k_new, *v = (const uint16_t *)v_new;
+    if (plan.n_seqs <= PKV_PLAN_FEW) {
+        if (d.dtype == PKV_BF16) hipLaunchKernelGGL((k_kv_append_chunk<PKV_BF16, PKV_PLAN_FEW>), grid, wg, 0, s, d, few_of(plan), k, v);
+        else hipLaunchKernelGGL((k_kv_append_chunk<PKV_E4M3, PKV_PLAN_FEW>), grid, wg, 0, s, d, few_of(plan), k, v);
+    } else {
+        if (d.dtype == PKV_BF16) hipLaunchKernelGGL((k_kv_append_chunk<PKV_BF16, PKV_PLAN_SEQS>), grid, wg, 0, s, d, plan, k, v);
+        else hipLaunchKernelGGL((k_kv_append_chunk<PKV_E4M3, PKV_PLAN_SEQS>), grid, wg, 0, s, d, plan, k, v);
+    }
     return hipGetLastError();
 }

@@ -47,20 +47,25 @@ struct PlanUnit {
 
 // One read of the plan for all 64 lanes and no further memory trip: the sequence is the last one that begins at
 // or before u (sequences without units share their start with the next one).
-__device__ __forceinline__ PlanUnit plan_find(const ChunkPlan &plan, uint32_t u) {
-    static_assert(PKV_PLAN_SEQS + 1 == 128, "two entries per lane");
+template <int SEQS>
+__device__ __forceinline__ PlanUnit plan_find(const PlanOf<SEQS> &plan, uint32_t u) {
+    constexpr int PER_LANE = (SEQS + 1) / 64;
+    static_assert(PER_LANE * 64 == SEQS + 1, "whole entries per lane");
     const int lane = threadIdx.x & 63, n = plan.n_seqs;
-    uint32_t unit[2], row[2];
+    uint32_t unit[PER_LANE], row[PER_LANE];
     int at = -1;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < PER_LANE; ++k) {
         const int i = lane + 64 * k;
         unit[k] = plan.s[i].unit;
         row[k] = plan.s[i].row;
         at += __popcll(__ballot(i < n && unit[k] <= u));
     }
     auto pick = [&](const uint32_t *x, int i) {
-        return (uint32_t)(i < 64 ? __builtin_amdgcn_readlane((int)x[0], i & 63) : __builtin_amdgcn_readlane((int)x[1], i & 63));
+        uint32_t v = 0;
+#pragma unroll
+        for (int k = 0; k < PER_LANE; ++k) v = i >> 6 == k ? (uint32_t)__builtin_amdgcn_readlane((int)x[k], i & 63) : v;
+        return v;
     };
     PlanUnit r;
     const uint32_t first = pick(row, at);

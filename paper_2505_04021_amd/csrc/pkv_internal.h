@@ -113,18 +113,36 @@ struct AttnDesc {
 
 // How a chunk call (prefill_attention, kv_append_chunk) falls into units of work, as far as the host decides it: per
 // sequence where its units and its packed rows begin.  It travels in the kernel's arguments, so a call copies
-// nothing to the device and needs no buffer; a call of more sequences is several launches.
-#define PKV_PLAN_SEQS 127
+// nothing to the device and needs no buffer.  A kernel's arguments end at 4 KB: a launch holds at most PKV_PLAN_SEQS
+// sequences, and every work-group reads the plan, so that few sequences come with a shorter one (an append of 17 tokens each
+// for 127 sequences 7.3 us, for 128 8.0).  With launches of 127 sequences, the last one often small, 128 x (1000 cached + 17
+// new) tokens of 32/8/128 took 151 us (one launch 128), 447 x (200 + 3) of 8/2/128 41 (24.5), their append 18 (7).
+#define PKV_PLAN_FEW 127
+#define PKV_PLAN_SEQS 447
 #define PKV_PLAN_PART_SHIFT 25       // of `row`: parts of the context per group above, first packed row (at most 2^24) below
 #define PKV_PLAN_ROWS 0x1ffffffu
 #define PKV_PLAN_MAX_PARTS 64
-struct ChunkPlan {
+template <int SEQS>
+struct PlanOf {
     int32_t n_seqs, seq0;                 // sequences seq0 .. seq0 + n_seqs - 1
     struct {
         uint32_t unit;                    // its first unit
         uint32_t row;                     // its first packed row | parts of the context per group << PKV_PLAN_PART_SHIFT
-    } s[PKV_PLAN_SEQS + 1];               // [n_seqs]: the totals
+    } s[SEQS + 1];                        // [n_seqs]: the totals
 };
+typedef PlanOf<PKV_PLAN_SEQS> ChunkPlan;
+
+// The same plan of at most PKV_PLAN_FEW sequences.
+inline PlanOf<PKV_PLAN_FEW> few_of(const ChunkPlan &plan) {
+    PlanOf<PKV_PLAN_FEW> few;
+    few.n_seqs = plan.n_seqs;
+    few.seq0 = plan.seq0;
+    for (int i = 0; i <= plan.n_seqs; ++i) {
+        few.s[i].unit = plan.s[i].unit;
+        few.s[i].row = plan.s[i].row;
+    }
+    return few;
+}
 
 #define PKV_MAX_GROUP 16
 #define PKV_PREFILL_WAVES 4     // waves of a prefill work-group

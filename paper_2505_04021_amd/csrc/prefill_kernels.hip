@@ -80,7 +80,8 @@ struct GroupInfo {
     int seq, q0, ntok, back, part, parts;
 };
 
-__device__ __forceinline__ GroupInfo group_info(const AttnDesc &d, const ChunkPlan &plan, int unit) {
+template <int SEQS>
+__device__ __forceinline__ GroupInfo group_info(const AttnDesc &d, const PlanOf<SEQS> &plan, int unit) {
     const PlanUnit pu = plan_find(plan, (uint32_t)unit);
     const int size = PF_WAVES * (d.cols / d.g), groups = (pu.rows + size - 1) / size;
     const int rank = pu.parts > 1 ? pu.unit / pu.parts : pu.unit;
@@ -95,8 +96,8 @@ __device__ __forceinline__ GroupInfo group_info(const AttnDesc &d, const ChunkPl
     return g;
 }
 
-template <int D, int DT>
-__global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, const ChunkPlan plan) {
+template <int D, int DT, int SEQS>
+__global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, const PlanOf<SEQS> plan) {
     using TL = PfTile<D, DT>;
     constexpr int SLOT = 2 * TL::BYTES;                    // the K (or V) tiles of a pair
     __shared__ __align__(16) uint8_t ring[2 * PF_SLOTS * SLOT];   // K slots, then V slots
@@ -487,7 +488,8 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
 // its sums eight parts a trip (one part after the other, 32 parts of one group took 80 of a call's 101 us).
 constexpr int MERGE_COLS = 8;
 
-__global__ __launch_bounds__(32 * MERGE_COLS) void k_prefill_merge(const AttnDesc d, const ChunkPlan plan) {
+template <int SEQS>
+__global__ __launch_bounds__(32 * MERGE_COLS) void k_prefill_merge(const AttnDesc d, const PlanOf<SEQS> plan) {
     __shared__ float s_f[MERGE_COLS][PKV_PLAN_MAX_PARTS];
     constexpr int BLOCKS = PKV_PREFILL_COLS / MERGE_COLS;
     const int sub = threadIdx.x & 31, cc = threadIdx.x >> 5;
@@ -539,21 +541,26 @@ __global__ __launch_bounds__(32 * MERGE_COLS) void k_prefill_merge(const AttnDes
     *reinterpret_cast<f32x4 *>(d.out + ((size_t)(row0 + tok) * d.Hq + kvh * d.g + (n - (n / d.g) * d.g)) * D + 4 * sub) = acc * inv;
 }
 
+template <int SEQS>
+void launch(const AttnDesc &d, const PlanOf<SEQS> &plan, int split_groups, hipStream_t s) {
+    const dim3 grid(plan.s[plan.n_seqs].unit * (unsigned)d.Hkv), wg(64 * PF_WAVES);
+    if (d.dtype == PKV_BF16) {
+        if (d.D == 128) hipLaunchKernelGGL((k_prefill<128, PKV_BF16, SEQS>), grid, wg, 0, s, d, plan);
+        else hipLaunchKernelGGL((k_prefill<64, PKV_BF16, SEQS>), grid, wg, 0, s, d, plan);
+    } else {
+        if (d.D == 128) hipLaunchKernelGGL((k_prefill<128, PKV_E4M3, SEQS>), grid, wg, 0, s, d, plan);
+        else hipLaunchKernelGGL((k_prefill<64, PKV_E4M3, SEQS>), grid, wg, 0, s, d, plan);
+    }
+    if (split_groups > 0)
+        hipLaunchKernelGGL(k_prefill_merge<SEQS>, dim3((unsigned)(split_groups * d.Hkv * (PKV_PREFILL_COLS / MERGE_COLS)), (unsigned)plan.n_seqs),
+                           dim3(32 * MERGE_COLS), 0, s, d, plan);
+}
+
 }  // namespace
 
 hipError_t pkv_launch_prefill(const AttnDesc &d, const ChunkPlan &plan, int split_groups, hipStream_t s) {
-    const uint32_t units = plan.s[plan.n_seqs].unit;
-    if (units == 0) return hipSuccess;
-    const dim3 grid(units * (unsigned)d.Hkv), wg(64 * PF_WAVES);
-    if (d.dtype == PKV_BF16) {
-        if (d.D == 128) hipLaunchKernelGGL((k_prefill<128, PKV_BF16>), grid, wg, 0, s, d, plan);
-        else hipLaunchKernelGGL((k_prefill<64, PKV_BF16>), grid, wg, 0, s, d, plan);
-    } else {
-        if (d.D == 128) hipLaunchKernelGGL((k_prefill<128, PKV_E4M3>), grid, wg, 0, s, d, plan);
-        else hipLaunchKernelGGL((k_prefill<64, PKV_E4M3>), grid, wg, 0, s, d, plan);
-    }
-    if (split_groups > 0)
-        hipLaunchKernelGGL(k_prefill_merge, dim3((unsigned)(split_groups * d.Hkv * (PKV_PREFILL_COLS / MERGE_COLS)), (unsigned)plan.n_seqs),
-                           dim3(32 * MERGE_COLS), 0, s, d, plan);
+    if (plan.s[plan.n_seqs].unit == 0) return hipSuccess;
+    if (plan.n_seqs <= PKV_PLAN_FEW) launch(d, few_of(plan), split_groups, s);
+    else launch(d, plan, split_groups, s);
     return hipGetLastError();
 }

@@ -31,9 +31,10 @@ def test_prefill_tile_edges(gpu, oracle, g, hkv, d, dtype, long):  # noqa: F811
     t.close()
 
 
-@pytest.mark.parametrize("n,dtype", [(127, BF16), (128, E4M3), (131, BF16), (260, E4M3)])
+@pytest.mark.parametrize("n,dtype", [(127, BF16), (128, E4M3), (131, BF16), (260, E4M3), (447, BF16), (448, E4M3), (900, BF16)])
 def test_chunk_of_many_sequences(gpu, oracle, n, dtype):  # noqa: F811
-    """Around 127 sequences, what the plan of one launch holds: a chunk of 0 to 3 tokens for each is appended, then attends."""
+    """Around 127 and 447 sequences, what the two plans of a launch hold: a chunk of 0 to 3 tokens for each is appended,
+    then attends."""
     hq, hkv, d = 4, 1, 64
     ctx = [3 + (5 * s) % 37 for s in range(n)]
     qlen = [(s * 7 + 3) % 4 for s in range(n)]
