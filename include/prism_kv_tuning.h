@@ -50,6 +50,8 @@ int pkv_set_kernel_form(int form);
 int pkv_last_kernel_form(void);
 /* The work items (waves; work-groups of four waves in form 2) of that launch, all its models together. */
 int pkv_last_launch_items(void);
+/* The most parts a sequence's context came in, in the most recent prefill_attention call (1: none was cut). */
+int pkv_last_prefill_parts(void);
 /* Cost model that shares the waves out among the models of a grouped launch: a page
  * costs per_mille/1000 + 0.1 per KiB of its K and V tile (-1 = the default: 800 in kernel
  * form 0, 1600 for bf16 pages in form 1). */

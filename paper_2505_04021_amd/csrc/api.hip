@@ -308,6 +308,7 @@ constexpr int kDefaultSegCost = 6;
 constexpr double kPageCost = 0.8, kDeepPageCost = 1.6;
 int g_plan_items = kDefaultItems;     // items of the launch being prepared, all models together
 AttnForm g_last_form = AttnForm::ordinary;  // what the most recent launch ran as
+int g_last_prefill_parts = 0;         // most parts a context came in, in the most recent prefill_attention call
 int g_last_items = 0;                 // its work items, work-groups of a small launch
 bool g_small_now = false;             // the launch being prepared is a small one: a work-group per (sequence, kv head) or part of one
 double g_small_pages = 0.0;           // its pages
@@ -735,6 +736,8 @@ int pkv_set_kernel_form(int form) {
 int pkv_last_kernel_form(void) { return g_last_form == AttnForm::small ? 2 : (g_last_form == AttnForm::deep ? 1 : 0); }
 
 int pkv_last_launch_items(void) { return g_last_items; }
+
+int pkv_last_prefill_parts(void) { return g_last_prefill_parts; }
 
 int pkv_set_segment_cost(int pages) {
     if (pages < -1 || pages > 256) return PKV_E_ARG;
@@ -1847,6 +1850,7 @@ int prefill_attention(int model, int batch, const void *q, const int32_t *q_lens
     };
     PlanBuilder plan(batch);
     double part_pairs = 0.0;
+    g_last_prefill_parts = 1;
     for (int s = 0; s < batch; ++s) {
         if (plan.full()) {
             const int rc = launch(plan.take(s));
@@ -1857,6 +1861,7 @@ int prefill_attention(int model, int batch, const void *q, const int32_t *q_lens
         const int parts = prefill_parts(*m, s, part_pairs), groups = (q_lens[s] + group - 1) / group;
         plan.add((uint32_t)q_lens[s], (uint32_t)(groups * parts), (uint32_t)parts);
         if (parts > 1 && groups > split_groups) split_groups = groups;
+        if (q_lens[s] > 0 && parts > g_last_prefill_parts) g_last_prefill_parts = parts;
     }
     return launch(plan.take(batch));
 }

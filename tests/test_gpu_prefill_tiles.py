@@ -89,3 +89,41 @@ def test_prefill_of_extreme_scores(gpu, oracle, dtype, score):  # noqa: F811
         assert rc_g == 0 and row_rel_err(out_g, out_o[last]) <= TOL[dtype]
     finally:
         t.close()
+
+
+@pytest.mark.parametrize("n,dtype", [(130, BF16), (460, BF16), (460, E4M3)])
+def test_cuts_among_many_sequences(gpu, oracle, n, dtype):  # noqa: F811
+    """A few sequences with contexts long enough to be cut, in every launch of the call, among many short ones."""
+    hq, hkv, d = 2, 1, 64
+    ctx = [2500 if s % 150 == 149 else (1800 if s == 3 else 1 + (7 * s) % 30) for s in range(n)]
+    qlen = [1 + s % 2 if c > 100 else (s % 3 if c > 2 else 1) for s, c in enumerate(ctx)]
+    t = Twin(gpu, oracle, hq, hkv, d, dtype, ctx, max_blocks=160)
+    try:
+        q = gen.queries((43, n), sum(qlen), hq, d)
+        rc_o, out_o = oracle.prefill_attention(t.models[1], q, qlen, ctx)
+        for _ in range(2):
+            rc_g, out_g = gpu.prefill_attention(t.models[0], q, qlen, ctx)
+            assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
+            assert gpu.last_prefill_parts() > 1
+            assert row_rel_err(out_g, out_o) <= TOL[dtype]
+    finally:
+        t.close()
+
+
+@pytest.mark.parametrize("ctx,parts,d,dtype", [([3200], (9, 15), 128, BF16), ([4700], (9, 32), 64, E4M3), ([9000, 2300], (17, 32), 64, BF16),
+                                               ([16640], (33, 64), 64, BF16), ([16640, 9000, 40], (33, 64), 64, E4M3), ([33000], (64, 64), 64, BF16)])
+def test_contexts_in_many_parts(gpu, oracle, ctx, parts, d, dtype):  # noqa: F811
+    """One to three queries in front of contexts cut into up to 64 parts: joined eight at a time, by 32 lanes that hold the
+    maximum and the denominator of two parts each."""
+    hq, hkv = 4, 1
+    t = Twin(gpu, oracle, hq, hkv, d, dtype, ctx, max_blocks=2100)
+    try:
+        for qlen in ([1] * len(ctx), [3] * len(ctx)):
+            q = gen.queries((71, sum(ctx)), sum(qlen), hq, d)
+            rc_o, out_o = oracle.prefill_attention(t.models[1], q, qlen, ctx)
+            rc_g, out_g = gpu.prefill_attention(t.models[0], q, qlen, ctx)
+            assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
+            assert parts[0] <= gpu.last_prefill_parts() <= parts[1]
+            assert row_rel_err(out_g, out_o) <= TOL[dtype]
+    finally:
+        t.close()
