@@ -46,7 +46,8 @@ int pkv_set_segment_cost(int pages);
 int pkv_set_kernel_form(int form);
 /* What the most recent decode attention launch of this process ran as: form 0 or 1, or 2, the kernel of
  * small launches (a work-group per (sequence, kv head), or per part of a long one), which the library takes
- * for launches of fewer than 11 000 pages while every knob of the split is at its default. */
+ * for launches of fewer than 11 000 pages while every knob of the split is at its default, unless a few of
+ * their rows are much longer than the many others. */
 int pkv_last_kernel_form(void);
 /* The work items (waves; work-groups of four waves in form 2) of that launch, all its models together. */
 int pkv_last_launch_items(void);

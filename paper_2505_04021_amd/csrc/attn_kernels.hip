@@ -12,7 +12,9 @@
 //     context lengths; where a share boundary
 //     cuts a sequence, the wave that finishes it last merges the pieces with the
 //     online-softmax rule inside the same kernel (partials and arrival counters sit in
-//     uncached memory: no cache flush, no second launch);
+//     uncached memory: no cache flush, no second launch).  Launches of few pages, whose
+//     rows suit it, run k_attention_small instead: a work-group per (sequence, kv head)
+//     or per part of a long one;
 //   * K and V tiles are stored inside a block in the lane order of the MFMA operands,
 //     so each 16-byte global load is fully coalesced (64 lanes x 16 B = 1 KiB
 //     contiguous) and lands directly in operand registers — no LDS round trip, no

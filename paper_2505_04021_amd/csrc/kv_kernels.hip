@@ -257,8 +257,8 @@ __device__ __forceinline__ void page_codes(uint8_t *tile, const PageRows &p) {
 // Four values over one scale as e4m3 codes, bit for bit e4m3_encode(v / scale) with the correctly rounded quotient.
 // The quotient is first taken between two products, v * lo and v * hi with lo < 1 / scale < hi (2^-21 either side of
 // v_rcp_f32, which is within 2^-23): where both round to the same code the exact quotient does too (rounding is
-// monotonic; the conversion instruction equals e4m3_encode for every float below 464 in magnitude, checked on all of
-// them).  Where they differ, or the code is a NaN, or the scale is out of the range in which this holds, the division is
+// monotonic; the conversion instruction equals e4m3_encode for every float below 464 in magnitude: a sweep over all of
+// them found no other; the tests compare the codes that calls write with the plain division).  Where they differ, or the code is a NaN, or the scale is out of the range in which this holds, the division is
 // done: a word in some thousand.
 struct Divisor {
     float scale, lo, hi;

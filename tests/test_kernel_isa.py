@@ -5,7 +5,9 @@ inside a streaming loop drains the whole KV pipeline every step and costs severa
 of bandwidth, without any test of results noticing.  Small source changes have flipped the
 compiler into that mode before, so the generated code itself is checked: in the innermost
 MFMA loops of k_attention there is no full wait on vector memory, no scratch traffic, and
-the kernel keeps two waves per SIMD (at most 256 VGPRs)."""
+the kernel keeps two waves per SIMD (at most 256 VGPRs).  The prefill kernel counts its
+requests into LDS by hand: the compiler may add no wait to its steps beside those for the
+block ids and scales of the next 64 page pairs."""
 import os
 import re
 import subprocess
@@ -14,11 +16,11 @@ import tempfile
 from paper_2505_04021_amd import build as B
 
 
-def device_assembly():
+def device_assembly(source="attn_kernels.hip"):
     out = os.path.join(tempfile.mkdtemp(prefix="pkv_isa_"), "attn.s")
     flags = [f for f in B.FLAGS if f not in ("-fPIC", "-shared")]
     cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + flags + ["--cuda-device-only", "-S",
-                                                                      os.path.join(B.CSRC, "attn_kernels.hip"), "-o", out]
+                                                                      os.path.join(B.CSRC, source), "-o", out]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     return open(out).read()
@@ -68,3 +70,22 @@ def test_streaming_loops_keep_exact_load_counts():
             assert not any(t.startswith("scratch_") for t in seg), f"{name} loop {a}..{b} spills to scratch"
         vg = [int(x) for x in re.findall(r"\.name:\s+\S*" + name + r"\S*\s*\n(?:.*\n){0,40}?\s+\.vgpr_count:\s+(\d+)", asm)]
         assert vg and max(vg) <= max_vgpr, (name, vg)
+
+
+def test_prefill_steps_wait_only_where_written():
+    asm = device_assembly("prefill_kernels.hip")
+    for seqs in (127, 447):                                     # sequences of the launch's plan
+        for d, dtype, mfma in ((128, 0, 24), (64, 0, 12), (128, 1, 16), (64, 1, 8)):
+            name = f"9k_prefillILi{d}ELi{dtype}ELi{seqs}E"
+            insn, labels, _ = kernel_body(asm, name)
+            loops = innermost_mfma_loops(insn, labels, min_mfma=mfma)
+            assert len(loops) == 2, (name, loops)               # steps without masks, and the others
+            for a, b in loops:
+                seg = insn[a:b]
+                assert sum(t.startswith("v_mfma") for t in seg) == mfma and seg.count("s_barrier") == 1
+                assert not any(t.startswith("scratch_") for t in seg), f"{name} loop {a}..{b} spills to scratch"
+                full = [t for t in seg if t.startswith("s_waitcnt") and "vmcnt(0)" in t]
+                # the meeting point, the two places where it may ask for the next ids; e4m3: both pages' ids and scales
+                assert len(full) <= (3 if dtype == 0 else 5), (name, full)
+            vg = [int(x) for x in re.findall(r"\.name:\s+\S*" + name + r"\S*\s*\n(?:.*\n){0,40}?\s+\.vgpr_count:\s+(\d+)", asm)]
+            assert vg and max(vg) <= 256, (name, vg)
