@@ -11,15 +11,15 @@
 // (kv_layout.h), one tile of the pair per wave.
 //
 // What bounds it: power, then the latency of a step.  On bf16 caches with 128-wide heads a wave's step is 24
-// products (768 matrix cycles, a third of them the low half of the probabilities) and 138 other vector
-// instructions; two waves per SIMD turn a step over in 2150 cycles each (71 % matrix occupancy) while the chip
-// holds about 1.5 GHz; with all operands zero the same kernel runs 25 % faster, and a plain 8192^3 matrix product
-// loses as much to random data.  Why this shape: 32x32x16 products read half as many operand registers and LDS
+// products (768 matrix cycles, a third of them the low half of the probabilities) and 118 other vector
+// instructions; by the counters of a launch a step takes a wave 2330 cycles, 1030 of them waiting, and the matrix
+// units are busy 54 % of the launch at 1.87 GHz; with all operands zero the same kernel runs 25 % faster, and a
+// plain 8192^3 matrix product loses as much to random data.  Why this shape: 32x32x16 products read half as many operand registers and LDS
 // bytes per flop as 16x16x32, need one lane exchange instead of two per maximum (and that only when the
 // reference point moves), and fill 32 columns better for odd g.  The step is software-pipelined by one pair:
 // scores of pair p + 1 and the V reads of pair p are issued before the softmax of pair p is needed.  The waves
 // meet once in two pairs (every pair: 2 % slower).  8 sequences x (2048 cached + 512 new) of 32/8/128: bf16 236
-// -> 212 us, e4m3 300 -> 180 us; 64-wide heads 183 -> 131 us.
+// -> 215 us, e4m3 300 -> 178 us; 64-wide heads 183 -> 131 us.
 #include "mfma_util.h"
 
 namespace {
