@@ -11,15 +11,17 @@
 // (kv_layout.h), one tile of the pair per wave.
 //
 // What bounds it: power, then the latency of a step.  On bf16 caches with 128-wide heads a wave's step is 24
-// products (768 matrix cycles, a third of them the low half of the probabilities) and 118 other vector
-// instructions; by the counters of a launch a step takes a wave 2330 cycles, 1030 of them waiting, and the matrix
-// units are busy 54 % of the launch at 1.87 GHz; with all operands zero the same kernel runs 25 % faster, and a
-// plain 8192^3 matrix product loses as much to random data.  Why this shape: 32x32x16 products read half as many operand registers and LDS
-// bytes per flop as 16x16x32, need one lane exchange instead of two per maximum (and that only when the
-// reference point moves), and fill 32 columns better for odd g.  The step is software-pipelined by one pair:
-// scores of pair p + 1 and the V reads of pair p are issued before the softmax of pair p is needed.  The waves
-// meet once in two pairs (every pair: 2 % slower).  8 sequences x (2048 cached + 512 new) of 32/8/128: bf16 236
-// -> 215 us, e4m3 300 -> 178 us; 64-wide heads 183 -> 131 us.
+// products (768 matrix cycles, a third of them the low half of the probabilities) and some 105 other vector
+// instructions (8 more with a maximum per step instead of the sum as the sign that the reference point has to move:
+// 228 -> 225 us a pass with its append, all shapes 0.7 to 1.3 % faster); by the counters of a launch a step takes a
+// wave 2330 cycles, 1030 of them waiting, and the matrix units are busy 54 % of the launch at 1.87 GHz; with all
+// operands zero the same kernel runs 25 % faster, and a plain 8192^3 matrix product loses as much to random data.  Why
+// this shape: 32x32x16 products read half as many operand registers and LDS bytes per flop as 16x16x32, need one lane
+// exchange instead of two per maximum (and that only when the reference point moves), and fill 32 columns better for
+// odd g.  The step is software-pipelined by one pair: scores of pair p + 1 and the V reads of pair p are issued before
+// the output products of pair p, between which the softmax of pair p + 1 runs.  The waves meet once in two pairs (every
+// pair: 2 % slower).  8 sequences x (2048 cached + 512 new) of 32/8/128: bf16 236 -> 215 us, e4m3 300 -> 178 us; 64-wide
+// heads 183 -> 131 us.
 #include "mfma_util.h"
 
 namespace {
@@ -35,6 +37,8 @@ static_assert(PF_WAVES * PF_COLS == PKV_PREFILL_COLS, "host and kernel must agre
 // special case (its probabilities are exp2(-inf) = 0), and the lowest number there is, so that the first visible token's
 // score, whatever it is, lies above it and replaces it.
 constexpr float PF_M0 = -3.402823466e+38f;
+// Sum of a lane's sixteen probabilities of a page pair beyond which the reference point moves.
+constexpr float kSumBar = 256.f;
 // Scores (log2 domain) beyond this are rounded to more than one.
 constexpr float PF_FAR = 0x1p24f;
 
@@ -285,39 +289,45 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
 
     // ---- one pair's softmax, in two parts.  Arguments: t = score * scale - m (log2 domain) against the reference
     // point m as it stands.  m need not be the column's maximum, only near it: it moves, and the sums are
-    // rescaled, when some argument exceeds kRescaleSlack, so that probabilities stay below 2^kRescaleSlack.
+    // rescaled, when a lane's sum of the pair's probabilities exceeds kSumBar, so that no probability does.
     // An argument takes the score before it is rounded, m is a rounded one: where that difference is no longer small
-    // (some |m| beyond PF_FAR), every step is settled (slack -inf), with arguments that take the rounded score too.
-    f32x16 s, t;
-    float slack = kRescaleSlack;                           // wave-uniform
+    // (some |m| beyond PF_FAR), every step is settled (bar -1), with arguments that take the rounded score too.
+    f32x16 s;
+    float bar = kSumBar;                                   // wave-uniform
+    f32x16 pr;
     auto args = [&](int p, bool masked, bool far = false) __attribute__((always_inline)) {
         if (far) {
 #pragma clang fp contract(off)
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 const float x = s[i] * (i < 8 ? sca : scb);
-                t[i] = x - m;
+                pr[i] = x - m;
             }
         } else {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) t[i] = __builtin_fmaf(s[i], i < 8 ? sca : scb, -m);
+            for (int i = 0; i < 16; ++i) pr[i] = __builtin_fmaf(s[i], i < 8 ? sca : scb, -m);
         }
         if (masked) {
             const int rel = col_lim - 32 * p - 4 * h;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const float x = t[i];
-                t[i] = 16 * (i >> 3) + 8 * ((i >> 2) & 1) + (i & 3) < rel ? x : -INFINITY;
+                const float x = pr[i];
+                pr[i] = 16 * (i >> 3) + 8 * ((i >> 2) & 1) + (i & 3) < rel ? x : -INFINITY;
             }
         }
     };
-    auto settle = [&](int p, bool masked) __attribute__((always_inline)) {
-        float mx = fmaxf(fmaxf(t[0], t[1]), t[2]);
+    // p = exp2(t) and their sum over this lane's tokens.  No probability is larger than the sum, so the sum tells when the
+    // reference point has to move: no maximum is taken in an ordinary step.
+    auto take = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 3; i < 15; i += 2) mx = fmaxf(fmaxf(mx, t[i]), t[i + 1]);
-        mx = fmaxf(mx, t[15]);
-        if (__builtin_expect(__any(mx > slack), 0)) {
-            // the column's maximum from the scores themselves (t is inexact when m is far off)
+        for (int i = 0; i < 16; ++i) pr[i] = __builtin_amdgcn_exp2f(pr[i]);
+        return (((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]))) +
+               (((pr[8] + pr[9]) + (pr[10] + pr[11])) + ((pr[12] + pr[13]) + (pr[14] + pr[15])));
+    };
+    auto settle = [&](int p, bool masked) __attribute__((always_inline)) {
+        float sum = take();
+        if (__builtin_expect(__any(sum > bar), 0)) {
+            // the column's maximum from the scores themselves (arguments are inexact when m is far off)
             const int rel = col_lim - 32 * p - 4 * h;
             float top = -INFINITY;
 #pragma unroll
@@ -334,9 +344,11 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
             for (int dt = 0; dt < TL::ND; ++dt) acc[dt] *= alpha;
             m = m_new;
             const bool far = __any(fabsf(m) > PF_FAR && m > PF_M0);
-            slack = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(far ? -INFINITY : kRescaleSlack)));
+            bar = __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(far ? -1.0f : kSumBar)));
             args(p, masked, far);
+            sum = take();
         }
+        l += sum;
     };
     auto scores = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -346,12 +358,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
             s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_op(kk), as_bf16x8(qf[kk]), s, 0, 0, 0);
     };
     u32x4 ph[2], pl[2];
-    f32x16 pr;
     auto probabilities = [&]() __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) pr[i] = __builtin_amdgcn_exp2f(t[i]);
-        l += (((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]))) +
-             (((pr[8] + pr[9]) + (pr[10] + pr[11])) + ((pr[12] + pr[13]) + (pr[14] + pr[15])));
         if (DT == PKV_E4M3) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) pr[i] *= i < 8 ? sva : svb;

@@ -91,6 +91,40 @@ def test_prefill_of_extreme_scores(gpu, oracle, dtype, score):  # noqa: F811
         t.close()
 
 
+@pytest.mark.parametrize("dtype", [BF16, E4M3])
+@pytest.mark.parametrize("step", [2.5, 2.75, 2.8125, 5.5, 5.75, 90.0])
+def test_scores_that_climb_a_stair(gpu, oracle, dtype, step):  # noqa: F811
+    """Every page pair's logits lie `step` above the one before, around the sum (256 for a lane's sixteen tokens: 2^4 each)
+    and the level (2^8) at which the reference point of a column's exponentials moves; a fall back to zero after five pairs."""
+    hq, hkv, d = 4, 2, 128
+    cases = [(700, 9), (33, 33), (2100, 2)]
+    ctx, qlen = [c for c, _ in cases], [n for _, n in cases]
+    t = Twin(gpu, oracle, hq, hkv, d, dtype, ctx, max_blocks=160)
+    try:
+        for s, c in enumerate(ctx):
+            kv = gen.seq_kv((17, s), c, hkv, d, dtype, 16)
+            level = (np.arange(c) // 32 % 6 * step).astype(np.float32)
+            if dtype == BF16:
+                k = np.zeros((c, hkv, d), dtype=np.float32)
+                k[:, :, 0] = level[:, None]
+                kv["k"] = (k.view(np.uint32) >> 16).astype(np.uint16)
+            else:
+                kv["k"] = np.zeros((c, hkv, d), dtype=np.uint8)
+                kv["k"][:, :, 0] = 0x38
+                kv["k_scale"] = np.maximum(np.repeat(level[::16, None], hkv, axis=1), 1e-3).astype(np.float32)
+            for be, m in zip(t.be, t.models):
+                assert be.kv_write(m, s, 0, kv["k"], kv["v"], kv["k_scale"], kv["v_scale"]) == c
+        q = np.zeros((sum(qlen), hq, d), dtype=np.float32)
+        q[:, :, 0] = np.float32(np.sqrt(d))
+        q = (q.view(np.uint32) >> 16).astype(np.uint16)
+        rc_o, out_o = oracle.prefill_attention(t.models[1], q, qlen, ctx)
+        rc_g, out_g = gpu.prefill_attention(t.models[0], q, qlen, ctx)
+        assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
+        assert row_rel_err(out_g, out_o) <= TOL[dtype]
+    finally:
+        t.close()
+
+
 @pytest.mark.parametrize("n,dtype", [(130, BF16), (460, BF16), (460, E4M3)])
 def test_cuts_among_many_sequences(gpu, oracle, n, dtype):  # noqa: F811
     """A few sequences with contexts long enough to be cut, in every launch of the call, among many short ones."""
