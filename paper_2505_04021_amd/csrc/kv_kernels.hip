@@ -134,14 +134,14 @@ struct PageRows {           // where the tokens come from and go to
     bool aligned;           // src may be read in 16-byte pieces
 };
 
-// N bytes of slot t's row from byte `at`; zeros for a slot that is not written.
-template <int N, int E>
+// N bytes of slot t's row from byte `at`; a slot that is not written takes the nearest one that is (what it holds is never
+// stored), so that all lanes read and no branch parts the requests.
+template <int N, int E, bool ALIGNED>
 __device__ __forceinline__ void row_bytes(uint32_t *w, const PageRows &p, int t, int at) {
-#pragma unroll
-    for (int i = 0; i < N / 4; ++i) w[i] = 0u;
-    if (t < p.s0 || t >= p.s0 + p.n) return;
-    const uint8_t *q = p.src + (size_t)(t - p.s0) * p.stride + at;
-    if (p.aligned) {
+    int r = t - p.s0;
+    r = r < 0 ? 0 : (r < p.n ? r : p.n - 1);
+    const uint8_t *q = p.src + (size_t)r * p.stride + at;
+    if constexpr (ALIGNED) {
         if constexpr (N == 16) {
             const u32x4 v = *reinterpret_cast<const u32x4 *>(q);
 #pragma unroll
@@ -155,11 +155,20 @@ __device__ __forceinline__ void row_bytes(uint32_t *w, const PageRows &p, int t,
         }
     } else {
 #pragma unroll
+        for (int i = 0; i < N / 4; ++i) w[i] = 0u;
+#pragma unroll
         for (int i = 0; i < N / E; ++i) {
             const uint32_t x = E == 2 ? reinterpret_cast<const uint16_t *>(q)[i] : q[i];
             w[i * E / 4] |= x << (8 * (i * E % 4));
         }
     }
+}
+
+// The same reads for rows that may be read in 16-byte pieces and for those that may not: read(std::true_type) or (false_type).
+template <typename READ>
+__device__ __forceinline__ void read_rows(const PageRows &p, const READ &read) {
+    if (p.aligned) read(std::true_type{});
+    else read(std::false_type{});
 }
 
 template <int R>
@@ -209,47 +218,68 @@ __device__ __forceinline__ void put_v_unit(uint8_t *unit, u32x4 v, int group, in
         }
 }
 
+// The three writers below ask for all of a wave's rows before they ask where the rows go (tile_of(), which waits for a
+// block id and may say nowhere): the two trips then overlap.
+__device__ __forceinline__ void asked_for() { asm volatile("" ::: "memory"); }      // the compiler would put the reads where they are used
+
 // bf16 values into a bf16 tile
-template <int D, bool IS_V>
-__device__ __forceinline__ void page_bf16(uint8_t *tile, const PageRows &p) {
+template <int D, bool IS_V, typename TILE_OF>
+__device__ __forceinline__ void page_bf16(const TILE_OF &tile_of, const PageRows &p) {
     const int lane = threadIdx.x & 63, t = lane & 15, c = lane >> 4, G = t >> 2, e = t & 3;
-    if constexpr (!IS_V) {
+    uint32_t w[D / 32][4];
+    read_rows(p, [&](auto a) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < D / 32; ++i) {
-            uint32_t w[4];
-            row_bytes<16, 2>(w, p, t, 16 * (4 * i + c));
-            if (t >= p.s0 && t < p.s0 + p.n) *reinterpret_cast<u32x4 *>(tile + ((4 * i + c) * 16 + t) * 16) = mk4(w[0], w[1], w[2], w[3]);
+            if constexpr (!IS_V) {
+                row_bytes<16, 2, decltype(a)::value>(w[i], p, t, 16 * (4 * i + c));
+            } else {
+                row_bytes<8, 2, decltype(a)::value>(w[i], p, t, 2 * (32 * i + 4 * c));
+                row_bytes<8, 2, decltype(a)::value>(w[i] + 2, p, t, 2 * (32 * i + 16 + 4 * c));
+            }
         }
-    } else {
+    });
+    asked_for();
+    uint8_t *tile = tile_of();
+    if (!tile) return;
 #pragma unroll
-        for (int jp = 0; jp < D / 32; ++jp) {
-            uint32_t a[2], b[2];
-            row_bytes<8, 2>(a, p, t, 2 * (32 * jp + 4 * c));
-            row_bytes<8, 2>(b, p, t, 2 * (32 * jp + 16 + 4 * c));
-            const u32x2 ta = transpose_halves(a[0], a[1], e), tb = transpose_halves(b[0], b[1], e);
-            put_v_unit<2>(tile + ((jp * 4 + G) * 16 + 4 * c + e) * 16, mk4(ta.x, ta.y, tb.x, tb.y), G, p.s0, p.s0 + p.n);
+    for (int i = 0; i < D / 32; ++i) {
+        if constexpr (!IS_V) {
+            if (t >= p.s0 && t < p.s0 + p.n) *reinterpret_cast<u32x4 *>(tile + ((4 * i + c) * 16 + t) * 16) = mk4(w[i][0], w[i][1], w[i][2], w[i][3]);
+        } else {
+            const u32x2 ta = transpose_halves(w[i][0], w[i][1], e), tb = transpose_halves(w[i][2], w[i][3], e);
+            put_v_unit<2>(tile + ((i * 4 + G) * 16 + 4 * c + e) * 16, mk4(ta.x, ta.y, tb.x, tb.y), G, p.s0, p.s0 + p.n);
         }
     }
 }
 
 // e4m3 codes as they are into an e4m3 tile
-template <int D, bool IS_V>
-__device__ __forceinline__ void page_codes(uint8_t *tile, const PageRows &p) {
+template <int D, bool IS_V, typename TILE_OF>
+__device__ __forceinline__ void page_codes(const TILE_OF &tile_of, const PageRows &p) {
     const int lane = threadIdx.x & 63, t = lane & 15, c = lane >> 4, G = t >> 2, e = t & 3;
+    uint32_t w[D / 64][4];
+    read_rows(p, [&](auto a) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < D / 64; ++j) {
+            if constexpr (!IS_V) {
+                row_bytes<8, 1, decltype(a)::value>(w[j], p, t, 8 * (8 * j + c));
+                row_bytes<8, 1, decltype(a)::value>(w[j] + 2, p, t, 8 * (8 * j + 4 + c));
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) row_bytes<4, 1, decltype(a)::value>(w[j] + u, p, t, 64 * j + 16 * u + 4 * c);
+            }
+        }
+    });
+    asked_for();
+    uint8_t *tile = tile_of();
+    if (!tile) return;
 #pragma unroll
     for (int j = 0; j < D / 64; ++j) {
-        uint32_t w[4];
         if constexpr (!IS_V) {
-            row_bytes<8, 1>(w, p, t, 8 * (8 * j + c));
-            row_bytes<8, 1>(w + 2, p, t, 8 * (8 * j + 4 + c));
-            if (t >= p.s0 && t < p.s0 + p.n) *reinterpret_cast<u32x4 *>(tile + ((j * 4 + c) * 16 + t) * 16) = mk4(w[0], w[1], w[2], w[3]);
+            if (t >= p.s0 && t < p.s0 + p.n) *reinterpret_cast<u32x4 *>(tile + ((j * 4 + c) * 16 + t) * 16) = mk4(w[j][0], w[j][1], w[j][2], w[j][3]);
         } else {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                row_bytes<4, 1>(w + u, p, t, 64 * j + 16 * u + 4 * c);
-                w[u] = transpose_bytes(w[u], e);
-            }
-            put_v_unit<1>(tile + ((j * 4 + G) * 16 + 4 * c + e) * 16, mk4(w[0], w[1], w[2], w[3]), G, p.s0, p.s0 + p.n);
+            for (int u = 0; u < 4; ++u) w[j][u] = transpose_bytes(w[j][u], e);
+            put_v_unit<1>(tile + ((j * 4 + G) * 16 + 4 * c + e) * 16, mk4(w[j][0], w[j][1], w[j][2], w[j][3]), G, p.s0, p.s0 + p.n);
         }
     }
 }
@@ -288,22 +318,28 @@ __device__ __forceinline__ uint32_t encode4(float a, float b, float c, float d, 
 // the scale (for 16 like tokens between two and three times).  Bound by the vector instructions of that: 8 x 512 tokens
 // of 8 heads x 128, K and V: 64 us with the tokens one after the other, a wave maximum through LDS and two divisions an
 // element each; 20 us so.
-template <int D, bool IS_V>
-__device__ __forceinline__ void page_quantise(uint8_t *tile, float *scale_p, const PageRows &p) {
+template <int D, bool IS_V, typename TILE_OF>
+__device__ __forceinline__ void page_quantise(const TILE_OF &tile_of, const PageRows &p) {
     constexpr int NW = D / 16;                           // words of codes per lane
     const int lane = threadIdx.x & 63, t = lane & 15, c = lane >> 4, G = t >> 2, e = t & 3;
     const int s0 = p.s0, end = p.s0 + p.n;
     uint32_t x[2 * NW];                                  // this lane's values, two per word
+    read_rows(p, [&](auto a) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < D / 64; ++i) {
-        if constexpr (!IS_V) {                           // elements of units (i, c): 8 (8 i + c) .. + 7 and 8 (8 i + 4 + c) .. + 7
-            row_bytes<16, 2>(x + 8 * i, p, t, 16 * (8 * i + c));
-            row_bytes<16, 2>(x + 8 * i + 4, p, t, 16 * (8 * i + 4 + c));
-        } else {                                         // elements 64 i + 16 u + 4 c .. + 3
+        for (int i = 0; i < D / 64; ++i) {
+            if constexpr (!IS_V) {                       // elements of units (i, c): 8 (8 i + c) .. + 7 and 8 (8 i + 4 + c) .. + 7
+                row_bytes<16, 2, decltype(a)::value>(x + 8 * i, p, t, 16 * (8 * i + c));
+                row_bytes<16, 2, decltype(a)::value>(x + 8 * i + 4, p, t, 16 * (8 * i + 4 + c));
+            } else {                                     // elements 64 i + 16 u + 4 c .. + 3
 #pragma unroll
-            for (int u = 0; u < 4; ++u) row_bytes<8, 2>(x + 8 * i + 2 * u, p, t, 2 * (64 * i + 16 * u + 4 * c));
+                for (int u = 0; u < 4; ++u) row_bytes<8, 2, decltype(a)::value>(x + 8 * i + 2 * u, p, t, 2 * (64 * i + 16 * u + 4 * c));
+            }
         }
-    }
+    });
+    asked_for();
+    float *scale_p;
+    uint8_t *tile = tile_of(scale_p);
+    if (!tile) return;
     // what the tile holds: codes of the slots before
     u32x4 old[D / 64];
     u32x4 *unit = reinterpret_cast<u32x4 *>(tile + (IS_V ? (G * 16 + 4 * c + e) * 16 : (c * 16 + t) * 16));
@@ -386,16 +422,26 @@ __device__ __forceinline__ void page_quantise(uint8_t *tile, float *scale_p, con
 }
 
 // One wave's share of a page: the K (which = 0) or V (1) tile of kv head h.  QUANT: bf16 values into an e4m3 block.
-template <int DT, bool QUANT>
-__device__ __forceinline__ void page_tile(const AttnDesc &d, uint8_t *blk, int h, int which, const PageRows &p) {
+// block_of(): the block, or NULL where nothing may be written.
+template <int DT, bool QUANT, typename BLOCK_OF>
+__device__ __forceinline__ void page_tile(const AttnDesc &d, const BLOCK_OF &block_of, int h, int which, const PageRows &p) {
     constexpr int E = DT == PKV_BF16 ? 2 : 1;
-    uint8_t *tile = blk + (DT == PKV_E4M3 ? PKV_FP8_HEADER : 0) + ((size_t)h * 2 + which) * PKV_T * d.D * E;
+    const size_t offset = (DT == PKV_E4M3 ? PKV_FP8_HEADER : 0) + ((size_t)h * 2 + which) * PKV_T * d.D * E;
     auto go = [&](auto dim, auto is_v) __attribute__((always_inline)) {
         constexpr int D = decltype(dim)::value;
         constexpr bool IS_V = decltype(is_v)::value;
-        if constexpr (DT == PKV_BF16) page_bf16<D, IS_V>(tile, p);
-        else if constexpr (QUANT) page_quantise<D, IS_V>(tile, reinterpret_cast<float *>(blk) + (IS_V ? d.Hkv : 0) + h, p);
-        else page_codes<D, IS_V>(tile, p);
+        auto tile_of = [&]() __attribute__((always_inline)) {
+            uint8_t *blk = block_of();
+            return blk ? blk + offset : blk;
+        };
+        if constexpr (DT == PKV_BF16) page_bf16<D, IS_V>(tile_of, p);
+        else if constexpr (!QUANT) page_codes<D, IS_V>(tile_of, p);
+        else
+            page_quantise<D, IS_V>([&](float *&scale_p) __attribute__((always_inline)) {
+                uint8_t *blk = block_of();
+                scale_p = reinterpret_cast<float *>(blk) + (IS_V ? d.Hkv : 0) + h;
+                return blk ? blk + offset : blk;
+            }, p);
     };
     if (d.D == 128) {
         if (which) go(std::integral_constant<int, 128>{}, std::true_type{});
@@ -413,12 +459,14 @@ template <int DT>
 __global__ __launch_bounds__(64 * PAGE_WAVES) void k_kv_write(const AttnDesc d, const int32_t *row, int tok_begin, int n_tok,
                                                               const uint8_t *k, const uint8_t *v, const float *ks, const float *vs) {
     constexpr int E = DT == PKV_BF16 ? 2 : 1;
+    ask_arguments(d, k, v);
+    asm volatile("" ::"s"(row), "s"(tok_begin), "s"(n_tok), "s"(ks), "s"(vs));
     const int x = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * PAGE_WAVES + (threadIdx.x >> 6)));
     const int which = x & 1, hp = x >> 1, j = hp / d.Hkv, h = hp - j * d.Hkv;
     const int page = tok_begin / PKV_T + j, end = tok_begin + n_tok;
     const int lo = page * PKV_T > tok_begin ? page * PKV_T : tok_begin, hi = (page + 1) * PKV_T < end ? (page + 1) * PKV_T : end;
     if (lo >= hi) return;
-    uint8_t *blk = block_ptr(d, (uint32_t)row[page]);
+    const uint32_t id = (uint32_t)PKV_CONST(int32_t, row)[page];
     const uint8_t *src = which ? v : k;
     PageRows p;
     p.stride = (size_t)d.Hkv * d.D * E;
@@ -426,9 +474,13 @@ __global__ __launch_bounds__(64 * PAGE_WAVES) void k_kv_write(const AttnDesc d, 
     p.s0 = lo % PKV_T;
     p.n = hi - lo;
     p.aligned = (reinterpret_cast<uintptr_t>(src) & 15) == 0;
-    if (DT == PKV_E4M3 && (threadIdx.x & 63) == 0)
-        reinterpret_cast<float *>(blk)[(which ? d.Hkv : 0) + h] = (which ? vs : ks)[(size_t)j * d.Hkv + h];
-    page_tile<DT, false>(d, blk, h, which, p);
+    float scale = 0.f;
+    if (DT == PKV_E4M3) scale = (which ? vs : ks)[(size_t)j * d.Hkv + h];
+    page_tile<DT, false>(d, [&]() __attribute__((always_inline)) {
+        uint8_t *blk = block_ptr(d, id);
+        if (DT == PKV_E4M3 && (threadIdx.x & 63) == 0) reinterpret_cast<float *>(blk)[(which ? d.Hkv : 0) + h] = scale;
+        return blk;
+    }, h, which, p);
 }
 
 // kv_append, the decode step: one wave per (sequence, kv head) writes the token with index ctx_lens[seq] - 1 from row
@@ -437,6 +489,7 @@ __global__ __launch_bounds__(64 * PAGE_WAVES) void k_kv_write(const AttnDesc d, 
 template <int DT>
 __global__ __launch_bounds__(64) void k_kv_append(const AttnDesc d, const uint16_t *k_new, const uint16_t *v_new) {
     const int lane = threadIdx.x;
+    ask_arguments(d, k_new, v_new);
     const int seq = blockIdx.x / d.Hkv, h = blockIdx.x - seq * d.Hkv;
     const int D = d.D;
     // The new token's values are asked for along with the context length: the launch is bound by its dependent memory
@@ -490,12 +543,15 @@ template <int DT, int SEQS>
 __global__ __launch_bounds__(64 * PAGE_WAVES) void k_kv_append_chunk(const AttnDesc d, const PlanOf<SEQS> plan, const uint16_t *k_new,
                                                                      const uint16_t *v_new) {
     const int lane = threadIdx.x & 63;
+    const PlanLanes<SEQS> lanes(plan);
+    ask_arguments(d, k_new, v_new);
+    asm volatile("" ::"s"(plan.n_seqs), "s"(plan.seq0));
     const int x = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * PAGE_WAVES + (threadIdx.x >> 6)));
     const int which = x & 1, hp = x >> 1, unit = hp / d.Hkv, h = hp - unit * d.Hkv;
-    if ((uint32_t)unit >= plan.s[plan.n_seqs].unit) return;          // the last work-group may have waves to spare
-    const PlanUnit pu = plan_find(plan, (uint32_t)unit);
+    if ((uint32_t)unit >= lanes.units(plan)) return;                 // the last work-group may have waves to spare
+    const PlanUnit pu = lanes.find(plan, (uint32_t)unit);
     const int ctx = PKV_CONST(int32_t, d.ctx_lens)[pu.seq], cap = PKV_CONST(int32_t, d.row_len)[pu.seq] * PKV_T;
-    if (ctx < pu.rows || ctx < 1 || ctx > cap) {
+    if ((ctx < pu.rows) | (ctx < 1) | (ctx > cap)) {
         if (lane == 0) atomicOr(d.err, 2u);
         return;
     }
@@ -503,10 +559,6 @@ __global__ __launch_bounds__(64 * PAGE_WAVES) void k_kv_append_chunk(const AttnD
     const int lo = tok0 > page * PKV_T ? tok0 : page * PKV_T, hi = ctx < (page + 1) * PKV_T ? ctx : (page + 1) * PKV_T;
     if (lo >= hi) return;
     const uint32_t id = (uint32_t)PKV_CONST(int32_t, d.table)[(size_t)pu.seq * d.row_stride + page];
-    if (id >= d.max_block_id) {
-        if (lane == 0) atomicOr(d.err, 1u);
-        return;
-    }
     const uint16_t *src = which ? v_new : k_new;
     PageRows p;
     p.stride = (size_t)d.Hkv * d.D * 2;
@@ -514,7 +566,13 @@ __global__ __launch_bounds__(64 * PAGE_WAVES) void k_kv_append_chunk(const AttnD
     p.s0 = lo % PKV_T;
     p.n = hi - lo;
     p.aligned = (reinterpret_cast<uintptr_t>(src) & 15) == 0;
-    page_tile<DT, true>(d, block_ptr(d, id), h, which, p);
+    page_tile<DT, true>(d, [&]() __attribute__((always_inline)) -> uint8_t * {
+        if (id >= d.max_block_id) {
+            if (lane == 0) atomicOr(d.err, 1u);
+            return nullptr;
+        }
+        return block_ptr(d, id);
+    }, h, which, p);
 }
 
 }  // namespace

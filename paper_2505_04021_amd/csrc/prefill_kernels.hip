@@ -85,8 +85,8 @@ struct GroupInfo {
 };
 
 template <int SEQS>
-__device__ __forceinline__ GroupInfo group_info(const AttnDesc &d, const PlanOf<SEQS> &plan, int unit) {
-    const PlanUnit pu = plan_find(plan, (uint32_t)unit);
+__device__ __forceinline__ GroupInfo group_info(const AttnDesc &d, const PlanOf<SEQS> &plan, const PlanLanes<SEQS> &lanes, int unit) {
+    const PlanUnit pu = lanes.find(plan, (uint32_t)unit);
     const int size = PF_WAVES * (d.cols / d.g), groups = (pu.rows + size - 1) / size;
     const int rank = pu.parts > 1 ? pu.unit / pu.parts : pu.unit;
     const int t0 = (groups - 1 - rank) * size;
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
 
     // groups of a sequence come longest context first; a group of few query tokens in front of a long context comes
     // as several work-groups, each with a part of the context, that leave partial results for k_prefill_merge
-    const GroupInfo gi = group_info(d, plan, group);
+    const GroupInfo gi = group_info(d, plan, PlanLanes<SEQS>(plan), group);
     const int seq = gi.seq, q0 = gi.q0, ntok = gi.ntok, split = gi.part, n_split = gi.parts;
     const int tile_tok = d.cols / d.g;                     // query tokens per wave
     const int tok = n / d.g, head = n - tok * d.g;         // this lane's column
