@@ -288,36 +288,72 @@ __device__ __forceinline__ void page_codes(const TILE_OF &tile_of, const PageRow
 // The quotient is first taken between two products, v * lo and v * hi with lo < 1 / scale < hi (2^-21 either side of
 // v_rcp_f32, which is within 2^-23): where both round to the same code the exact quotient does too (rounding is
 // monotonic; the conversion instruction equals e4m3_encode for every float below 464 in magnitude: a sweep over all of
-// them found no other; the tests compare the codes that calls write with the plain division).  Where they differ, or the code is a NaN, or the scale is out of the range in which this holds, the division is
-// done: a word in some thousand.
+// them found no other; the tests compare the codes that calls write with the plain division).  Where they differ, or the code
+// is a NaN, or the scale is out of the range in which this holds, the division is done.
 struct Divisor {
-    float scale, lo, hi;
+    float scale, r, lo, hi;
     bool plain;             // the scale is small or large: always divide
 };
 __device__ __forceinline__ Divisor divisor(float scale) {
     const float r = __builtin_amdgcn_rcpf(scale);
-    return Divisor{scale, r * (1.0f - 0x1p-21f), r * (1.0f + 0x1p-21f), !(scale > 0x1p-100f && scale < 0x1p100f)};
+    return Divisor{scale, r, r * (1.0f - 0x1p-21f), r * (1.0f + 0x1p-21f), !(scale > 0x1p-100f && scale < 0x1p100f)};
 }
-__device__ __forceinline__ uint32_t encode4(float a, float b, float c, float d, const Divisor &s) {
-    int x = __builtin_amdgcn_cvt_pk_fp8_f32(a * s.lo, b * s.lo, 0, false);
-    x = __builtin_amdgcn_cvt_pk_fp8_f32(c * s.lo, d * s.lo, x, true);
-    int y = __builtin_amdgcn_cvt_pk_fp8_f32(a * s.hi, b * s.hi, 0, false);
-    y = __builtin_amdgcn_cvt_pk_fp8_f32(c * s.hi, d * s.hi, y, true);
-    const bool odd = s.plain || x != y || (((x & 0x7f7f7f7f) + 0x01010101) & 0x80808080) != 0;
-    if (__any(odd)) {
-        const uint32_t z = e4m3_encode(__fdiv_rn(a, s.scale)) | e4m3_encode(__fdiv_rn(b, s.scale)) << 8 |
-                           e4m3_encode(__fdiv_rn(c, s.scale)) << 16 | e4m3_encode(__fdiv_rn(d, s.scale)) << 24;
-        return odd ? z : (uint32_t)x;
+// The correctly rounded quotient of a bf16 value and a scale that is some bf16 value / 448, rounded: a first quotient within
+// two units and one correction by its exact remainder (Markstein).  In general the outcome may be a unit off where the exact
+// quotient all but lies between two floats; of these quotients, of 8 by 8 digits, none does (all pairs are tried in a test, with
+// every reciprocal that v_rcp_f32's error allows).  Signs of zeros are kept: the remainder is taken negative.
+__device__ __forceinline__ float quotient(float v, const Divisor &s) {
+    const float q = v * s.r;
+    return __builtin_fmaf(__builtin_fmaf(q, s.scale, -v), -s.r, q);
+}
+__device__ __forceinline__ uint32_t pack4(float a, float b, float c, float d) {
+    const int x = __builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false);
+    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(c, d, x, true);
+}
+__device__ __forceinline__ uint32_t divide4(float a, float b, float c, float d, float s) {
+    uint32_t z = 0u;
+#pragma unroll 1
+    for (int k = 0; k < 4; ++k) {                        // (a rare path, which comes up to sixteen times: kept short)
+        z = z >> 8 | e4m3_encode(__fdiv_rn(a, s)) << 24;
+        a = b;
+        b = c;
+        c = d;
     }
-    return (uint32_t)x;
+    return z;
+}
+constexpr uint32_t SIGNS = 0x80808080u;
+__device__ __forceinline__ uint32_t nan_codes(uint32_t w) { return (w & ~SIGNS) + 0x01010101u; }      // sign bit of a byte: its code is a NaN
+__device__ __forceinline__ uint32_t encode4(float a, float b, float c, float d, const Divisor &s) {
+    const uint32_t x = pack4(a * s.lo, b * s.lo, c * s.lo, d * s.lo), y = pack4(a * s.hi, b * s.hi, c * s.hi, d * s.hi);
+    const bool odd = s.plain || x != y || (nan_codes(x) & SIGNS) != 0;
+    if (__any(odd)) {
+        const uint32_t z = divide4(a, b, c, d, s.scale);
+        return odd ? z : x;
+    }
+    return x;
+}
+
+// What a raise of the scale from s to r > s does to a code, encode(decode(c) * s / r), depends on its three mantissa bits
+// alone as long as code and outcome are normal numbers: both roundings are to a relative step, whatever the exponent.  The
+// code then falls by a number of steps that a table of eight bytes holds (lo: mantissas 0 to 3, hi: 4 to 7), and two raises
+// one after the other are one table again.  Four codes at a time, one byte permute.  A byte of `fit` keeps its sign bit
+// where the outcome is normal.
+__device__ __forceinline__ uint32_t lower_codes(uint32_t w, uint32_t lo, uint32_t hi, uint32_t &fit) {
+    const uint32_t y = (w | SIGNS) - __builtin_amdgcn_perm(hi, lo, w & 0x07070707u);      // steps are at most 60: no byte borrows
+    fit &= y - 0x08080808u;
+    return (y & ~SIGNS) | (w & SIGNS);
 }
 
 // bf16 values into an e4m3 tile under its running scale, with the outcome, bit for bit, of append_row_e4m3 called for
 // each token in turn.  The scale after a token is the largest amax / 448 so far, so all 16 are known at once from one
 // prefix maximum; a token is encoded under the scale of its own step and then re-encoded at every later step that raises
-// the scale (for 16 like tokens between two and three times).  Bound by the vector instructions of that: 8 x 512 tokens
-// of 8 heads x 128, K and V: 64 us with the tokens one after the other, a wave maximum through LDS and two divisions an
-// element each; 20 us so.
+// the scale (for 16 like tokens between two and three times), by the table of those raises taken together (lower_codes):
+// each lane works two entries of its token's table out with the divisions that define it.  Codes that a table does not
+// cover (zeros and subnormals, one in some ten thousand, and raises by more than 2^7) are re-encoded step by step.
+// Bound by memory trips and vector instructions alike: 8 x 512 tokens of 8 heads x 128, K and V, us a call: 65 with the
+// tokens one after the other, a wave maximum through LDS and two divisions an element each; 22.8 with every raise worked
+// out code by code and quotients between two products (1315 vector instructions a wave, half of them for quotients that fall
+// on the border of two codes, as two of three waves hold some); 10.0 so (517).
 template <int D, bool IS_V, typename TILE_OF>
 __device__ __forceinline__ void page_quantise(const TILE_OF &tile_of, const PageRows &p) {
     constexpr int NW = D / 16;                           // words of codes per lane
@@ -378,15 +414,31 @@ __device__ __forceinline__ void page_quantise(const TILE_OF &tile_of, const Page
     const float scale = top > start ? top : start;       // after this lane's token
     float before = up(scale, 1);
     before = t == s0 ? start : before;
-    uint32_t events = (uint32_t)__ballot(t >= s0 && t > 0 && t < end && scale > before) & 0xffffu;
+    const uint32_t events = (uint32_t)__ballot(t >= s0 && t > 0 && t < end && scale > before) & 0xffffu;
     const bool raised = events != 0u;
 
     uint32_t w[NW];
-    const Divisor own = divisor(scale);
+    {
+        // a page's first token comes with its scale, so all scales here are bf16 amax / 448 (or 1 = 448 / 448, the scale of zeros);
+        // behind tokens that the page holds already it may be any number
+        const Divisor own = divisor(scale);
+        auto value = [&](int i) __attribute__((always_inline)) { return __uint_as_float((i & 1) ? x[i >> 1] & 0xffff0000u : x[i >> 1] << 16); };
+        uint32_t nan = 0u;
+        bool plain = s0 > 0 || !(scale > 0x1p-60f && scale < 0x1p100f);
+        if (!__any(plain)) {
 #pragma unroll
-    for (int i = 0; i < NW; ++i)
-        w[i] = encode4(__uint_as_float(x[2 * i] << 16), __uint_as_float(x[2 * i] & 0xffff0000u), __uint_as_float(x[2 * i + 1] << 16),
-                       __uint_as_float(x[2 * i + 1] & 0xffff0000u), own);
+            for (int i = 0; i < NW; ++i) {
+                w[i] = pack4(quotient(value(4 * i), own), quotient(value(4 * i + 1), own), quotient(value(4 * i + 2), own),
+                             quotient(value(4 * i + 3), own));
+                nan |= nan_codes(w[i]);
+            }
+            plain = (nan & SIGNS) != 0u;
+        }
+        if (__any(plain)) {
+#pragma unroll
+            for (int i = 0; i < NW; ++i) w[i] = encode4(value(4 * i), value(4 * i + 1), value(4 * i + 2), value(4 * i + 3), own);
+        }
+    }
     if (s0 > 0) {
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
@@ -395,17 +447,63 @@ __device__ __forceinline__ void page_quantise(const TILE_OF &tile_of, const Page
             w[i] = t < s0 ? held : w[i];
         }
     }
-    while (events) {                                     // wave-uniform; in the order of the tokens
-        const int u = __ffs((int)events) - 1;
-        events &= events - 1u;
-        const float was = of_lane(before, u);
-        const Divisor now = divisor(of_lane(scale, u));
+    if (raised) {                                        // wave-uniform
+        // entries 2 c and 2 c + 1 of the table of this token's raise, from codes of exponent 14
+        uint32_t two = 0u;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const uint32_t mant = 2u * (uint32_t)c + (uint32_t)k;
+            const float v = __fmul_rn((float)(128u + 16u * mant), before);
+            const uint32_t a = __float_as_uint(__fdiv_rn(v, scale));
+            const uint32_t code = ((a + 0x7ffffu + ((a >> 20) & 1u)) >> 20) - ((127u - 7u) << 3);       // e4m3_encode of a normal outcome
+            uint32_t steps = (0x70u | mant) - code;
+            if (!(before > 0x1p-100f && scale < 0x1p100f) || steps > 60u) steps = 127u;
+            two |= steps << (8 * k);
+        }
+        // all raises behind this lane's token as one table
+        uint32_t lo = 0u, hi = 0u, far = 0u;
+        for (uint32_t rest = events; rest; rest &= rest - 1u) {       // in the order of the tokens
+            const int u = __ffs((int)rest) - 1;
+            auto entries = [&](int l) __attribute__((always_inline)) { return (uint32_t)__builtin_amdgcn_readlane((int)two, l); };
+            const uint32_t d0 = entries(u) | entries(u + 16) << 16, d1 = entries(u + 32) | entries(u + 48) << 16;
+            const uint32_t lo_n = lo + __builtin_amdgcn_perm(d1, d0, (0x83828180u - lo) & 0x07070707u);
+            const uint32_t hi_n = hi + __builtin_amdgcn_perm(d1, d0, (0x87868584u - hi) & 0x07070707u);
+            if (t < u) {
+                lo = lo_n;
+                hi = hi_n;
+                far |= (lo_n + 0x43434343u) | (hi_n + 0x43434343u);   // sign bit: more than 60 steps
+            }
+        }
+        // a token of zeros stays as it is; any other code that the table does not cover is looked at again
+        const bool zeros = t >= s0 && !(amax > 0.f);
+        const bool lowered = t < 31 - __clz((int)events) && !zeros;
+        if (zeros) lo = hi = 0u;
+        uint32_t low[NW], fit = SIGNS, nan = 0u;
 #pragma unroll
         for (int i = 0; i < NW; ++i) {
-            const f32x2 lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[i], false), hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)w[i], true);
-            const uint32_t again = encode4(__fmul_rn(lo[0], was), __fmul_rn(lo[1], was), __fmul_rn(hi[0], was), __fmul_rn(hi[1], was), now);
-            w[i] = t < u ? again : w[i];
+            low[i] = lower_codes(w[i], lo, hi, fit);
+            nan |= nan_codes(w[i]);
         }
+        auto uncovered = [&](uint32_t f, uint32_t n) __attribute__((always_inline)) { return __any(lowered && ((far | n | ~f) & SIGNS) != 0u); };
+        if (uncovered(fit, nan)) {
+#pragma unroll
+            for (int i = 0; i < NW; ++i) {
+                uint32_t f = SIGNS, again = w[i];
+                (void)lower_codes(w[i], lo, hi, f);
+                if (!uncovered(f, nan_codes(w[i]))) continue;
+                for (uint32_t rest = events; rest; rest &= rest - 1u) {
+                    const int u = __ffs((int)rest) - 1;
+                    const float was = of_lane(before, u);
+                    const Divisor now = divisor(of_lane(scale, u));
+                    const f32x2 l2 = __builtin_amdgcn_cvt_pk_f32_fp8((int)again, false), h2 = __builtin_amdgcn_cvt_pk_f32_fp8((int)again, true);
+                    const uint32_t z = encode4(__fmul_rn(l2[0], was), __fmul_rn(l2[1], was), __fmul_rn(h2[0], was), __fmul_rn(h2[1], was), now);
+                    again = t < u ? z : again;
+                }
+                low[i] = again;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NW; ++i) w[i] = low[i];
     }
     if (lane == 0) *scale_p = of_lane(scale, end - 1);
     const int first = raised ? 0 : s0;                   // slots below it still hold what memory holds
