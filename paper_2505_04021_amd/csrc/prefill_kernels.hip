@@ -105,6 +105,8 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
     using TL = PfTile<D, DT>;
     constexpr int SLOT = 2 * TL::BYTES;                    // the K (or V) tiles of a pair
     __shared__ __align__(16) uint8_t ring[2 * PF_SLOTS * SLOT];   // K slots, then V slots
+    const PlanLanes<SEQS> lanes(plan);
+    ask_arguments(d, plan);
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int h = lane >> 5, n = lane & 31, c16 = lane & 15, hi16 = (lane >> 4) & 1;
@@ -112,7 +114,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
 
     // groups of a sequence come longest context first; a group of few query tokens in front of a long context comes
     // as several work-groups, each with a part of the context, that leave partial results for k_prefill_merge
-    const GroupInfo gi = group_info(d, plan, PlanLanes<SEQS>(plan), group);
+    const GroupInfo gi = group_info(d, plan, lanes, group);
     const int seq = gi.seq, q0 = gi.q0, ntok = gi.ntok, split = gi.part, n_split = gi.parts;
     const int tile_tok = d.cols / d.g;                     // query tokens per wave
     const int tok = n / d.g, head = n - tok * d.g;         // this lane's column
@@ -120,9 +122,29 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
     const int32_t *row = d.table + (size_t)seq * d.row_stride;
     auto table_id = [&](int page) __attribute__((always_inline)) { return (uint32_t)row[page < d.row_stride ? page : d.row_stride - 1]; };
     const uint32_t first_id = table_id(2 * lane + (w >> 1));
+    // e4m3: of both pages of the pair, for their scales
+    const uint32_t first_a = DT == PKV_E4M3 ? table_id(2 * lane) : 0u, first_b = DT == PKV_E4M3 ? table_id(2 * lane + 1) : 0u;
+
+    // this wave's tile: the group's tokens [w * tile_tok, ...)
+    const int t0 = w * tile_tok;
+    int my_tok = ntok - t0;
+    my_tok = my_tok < 0 ? 0 : (my_tok > tile_tok ? tile_tok : my_tok);
+    const bool col_live = n < d.cols && tok < my_tok;
+
+    // q as the column operand: lane (h, n) holds q[column n][16 kk + 8 h .. + 7], zeros in a column that stands for no query
+    u32x4 qf[TL::NK];
+    {
+        const uint16_t *qrow = d.q + ((size_t)(q0 + (col_live ? t0 + tok : 0)) * d.Hq + kvh * d.g + (col_live ? head : 0)) * D + 8 * h;
+#pragma unroll
+        for (int kk = 0; kk < TL::NK; ++kk) qf[kk] = *reinterpret_cast<const u32x4 *>(qrow + 16 * kk);
+    }
+
     // tokens the group's last query sees, never beyond what the row holds
-    int L = PKV_CONST(int32_t, d.ctx_lens)[seq] - gi.back;
-    const int cap = PKV_CONST(int32_t, d.row_len)[seq] * PKV_T;
+    int L = PKV_CONST(int32_t, d.ctx_lens)[seq];
+    int cap = PKV_CONST(int32_t, d.row_len)[seq];
+    asm volatile("" : "+s"(L), "+s"(cap));                 // both at once
+    L -= gi.back;
+    cap *= PKV_T;
     L = L < 0 ? 0 : (L > cap ? cap : L);
     const int n_pages = (L + PKV_T - 1) / PKV_T, n_pairs = (n_pages + 1) >> 1;
     // the pairs this work-group walks
@@ -134,24 +156,8 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
     const int causal_from = L - (ntok - 1);
     const int p_plain = causal_from > 0 ? causal_from >> 5 : 0;
 
-    // this wave's tile: the group's tokens [w * tile_tok, ...)
-    const int t0 = w * tile_tok;
-    int my_tok = ntok - t0;
-    my_tok = my_tok < 0 ? 0 : (my_tok > tile_tok ? tile_tok : my_tok);
-    const bool col_live = n < d.cols && tok < my_tok;
     const int col_lim = col_live ? L - (ntok - 1 - (t0 + tok)) : L;          // tokens this column sees
     const int tile_lim = my_tok > 0 ? L - (ntok - t0 - my_tok) : 0;          // tokens some column of the tile sees
-
-    // q as the column operand: lane (h, n) holds q[column n][16 kk + 8 h .. + 7]
-    u32x4 qf[TL::NK];
-    {
-        const uint16_t *qrow = d.q + ((size_t)(q0 + t0 + tok) * d.Hq + kvh * d.g + head) * D + 8 * h;
-#pragma unroll
-        for (int kk = 0; kk < TL::NK; ++kk) {
-            qf[kk] = mk4(0, 0, 0, 0);
-            if (col_live) qf[kk] = *reinterpret_cast<const u32x4 *>(qrow + 16 * kk);
-        }
-    }
 
     f32x16 acc[TL::ND];
 #pragma unroll
@@ -205,7 +211,11 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
         if (p - scale_win >= 64) {
             scale_win = p;
             const int page = 2 * (p + lane);
-            const uint32_t ida = table_id(page), idb = table_id(page + 1);
+            uint32_t ida = first_a, idb = first_b;
+            if (p > 0) {
+                ida = table_id(page);
+                idb = table_id(page + 1);
+            }
             const float *ha = reinterpret_cast<const float *>(block_of(page, ida, 0));
             const float *hb = reinterpret_cast<const float *>(block_of(page + 1, idb, 0));
             w_ska = ha[kvh]; w_sva = ha[d.Hkv + kvh];
@@ -399,6 +409,9 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
         load_addr(p_begin);
         const int ahead = is_v ? PF_SLOTS - 1 : PF_SLOTS, first = ahead < np ? ahead : np;
         for (int r = 0; r < first; ++r) fetch(r);
+#pragma unroll
+        for (int kk = 0; kk < TL::NK; ++kk)
+            if (!col_live) qf[kk] = mk4(0, 0, 0, 0);
         wait_requests<TL::NL>(first - 2);                  // K 0, K 1 and V 0, V 1
         __builtin_amdgcn_s_barrier();
         const bool live = my_tok > 0;
