@@ -397,7 +397,21 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
     // the meeting point of the steps r and r + 1 (r even), in the middle of step r: all requests under way have
     // landed; behind it K of pairs r + 2, r + 3 and V of pairs r + 1, r + 2 are visible to all waves, and the slots
     // of K r, r + 1 and V r - 1, r take the pairs PF_SLOTS ahead of them
+    // Issue favours the older of the two waves of a SIMD: of two work-groups that share a CU from the start one was done after
+    // 265 us and the other, alone from then on, after 375, and a wave alone turns over an eighth less than two together.
+    // So a wave steps down one priority level per quarter of its pairs, and whichever work-group is behind is favoured
+    // (us a pass, without and with: 512 behind 15872 of 64/8/128 351.8, 345.7; 8 x (2048 + 512) of 32/8/128 bf16 218.7, 216.1,
+    // e4m3 185.3, 178.6; short prompts 68.1, 68.2).
+    int level = 3, next_level = np / 4;
+    __builtin_amdgcn_s_setprio(3);
     auto meet = [&](int r) __attribute__((always_inline)) {
+        if (r >= next_level) {
+            --level;
+            next_level += np / 4;
+            if (level == 2) __builtin_amdgcn_s_setprio(2);
+            else if (level == 1) __builtin_amdgcn_s_setprio(1);
+            else __builtin_amdgcn_s_setprio(0);
+        }
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         const int next = r + PF_SLOTS - (is_v ? 1 : 0);
