@@ -402,16 +402,13 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
     // So a wave steps down one priority level per quarter of its pairs, and whichever work-group is behind is favoured
     // (us a pass, without and with: 512 behind 15872 of 64/8/128 351.8, 345.7; 8 x (2048 + 512) of 32/8/128 bf16 218.7, 216.1,
     // e4m3 185.3, 178.6; short prompts 68.1, 68.2).
-    int level = 3, next_level = np / 4;
+    // (the waves meet in even steps)
+    const int quarter = (np / 4 + 1) & ~1, half = (np / 2 + 1) & ~1, three_quarters = (3 * np / 4 + 1) & ~1;
     __builtin_amdgcn_s_setprio(3);
     auto meet = [&](int r) __attribute__((always_inline)) {
-        if (r >= next_level) {
-            --level;
-            next_level += np / 4;
-            if (level == 2) __builtin_amdgcn_s_setprio(2);
-            else if (level == 1) __builtin_amdgcn_s_setprio(1);
-            else __builtin_amdgcn_s_setprio(0);
-        }
+        if (r == quarter) __builtin_amdgcn_s_setprio(2);
+        if (r == half) __builtin_amdgcn_s_setprio(1);
+        if (r == three_quarters) __builtin_amdgcn_s_setprio(0);
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         const int next = r + PF_SLOTS - (is_v ? 1 : 0);
@@ -440,9 +437,10 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
             settle(p_begin, masked);
         }
         int r = 0;
-        if (live) {
-            // pairs without masks: straight-line steps
-            for (; r + 1 < np && p_begin + r + 1 < p_plain; ++r) {
+        // pairs in front of pairs without masks: straight-line steps
+        const int plain = live ? (np < p_plain - p_begin ? np : p_plain - p_begin) - 1 : 0;
+        if (plain > 0) {
+            do {
                 read_v(r);
                 scales(p_begin + r + 1);
                 scores();
@@ -457,7 +455,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
                 }
                 args(p_begin + r + 1, false);
                 settle(p_begin + r + 1, false);
-            }
+            } while (++r < plain);
         }
         for (; r < np; ++r) {
             const int p = p_begin + r;
