@@ -1171,6 +1171,7 @@ int model_register_layers(int pool, int q_heads, int kv_heads, int head_dim, int
     ModelDev &d = m.dev;
     d.model_id = id;
     d.slots = (int)slots;
+    d.slots_div = fastdiv_make((uint32_t)d.slots);
     d.wpf = (int)((slots + 31) / 32);
     d.max_seqs = max_seqs;
     d.max_blocks = max_blocks_per_seq;

@@ -10,6 +10,8 @@
 // an order.  The data moved per call is a few KB, the cost is launch latency.
 #include "pkv_internal.h"
 
+#include <type_traits>
+
 namespace {
 
 constexpr int NT = PKV_BOOK_THREADS;
@@ -20,27 +22,47 @@ constexpr int NW = NT / 64;
 // everything else such a kernel does between two barriers).
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// Exclusive prefix sum of one int per lane over the work-group; `total` is uniform.
-__device__ inline int block_excl_scan(int v, int &total, int *s_wave) {
+// Inclusive prefix sum over a wave, by lane moves inside the vector unit: 1, 2, 4 and 8 lanes up within a row of 16, then
+// the last lane of a row to the next one, then of the lower half to the upper one.
+__device__ inline int wave_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
+}
+
+// Exclusive prefix sums of N ints per lane over the work-group, side by side; the totals are uniform.  s_wave: N * NW ints.
+template <int N>
+__device__ inline void block_excl_scans(int *v, int *total, int *s_wave) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int inc = v;
+    int inc[N];
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        int o = __shfl_up(inc, d);
-        if (lane >= d) inc += o;
-    }
+    for (int c = 0; c < N; ++c) inc[c] = wave_scan(v[c]);
     lds_barrier();                   // protect s_wave from the previous call's readers
-    if (lane == 63) s_wave[wave] = inc;
-    lds_barrier();
-    int before = 0, sum = 0;
+    if (lane == 63) {
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        int x = s_wave[w];
-        if (w < wave) before += x;
-        sum += x;
+        for (int c = 0; c < N; ++c) s_wave[c * NW + wave] = inc[c];
     }
-    total = sum;
-    return before + inc - v;
+    lds_barrier();
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        int before = 0, sum = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const int x = s_wave[c * NW + w];
+            if (w < wave) before += x;
+            sum += x;
+        }
+        total[c] = sum;
+        v[c] = before + inc[c] - v[c];
+    }
+}
+__device__ inline int block_excl_scan(int v, int &total, int *s_wave) {
+    block_excl_scans<1>(&v, &total, s_wave);
+    return v;
 }
 
 __global__ void k_pool_init(PoolDev p, const uint32_t *perm) {
@@ -187,7 +209,7 @@ constexpr int RESERVE_WIN = 8192;       // ranks whose blocks k_reserve collects
 __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, const int32_t *host_ops, const BookList list,
                                                 BookResult *res, uint32_t *err) {
     const int32_t *ops = host_ops ? host_ops : list.v;
-    __shared__ int s_wave[NW];
+    __shared__ int s_wave[4 * NW];
     __shared__ int s_cur[PKV_MAX_SEQS];             // row lengths: as the call finds them, then with its wants
     __shared__ int s_start[PKV_MAX_BATCH_OPS + 1];  // first rank of entry i
     __shared__ uint32_t s_ent[PKV_MAX_BATCH_OPS];   // entry i: sequence << 20 | row length before the entry
@@ -247,21 +269,29 @@ __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, co
     }
     __syncthreads();
     int total = 0;
+    auto rank_chunks = [&](auto count) __attribute__((always_inline)) {       // the first `count` chunks, side by side
+        constexpr int N = decltype(count)::value;
+        int rank[N], sum[N];
 #pragma unroll
-    for (int c = 0; c < CHUNKS; ++c) {
-        const int c0 = c * NT, i = c0 + tid;
-        if (c0 >= n) break;                                      // uniform
-        const int seq = e_seq[c], want = e_want[c], prev = e_prev[c];
-        if (seq >= 0) atomicMax(&s_cur[seq], want);              // the row's length after the call
-        const int need = (seq >= 0 && want > prev) ? want - prev : 0;
-        int chunk_total;
-        const int excl = block_excl_scan(need, chunk_total, s_wave);
-        if (i < n) {
-            s_start[i] = total + excl;
-            s_ent[i] = ((uint32_t)(seq >= 0 ? seq : 0) << 20) | (uint32_t)prev;
+        for (int c = 0; c < N; ++c) {
+            if (e_seq[c] >= 0) atomicMax(&s_cur[e_seq[c]], e_want[c]);       // the row's length after the call
+            rank[c] = e_seq[c] >= 0 && e_want[c] > e_prev[c] ? e_want[c] - e_prev[c] : 0;
         }
-        total += chunk_total;
-    }
+        block_excl_scans<N>(rank, sum, s_wave);
+#pragma unroll
+        for (int c = 0; c < N; ++c) {
+            const int i = c * NT + tid;
+            if (i < n) {
+                s_start[i] = total + rank[c];
+                s_ent[i] = ((uint32_t)(e_seq[c] >= 0 ? e_seq[c] : 0) << 20) | (uint32_t)e_prev[c];
+            }
+            total += sum[c];
+        }
+    };
+    static_assert(CHUNKS == 4, "chunks of the list");
+    if (n <= NT) rank_chunks(std::integral_constant<int, 1>{});
+    else if (n <= 2 * NT) rank_chunks(std::integral_constant<int, 2>{});
+    else rank_chunks(std::integral_constant<int, 4>{});
     if (tid == 0) s_start[n] = total;
     __syncthreads();
     int status = 0;
@@ -317,21 +347,41 @@ __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, co
                 s_fid[tid] = f;
                 rank += __popc(freeb);
                 lds_barrier();
-                for (int idx = tid; idx < nf * 32; idx += NT) {
-                    const int j = idx >> 5, bit = idx & 31;
-                    const uint32_t fr = s_free[j];
-                    const int r = s_rank[j] + __popc(fr & ((1u << bit) - 1u));
-                    if (((fr >> bit) & 1u) && r >= win0 && r < win1) s_blk[r - win0] = s_fid[j] * (uint32_t)slots + (uint32_t)(32 * w + bit);
+                for (int idx0 = tid; idx0 < nf * 32; idx0 += 4 * NT) {       // four frames' words on the way at a time
+                    uint32_t fr[4], fid[4];
+                    int first[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int j = (idx0 + u * NT) >> 5, in = j < nf ? j : nf - 1;
+                        fr[u] = j < nf ? s_free[in] : 0u;
+                        first[u] = s_rank[in];
+                        fid[u] = s_fid[in];
+                    }
+                    const int bit = idx0 & 31;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int r = first[u] + __popc(fr[u] & ((1u << bit) - 1u));
+                        if (((fr[u] >> bit) & 1u) && r >= win0 && r < win1) s_blk[r - win0] = fid[u] * (uint32_t)slots + (uint32_t)(32 * w + bit);
+                    }
                 }
                 lds_barrier();
             }
-            for (int e = tid / group; e < n; e += NT / group) {
-                const int st = s_start[e], en = s_start[e + 1];
-                const int lo = st > win0 ? st : win0, hi = en < win1 ? en : win1;
-                if (lo >= hi) continue;
-                const uint32_t ent = s_ent[e];
-                int32_t *row = m.rows + (int64_t)(ent >> 20) * m.max_blocks + (ent & 0xfffffu);
-                for (int r = lo + sub; r < hi; r += group) row[r - st] = (int32_t)s_blk[r - win0];
+            for (int e0 = tid / group; e0 < n; e0 += 4 * (NT / group)) {       // four entries on the way at a time
+                int st[4], en[4];
+                uint32_t ent[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int e = e0 + u * (NT / group), in = e < n ? e : n - 1;
+                    st[u] = s_start[in];
+                    en[u] = e < n ? s_start[in + 1] : st[u];
+                    ent[u] = s_ent[in];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int lo = st[u] > win0 ? st[u] : win0, hi = en[u] < win1 ? en[u] : win1;
+                    int32_t *row = m.rows + (int64_t)(ent[u] >> 20) * m.max_blocks + (ent[u] & 0xfffffu);
+                    for (int r = lo + sub; r < hi; r += group) row[r - st[u]] = (int32_t)s_blk[r - win0];
+                }
             }
             lds_barrier();
         }
@@ -380,7 +430,7 @@ __global__ __launch_bounds__(NT) void k_release(PoolDev p, ModelDev m, int n, co
     __shared__ uint32_t s_win[RELEASE_WIN];
     const int tid = threadIdx.x;
     for (int i = tid; i < PKV_MAX_SEQS / 32; i += NT) s_seen[i] = 0u;
-    const int64_t words_total = m.counters[0] * m.wpf;
+    const int64_t words_total = m.counters[0] * m.wpf, spare = m.counters[1];
     __syncthreads();
     int total = 0;
     for (int c0 = 0; c0 < n; c0 += NT) {
@@ -411,32 +461,39 @@ __global__ __launch_bounds__(NT) void k_release(PoolDev p, ModelDev m, int n, co
     // then rewritten once by one lane: thirty atomics on the same word in memory cost more than the
     // rest of the kernel.
     constexpr int RELEASE_BATCH = 8;
+    const int top_step = n > 1 ? 1 << (31 - __clz(n - 1)) : 0;
     for (int64_t win0 = 0; win0 < words_total && total > 0; win0 += RELEASE_WIN) {
         for (int i = tid; i < RELEASE_WIN; i += NT) s_win[i] = 0u;
         lds_barrier();
         for (int x0 = 0; x0 < total; x0 += NT * RELEASE_BATCH) {
-            uint32_t id[RELEASE_BATCH];
+            uint32_t id[RELEASE_BATCH], frame[RELEASE_BATCH];
             int64_t at[RELEASE_BATCH];
+            int ent[RELEASE_BATCH];                          // last entry with s_start <= x: the eight searches side by side
+#pragma unroll
+            for (int u = 0; u < RELEASE_BATCH; ++u) ent[u] = 0;
+            for (int step = top_step; step > 0; step >>= 1) {
+#pragma unroll
+                for (int u = 0; u < RELEASE_BATCH; ++u) {
+                    const int next = ent[u] + step;
+                    const int begins = s_start[next < n ? next : n];
+                    if (next < n && begins <= x0 + u * NT + tid) ent[u] = next;
+                }
+            }
 #pragma unroll
             for (int u = 0; u < RELEASE_BATCH; ++u) {
                 const int x = x0 + u * NT + tid;
                 id[u] = 0xffffffffu;
-                if (x < total) {
-                    int lo = 0, hi = n;                      // last entry with s_start <= x
-                    while (hi - lo > 1) {
-                        const int mid = (lo + hi) >> 1;
-                        if (s_start[mid] <= x) lo = mid; else hi = mid;
-                    }
-                    id[u] = (uint32_t)m.rows[(int64_t)s_seq[lo] * m.max_blocks + (x - s_start[lo])];
-                }
+                if (x < total) id[u] = (uint32_t)m.rows[(int64_t)s_seq[ent[u]] * m.max_blocks + (x - s_start[ent[u]])];
+            }
+#pragma unroll
+            for (int u = 0; u < RELEASE_BATCH; ++u) {
+                frame[u] = fastdiv_div(id[u], m.slots_div);
+                at[u] = id[u] != 0xffffffffu ? p.pos[frame[u]] : 0;
             }
 #pragma unroll
             for (int u = 0; u < RELEASE_BATCH; ++u)
-                at[u] = id[u] != 0xffffffffu ? p.pos[id[u] / (uint32_t)m.slots] : 0;
-#pragma unroll
-            for (int u = 0; u < RELEASE_BATCH; ++u)
                 if (id[u] != 0xffffffffu) {
-                    const uint32_t sl = id[u] % (uint32_t)m.slots;
+                    const uint32_t sl = id[u] - frame[u] * (uint32_t)m.slots;
                     const int64_t word = at[u] * m.wpf + (sl >> 5) - win0;
                     if (word >= 0 && word < RELEASE_WIN) atomicOr(&s_win[word], 1u << (sl & 31));
                 }
@@ -452,7 +509,7 @@ __global__ __launch_bounds__(NT) void k_release(PoolDev p, ModelDev m, int n, co
     for (int i = tid; i < n; i += NT)
         if (s_seq[i] >= 0) m.row_len[s_seq[i]] = 0;
     if (tid == 0) {
-        m.counters[1] += total;
+        m.counters[1] = spare + total;
         book_finish(res, err, total);
     }
 }
