@@ -1173,6 +1173,7 @@ int model_register_layers(int pool, int q_heads, int kv_heads, int head_dim, int
     d.slots = (int)slots;
     d.slots_div = fastdiv_make((uint32_t)d.slots);
     d.wpf = (int)((slots + 31) / 32);
+    d.wpf_div = fastdiv_make((uint32_t)d.wpf);
     d.max_seqs = max_seqs;
     d.max_blocks = max_blocks_per_seq;
     d.page_tokens = p->T;

@@ -81,6 +81,7 @@ struct ModelDev {
     int32_t slots, wpf;    // slots per frame, 32-bit words per frame in `bits`
     int32_t max_seqs, max_blocks, page_tokens;
     FastDiv slots_div;     // division by `slots`
+    FastDiv wpf_div;       // division by `wpf`
 };
 
 // What one attention work-group needs to know about its model.

@@ -204,7 +204,7 @@ __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, co
     __shared__ int s_cur[PKV_MAX_SEQS];             // row lengths: as the call finds them, then with its wants
     __shared__ int s_start[PKV_MAX_BATCH_OPS + 1];  // first rank of entry i
     __shared__ uint32_t s_ent[PKV_MAX_BATCH_OPS];   // entry i: sequence << 20 | row length before the entry
-    __shared__ uint32_t s_free[NT], s_fid[NT];      // placement: free bits of frame j's current word, its frame id
+    __shared__ uint32_t s_free[NT], s_fid[NT];      // placement: free bits of unit j's current word, the block id of its slot 0
     __shared__ int s_rank[NT];                      // placement: rank of the first free slot of that word
     __shared__ uint32_t s_blk[RESERVE_WIN];         // placement: the blocks of a window of ranks
     __shared__ int s_fail;
@@ -228,7 +228,9 @@ __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, co
     // not wait for the count of owned frames to arrive)
 #pragma unroll
     for (int w = 0; w < PRE_WORDS; ++w) pre_bits[w] = (tid < p.n_frames && w < wpf) ? m.bits[(int64_t)tid * wpf + w] : 0u;
-    const uint32_t pre_frame = tid < p.n_frames ? m.frames[tid] : 0u;
+    uint32_t pre_frame = tid < p.n_frames ? m.frames[tid] : 0u;
+    const int flat_frame = (int)fastdiv_div((uint32_t)tid, m.wpf_div);       // (word `tid` of the bitmap, for the flat split below)
+    const uint32_t flat_bits = flat_frame < p.n_frames ? m.bits[tid] : 0u, flat_id = flat_frame < p.n_frames ? m.frames[flat_frame] : 0u;
     for (int s = tid; s < m.max_seqs; s += NT) s_cur[s] = m.row_len[s];
     if (tid == 0) s_fail = 0x7fffffff;
     __syncthreads();
@@ -298,13 +300,25 @@ __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, co
     // (frame, slot) of that word takes over: a free slot knows its rank from the bits below it and puts its block id
     // there, in LDS.  The entries then copy their ranks into their rows, `group` lanes each (a search for the entry of
     // every slot took 4 of this kernel's 13 us).  The frame's lane sets the bits that were taken.
+    // A model whose bitmap has no more words than the work-group lanes gets a lane per word instead: one turn, where small
+    // blocks (8/2/64 bf16: 256 slots a frame) take eight, two barriers each, with most lanes idle (us: an admission
+    // of 64 rows around 1500 tokens of that model 22.3 -> 15.1, of three around 118 of 2/1/64, 16 words, 14.2 -> 8.0).  With more words than
+    // lanes that would be a turn, with its scan and its trip to memory, for every 1024 words passed over: they stay with the frames.
     int group = 4;
     while (group < NT && group * 2 * n <= NT) group *= 2;
     const int sub = tid & (group - 1);
     int running = 0;
-    for (int64_t base = 0; base < owned && running < total; base += NT) {
+    const bool flat = owned * wpf <= NT;
+    const int per = flat ? 1 : wpf;                          // words of a lane's unit (a word, or a frame)
+    const int64_t units = flat ? owned * wpf : owned;
+    if (flat) {
+        pre_bits[0] = flat_bits;
+        pre_frame = flat_id;
+    }
+    auto first_slot = [&](int w) { return 32 * (flat ? tid - flat_frame * wpf : w); };
+    for (int64_t base = 0; base < units && running < total; base += NT) {
         const int64_t i = base + tid;
-        const bool pre = base == 0 && wpf <= PRE_WORDS;      // this pass's words are already here
+        const bool pre = base == 0 && per <= PRE_WORDS;      // this pass's words are already here
         auto word_of = [&](int w) {
             uint32_t word = 0u;
             if (pre) {
@@ -312,73 +326,86 @@ __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, co
                 for (int k = 0; k < PRE_WORDS; ++k)
                     if (k == w) word = pre_bits[k];
             } else {
-                word = m.bits[i * wpf + w];
+                word = m.bits[i * per + w];
             }
             return word;
         };
         auto valid_of = [&](int w) {
-            const int nb = slots - 32 * w;
+            const int nb = slots - first_slot(w);
             return nb >= 32 ? 0xffffffffu : ((1u << nb) - 1u);
         };
         int zeros = 0;
-        if (i < owned)
-            for (int w = 0; w < wpf; ++w) zeros += __popc(~word_of(w) & valid_of(w));
+        if (i < units)
+            for (int w = 0; w < per; ++w) zeros += __popc(~word_of(w) & valid_of(w));
         int chunk_total;
-        const int rank0 = running + block_excl_scan(zeros, chunk_total, s_wave);    // rank of this frame's first free slot
-        const uint32_t f = i < owned ? (base == 0 ? pre_frame : m.frames[i]) : 0u;
-        const int nf = (int)(owned - base < NT ? owned - base : NT);
+        const int rank0 = running + block_excl_scan(zeros, chunk_total, s_wave);    // rank of this unit's first free slot
+        const uint32_t f = i < units ? (base == 0 ? pre_frame : m.frames[i]) : 0u;
+        const int nu = (int)(units - base < NT ? units - base : NT);
         const int pass_end = running + chunk_total < total ? running + chunk_total : total;
         for (int win0 = running; win0 < pass_end; win0 += RESERVE_WIN) {
             const int win1 = win0 + RESERVE_WIN < pass_end ? win0 + RESERVE_WIN : pass_end;
-            int rank = rank0;
-            for (int w = 0; w < wpf; ++w) {
-                const uint32_t freeb = i < owned && zeros && rank < win1 ? ~word_of(w) & valid_of(w) : 0u;
-                s_free[tid] = freeb;
-                s_rank[tid] = rank;
-                s_fid[tid] = f;
-                rank += __popc(freeb);
-                lds_barrier();
-                for (int idx0 = tid; idx0 < nf * 32; idx0 += 4 * NT) {       // four frames' words on the way at a time
-                    uint32_t fr[4], fid[4];
-                    int first[4];
+            // four look-ups on the way at a time, where there is work for that
+            auto place = [&](auto count) __attribute__((always_inline)) {
+                constexpr int N = decltype(count)::value;
+                for (int idx0 = tid; idx0 < nu * 32; idx0 += N * NT) {
+                    uint32_t fr[N], id[N];
+                    int first[N];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int j = (idx0 + u * NT) >> 5, in = j < nf ? j : nf - 1;
-                        fr[u] = j < nf ? s_free[in] : 0u;
+                    for (int u = 0; u < N; ++u) {
+                        const int j = (idx0 + u * NT) >> 5, in = j < nu ? j : nu - 1;
+                        fr[u] = j < nu ? s_free[in] : 0u;
                         first[u] = s_rank[in];
-                        fid[u] = s_fid[in];
+                        id[u] = s_fid[in];
                     }
                     const int bit = idx0 & 31;
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
+                    for (int u = 0; u < N; ++u) {
                         const int r = first[u] + __popc(fr[u] & ((1u << bit) - 1u));
-                        if (((fr[u] >> bit) & 1u) && r >= win0 && r < win1) s_blk[r - win0] = fid[u] * (uint32_t)slots + (uint32_t)(32 * w + bit);
+                        if (((fr[u] >> bit) & 1u) && r >= win0 && r < win1) s_blk[r - win0] = id[u] + (uint32_t)bit;
                     }
                 }
+            };
+            auto hand_out = [&](auto count) __attribute__((always_inline)) {
+                constexpr int N = decltype(count)::value;
+                for (int e0 = tid / group; e0 < n; e0 += N * (NT / group)) {
+                    int st[N], en[N];
+                    uint32_t ent[N];
+#pragma unroll
+                    for (int u = 0; u < N; ++u) {
+                        const int e = e0 + u * (NT / group), in = e < n ? e : n - 1;
+                        st[u] = s_start[in];
+                        en[u] = e < n ? s_start[in + 1] : st[u];
+                        ent[u] = s_ent[in];
+                    }
+#pragma unroll
+                    for (int u = 0; u < N; ++u) {
+                        const int lo = st[u] > win0 ? st[u] : win0, hi = en[u] < win1 ? en[u] : win1;
+                        int32_t *row = m.rows + (int64_t)(ent[u] >> 20) * m.max_blocks + (ent[u] & 0xfffffu);
+                        for (int r = lo + sub; r < hi; r += group) row[r - st[u]] = (int32_t)s_blk[r - win0];
+                    }
+                }
+            };
+            using One = std::integral_constant<int, 1>;
+            using Four = std::integral_constant<int, 4>;
+            int rank = rank0;
+            for (int w = 0; w < per; ++w) {
+                const uint32_t freeb = i < units && zeros && rank < win1 ? ~word_of(w) & valid_of(w) : 0u;
+                s_free[tid] = freeb;
+                s_rank[tid] = rank;
+                s_fid[tid] = f * (uint32_t)slots + (uint32_t)first_slot(w);
+                rank += __popc(freeb);
+                lds_barrier();
+                if (nu * 32 <= NT) place(One{});
+                else place(Four{});
                 lds_barrier();
             }
-            for (int e0 = tid / group; e0 < n; e0 += 4 * (NT / group)) {       // four entries on the way at a time
-                int st[4], en[4];
-                uint32_t ent[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int e = e0 + u * (NT / group), in = e < n ? e : n - 1;
-                    st[u] = s_start[in];
-                    en[u] = e < n ? s_start[in + 1] : st[u];
-                    ent[u] = s_ent[in];
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int lo = st[u] > win0 ? st[u] : win0, hi = en[u] < win1 ? en[u] : win1;
-                    int32_t *row = m.rows + (int64_t)(ent[u] >> 20) * m.max_blocks + (ent[u] & 0xfffffu);
-                    for (int r = lo + sub; r < hi; r += group) row[r - st[u]] = (int32_t)s_blk[r - win0];
-                }
-            }
+            if (n * group <= NT) hand_out(One{});
+            else hand_out(Four{});
             lds_barrier();
         }
         int rank = rank0;
-        if (i < owned && zeros)
-            for (int w = 0; w < wpf && rank < total; ++w) {
+        if (i < units && zeros)
+            for (int w = 0; w < per && rank < total; ++w) {
                 const uint32_t word = word_of(w), freeb = ~word & valid_of(w);
                 const int c = __popc(freeb);
                 int take = total - rank;
@@ -392,7 +419,7 @@ __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, co
                         rest &= rest - 1u;
                     }
                 }
-                if (mask) m.bits[i * wpf + w] = word | mask;
+                if (mask) m.bits[i * per + w] = word | mask;
                 rank += c;
             }
         running += chunk_total;
@@ -422,6 +449,7 @@ __global__ __launch_bounds__(NT) void k_release(PoolDev p, ModelDev m, int n, co
     const int tid = threadIdx.x;
     for (int i = tid; i < PKV_MAX_SEQS / 32; i += NT) s_seen[i] = 0u;
     const int64_t words_total = m.counters[0] * m.wpf, spare = m.counters[1];
+    const uint32_t first_word = tid < p.n_frames * m.wpf ? m.bits[tid] : 0u;       // (also of a frame the model does not own: not looked at then)
     __syncthreads();
     int total = 0;
     for (int c0 = 0; c0 < n; c0 += NT) {
@@ -452,29 +480,26 @@ __global__ __launch_bounds__(NT) void k_release(PoolDev p, ModelDev m, int n, co
     // then rewritten once by one lane: thirty atomics on the same word in memory cost more than the
     // rest of the kernel.
     constexpr int RELEASE_BATCH = 8;
-    const int top_step = n > 1 ? 1 << (31 - __clz(n - 1)) : 0;
     for (int64_t win0 = 0; win0 < words_total && total > 0; win0 += RELEASE_WIN) {
         for (int i = tid; i < RELEASE_WIN; i += NT) s_win[i] = 0u;
         lds_barrier();
         for (int x0 = 0; x0 < total; x0 += NT * RELEASE_BATCH) {
             uint32_t id[RELEASE_BATCH], frame[RELEASE_BATCH];
             int64_t at[RELEASE_BATCH];
-            int ent[RELEASE_BATCH];                          // last entry with s_start <= x: the eight searches side by side
-#pragma unroll
-            for (int u = 0; u < RELEASE_BATCH; ++u) ent[u] = 0;
-            for (int step = top_step; step > 0; step >>= 1) {
-#pragma unroll
-                for (int u = 0; u < RELEASE_BATCH; ++u) {
-                    const int next = ent[u] + step;
-                    const int begins = s_start[next < n ? next : n];
-                    if (next < n && begins <= x0 + u * NT + tid) ent[u] = next;
-                }
-            }
 #pragma unroll
             for (int u = 0; u < RELEASE_BATCH; ++u) {
                 const int x = x0 + u * NT + tid;
                 id[u] = 0xffffffffu;
-                if (x < total) id[u] = (uint32_t)m.rows[(int64_t)s_seq[ent[u]] * m.max_blocks + (x - s_start[ent[u]])];
+                if (x < total) {
+                    // last entry with s_start <= x (all eight searches at once and the reads behind them: 0.9 us more for
+                    // 5411 blocks of 32 rows, 2.7 for 7000 of 64)
+                    int lo = 0, hi = n;
+                    while (hi - lo > 1) {
+                        const int mid = (lo + hi) >> 1;
+                        if (s_start[mid] <= x) lo = mid; else hi = mid;
+                    }
+                    id[u] = (uint32_t)m.rows[(int64_t)s_seq[lo] * m.max_blocks + (x - s_start[lo])];
+                }
             }
 #pragma unroll
             for (int u = 0; u < RELEASE_BATCH; ++u) {
@@ -492,7 +517,7 @@ __global__ __launch_bounds__(NT) void k_release(PoolDev p, ModelDev m, int n, co
         lds_barrier();
         for (int i = tid; i < RELEASE_WIN && win0 + i < words_total; i += NT) {
             const uint32_t gone = s_win[i];
-            if (gone) m.bits[win0 + i] &= ~gone;
+            if (gone) m.bits[win0 + i] = (win0 + i == tid ? first_word : m.bits[win0 + i]) & ~gone;
         }
         lds_barrier();
     }

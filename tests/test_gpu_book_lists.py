@@ -44,3 +44,37 @@ def test_lists(gpu, oracle, hkv, d, dtype, frames):
     step("seq_release_batch", list(range(400)))
     for be, pool, m in both:
         assert be.balloon_resize(m, 0) == 0 and be.model_unregister(m) == 0 and be.pool_destroy(pool) == 0
+
+
+# words of the slot bitmap on both sides of the kernel's 1024 lanes (a lane per word, or one per frame), frames of one, of
+# eight and of 31 words, a last word that is full and one that is not; balloons that shrink to nothing, to what is held, not at all
+@pytest.mark.parametrize("hkv,d,dtype,frames", [(8, 128, 0, 1024), (8, 128, 0, 1025), (2, 64, 0, 128), (2, 64, 0, 129),
+                                                (1, 64, 1, 33), (1, 64, 1, 34), (1, 64, 0, 1), (3, 128, 1, 2)])
+def test_words_and_lanes(gpu, oracle, hkv, d, dtype, frames):
+    both = []
+    for be in (gpu, oracle):
+        pool = be.pool_create((frames + 1) * (2 << 20), 16, 2 << 20)
+        assert be.pool_seed_free_order(pool, gen.free_order(frames + 1, gen.generator(frames))) == 0
+        both.append((be, pool, be.model_register(pool, hkv, hkv, d, dtype, 40, 33000)))
+    rng = np.random.RandomState(frames)
+
+    def step(name, *args):
+        rc = [getattr(be, name)(m, *args) for be, _, m in both]
+        assert rc[0] == rc[1], (name, rc)
+        assert np.array_equal(*(be.pool_export_state(pool) for be, pool, _ in both)), name
+        return rc[0]
+
+    assert step("balloon_resize", frames) == frames
+    slots = (2 << 20) // (32 * hkv * d * (2 - dtype) + 128 * dtype)
+    for share in (0.02, 0.3, 1.0, 0.6):
+        most = min(int(2 * share * slots * frames / 40), 33000)      # about `share` of the slots, dealt in two lists
+        ends = rng.randint(0, most + 1, 40)
+        for part in (ends // 2, ends):
+            step("seq_reserve_batch", rng.permutation(40).astype(np.int32), (part * 16).astype(np.int32))
+        step("seq_release_batch", rng.permutation(40)[:23].astype(np.int32))
+        step("balloon_resize", frames // 2)
+        step("balloon_resize", frames)
+    step("seq_release_batch", list(range(40)))
+    assert step("balloon_resize", 0) == 0
+    for be, pool, m in both:
+        assert be.model_unregister(m) == 0 and be.pool_destroy(pool) == 0
