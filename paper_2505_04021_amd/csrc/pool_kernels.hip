@@ -449,7 +449,8 @@ __global__ __launch_bounds__(NT) void k_release(PoolDev p, ModelDev m, int n, co
     const int tid = threadIdx.x;
     for (int i = tid; i < PKV_MAX_SEQS / 32; i += NT) s_seen[i] = 0u;
     const int64_t words_total = m.counters[0] * m.wpf, spare = m.counters[1];
-    const uint32_t first_word = tid < p.n_frames * m.wpf ? m.bits[tid] : 0u;       // (also of a frame the model does not own: not looked at then)
+    // (also where no frame of the model's lies: not looked at then)
+    const uint32_t first_word = tid < p.n_frames * m.wpf ? m.bits[tid] : 0u;
     __syncthreads();
     int total = 0;
     for (int c0 = 0; c0 < n; c0 += NT) {
