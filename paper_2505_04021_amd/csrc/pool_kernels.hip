@@ -178,7 +178,7 @@ __device__ inline void deflate_body(const PoolDev &p, const ModelDev &m, int64_t
 // balloon_resize: the direction is decided here, from the device's own count of owned frames, so
 // that a caller can enqueue the call without knowing how earlier enqueued calls ended.  All counts are asked for at once, for
 // both directions; a deflate reads frames along with their words and compacts only if something stays (us: inflate of 170 frames
-// 2.4 -> 2.2, deflate of as many that are all empty 4.9 -> 3.1).
+// 2.4 -> 2.2, deflate of as many that are all empty 4.2 -> 3.1).
 __global__ __launch_bounds__(NT) void k_resize(PoolDev p, ModelDev m, int64_t target, BookResult *res, uint32_t *err) {
     __shared__ int s_wave[NW];
     const int64_t owned = m.counters[0], spare = m.counters[1], n_free = *p.n_free;          // uniform: every lane takes the same branch
@@ -204,15 +204,15 @@ __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, co
     __shared__ int s_cur[PKV_MAX_SEQS];             // row lengths: as the call finds them, then with its wants
     __shared__ int s_start[PKV_MAX_BATCH_OPS + 1];  // first rank of entry i
     __shared__ uint32_t s_ent[PKV_MAX_BATCH_OPS];   // entry i: sequence << 20 | row length before the entry
-    __shared__ uint32_t s_free[NT], s_fid[NT];      // placement: free bits of unit j's current word, the block id of its slot 0
+    __shared__ uint32_t s_free[NT], s_id[NT];       // placement: free bits of word j of the turn, the block id of its slot 0
     __shared__ int s_rank[NT];                      // placement: rank of the first free slot of that word
     __shared__ uint32_t s_blk[RESERVE_WIN];         // placement: the blocks of a window of ranks
     __shared__ int s_fail;
     const int tid = threadIdx.x;
     // Everything the kernel will read is asked for here, before the first answer is needed: the list
-    // (host memory, the longest trip), the rows' lengths, the counters and the lane's own frame of the
-    // first pass of the placement.  The call then costs one such trip instead of five in a row.
-    constexpr int CHUNKS = PKV_MAX_BATCH_OPS / NT, PRE_WORDS = 4;
+    // (host memory, the longest trip), the rows' lengths, the counters and the lane's own word of the
+    // first turn of the placement.  The call then costs one such trip instead of five in a row.
+    constexpr int CHUNKS = PKV_MAX_BATCH_OPS / NT;
     int o_seq[CHUNKS], o_ctx[CHUNKS], o_ear[CHUNKS];
 #pragma unroll
     for (int c = 0; c < CHUNKS; ++c) {
@@ -223,14 +223,10 @@ __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, co
     }
     const int64_t owned = m.counters[0], spare = m.counters[1];
     const int wpf = m.wpf, slots = m.slots;
-    uint32_t pre_bits[PRE_WORDS];
-    // (list positions the model does not own yet are read too, and never looked at: the address then does
+    // (words and list positions that the model does not own yet are read too, and never looked at: the addresses then do
     // not wait for the count of owned frames to arrive)
-#pragma unroll
-    for (int w = 0; w < PRE_WORDS; ++w) pre_bits[w] = (tid < p.n_frames && w < wpf) ? m.bits[(int64_t)tid * wpf + w] : 0u;
-    uint32_t pre_frame = tid < p.n_frames ? m.frames[tid] : 0u;
-    const int flat_frame = (int)fastdiv_div((uint32_t)tid, m.wpf_div);       // (word `tid` of the bitmap, for the flat split below)
-    const uint32_t flat_bits = flat_frame < p.n_frames ? m.bits[tid] : 0u, flat_id = flat_frame < p.n_frames ? m.frames[flat_frame] : 0u;
+    const uint32_t first_frame = fastdiv_div((uint32_t)tid, m.wpf_div);
+    const uint32_t first_word = first_frame < p.n_frames ? m.bits[tid] : 0u, first_id = first_frame < p.n_frames ? m.frames[first_frame] : 0u;
     for (int s = tid; s < m.max_seqs; s += NT) s_cur[s] = m.row_len[s];
     if (tid == 0) s_fail = 0x7fffffff;
     __syncthreads();
@@ -295,134 +291,87 @@ __global__ __launch_bounds__(NT) void k_reserve(PoolDev p, ModelDev m, int n, co
         return;
     }
     // Placement.  Free slots are ranked in frame-list order, ascending slot inside a frame; rank r goes to
-    // the entry e with s_start[e] <= r < s_start[e + 1].  A lane per frame counts the frame's free slots (a
-    // prefix sum gives the rank of its first one) and publishes one 32-slot word at a time; then a lane per
-    // (frame, slot) of that word takes over: a free slot knows its rank from the bits below it and puts its block id
-    // there, in LDS.  The entries then copy their ranks into their rows, `group` lanes each (a search for the entry of
-    // every slot took 4 of this kernel's 13 us).  The frame's lane sets the bits that were taken.
-    // A model whose bitmap has no more words than the work-group lanes gets a lane per word instead: one turn, where small
-    // blocks (8/2/64 bf16: 256 slots a frame) take eight, two barriers each, with most lanes idle (us: an admission
-    // of 64 rows around 1500 tokens of that model 22.3 -> 15.1, of three around 118 of 2/1/64, 16 words, 14.2 -> 8.0).  With more words than
-    // lanes that would be a turn, with its scan and its trip to memory, for every 1024 words passed over: they stay with the frames.
+    // the entry e with s_start[e] <= r < s_start[e + 1].  A lane per 32-slot word of the bitmap counts the word's free slots (a
+    // prefix sum gives the rank of its first one) and publishes it; then a lane per (word, slot) takes over: a free slot knows
+    // its rank from the bits below it and puts its block id there, in LDS.  The entries then copy their ranks into their rows,
+    // `group` lanes each (a search for the entry of every slot took 4 of this kernel's 13 us).  The word's lane sets the bits
+    // that were taken.
+    // A turn is 1024 words.  A lane per frame instead, one word of the frame after the other, leaves most lanes idle and takes
+    // two barriers a word: slower for every model, also where turns are many and a list is short.  Us of a release and a reserve
+    // of all rows, and of one row at the far end of the list, a lane per frame and so: 39 frames of 31 words 146 -> 78 and
+    // 34 -> 13; 462 of 8 572 -> 382 and 29 -> 15; 8339 of 2 3821 -> 3359 and 28 -> 26; 137 of one 18.2 -> 16.8 and 13.0 -> 12.0.
+    // Four look-ups are on the way at a time while all four are live (dead ones among them: 151 us of this kernel for the
+    // first model, where one at a time takes 98).  Reading a turn's words ahead of the turn before made it 2 to 8 % slower.
     int group = 4;
     while (group < NT && group * 2 * n <= NT) group *= 2;
     const int sub = tid & (group - 1);
     int running = 0;
-    const bool flat = owned * wpf <= NT;
-    const int per = flat ? 1 : wpf;                          // words of a lane's unit (a word, or a frame)
-    const int64_t units = flat ? owned * wpf : owned;
-    if (flat) {
-        pre_bits[0] = flat_bits;
-        pre_frame = flat_id;
-    }
-    auto first_slot = [&](int w) { return 32 * (flat ? tid - flat_frame * wpf : w); };
-    for (int64_t base = 0; base < units && running < total; base += NT) {
+    const int64_t words = owned * wpf;
+    for (int64_t base = 0; base < words && running < total; base += NT) {
         const int64_t i = base + tid;
-        const bool pre = base == 0 && per <= PRE_WORDS;      // this pass's words are already here
-        auto word_of = [&](int w) {
-            uint32_t word = 0u;
-            if (pre) {
-#pragma unroll
-                for (int k = 0; k < PRE_WORDS; ++k)
-                    if (k == w) word = pre_bits[k];
-            } else {
-                word = m.bits[i * per + w];
-            }
-            return word;
-        };
-        auto valid_of = [&](int w) {
-            const int nb = slots - first_slot(w);
-            return nb >= 32 ? 0xffffffffu : ((1u << nb) - 1u);
-        };
-        int zeros = 0;
-        if (i < units)
-            for (int w = 0; w < per; ++w) zeros += __popc(~word_of(w) & valid_of(w));
-        int chunk_total;
-        const int rank0 = running + block_excl_scan(zeros, chunk_total, s_wave);    // rank of this unit's first free slot
-        const uint32_t f = i < units ? (base == 0 ? pre_frame : m.frames[i]) : 0u;
-        const int nu = (int)(units - base < NT ? units - base : NT);
-        const int pass_end = running + chunk_total < total ? running + chunk_total : total;
-        for (int win0 = running; win0 < pass_end; win0 += RESERVE_WIN) {
-            const int win1 = win0 + RESERVE_WIN < pass_end ? win0 + RESERVE_WIN : pass_end;
-            // four look-ups on the way at a time, where there is work for that
-            auto place = [&](auto count) __attribute__((always_inline)) {
+        const uint32_t frame = fastdiv_div((uint32_t)i, m.wpf_div);
+        const uint32_t word = base == 0 ? first_word : i < words ? m.bits[i] : 0u;
+        const uint32_t f = base == 0 ? first_id : i < words ? m.frames[frame] : 0u;
+        const int first_slot = 32 * (int)((uint32_t)i - frame * (uint32_t)wpf), nb = slots - first_slot;
+        const uint32_t freeb = i < words ? ~word & (nb >= 32 ? 0xffffffffu : (1u << nb) - 1u) : 0u;
+        const int zeros = __popc(freeb);
+        int turn_total;
+        const int rank0 = running + block_excl_scan(zeros, turn_total, s_wave);     // rank of this word's first free slot
+        if (turn_total == 0) continue;                       // (uniform)
+        s_free[tid] = freeb;
+        s_rank[tid] = rank0;
+        s_id[tid] = f * (uint32_t)slots + (uint32_t)first_slot;
+        lds_barrier();
+        const int lookups = 32 * (int)(words - base < NT ? words - base : NT);
+        const int turn_end = running + turn_total < total ? running + turn_total : total;
+        for (int win0 = running; win0 < turn_end; win0 += RESERVE_WIN) {
+            const int win1 = win0 + RESERVE_WIN < turn_end ? win0 + RESERVE_WIN : turn_end;
+            auto place = [&](int idx, auto count) __attribute__((always_inline)) {       // look-ups idx, idx + NT, ...
                 constexpr int N = decltype(count)::value;
-                for (int idx0 = tid; idx0 < nu * 32; idx0 += N * NT) {
-                    uint32_t fr[N], id[N];
-                    int first[N];
+                uint32_t fr[N], id[N];
+                int first[N];
 #pragma unroll
-                    for (int u = 0; u < N; ++u) {
-                        const int j = (idx0 + u * NT) >> 5, in = j < nu ? j : nu - 1;
-                        fr[u] = j < nu ? s_free[in] : 0u;
-                        first[u] = s_rank[in];
-                        id[u] = s_fid[in];
-                    }
-                    const int bit = idx0 & 31;
+                for (int u = 0; u < N; ++u) {
+                    const int j = (idx + u * NT) >> 5;
+                    fr[u] = s_free[j];
+                    first[u] = s_rank[j];
+                    id[u] = s_id[j];
+                }
+                const int bit = idx & 31;
 #pragma unroll
-                    for (int u = 0; u < N; ++u) {
-                        const int r = first[u] + __popc(fr[u] & ((1u << bit) - 1u));
-                        if (((fr[u] >> bit) & 1u) && r >= win0 && r < win1) s_blk[r - win0] = id[u] + (uint32_t)bit;
-                    }
+                for (int u = 0; u < N; ++u) {
+                    const int r = first[u] + __popc(fr[u] & ((1u << bit) - 1u));
+                    if (((fr[u] >> bit) & 1u) && r >= win0 && r < win1) s_blk[r - win0] = id[u] + (uint32_t)bit;
                 }
             };
-            auto hand_out = [&](auto count) __attribute__((always_inline)) {
-                constexpr int N = decltype(count)::value;
-                for (int e0 = tid / group; e0 < n; e0 += N * (NT / group)) {
-                    int st[N], en[N];
-                    uint32_t ent[N];
-#pragma unroll
-                    for (int u = 0; u < N; ++u) {
-                        const int e = e0 + u * (NT / group), in = e < n ? e : n - 1;
-                        st[u] = s_start[in];
-                        en[u] = e < n ? s_start[in + 1] : st[u];
-                        ent[u] = s_ent[in];
-                    }
-#pragma unroll
-                    for (int u = 0; u < N; ++u) {
-                        const int lo = st[u] > win0 ? st[u] : win0, hi = en[u] < win1 ? en[u] : win1;
-                        int32_t *row = m.rows + (int64_t)(ent[u] >> 20) * m.max_blocks + (ent[u] & 0xfffffu);
-                        for (int r = lo + sub; r < hi; r += group) row[r - st[u]] = (int32_t)s_blk[r - win0];
-                    }
-                }
-            };
-            using One = std::integral_constant<int, 1>;
-            using Four = std::integral_constant<int, 4>;
-            int rank = rank0;
-            for (int w = 0; w < per; ++w) {
-                const uint32_t freeb = i < units && zeros && rank < win1 ? ~word_of(w) & valid_of(w) : 0u;
-                s_free[tid] = freeb;
-                s_rank[tid] = rank;
-                s_fid[tid] = f * (uint32_t)slots + (uint32_t)first_slot(w);
-                rank += __popc(freeb);
-                lds_barrier();
-                if (nu * 32 <= NT) place(One{});
-                else place(Four{});
-                lds_barrier();
+            int from = 0;
+            for (; from + 4 * NT <= lookups; from += 4 * NT) place(from + tid, std::integral_constant<int, 4>{});
+            for (; from + tid < lookups; from += NT) place(from + tid, std::integral_constant<int, 1>{});
+            lds_barrier();
+            for (int e = tid / group; e < n; e += NT / group) {
+                const int st = s_start[e], en = s_start[e + 1];
+                const int lo = st > win0 ? st : win0, hi = en < win1 ? en : win1;
+                if (lo >= hi) continue;
+                const uint32_t ent = s_ent[e];
+                int32_t *row = m.rows + (int64_t)(ent >> 20) * m.max_blocks + (ent & 0xfffffu);
+                for (int r = lo + sub; r < hi; r += group) row[r - st] = (int32_t)s_blk[r - win0];
             }
-            if (n * group <= NT) hand_out(One{});
-            else hand_out(Four{});
             lds_barrier();
         }
-        int rank = rank0;
-        if (i < units && zeros)
-            for (int w = 0; w < per && rank < total; ++w) {
-                const uint32_t word = word_of(w), freeb = ~word & valid_of(w);
-                const int c = __popc(freeb);
-                int take = total - rank;
-                take = take > c ? c : take;
-                uint32_t mask = freeb;                   // the lowest `take` free bits
-                if (take < c) {
-                    mask = 0u;
-                    uint32_t rest = freeb;
-                    for (int k = 0; k < take; ++k) {
-                        mask |= rest & (0u - rest);
-                        rest &= rest - 1u;
-                    }
+        if (zeros && rank0 < total) {
+            const int take = total - rank0;
+            uint32_t mask = freeb;                           // the lowest `take` free bits
+            if (take < zeros) {
+                mask = 0u;
+                uint32_t rest = freeb;
+                for (int k = 0; k < take; ++k) {
+                    mask |= rest & (0u - rest);
+                    rest &= rest - 1u;
                 }
-                if (mask) m.bits[i * per + w] = word | mask;
-                rank += c;
             }
-        running += chunk_total;
+            m.bits[i] = word | mask;
+        }
+        running += turn_total;
     }
     __syncthreads();
     for (int s = tid; s < m.max_seqs; s += NT) m.row_len[s] = s_cur[s];
