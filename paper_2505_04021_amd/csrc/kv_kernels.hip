@@ -337,9 +337,11 @@ __device__ __forceinline__ uint32_t encode4(float a, float b, float c, float d, 
 // alone as long as code and outcome are normal numbers: both roundings are to a relative step, whatever the exponent.  The
 // code then falls by a number of steps that a table of eight bytes holds (lo: mantissas 0 to 3, hi: 4 to 7), and two raises
 // one after the other are one table again.  Four codes at a time, one byte permute.  A byte of `fit` keeps its sign bit
-// where the outcome is normal.
+// where the outcome is normal.  With at most 60 steps an entry no byte borrows from the next one; entries above that are
+// possible, and then neither result counts: the lane's `far` has been set when the first entry passed 60, stays set, and has all
+// its words looked at again.
 __device__ __forceinline__ uint32_t lower_codes(uint32_t w, uint32_t lo, uint32_t hi, uint32_t &fit) {
-    const uint32_t y = (w | SIGNS) - __builtin_amdgcn_perm(hi, lo, w & 0x07070707u);      // steps are at most 60: no byte borrows
+    const uint32_t y = (w | SIGNS) - __builtin_amdgcn_perm(hi, lo, w & 0x07070707u);
     fit &= y - 0x08080808u;
     return (y & ~SIGNS) | (w & SIGNS);
 }
@@ -349,11 +351,20 @@ __device__ __forceinline__ uint32_t lower_codes(uint32_t w, uint32_t lo, uint32_
 // prefix maximum; a token is encoded under the scale of its own step and then re-encoded at every later step that raises
 // the scale (for 16 like tokens between two and three times), by the table of those raises taken together (lower_codes):
 // each lane works two entries of its token's table out with the divisions that define it.  Codes that a table does not
-// cover (zeros and subnormals, one in some ten thousand, and raises by more than 2^7) are re-encoded step by step.
+// cover (zeros, subnormals, and raises by more than 2^7) are looked at again: of N(0, 1) values one in some ten thousand,
+// of rectified or sparse rows, rows with a channel far above the others or tokens that keep growing a good part.  Where few lanes
+// hold such codes, the words that do are re-encoded raise by raise.  Where more do, zeros are put back first (no raise changes
+// them) and the words left go together, raise by raise: each by itself they are a chain of divisions, which with the table's work
+// made such rows slower than no table at all.  8 x 512 tokens of 8 heads x 128, us a call, without a table, each word by itself,
+// so: N(0, 1) 25.3, 10.0, 10.1; one channel x 100 26.3, 20.8, 19.7; rectified 24.5, 25.1, 10.6; one value in ten 22.6, 25.7, 10.2;
+// each token sqrt 2 times the one before 54.4, 58.2, 50.1; lognormal magnitudes (sigma 1.5) 25.6, 24.4, 22.8.  With all lanes put
+// on the second way N(0, 1) takes 10.3; with 8 and 16 lanes as the line rectified rows take 13.4 and 15.3.
 // Bound by memory trips and vector instructions alike: 8 x 512 tokens of 8 heads x 128, K and V, us a call: 65 with the
 // tokens one after the other, a wave maximum through LDS and two divisions an element each; 22.8 with every raise worked
 // out code by code and quotients between two products (1315 vector instructions a wave, half of them for quotients that fall
 // on the border of two codes, as two of three waves hold some); 10.0 so (517).
+constexpr int FEW_LANES = 4;
+
 template <int D, bool IS_V, typename TILE_OF>
 __device__ __forceinline__ void page_quantise(const TILE_OF &tile_of, const PageRows &p) {
     constexpr int NW = D / 16;                           // words of codes per lane
@@ -484,23 +495,47 @@ __device__ __forceinline__ void page_quantise(const TILE_OF &tile_of, const Page
             low[i] = lower_codes(w[i], lo, hi, fit);
             nan |= nan_codes(w[i]);
         }
-        auto uncovered = [&](uint32_t f, uint32_t n) __attribute__((always_inline)) { return __any(lowered && ((far | n | ~f) & SIGNS) != 0u); };
-        if (uncovered(fit, nan)) {
+        auto uncovered = [&](uint32_t f, uint32_t n) __attribute__((always_inline)) { return __ballot(lowered && ((far | n | ~f) & SIGNS) != 0u); };
+        auto each_raise = [&](const auto &f) __attribute__((always_inline)) {
+            for (uint32_t rest = events; rest; rest &= rest - 1u) {
+                const int u = __ffs((int)rest) - 1;
+                f(u, of_lane(before, u), divisor(of_lane(scale, u)));
+            }
+        };
+        auto again = [&](uint32_t x, int u, float was, const Divisor &now) __attribute__((always_inline)) {
+            const f32x2 l2 = __builtin_amdgcn_cvt_pk_f32_fp8((int)x, false), h2 = __builtin_amdgcn_cvt_pk_f32_fp8((int)x, true);
+            const uint32_t z = encode4(__fmul_rn(l2[0], was), __fmul_rn(l2[1], was), __fmul_rn(h2[0], was), __fmul_rn(h2[1], was), now);
+            return t < u ? z : x;
+        };
+        const uint64_t missed = uncovered(fit, nan);
+        if (missed != 0u && __popcll(missed) < FEW_LANES) {
 #pragma unroll
             for (int i = 0; i < NW; ++i) {
-                uint32_t f = SIGNS, again = w[i];
+                uint32_t f = SIGNS;
                 (void)lower_codes(w[i], lo, hi, f);
-                if (!uncovered(f, nan_codes(w[i]))) continue;
-                for (uint32_t rest = events; rest; rest &= rest - 1u) {
-                    const int u = __ffs((int)rest) - 1;
-                    const float was = of_lane(before, u);
-                    const Divisor now = divisor(of_lane(scale, u));
-                    const f32x2 l2 = __builtin_amdgcn_cvt_pk_f32_fp8((int)again, false), h2 = __builtin_amdgcn_cvt_pk_f32_fp8((int)again, true);
-                    const uint32_t z = encode4(__fmul_rn(l2[0], was), __fmul_rn(l2[1], was), __fmul_rn(h2[0], was), __fmul_rn(h2[1], was), now);
-                    again = t < u ? z : again;
-                }
-                low[i] = again;
+                if (uncovered(f, nan_codes(w[i])) == 0u) continue;
+                low[i] = w[i];
+                each_raise([&](int u, float was, const Divisor &now) __attribute__((always_inline)) { low[i] = again(low[i], u, was, now); });
             }
+        } else if (missed != 0u) {
+            uint32_t todo = 0u;
+#pragma unroll
+            for (int i = 0; i < NW; ++i) {
+                const uint32_t zero = ~((w[i] & ~SIGNS) + 0x7f7f7f7fu) & SIGNS, same = (zero >> 7) * 0xffu;
+                uint32_t f = SIGNS;
+                (void)lower_codes(w[i], lo, hi, f);
+                low[i] = (low[i] & ~same) | (w[i] & same);
+                if (uncovered(f | zero, nan_codes(w[i])) != 0u) {
+                    low[i] = w[i];
+                    todo |= 1u << i;
+                }
+            }
+            if (todo)
+                each_raise([&](int u, float was, const Divisor &now) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int i = 0; i < NW; ++i)
+                        if (todo >> i & 1u) low[i] = again(low[i], u, was, now);
+                });
         }
 #pragma unroll
         for (int i = 0; i < NW; ++i) w[i] = low[i];
