@@ -54,7 +54,85 @@ def test_table_of_raises(spread):
         assert np.array_equal(got[ok], want[ok])
         assert (want[~ok] <= 8).all()                     # nothing that stays normal goes unseen
         covered += int(ok.sum())
-    assert covered > 300
+    assert covered > 9000                                 # 9890 to 33300
+
+
+SIGNS = np.uint32(0x80808080)
+
+
+def u32(x):
+    return np.asarray(x & 0xffffffff, dtype=np.uint64).astype(np.uint32)
+
+
+def bytes_of(w):
+    return [w >> np.uint32(8 * k) & np.uint32(255) for k in range(4)]
+
+
+def word_of(parts):
+    out = np.uint32(0)
+    for k, p in enumerate(parts):
+        out = out | np.asarray(p, dtype=np.uint32) << np.uint32(8 * k)
+    return out
+
+
+def perm(hi, lo, select):
+    """v_perm_b32 for selectors 0 to 7: byte s of the eight bytes hi:lo."""
+    table = bytes_of(np.uint32(lo)) + bytes_of(np.uint32(hi))
+    return word_of([np.choose(b.astype(np.int64), table) for b in bytes_of(select)])
+
+
+def plus(a, b):
+    return u32(np.uint64(a) + np.uint64(b))
+
+
+def minus(a, b):
+    return u32(np.uint64(a) + np.uint64(1 << 32) - np.uint64(b))
+
+
+@pytest.mark.parametrize("spread", [0.02, 0.5, 3.0, 6.0, 40.0])
+def test_packed_words_and_tables(spread):
+    """The same in the words that the kernel computes with: entries above 60 steps make bytes borrow and carry, and `far`
+    has to tell of every such lane; words that are not called uncovered hold the codes of re-encoding raise by raise."""
+    rng = np.random.RandomState(int(spread * 100) + 1)
+    words = far_chains = 0
+    for _ in range(400):
+        n = rng.randint(2, 17)
+        scales = np.sort(np.exp(rng.uniform(0, spread, n)).astype(F) * F(2.0) ** rng.randint(-50, 30))
+        codes = rng.randint(0, 256, (4, 64)).astype(np.int64)
+        codes[:, ::5] &= 0x80                             # zeros of both signs
+        codes[0, 1::5] &= 0x87                            # subnormals
+        want, lo, hi, far, sums = codes & 127, np.uint32(0), np.uint32(0), np.uint32(0), np.zeros(8, dtype=np.int64)
+        passed = False
+        nan = (want == 127).any(axis=0)
+        for s, r in zip(scales, scales[1:]):
+            if not r > s:
+                continue
+            want = raised(np.minimum(want, 126), s, r)
+            steps = 0x70 + np.arange(8) - raised(0x70 + np.arange(8), s, r)
+            steps = np.where((steps > 60) | (steps < 0), 127, steps)
+            sums = sums + steps[(np.arange(8) - sums) & 7]
+            passed = passed or bool((sums > 60).any())
+            d0, d1 = word_of(steps[:4]), word_of(steps[4:])
+            lo, hi = (plus(t, perm(d1, d0, minus(first, t) & np.uint32(0x07070707))) for t, first in ((lo, 0x83828180), (hi, 0x87868584)))
+            far = far | plus(lo, 0x43434343) | plus(hi, 0x43434343)
+        assert bool(far & SIGNS) == passed                # once set it stays, and it is never set without need
+        far_chains += passed
+        w = word_of(codes)
+        y = minus(w | SIGNS, perm(hi, lo, w & np.uint32(0x07070707)))
+        fit = minus(y, 0x08080808)
+        low = (y & ~SIGNS) | (w & SIGNS)
+        zero = ~plus(w & ~SIGNS, 0x7f7f7f7f) & SIGNS
+        same = u32(np.uint64(zero >> np.uint32(7)) * np.uint64(255))
+        assert np.array_equal((plus(w & ~SIGNS, 0x01010101) & SIGNS) != 0, nan)
+        if passed:
+            continue
+        again = word_of(want | (codes & 128))
+        for out, ok in ((low, (fit & SIGNS) == SIGNS), ((low & ~same) | (w & same), ((fit | zero) & SIGNS) == SIGNS)):
+            ok = ok & ~nan
+            assert np.array_equal(out[ok], again[ok])
+            words += int(ok.sum())
+    assert words > 7000 or spread > 3.0
+    assert far_chains > 100 or spread <= 3.0
 
 
 def exponent(x):
