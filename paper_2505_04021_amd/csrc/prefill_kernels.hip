@@ -394,21 +394,28 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
                 acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_op(dt, k), as_bf16x8(p[k]), acc[dt], 0, 0, 0);
     };
 
+    // 128-wide heads, two work-groups a CU: issue favours the older of the two waves of a SIMD.  Of the 512 work-groups of 512
+    // tokens behind 15872 of 64/8/128, which all start together, half end within 236 to 291 us and half within 291 to 349, alone
+    // from then on.  So a wave steps down one priority level per quarter of its pairs, and whichever work-group is behind is
+    // favoured: they end within 286 to 343.  Us without and with: that pass 361.1, 358.1; 8 x (2048 + 512) of 32/8/128 bf16 223.8,
+    // 222.3, e4m3 183.0, 181.2; 8 x (1024 + 512) 136.2, 133.8 and 118.3, 112.9; launches of few work-groups lose 1 to 2 %
+    // (2 x (768 + 256) 29.3, 29.9).  64-wide heads have three work-groups a CU, which even out by themselves: they go without
+    // (8 x (1024 + 512) of 32/8/64 bf16 86.5, 95.8, e4m3 80.3, 90.2).  A decode step of another model on a stream beside it takes as
+    // long either way (16 x 2048 beside 8 x (2048 + 512) 218.5, 217.0; 4 x 300 beside 1 x (3968 + 128) 15.9, 15.5).
+    // (the waves meet in even steps; a walk of less than eight pairs may end above level 0)
+    constexpr bool LEVELS = D == 128;
+    const int quarter = (np / 4 + 1) & ~1, half = (np / 2 + 1) & ~1, three_quarters = (3 * np / 4 + 1) & ~1;
+    if constexpr (LEVELS) __builtin_amdgcn_s_setprio(3);
+
     // the meeting point of the steps r and r + 1 (r even), in the middle of step r: all requests under way have
     // landed; behind it K of pairs r + 2, r + 3 and V of pairs r + 1, r + 2 are visible to all waves, and the slots
     // of K r, r + 1 and V r - 1, r take the pairs PF_SLOTS ahead of them
-    // Issue favours the older of the two waves of a SIMD: of two work-groups that share a CU from the start one was done after
-    // 265 us and the other, alone from then on, after 375, and a wave alone turns over an eighth less than two together.
-    // So a wave steps down one priority level per quarter of its pairs, and whichever work-group is behind is favoured
-    // (us a pass, without and with: 512 behind 15872 of 64/8/128 351.8, 345.7; 8 x (2048 + 512) of 32/8/128 bf16 218.7, 216.1,
-    // e4m3 185.3, 178.6; short prompts 68.1, 68.2).
-    // (the waves meet in even steps)
-    const int quarter = (np / 4 + 1) & ~1, half = (np / 2 + 1) & ~1, three_quarters = (3 * np / 4 + 1) & ~1;
-    __builtin_amdgcn_s_setprio(3);
     auto meet = [&](int r) __attribute__((always_inline)) {
-        if (r == quarter) __builtin_amdgcn_s_setprio(2);
-        if (r == half) __builtin_amdgcn_s_setprio(1);
-        if (r == three_quarters) __builtin_amdgcn_s_setprio(0);
+        if constexpr (LEVELS) {
+            if (r == quarter) __builtin_amdgcn_s_setprio(2);
+            if (r == half) __builtin_amdgcn_s_setprio(1);
+            if (r == three_quarters) __builtin_amdgcn_s_setprio(0);
+        }
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         const int next = r + PF_SLOTS - (is_v ? 1 : 0);

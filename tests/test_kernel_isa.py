@@ -89,3 +89,13 @@ def test_prefill_steps_wait_only_where_written():
                 assert len(full) <= (3 if dtype == 0 else 5), (name, full)
             vg = [int(x) for x in re.findall(r"\.name:\s+\S*" + name + r"\S*\s*\n(?:.*\n){0,40}?\s+\.vgpr_count:\s+(\d+)", asm)]
             assert vg and max(vg) <= 256, (name, vg)
+
+
+def test_prefill_steps_down_only_where_two_work_groups_share_a_cu():
+    """Priority levels help the two work-groups a CU has on 128-wide heads; the three of 64-wide heads lost up to a tenth."""
+    asm = device_assembly("prefill_kernels.hip")
+    for seqs in (127, 447):
+        for d, dtype in ((128, 0), (64, 0), (128, 1), (64, 1)):
+            insn, _, _ = kernel_body(asm, f"9k_prefillILi{d}ELi{dtype}ELi{seqs}E")
+            levels = {t.split()[1] for t in insn if t.startswith("s_setprio")}
+            assert levels == ({"0", "1", "2", "3"} if d == 128 else set()), (d, dtype, levels)
