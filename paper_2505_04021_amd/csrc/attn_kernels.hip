@@ -972,8 +972,10 @@ __device__ __forceinline__ void attn_part(const AttnDesc &d, int wg, float *s_ac
     if (*s_arrived != (uint32_t)(n_parts - 1)) return;
     if (threadIdx.x == 0) d.cnt[seg] = 0u;                // ready for the next launch
     const float *base = d.ws + (size_t)seg * d.parts * pf;
-    // All maxima and sums travel together with the sums of the first eight parts (one trip to uncached memory, 1 us, instead
-    // of two: eight lognormal rows of 2048 tokens, where 56 of 64 rows are joined, 0.3 us a launch).
+    // All maxima and sums travel together with the sums of the first eight parts: one trip to uncached memory instead of two.
+    // Us a launch, rows in many parts: 1 x 32000 tokens of 8/1/128 17.5 -> 15.4, 1 x 12000 of 64/8/128 14.6 -> 13.6, 3 x 6000 of
+    // 28/4/128 12.6 -> 12.0, 2 x 9000 of 32/8/128 e4m3 15.7 -> 15.2; with its append 8 x 2048 of 32/8/128 16.8 -> 16.4; rows in one
+    // part (4 x 128 of 8/2/64) the same.  (The read is there twice, 7 KB more over all variants.)
     auto part_sums = [&](f32x4 *v, int c0, int hn, int x) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < 8; ++u)

@@ -32,22 +32,19 @@ __device__ __forceinline__ size_t v_elem_off(int t, int dd) {
     return ((size_t)((jq * 4 + G) * 16 + dl)) * 16 + u * 4 + e;
 }
 
-// Has all of a model's descriptor (kernel arguments) asked for here, in one go.  Left to itself the compiler reads a few
+// Has what every wave uses of a model's descriptor (kernel arguments) asked for here, in one go.  Left to itself the compiler reads a few
 // arguments where they are first used, each time a cache line that has not been read before, one memory trip after the
 // other in front of the kernel's own: a chunk append waited ten times in a row for its first rows, so three times.  With
 // the rows asked for ahead of the block id (page_bf16 and its like), us a pass: append of 8 x 512 tokens into an e4m3 cache
 // 24.3 -> 22.8, ragged prompts (append and prefill) 72.2 -> 68.4.
-// `also`, `and_also`: further arguments of the launch.  (What is used at the end only, or not at all in an ordinary call, is left
-// out: it would hold registers meanwhile.)
-__device__ __forceinline__ void ask_arguments(const AttnDesc &d, const void *also = nullptr, const void *and_also = nullptr) {
+// `also`, `and_also`: two further arguments of the launch, addresses or whole numbers.  (What is used at the end only, or not at all
+// in an ordinary call, is left out - out, ws, cnt, err, safe -: it would hold registers meanwhile.)
+template <typename A, typename B>
+__device__ __forceinline__ void ask_arguments(const AttnDesc &d, A also, B and_also) {
     asm volatile("" ::"s"(also), "s"(and_also), "s"(d.pool_base), "s"(d.q), "s"(d.table), "s"(d.ctx_lens), "s"(d.row_len),
                  "s"(d.frame_bytes), "s"(d.block_bytes), "s"(d.slots_div.d), "s"(d.slots_div.mul), "s"(d.slots_div.sh1),
                  "s"(d.slots_div.sh2), "s"(d.max_block_id), "s"(d.row_stride), "s"(d.Hq), "s"(d.Hkv), "s"(d.g), "s"(d.D), "s"(d.cols),
                  "s"(d.scale_log2));
-}
-template <int SEQS>
-__device__ __forceinline__ void ask_arguments(const AttnDesc &d, const PlanOf<SEQS> &plan) {
-    ask_arguments(d, reinterpret_cast<const void *>((uintptr_t)(uint32_t)plan.n_seqs), reinterpret_cast<const void *>((uintptr_t)(uint32_t)plan.seq0));
 }
 
 // start of a block in the pool

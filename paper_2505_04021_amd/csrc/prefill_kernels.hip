@@ -106,7 +106,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
     constexpr int SLOT = 2 * TL::BYTES;                    // the K (or V) tiles of a pair
     __shared__ __align__(16) uint8_t ring[2 * PF_SLOTS * SLOT];   // K slots, then V slots
     const PlanLanes<SEQS> lanes(plan);
-    ask_arguments(d, plan);
+    ask_arguments(d, plan.n_seqs, plan.seq0);
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int h = lane >> 5, n = lane & 31, c16 = lane & 15, hi16 = (lane >> 4) & 1;
