@@ -588,12 +588,18 @@ __device__ __forceinline__ void page_tile(const AttnDesc &d, const BLOCK_OF &blo
 constexpr int PAGE_WAVES = 4;       // waves of a work-group; wave x of the launch: K or V, kv head, page, fastest first
 
 // kv_write: logical [n_tok][Hkv][D] values (bf16) or codes with their scales (e4m3) -> the in-block operand layouts.
+// Rows first, then the block: us a launch on 8 x 128 heads, element loops that wait for the block first and now: one token 3.3 ->
+// 2.6 bf16, 3.3 -> 2.4 e4m3, 8192 bf16 tokens 11.8 -> 12.0, 16000 21.0 -> 21.5, 32000 49.7 -> 39.6.  All arguments at once pay off
+// for bf16 and for few e4m3 tokens (0.1 us), but cost many e4m3 tokens more than they had gained: 8192 10.0 and 9.6 without, 12000 14.1
+// and 12.5 (13.0 before), 32000 28.5 and 26.8.
 template <int DT>
 __global__ __launch_bounds__(64 * PAGE_WAVES) void k_kv_write(const AttnDesc d, const int32_t *row, int tok_begin, int n_tok,
                                                               const uint8_t *k, const uint8_t *v, const float *ks, const float *vs) {
     constexpr int E = DT == PKV_BF16 ? 2 : 1;
-    ask_arguments(d, k, v);
-    asm volatile("" ::"s"(row), "s"(tok_begin), "s"(n_tok), "s"(ks), "s"(vs));
+    if constexpr (DT == PKV_BF16) {                        // (e4m3: see above)
+        ask_arguments(d, k, v);
+        asm volatile("" ::"s"(row), "s"(tok_begin), "s"(n_tok));
+    }
     const int x = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * PAGE_WAVES + (threadIdx.x >> 6)));
     const int which = x & 1, hp = x >> 1, j = hp / d.Hkv, h = hp - j * d.Hkv;
     const int page = tok_begin / PKV_T + j, end = tok_begin + n_tok;
