@@ -177,8 +177,8 @@ __device__ inline void deflate_body(const PoolDev &p, const ModelDev &m, int64_t
 
 // balloon_resize: the direction is decided here, from the device's own count of owned frames, so
 // that a caller can enqueue the call without knowing how earlier enqueued calls ended.  All counts are asked for at once, for
-// both directions; a deflate reads frames along with their words and compacts only if something stays (us: inflate of 170 frames
-// 2.4 -> 2.2, deflate of as many that are all empty 4.2 -> 3.1).
+// both directions; a deflate reads frames along with their words and compacts only if something stays (us, in turn on one
+// machine: inflate of 170 frames 2.3 -> 2.2, deflate of as many that are all empty 4.8 -> 3.0).
 __global__ __launch_bounds__(NT) void k_resize(PoolDev p, ModelDev m, int64_t target, BookResult *res, uint32_t *err) {
     __shared__ int s_wave[NW];
     const int64_t owned = m.counters[0], spare = m.counters[1], n_free = *p.n_free;          // uniform: every lane takes the same branch

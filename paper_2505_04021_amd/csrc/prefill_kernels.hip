@@ -14,14 +14,15 @@
 // products (768 matrix cycles, a third of them the low half of the probabilities) and some 105 other vector
 // instructions (8 more with a maximum per step instead of the sum as the sign that the reference point has to move:
 // 228 -> 225 us a pass with its append, all shapes 0.7 to 1.3 % faster); by the counters of a launch a step takes a
-// wave 2330 cycles, 1050 of them waiting, and the matrix units are busy 57 % of the launch at 1.81 GHz; with all
+// wave 2270 cycles, 1030 of them waiting, and the matrix units are busy 57 % of the launch at 1.81 GHz; with all
 // operands zero the same kernel runs 25 % faster, and a plain 8192^3 matrix product loses as much to random data.  Why
 // this shape: 32x32x16 products read half as many operand registers and LDS bytes per flop as 16x16x32, need one lane
 // exchange instead of two per maximum (and that only when the reference point moves), and fill 32 columns better for
 // odd g.  The step is software-pipelined by one pair: scores of pair p + 1 and the V reads of pair p are issued before
 // the output products of pair p, between which the softmax of pair p + 1 runs.  The waves meet once in two pairs (every
-// pair: 2 % slower).  8 sequences x (2048 cached + 512 new) of 32/8/128: bf16 236 -> 215 us, e4m3 300 -> 174 us; 64-wide
-// heads 183 -> 131 us.
+// pair: 2 % slower).  8 sequences x (2048 cached + 512 new) of 32/8/128, a maximum in every step, arguments read where they are
+// used and no priority levels, and so, in turn on one machine: bf16 221.9, 213.3 us, e4m3 180.6, 171.8; of 32/8/64: bf16 140.1,
+// 137.1, e4m3 131.2, 127.2.
 #include "mfma_util.h"
 
 namespace {
