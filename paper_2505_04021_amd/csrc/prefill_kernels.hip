@@ -239,23 +239,33 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
 #pragma unroll
         for (int u = 0; u < TL::NU; ++u) kr[u] = *reinterpret_cast<const u32x4 *>(src + u * 512);
     };
-    // V: output element 32 dt + n of tokens 4h..4h+3 and 8+4h..8+4h+3 of a page (lane row groups h and 2 + h)
+    // V: one output element of tokens 4h..4h+3 and 8+4h..8+4h+3 of a page (lane row groups h and 2 + h).  Which element is row
+    // n of tile dt is free: it is chosen so that the lanes of a half read side by side.
+    //   e4m3, D = 128: element 64 (n >> 4) + 16 dt + (n & 15), whole units, the words of one for the four tiles
+    //   otherwise: element V_BASE dt + V_STEP (n & 1) + (n >> 1), half a unit
+    constexpr bool UNITS = DT == PKV_E4M3 && D == 128;
+    constexpr int V_BASE = DT == PKV_BF16 ? 32 : 16, V_STEP = DT == PKV_BF16 ? 16 : 32;
     constexpr int VW = DT == PKV_BF16 ? 2 : 1;             // words per token group
     uint32_t vr[TL::ND][2][2 * VW];
-    const uint8_t *v_lane = ring + PF_SLOTS * SLOT + h * 256 + c16 * 16 + hi16 * 4 * VW;
+    const uint8_t *v_lane = ring + PF_SLOTS * SLOT + h * 256 + (UNITS ? hi16 * 1024 + c16 * 16 : n * 8);
     auto read_v = [&](int r) __attribute__((always_inline)) {
         const uint8_t *src = v_lane + (r & (PF_SLOTS - 1)) * SLOT;
 #pragma unroll
-        for (int dt = 0; dt < TL::ND; ++dt)
+        for (int k = 0; k < 2; ++k)
+            if constexpr (DT == PKV_BF16) {
 #pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                const uint8_t *at = src + k * TL::BYTES + (DT == PKV_BF16 ? dt * 1024 : (dt >> 1) * 1024 + (dt & 1) * 8);
-                if constexpr (DT == PKV_BF16) {
+                for (int dt = 0; dt < TL::ND; ++dt) {
+                    const uint8_t *at = src + k * TL::BYTES + dt * 1024;
                     const u32x2 a = *reinterpret_cast<const u32x2 *>(at), b = *reinterpret_cast<const u32x2 *>(at + 512);
                     vr[dt][k][0] = a.x; vr[dt][k][1] = a.y; vr[dt][k][2] = b.x; vr[dt][k][3] = b.y;
-                } else {
-                    vr[dt][k][0] = *reinterpret_cast<const uint32_t *>(at);
-                    vr[dt][k][1] = *reinterpret_cast<const uint32_t *>(at + 512);
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    typedef uint32_t words __attribute__((ext_vector_type(TL::ND)));
+                    const words a = *reinterpret_cast<const words *>(src + k * TL::BYTES + q * 512);
+#pragma unroll
+                    for (int dt = 0; dt < TL::ND; ++dt) vr[dt][k][q] = a[dt];
                 }
             }
     };
@@ -496,15 +506,33 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
     }
 
     l += __shfl_xor(l, 32);
+    // this lane's sums of its column, four elements at a time
+    auto put_sums = [&](float *row, float f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int dt = 0; dt < TL::ND; ++dt)
+            if constexpr (UNITS) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    *reinterpret_cast<f32x4 *>(row + 64 * (j >> 1) + 16 * dt + 8 * (j & 1) + 4 * h) =
+                        f32x4{acc[dt][4 * j], acc[dt][4 * j + 1], acc[dt][4 * j + 2], acc[dt][4 * j + 3]} * f;
+            } else {
+                // rows 8 j + 4 h + i: elements 4 j + 2 h + (i >> 1) of the first (i even) and the second half; lanes l and l ^ 32 exchange
+                // theirs so that each has four in a row
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+#pragma unroll
+                    for (int j = 0; j < 4; j += 2) {
+                        const u32x2 a = halves_swap(acc[dt][4 * j + e], acc[dt][4 * j + 4 + e]);
+                        const u32x2 b = halves_swap(acc[dt][4 * j + 2 + e], acc[dt][4 * j + 6 + e]);
+                        *reinterpret_cast<f32x4 *>(row + V_BASE * dt + V_STEP * e + 4 * j + 4 * h) =
+                            f32x4{__uint_as_float(a.x), __uint_as_float(b.x), __uint_as_float(a.y), __uint_as_float(b.y)} * f;
+                    }
+            }
+    };
     if (n_split > 1) {
         // a part of the context: the unnormalised sums, the reference point and the denominator of every column
         float *part = d.ws + (((size_t)group * d.Hkv + kvh) * PKV_PREFILL_COLS + w * PF_COLS + n) * (D + 4);
-#pragma unroll
-        for (int dt = 0; dt < TL::ND; ++dt)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                *reinterpret_cast<f32x4 *>(part + 32 * dt + 8 * j + 4 * h) =
-                    f32x4{acc[dt][4 * j], acc[dt][4 * j + 1], acc[dt][4 * j + 2], acc[dt][4 * j + 3]};
+        put_sums(part, 1.f);
         if (h == 0) {
             part[D] = m;
             part[D + 1] = l;
@@ -512,12 +540,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
     } else if (col_live) {
         float *out_row = d.out + ((size_t)(q0 + t0 + tok) * d.Hq + kvh * d.g + head) * D;
         const float inv = l > 0.f ? 1.0f / l : 0.f;        // no visible token: the row is defined as zero
-#pragma unroll
-        for (int dt = 0; dt < TL::ND; ++dt)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                *reinterpret_cast<f32x4 *>(out_row + 32 * dt + 8 * j + 4 * h) =
-                    f32x4{acc[dt][4 * j], acc[dt][4 * j + 1], acc[dt][4 * j + 2], acc[dt][4 * j + 3]} * inv;
+        put_sums(out_row, inv);
     }
     if (__any(bad != 0) && lane == 0) atomicOr(d.err, 1u);
 }
