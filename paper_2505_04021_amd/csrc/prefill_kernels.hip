@@ -19,10 +19,10 @@
 // this shape: 32x32x16 products read half as many operand registers and LDS bytes per flop as 16x16x32, need one lane
 // exchange instead of two per maximum (and that only when the reference point moves), and fill 32 columns better for
 // odd g.  The step is software-pipelined by one pair: scores of pair p + 1 and the V reads of pair p are issued before
-// the output products of pair p, between which the softmax of pair p + 1 runs.  The waves meet once in two pairs (every
-// pair: 2 % slower).  8 sequences x (2048 cached + 512 new) of 32/8/128, a maximum in every step, arguments read where they are
-// used and no priority levels, and so, in turn on one machine: bf16 221.9, 213.3 us, e4m3 180.6, 171.8; of 32/8/64: bf16 140.1,
-// 137.1, e4m3 131.2, 127.2.
+// the output products of pair p, between which the softmax of pair p + 1 runs.  The waves meet once in two pairs, four on
+// e4m3 caches (every pair: 2 % slower).  8 sequences x (2048 cached + 512 new) of 32/8/128, a maximum in every step, arguments read where they are
+// used and no priority levels, and with these mended: bf16 221.9, 213.3 us, e4m3 180.6, 171.8; of 32/8/64: bf16 140.1, 137.1, e4m3
+// 131.2, 127.2.
 #include "mfma_util.h"
 
 namespace {
@@ -31,7 +31,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int PF_WAVES = PKV_PREFILL_WAVES;
 constexpr int PF_COLS = 32;     // MFMA columns per wave
-constexpr int PF_SLOTS = 4;     // page pairs per ring (K and V have a ring each)
 static_assert(PF_WAVES * PF_COLS == PKV_PREFILL_COLS, "host and kernel must agree on the group size");
 
 // Where the reference point of the exponentials starts: finite, so that a column that has seen no token yet needs no
@@ -74,7 +73,9 @@ __device__ __forceinline__ void lds_fill(const uint8_t *src, uint32_t dst, uint3
 
 template <int NL>
 __device__ __forceinline__ void wait_requests(int ahead) {      // all but the `ahead` most recent requests have landed
-    if (ahead >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
+    if (ahead >= 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * NL) : "memory");
+    else if (ahead == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * NL) : "memory");
+    else if (ahead == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NL) : "memory");
     else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NL) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
@@ -105,6 +106,11 @@ template <int D, int DT, int SEQS>
 __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, const PlanOf<SEQS> plan) {
     using TL = PfTile<D, DT>;
     constexpr int SLOT = 2 * TL::BYTES;                    // the K (or V) tiles of a pair
+    // The waves meet once in so many pairs, and no wave runs further ahead than that.  An e4m3 cache leaves room in LDS for twice the
+    // slots that bf16 has (two work-groups a CU, three with 64-wide heads).  Us a pass, met in two and in four pairs: 8 x (2048 + 512)
+    // tokens of 32/8/128 179.3, 176.0; 8192 + 256 58.4, 56.5; ragged prompts 76.2, 75.1.
+    constexpr int MEET = DT == PKV_BF16 ? 2 : 4;
+    constexpr int PF_SLOTS = 2 * MEET;                     // page pairs per ring (K and V have a ring each)
     __shared__ __align__(16) uint8_t ring[2 * PF_SLOTS * SLOT];   // K slots, then V slots
     const PlanLanes<SEQS> lanes(plan);
     ask_arguments(d, plan.n_seqs, plan.seq0);
@@ -198,7 +204,6 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
     };
     auto fetch = [&](int r) __attribute__((always_inline)) {                              // request this wave's tile of pair p_begin + r
         const int p = p_begin + r;
-        if (p - addr_win >= 64) load_addr(p);
         const int at = p - addr_win;
         const uint64_t src = (uint32_t)__builtin_amdgcn_readlane((int)addr_lo, at) |
                              ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)addr_hi, at) << 32);
@@ -413,14 +418,14 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
     // (2 x (768 + 256) 29.3, 29.9).  64-wide heads have three work-groups a CU, which even out by themselves: they go without
     // (8 x (1024 + 512) of 32/8/64 bf16 86.5, 95.8, e4m3 80.3, 90.2).  A decode step of another model on a stream beside it takes as
     // long either way (16 x 2048 beside 8 x (2048 + 512) 218.5, 217.0; 4 x 300 beside 1 x (3968 + 128) 15.9, 15.5).
-    // (the waves meet in even steps; a walk of less than eight pairs may end above level 0)
+    // (the waves meet in every second or fourth step; a walk of less than 4 * MEET pairs may end above level 0)
     constexpr bool LEVELS = D == 128;
-    const int quarter = (np / 4 + 1) & ~1, half = (np / 2 + 1) & ~1, three_quarters = (3 * np / 4 + 1) & ~1;
+    const int quarter = (np / 4 + MEET / 2) & -MEET, half = (np / 2 + MEET / 2) & -MEET, three_quarters = (3 * np / 4 + MEET / 2) & -MEET;
     if constexpr (LEVELS) __builtin_amdgcn_s_setprio(3);
 
-    // the meeting point of the steps r and r + 1 (r even), in the middle of step r: all requests under way have
-    // landed; behind it K of pairs r + 2, r + 3 and V of pairs r + 1, r + 2 are visible to all waves, and the slots
-    // of K r, r + 1 and V r - 1, r take the pairs PF_SLOTS ahead of them
+    // the meeting point of the steps r to r + MEET - 1, in the middle of step r: all requests under way have landed; behind
+    // it K of pairs r + 2 to r + MEET + 1 and V of pairs r + 1 to r + MEET are visible to all waves, and the slots read up to now
+    // take the next MEET pairs
     auto meet = [&](int r) __attribute__((always_inline)) {
         if constexpr (LEVELS) {
             if (r == quarter) __builtin_amdgcn_s_setprio(2);
@@ -429,14 +434,16 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
         }
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
-        const int next = r + PF_SLOTS - (is_v ? 1 : 0);
-        if (next < np) fetch(next);
-        if (next + 1 < np) fetch(next + 1);
+        const int next = r + MEET + 2 - (is_v ? 1 : 0);
+        if (next < np && p_begin + next + MEET - 1 - addr_win >= 64) load_addr(p_begin + next);
+#pragma unroll
+        for (int i = 0; i < MEET; ++i)
+            if (next + i < np) fetch(next + i);
     };
 
     if (np > 0) {
         load_addr(p_begin);
-        const int ahead = is_v ? PF_SLOTS - 1 : PF_SLOTS, first = ahead < np ? ahead : np;
+        const int ahead = MEET + 2 - (is_v ? 1 : 0), first = ahead < np ? ahead : np;
         for (int r = 0; r < first; ++r) fetch(r);
 #pragma unroll
         for (int kk = 0; kk < TL::NK; ++kk)
@@ -463,7 +470,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
                 scales(p_begin + r + 1);
                 scores();
                 probabilities();
-                if (!(r & 1)) meet(r);
+                if (!(r & (MEET - 1))) meet(r);
                 if (r + 2 < np) read_k(r + 2);
                 sva = sva_n; svb = svb_n;
                 accumulate(ph);
@@ -477,7 +484,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
         }
         for (; r < np; ++r) {
             const int p = p_begin + r;
-            const bool now = live && 32 * p < tile_lim, next = live && r + 1 < np && 32 * (p + 1) < tile_lim;
+            const bool now = 32 * p < tile_lim, next = (r + 1 < np) & (32 * (p + 1) < tile_lim);     // (neither where no token is the wave's)
             if (now) {
                 read_v(r);
                 probabilities();
@@ -486,7 +493,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
                 scales(p + 1);
                 scores();
             }
-            if (r + 1 < np && !(r & 1)) meet(r);
+            if (r + 1 < np && !(r & (MEET - 1))) meet(r);
             if (next && r + 2 < np) read_k(r + 2);
             if (now) {
                 if (32 * (p + 1) > L) blank_v(p);
