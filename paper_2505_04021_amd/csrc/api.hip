@@ -9,6 +9,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <algorithm>
 
 #include <condition_variable>
 #include <mutex>
@@ -1587,28 +1588,40 @@ int kv_read(int model, int seq, int tok_begin, int n_tok, void *k_out, void *v_o
 // about equal size.
 struct PlanBuilder {
     ChunkPlan p;
-    uint32_t row = 0, unit = 0;
+    uint32_t row = 0;
     int per_launch;
+    uint32_t units[PKV_PLAN_SEQS];
+    uint64_t order[PKV_PLAN_SEQS];               // length, the last sequence's number first among equals
+    bool in_order = true;
     explicit PlanBuilder(int batch) {
         const int launches = (batch + PKV_PLAN_SEQS - 1) / PKV_PLAN_SEQS;
         per_launch = (batch + launches - 1) / launches;
         p.n_seqs = p.seq0 = 0;
     }
     bool full() const { return p.n_seqs == per_launch; }
-    void add(uint32_t rows, uint32_t units, uint32_t parts) {
-        p.s[p.n_seqs].unit = unit;
-        p.s[p.n_seqs].row = row | parts << PKV_PLAN_PART_SHIFT;
-        ++p.n_seqs;
+    // length: how long a unit of the sequence takes, in whatever measure; longer ones come first in the launch
+    void add(uint32_t rows, uint32_t n_units, uint32_t parts, uint32_t length) {
+        const int i = p.n_seqs++;
+        p.s[i].row = row | parts << PKV_PLAN_PART_SHIFT;
+        units[i] = n_units;
+        order[i] = (uint64_t)length << 32 | (uint32_t)(PKV_PLAN_SEQS - i);
+        in_order = in_order && (i == 0 || order[i] < order[i - 1]);
         row += rows;
-        unit += units;
     }
     ChunkPlan take(int next_seq) {               // the plan so far; the next one begins at sequence next_seq
+        if (!in_order) std::sort(order, order + p.n_seqs, std::greater<uint64_t>());
+        uint32_t unit = 0;
+        for (int i = 0; i < p.n_seqs; ++i) {
+            const uint32_t seq = PKV_PLAN_SEQS - (uint32_t)order[i];
+            p.s[i].unit = unit | seq << PKV_PLAN_SEQ_SHIFT;
+            unit += units[seq];
+        }
         p.s[p.n_seqs].unit = unit;
         p.s[p.n_seqs].row = row;
         const ChunkPlan done = p;
         p.n_seqs = 0;
         p.seq0 = next_seq;
-        unit = 0;
+        in_order = true;
         return done;
     }
 };
@@ -1638,7 +1651,7 @@ int kv_append_chunk(int model, int batch, const void *k_new, const void *v_new, 
         if (plan.full()) {
             HIP_TRY(pkv_launch_kv_append_chunk(d, plan.take(s), k_new, v_new, g_stream));
         }
-        plan.add((uint32_t)q_lens[s], q_lens[s] > 0 ? (uint32_t)((q_lens[s] + T - 1) / T + 1) : 0u, 0u);
+        plan.add((uint32_t)q_lens[s], q_lens[s] > 0 ? (uint32_t)((q_lens[s] + T - 1) / T + 1) : 0u, 0u, 0u);
     }
     HIP_TRY(pkv_launch_kv_append_chunk(d, plan.take(batch), k_new, v_new, g_stream));
     return (int)total;
@@ -1862,7 +1875,7 @@ int prefill_attention(int model, int batch, const void *q, const int32_t *q_lens
         if (s % plan.per_launch == 0)
             part_pairs = prefill_part_pairs(*m, s, s + plan.per_launch < batch ? s + plan.per_launch : batch, q_lens, group);
         const int parts = prefill_parts(*m, s, part_pairs), groups = (q_lens[s] + group - 1) / group;
-        plan.add((uint32_t)q_lens[s], (uint32_t)(groups * parts), (uint32_t)parts);
+        plan.add((uint32_t)q_lens[s], (uint32_t)(groups * parts), (uint32_t)parts, (uint32_t)(m->row_len[s] / parts));
         if (parts > 1 && groups > split_groups) split_groups = groups;
         if (q_lens[s] > 0 && parts > g_last_prefill_parts) g_last_prefill_parts = parts;
     }

@@ -61,7 +61,7 @@ struct PlanUnit {
 };
 
 // One read of the plan for all 64 lanes (the constructor) and no further memory trip: the sequence is the last one that
-// begins at or before u (sequences without units share their start with the next one).
+// begins at or before u in the order of the units (sequences without units share their start with the next one).
 template <int SEQS>
 struct PlanLanes {
     static constexpr int PER_LANE = (SEQS + 1) / 64;
@@ -87,13 +87,15 @@ struct PlanLanes {
         const int n = plan.n_seqs;
         int at = -1;
 #pragma unroll
-        for (int k = 0; k < PER_LANE; ++k) at += __popcll(__ballot((int)(threadIdx.x & 63) + 64 * k < n && unit[k] <= u));
+        for (int k = 0; k < PER_LANE; ++k) at += __popcll(__ballot((int)(threadIdx.x & 63) + 64 * k < n && (unit[k] & PKV_PLAN_UNITS) <= u));
         PlanUnit r;
-        const uint32_t first = pick(row, at);
-        r.seq = plan.seq0 + at;
-        r.unit = (int)(u - pick(unit, at));
+        const uint32_t entry = pick(unit, at);
+        const int seq = (int)(entry >> PKV_PLAN_SEQ_SHIFT);
+        const uint32_t first = pick(row, seq);
+        r.seq = plan.seq0 + seq;
+        r.unit = (int)(u - (entry & PKV_PLAN_UNITS));
         r.row = (int)(first & PKV_PLAN_ROWS);
-        r.rows = (int)(pick(row, at + 1) & PKV_PLAN_ROWS) - r.row;
+        r.rows = (int)(pick(row, seq + 1) & PKV_PLAN_ROWS) - r.row;
         r.parts = (int)(first >> PKV_PLAN_PART_SHIFT);
         return r;
     }

@@ -114,13 +114,15 @@ struct AttnDesc {
 };
 
 // How a chunk call (prefill_attention, kv_append_chunk) falls into units of work, as far as the host decides it: per
-// sequence where its units and its packed rows begin.  It travels in the kernel's arguments, so a call copies
+// sequence where its units and its packed rows begin.  Units may come in another order of the sequences than rows.  It travels in the kernel's arguments, so a call copies
 // nothing to the device and needs no buffer.  A kernel's arguments end at 4 KB: a launch holds at most PKV_PLAN_SEQS
 // sequences, and every work-group reads the plan, so that few sequences come with a shorter one (an append of 17 tokens each
 // for 127 sequences 7.3 us, for 128 8.0).  With launches of 127 sequences, the last one often small, 128 x (1000 cached + 17
 // new) tokens of 32/8/128 took 151 us (one launch 128), 447 x (200 + 3) of 8/2/128 41 (24.5), their append 18 (7).
 #define PKV_PLAN_FEW 127
 #define PKV_PLAN_SEQS 447
+#define PKV_PLAN_SEQ_SHIFT 23        // of `unit`: the entry's sequence above, its first unit (fewer than 2^22) below
+#define PKV_PLAN_UNITS 0x7fffffu
 #define PKV_PLAN_PART_SHIFT 25       // of `row`: parts of the context per group above, first packed row (at most 2^24) below
 #define PKV_PLAN_ROWS 0x1ffffffu
 #define PKV_PLAN_MAX_PARTS 64
@@ -128,8 +130,8 @@ template <int SEQS>
 struct PlanOf {
     int32_t n_seqs, seq0;                 // sequences seq0 .. seq0 + n_seqs - 1
     struct {
-        uint32_t unit;                    // its first unit
-        uint32_t row;                     // its first packed row | parts of the context per group << PKV_PLAN_PART_SHIFT
+        uint32_t unit;                    // entry i in the order of the units: its first one | its sequence << PKV_PLAN_SEQ_SHIFT
+        uint32_t row;                     // sequence i: its first packed row | parts of the context per group << PKV_PLAN_PART_SHIFT
     } s[SEQS + 1];                        // [n_seqs]: the totals
 };
 typedef PlanOf<PKV_PLAN_SEQS> ChunkPlan;

@@ -565,9 +565,9 @@ __global__ __launch_bounds__(32 * MERGE_COLS) void k_prefill_merge(const AttnDes
     const int sub = threadIdx.x & 31, cc = threadIdx.x >> 5;
     const int x = blockIdx.x / BLOCKS, rank = x / d.Hkv, kvh = x - rank * d.Hkv;
     const int c = (blockIdx.x - x * BLOCKS) * MERGE_COLS + cc;
-    const uint32_t first = plan.s[blockIdx.y].row;
+    const uint32_t entry = plan.s[blockIdx.y].unit, seq = entry >> PKV_PLAN_SEQ_SHIFT, first = plan.s[seq].row;
     const int parts = (int)(first >> PKV_PLAN_PART_SHIFT), row0 = (int)(first & PKV_PLAN_ROWS);
-    const int rows = (int)(plan.s[blockIdx.y + 1].row & PKV_PLAN_ROWS) - row0;
+    const int rows = (int)(plan.s[seq + 1].row & PKV_PLAN_ROWS) - row0;
     const int tile_tok = d.cols / d.g, size = PF_WAVES * tile_tok, groups = (rows + size - 1) / size;
     if (parts <= 1 || rank >= groups) return;
     const int t0 = (groups - 1 - rank) * size;
@@ -575,7 +575,7 @@ __global__ __launch_bounds__(32 * MERGE_COLS) void k_prefill_merge(const AttnDes
     if (__syncthreads_or(n < d.cols && tok < rows) == 0) return;
     const int D = d.D, stride = D + 4;       // D sums, the reference point, the denominator, two unused (16-byte rows)
     const size_t step = (size_t)d.Hkv * PKV_PREFILL_COLS * stride;
-    const float *part = d.ws + (((size_t)plan.s[blockIdx.y].unit + (size_t)rank * parts) * d.Hkv + kvh) * PKV_PREFILL_COLS * stride + (size_t)c * stride;
+    const float *part = d.ws + (((size_t)(entry & PKV_PLAN_UNITS) + (size_t)rank * parts) * d.Hkv + kvh) * PKV_PREFILL_COLS * stride + (size_t)c * stride;
     float m[2], l[2], M = PF_M0;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
