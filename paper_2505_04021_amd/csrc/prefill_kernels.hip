@@ -412,15 +412,19 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
 
     // 128-wide heads, two work-groups a CU: issue favours the older of the two waves of a SIMD.  Of the 512 work-groups of 512
     // tokens behind 15872 of 64/8/128, which all start together, half end within 236 to 291 us and half within 291 to 349, alone
-    // from then on.  So a wave steps down one priority level per quarter of its pairs, and whichever work-group is behind is
-    // favoured: they end within 286 to 343.  Us without and with: that pass 361.1, 358.1; 8 x (2048 + 512) of 32/8/128 bf16 223.8,
-    // 222.3, e4m3 183.0, 181.2; 8 x (1024 + 512) 136.2, 133.8 and 118.3, 112.9; launches of few work-groups lose 1 to 2 %
+    // from then on.  So a wave steps down a priority level in the course of its walk, and whichever work-group is behind is
+    // favoured until it reaches the same level.  On it the older one draws ahead again, by some 0.4 of the level's length, and its lead
+    // on the last level is how long the other one is alone at the end: so each level is half as long as the one before (8, 4, 2 and 1
+    // fifteenths of the walk).  With four equal levels the two of a CU ended 32 us apart.  Us a pass without and with equal levels:
+    // that pass 361.1, 358.1; 8 x (2048 + 512) of 32/8/128 bf16 223.8, 222.3, e4m3 183.0, 181.2; 8 x (1024 + 512) 136.2, 133.8 and 118.3,
+    // 112.9; with halved ones, by the ratio to one older code: 0.6 % less, 2.0 %, 1.5 % (last levels of 1/24 or 1/8 instead of 1/15:
+    // 0.2 to 1.2 % more again).  Launches of few work-groups lose 1 to 2 %
     // (2 x (768 + 256) 29.3, 29.9).  64-wide heads have three work-groups a CU, which even out by themselves: they go without
     // (8 x (1024 + 512) of 32/8/64 bf16 86.5, 95.8, e4m3 80.3, 90.2).  A decode step of another model on a stream beside it takes as
     // long either way (16 x 2048 beside 8 x (2048 + 512) 218.5, 217.0; 4 x 300 beside 1 x (3968 + 128) 15.9, 15.5).
     // (the waves meet in every second or fourth step; a walk of less than 4 * MEET pairs may end above level 0)
     constexpr bool LEVELS = D == 128;
-    const int quarter = (np / 4 + MEET / 2) & -MEET, half = (np / 2 + MEET / 2) & -MEET, three_quarters = (3 * np / 4 + MEET / 2) & -MEET;
+    const int first_step = (np / 2 + np / 32 + MEET / 2) & -MEET, second_step = (np - np / 5 + MEET / 2) & -MEET, third_step = (np - np / 15 + MEET / 2) & -MEET;
     if constexpr (LEVELS) __builtin_amdgcn_s_setprio(3);
 
     // the meeting point of the steps r to r + MEET - 1, in the middle of step r: all requests under way have landed; behind
@@ -428,9 +432,9 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
     // take the next MEET pairs
     auto meet = [&](int r) __attribute__((always_inline)) {
         if constexpr (LEVELS) {
-            if (r == quarter) __builtin_amdgcn_s_setprio(2);
-            if (r == half) __builtin_amdgcn_s_setprio(1);
-            if (r == three_quarters) __builtin_amdgcn_s_setprio(0);
+            if (r == first_step) __builtin_amdgcn_s_setprio(2);
+            if (r == second_step) __builtin_amdgcn_s_setprio(1);
+            if (r == third_step) __builtin_amdgcn_s_setprio(0);
         }
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
