@@ -295,7 +295,7 @@ constexpr double kDeepCapacity = 1.3;          // waves' own rate over the memor
 // 12 x 2048 (12 300) 25.2 -> 24.5, 16 x 2048 (27 100) 44.5 -> 45.4; e4m3 8 x 2048 22.2 -> 14.0 and, 64-wide, 21.6 -> 11.2.
 // The line lies on the safe side of where the two meet: lognormal rows of 11 200 to 12 600 pages still take 4 to 14 % less here.
 constexpr double kSmallMaxPages = 11000.0;
-constexpr int kSmallPart[] = {32, 48, 64, 96, 128, 256, PKV_MAX_ROW_BLOCKS}, kSmallMaxParts = 64;
+constexpr int kSmallPart[] = {24, 32, 40, 64, 96, 128, 256, PKV_MAX_ROW_BLOCKS}, kSmallMaxParts = 64;
 constexpr long kSmallWorkGroups = 512;         // that the chip holds at once
 // Smallest share of a wave, in pages.  It only binds in launches too small to give every wave slot a
 // share; there the last wave of a (sequence, kv head) merges one partial per piece, one after the
@@ -579,7 +579,9 @@ static int tune_setup() {
 // Lays a small launch out with parts of `size` pages: pages per part and parts per (sequence, kv head).  Returns an
 // estimate of what it takes (us) beside what any small launch takes, or a negative number if the partials of some model do
 // not fit.  Every row comes in as many parts as the longest one, so a long row among many short ones means work-groups
-// without pages.
+// without pages.  The figures are fitted to 84 random launches of one to three models, each timed with parts of 16 to 256 pages: the
+// length chosen takes 4 % more than the best of them, and 7.5 % less than parts of at least 32 pages by the rule before (parts of 24
+// pages are three pairs a wave; 2 x 767 tokens of 16/4/128 bf16 9.3 us in parts of 32 pages, 7.4 in parts of 24).
 static double lay_out_small(AttnGroup &grp, int size) {
     const int grain = 8;                                  // a page pair for every wave of a work-group
     long grid = 0;
@@ -592,7 +594,7 @@ static double lay_out_small(AttnGroup &grp, int size) {
         grid += (long)d.batch * d.Hkv * d.parts;
     }
     double walk = 0.0, empty = 0.0;
-    bool cut = false;
+    int most = 1;
     for (int i = 0; i < grp.n; ++i) {
         AttnDesc &d = grp.m[i];
         // Where the kv heads come fastest, the CUs of an XCD are dealt (row, part) in turn, and with an even number of parts
@@ -602,14 +604,15 @@ static double lay_out_small(AttnGroup &grp, int size) {
         // partials: one per work-group, in a workspace made for two per work item
         const long wgs = (long)d.batch * d.Hkv * d.parts;
         if (wgs > 2L * kDefaultItems) return -1.0;
-        cut |= d.parts > 1;
+        most = d.parts > most ? d.parts : most;
         const double page_kib = d.D * (d.dtype == PKV_BF16 ? 4 : 2) / 64.0;      // K and V of 16 tokens
         const int pages = d.max_pages < d.part_pages ? d.max_pages : d.part_pages;
-        const double us = (double)((pages + grain - 1) / grain) * (0.5 + 0.07 * page_kib);
+        const double us = (double)((pages + grain - 1) / grain) * (0.3 + 0.085 * page_kib);
         walk = us > walk ? us : walk;
-        empty += (double)wgs * (d.Hkv % 8 == 0 ? 0.003 : 0.0015);       // (a work-group without pages costs less where these come last)
+        empty += (double)wgs * (d.Hkv % 8 == 0 ? 0.003 : 0.002);
     }
-    return walk + (cut ? 2.0 + empty : grid > kSmallWorkGroups ? 0.0035 * grid : 0.0);
+    if (most == 1) return walk + (grid > kSmallWorkGroups ? 0.0035 * grid : 0.0);
+    return walk + 1.0 + empty + 0.4 * (most < 8 ? most - 1 : 7) + (most > 8 ? 0.1 * (most - 8) : 0.0);     // joined eight a trip
 }
 
 // Lays a small launch out with the best of the part lengths.  False where the ordinary forms are the better ones, which

@@ -184,29 +184,20 @@ __device__ __forceinline__ void split_p(const float *p, u32x2 &hi, u32x2 &lo) {
     lo = mk2(pack_bf16_rne(l0, l1), pack_bf16_rne(l2, l3));
 }
 
-// One online-softmax step over the 32 tokens of a page pair.  valid_a is 1..16,
-// valid_b 0..16 (0: the pair has no second page; its registers hold zeros).  Whether the
-// pair needs masks is decided at run time inside (one code path with selects: the kernel is
-// bound by memory).  MAY_BE_EMPTY: logits of -inf may be all that a column has seen so far; they weigh nothing.
-template <int D, int DT, bool MAY_BE_EMPTY = false>
-__device__ __forceinline__ void process_pair(State<D, DT> &st, const PairRegs<D, DT> &r, const bf16x8 *qf,
-                                             float scale_log2, int valid_a, int valid_b, int G) {
-    using TL = Tile<D, DT>;
-    const bool tail = valid_a < T || valid_b < T;
-    f32x4 sa = qk_page<D, DT>(r.a, qf);
-    f32x4 sb = qk_page<D, DT>(r.b, qf);
-    const float sca = DT == PKV_E4M3 ? scale_log2 * r.a.sk : scale_log2;
-    const float scb = DT == PKV_E4M3 ? scale_log2 * r.b.sk : scale_log2;
-    float s[8];
+// Blanks the tokens of a V tile past the context, which may hold anything (even NaN); live of the four that this lane holds count.
+template <int D, int DT>
+__device__ __forceinline__ void blank_v(u32x4 *v, int live) {
+    const uint32_t m01 = live >= 2 ? 0xffffffffu : (live == 1 ? 0x0000ffffu : 0u), m23 = live >= 4 ? 0xffffffffu : (live == 3 ? 0x0000ffffu : 0u);
+    const uint32_t m = live >= 4 ? 0xffffffffu : (live <= 0 ? 0u : (1u << (8 * live)) - 1u);      // codes
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        s[i] = sa[i] * sca;
-        s[4 + i] = sb[i] * scb;
-        if (tail) {                                        // select, so a NaN logit of a dead token cannot leak
-            if (4 * G + i >= valid_a) s[i] = -INFINITY;
-            if (4 * G + i >= valid_b) s[4 + i] = -INFINITY;
-        }
-    }
+    for (int j = 0; j < Tile<D, DT>::NL; ++j) v[j] &= DT == PKV_BF16 ? mk4(m01, m23, m01, m23) : mk4(m, m, m, m);
+}
+
+// The reference point, the sums and the probabilities of one online-softmax step over the 32 tokens of a page pair, whose
+// scaled and masked logits are s.  MAY_BE_EMPTY: logits of -inf may be all that a column has seen so far; they weigh nothing.
+template <int D, int DT, bool MAY_BE_EMPTY>
+__device__ __forceinline__ void softmax_pair(State<D, DT> &st, const float *s, float sva, float svb, bf16x8 &phv, bf16x8 &plv) {
+    using TL = Tile<D, DT>;
     float mx = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
     mx = rows_max(mx);
     const float m_new = fmaxf(st.m, mx);
@@ -227,8 +218,8 @@ __device__ __forceinline__ void process_pair(State<D, DT> &st, const PairRegs<D,
     if (DT == PKV_E4M3) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            p[i] *= r.a.sv;
-            p[4 + i] *= r.b.sv;
+            p[i] *= sva;
+            p[4 + i] *= svb;
         }
     }
     // B operand of the PV product: lane (G, head) holds P for tokens 4G..4G+3 of page a, then of page b
@@ -236,7 +227,35 @@ __device__ __forceinline__ void process_pair(State<D, DT> &st, const PairRegs<D,
     split_p(p, ha, la);
     split_p(p + 4, hb, lb);
     u32x4 ph = mk4(ha.x, ha.y, hb.x, hb.y), pl = mk4(la.x, la.y, lb.x, lb.y);
-    const bf16x8 phv = *reinterpret_cast<bf16x8 *>(&ph), plv = *reinterpret_cast<bf16x8 *>(&pl);
+    phv = *reinterpret_cast<bf16x8 *>(&ph);
+    plv = *reinterpret_cast<bf16x8 *>(&pl);
+}
+
+// One online-softmax step over the 32 tokens of a page pair.  valid_a is 1..16,
+// valid_b 0..16 (0: the pair has no second page; its registers hold zeros).  Whether the
+// pair needs masks is decided at run time inside (one code path with selects: the kernel is
+// bound by memory).
+template <int D, int DT>
+__device__ __forceinline__ void process_pair(State<D, DT> &st, const PairRegs<D, DT> &r, const bf16x8 *qf,
+                                             float scale_log2, int valid_a, int valid_b, int G) {
+    using TL = Tile<D, DT>;
+    const bool tail = valid_a < T || valid_b < T;
+    f32x4 sa = qk_page<D, DT>(r.a, qf);
+    f32x4 sb = qk_page<D, DT>(r.b, qf);
+    const float sca = DT == PKV_E4M3 ? scale_log2 * r.a.sk : scale_log2;
+    const float scb = DT == PKV_E4M3 ? scale_log2 * r.b.sk : scale_log2;
+    float s[8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        s[i] = sa[i] * sca;
+        s[4 + i] = sb[i] * scb;
+        if (tail) {                                        // select, so a NaN logit of a dead token cannot leak
+            if (4 * G + i >= valid_a) s[i] = -INFINITY;
+            if (4 * G + i >= valid_b) s[4 + i] = -INFINITY;
+        }
+    }
+    bf16x8 phv, plv;
+    softmax_pair<D, DT, false>(st, s, r.a.sv, r.b.sv, phv, plv);
     // tokens past the context length may hold anything (even NaN): blank their V
     uint32_t ma01 = 0xffffffffu, ma23 = 0xffffffffu, mb01 = 0xffffffffu, mb23 = 0xffffffffu;
     if (tail) {
@@ -849,6 +868,12 @@ __global__ __launch_bounds__(64, 2) void k_attention_static(const AttnGroup grp)
 // the work-group take the part's page pairs in turn and join their sums through LDS.  Only segments longer than
 // `part_pages` pages come in several parts, whose partials the last to arrive joins.  The host sizes the parts
 // (plan_small); a context that has outgrown them (a launch replayed from a graph) gets longer parts here.
+//
+// A wave alone on its SIMD issues an instruction every four or five cycles, so once its pages are there it is bound by how many a
+// page pair costs: with the addresses of both pages worked out by scalar instructions and masks in every pair 560, so some
+// 230.  Stream of a row in parts of 32 pages, four pairs a wave, after the first pair 2.7 us, so 1.7; us a launch: 1 x 9735 tokens
+// of 4/1/128 bf16 9.9, 9.2; 3 x 1717 of 2/1/128 e4m3 8.6, 7.7; 7 x 573 of 16/8/64 e4m3 6.5, 5.2.  Eight waves a work-group instead of four
+// take longer everywhere (2 x 767 of 16/4/128 9.2, 9.9).
 constexpr int SMALL_WAVES = 4;
 
 // Weight of a wave's sums with maximum m beside a joint maximum of M.  A wave that has seen nothing but logits of -inf has
@@ -881,43 +906,160 @@ __device__ __forceinline__ void attn_part(const AttnDesc &d, int wg, float *s_ac
     const int32_t *row = d.table + (size_t)seq * d.row_stride;
     bf16x8 qf[TL::NK];
     load_q<D>(qf, d, seq, kvh, lane);
-    PairIds ids = fetch_ids(d, row, part * d.part_pages + 2 * w);
+    // This wave's pairs: pages page0 + STEP k and the one behind it, k = 0, 1, ...  The ids of the first come by themselves, so that a
+    // row of one pair a wave pays for nothing else; those of the next 32 in one read, and lane i works out where page i & 1 of pair
+    // 1 + (i >> 1) is.  All are asked for with the context length and the queries.
+    constexpr int STEP = 2 * SMALL_WAVES;
+    const int ahead = STEP * (lane >> 1) + (lane & 1);
+    auto id_of = [&](int page) __attribute__((always_inline)) { return (uint32_t)row[page < d.row_stride ? page : d.row_stride - 1]; };
+    int page0 = part * d.part_pages + 2 * w;
+    PairIds ids = fetch_ids(d, row, page0);
+    uint32_t id = d.part_pages > STEP ? id_of(page0 + STEP + ahead) : 0u;
     const int L = __builtin_amdgcn_readfirstlane(ctx_clamped(d, seq));
     const int n_pages = (L + T - 1) / T;
     int size = d.part_pages;
     if (n_pages > d.parts * size) {                       // longer than the host knew
         size = (n_pages + d.parts - 1) / d.parts;
-        size = (size + 2 * SMALL_WAVES - 1) / (2 * SMALL_WAVES) * (2 * SMALL_WAVES);
-        ids = fetch_ids(d, row, part * size + 2 * w);
+        size = (size + STEP - 1) / STEP * STEP;
+        page0 = part * size + 2 * w;
+        ids = fetch_ids(d, row, page0);
+        id = id_of(page0 + STEP + ahead);
     }
     const int n_parts = n_pages > size ? (n_pages + size - 1) / size : 1;
     if (part >= n_parts) return;
     const int pe = (part + 1) * size < n_pages ? (part + 1) * size : n_pages;
     const int last_valid = L - (n_pages - 1) * T;
-    uint32_t bad = 0;
     State<D, DT> st;
 #pragma unroll
     for (int jt = 0; jt < TL::NV; ++jt) st.acc[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
     st.m = -INFINITY;
     st.l = 0.f;
-    // this wave's pairs: pages p, p + 1 for p = first, first + 2 * SMALL_WAVES, ...; one pair ahead of the one in use
-    constexpr int STEP = 2 * SMALL_WAVES;
-    PairRegs<D, DT> ring[2];
-    int p = part * size + 2 * w;
-    load_pair<D, DT>(ring[0], d, ids, p < pe, p + 1 < pe, kvh, lane, bad);
-    ids = fetch_ids(d, row, p + STEP);
-    while (p < pe) {
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-            load_pair<D, DT>(ring[r ^ 1], d, ids, p + STEP < pe, p + STEP + 1 < pe, kvh, lane, bad);
-            ids = fetch_ids(d, row, p + 2 * STEP);
-            if (p < pe) {
-                const int va = p == n_pages - 1 ? last_valid : T;
-                const int vb = p + 1 < pe ? (p + 1 == n_pages - 1 ? last_valid : T) : 0;
-                process_pair<D, DT, true>(st, ring[r], qf, d.scale_log2, va, vb, G);
-            }
-            p += STEP;
+
+    // where the tiles of this lane's page are, in how many bytes (none: the page is beyond the part, or its id outside the
+    // pool, and is never read), and its scales
+    bool bad = false;
+    uint32_t addr_lo = 0, addr_hi = 0, records = 0;
+    float page_sk = 0.f, page_sv = 0.f;
+    auto locate = [&](int page, uint32_t id) __attribute__((always_inline)) {
+        const bool in_pool = id < d.max_block_id, live = page < pe;
+        bad |= live && !in_pool;
+        const uint32_t f = fastdiv_div(id, d.slots_div);
+        const uint8_t *blk = d.pool_base + (uint64_t)f * d.frame_bytes + (uint64_t)(id - f * d.slots_div.d) * d.block_bytes;
+        if (DT == PKV_E4M3) {
+            const float *hdr = reinterpret_cast<const float *>(live && in_pool ? blk : reinterpret_cast<const uint8_t *>(d.safe));
+            page_sk = hdr[kvh];
+            page_sv = hdr[d.Hkv + kvh];
+            blk += PKV_FP8_HEADER;
         }
+        blk += (size_t)kvh * 2 * TL::TILE_BYTES;
+        addr_lo = (uint32_t)(uintptr_t)blk;
+        addr_hi = (uint32_t)((uintptr_t)blk >> 32);
+        records = live && in_pool ? 2 * TL::TILE_BYTES : 0;
+    };
+    int window = 1;                                       // the lanes' pages are those of pairs window .. window + 31
+    auto lane_of = [&](uint32_t x, int at) __attribute__((always_inline)) { return (uint32_t)__builtin_amdgcn_readlane((int)x, at); };
+    auto tiles = [&](int k, int half) __attribute__((always_inline)) {
+        const int at = 2 * (k - window) + half;
+        return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<uint8_t *>(lane_of(addr_lo, at) | (uint64_t)lane_of(addr_hi, at) << 32), 0,
+                                                 (int)lane_of(records, at), 0x00020000);
+    };
+    auto first_tiles = [&](uint32_t id, bool live, float &sk, float &sv) __attribute__((always_inline)) {
+        const bool in_pool = id < d.max_block_id;
+        bad |= live && !in_pool;
+        live = live && in_pool;
+        const uint32_t f = fastdiv_div(id, d.slots_div);
+        const uint8_t *blk = d.pool_base + (uint64_t)f * d.frame_bytes + (uint64_t)(id - f * d.slots_div.d) * d.block_bytes;
+        if (DT == PKV_E4M3) {
+            const float *hdr = reinterpret_cast<const float *>(live ? blk : reinterpret_cast<const uint8_t *>(d.safe));
+            sk = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(PKV_CONST(float, hdr)[kvh])));
+            sv = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(PKV_CONST(float, hdr)[d.Hkv + kvh])));
+            blk += PKV_FP8_HEADER;
+        }
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(blk + (size_t)kvh * 2 * TL::TILE_BYTES), 0, live ? 2 * TL::TILE_BYTES : 0, 0x00020000);
+    };
+    const int voff = lane * 16;
+    auto load = [&](u32x4 *r, __amdgpu_buffer_rsrc_t rsrc, int at) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < TL::NL; ++j) r[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff + j * 1024, at, 2 /* non-temporal */);
+        asm volatile("" ::: "memory");                    // in this order everywhere: loads in flight are counted
+    };
+    auto load_pages = [&](PairRegs<D, DT> &r, __amdgpu_buffer_rsrc_t a, __amdgpu_buffer_rsrc_t b) __attribute__((always_inline)) {
+        load(r.a.k, a, 0);
+        load(r.a.v, a, TL::TILE_BYTES);
+        load(r.b.k, b, 0);
+        load(r.b.v, b, TL::TILE_BYTES);
+    };
+    auto scales = [&](PairRegs<D, DT> &r, int k) __attribute__((always_inline)) {
+        if (DT != PKV_E4M3) return;
+        const int at = 2 * (k - window);
+        r.a.sk = __uint_as_float(lane_of(__float_as_uint(page_sk), at));
+        r.a.sv = __uint_as_float(lane_of(__float_as_uint(page_sv), at));
+        r.b.sk = __uint_as_float(lane_of(__float_as_uint(page_sk), at + 1));
+        r.b.sv = __uint_as_float(lane_of(__float_as_uint(page_sv), at + 1));
+    };
+    // Pair k; `more`: pair k + 1 is asked for ahead of it.  (Asked for earlier, K of pair k + 2 behind the scores and V behind the
+    // products of pair k, launches took 2 to 10 % longer: 8 lognormal rows of 2048 tokens of 32/8/128 bf16 19.0, 20.0 us, 16 of 4717
+    // of 10/2/128 25.3, 27.2, 30 of 366 of 40/8/128 7.7, 8.5.  Whole pages one after the other, K and V, cost 1 to 3 % less than K of
+    // both and then V.)
+    auto step = [&](PairRegs<D, DT> &r, PairRegs<D, DT> &o, int k, bool more) __attribute__((always_inline)) {
+        if (more) {
+            load_pages(o, tiles(k + 1, 0), tiles(k + 1, 1));
+            scales(o, k + 1);
+        }
+        const int p = page0 + STEP * k;
+        const int valid_a = p == n_pages - 1 ? last_valid : T;
+        const int valid_b = p + 1 < pe ? (p + 1 == n_pages - 1 ? last_valid : T) : 0;
+        const bool tail = valid_a < T || valid_b < T;
+        const float sca = DT == PKV_E4M3 ? d.scale_log2 * r.a.sk : d.scale_log2, scb = DT == PKV_E4M3 ? d.scale_log2 * r.b.sk : d.scale_log2;
+        const f32x4 sa = qk_page<D, DT>(r.a, qf), sb = qk_page<D, DT>(r.b, qf);
+        float s[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s[i] = sa[i] * sca;
+            s[4 + i] = sb[i] * scb;
+        }
+        // only a row's last pair holds tokens past its context: a branch of its own, not selects in every step
+        if (tail) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (4 * G + i >= valid_a) s[i] = -INFINITY;
+                if (4 * G + i >= valid_b) s[4 + i] = -INFINITY;
+            }
+            blank_v<D, DT>(r.a.v, valid_a - 4 * G);
+            blank_v<D, DT>(r.b.v, valid_b - 4 * G);
+        }
+        bf16x8 phv, plv;
+        softmax_pair<D, DT, true>(st, s, r.a.sv, r.b.sv, phv, plv);
+#pragma unroll
+        for (int jt = 0; jt < TL::NV; ++jt) {
+            const u32x2 va = v_half<D, DT>(r.a, jt), vb = v_half<D, DT>(r.b, jt);
+            const bf16x8 av = as_bf16x8(mk4(va.x, va.y, vb.x, vb.y));
+            st.acc[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, phv, st.acc[jt], 0, 0, 0);
+            st.acc[jt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, plv, st.acc[jt], 0, 0, 0);
+        }
+    };
+    const int n_pairs = page0 < pe ? (pe - page0 + STEP - 1) / STEP : 0;
+    if (n_pairs > 0) {
+        PairRegs<D, DT> ring[2];
+        const __amdgpu_buffer_rsrc_t a = first_tiles(ids.a, true, ring[0].a.sk, ring[0].a.sv);
+        const __amdgpu_buffer_rsrc_t b = first_tiles(ids.b, page0 + 1 < pe, ring[0].b.sk, ring[0].b.sv);
+        load_pages(ring[0], a, b);
+        // (The loads in flight are counted along every way the compiler sees: the loop is entered from here only, two whole steps
+        // a turn with no way out between them, the odd step by itself.)
+        int k = 0;
+        if (n_pairs > 1) {
+            locate(page0 + STEP + ahead, id);
+            do {
+                if (k + 2 - window >= 32) {
+                    window = k + 1;
+                    locate(page0 + STEP * window + ahead, id_of(page0 + STEP * window + ahead));
+                }
+                step(ring[0], ring[1], k, true);
+                step(ring[1], ring[0], k + 1, true);
+                k += 2;
+            } while (k + 2 <= n_pairs);
+        }
+        if (k < n_pairs) step(ring[0], ring[1], k, false);
     }
     float l = st.l;
     l += __shfl_xor(l, 16);
@@ -931,7 +1073,7 @@ __device__ __forceinline__ void attn_part(const AttnDesc &d, int wg, float *s_ac
             s_l[w * 16 + n] = l;
         }
     }
-    if (bad && lane == 0) atomicOr(d.err, 1u);
+    if (__any(bad) && lane == 0) atomicOr(d.err, 1u);
     __syncthreads();
     // the sums of the work-group: lane by lane four output elements of one head
     const int quads = g * (D / 4), pf = partial_floats(g, D);

@@ -1,4 +1,4 @@
-"""Small decode launches (a work-group per row and kv head, or per part of 32 pages): rows at the edges of pages, pairs
+"""Small decode launches (a work-group per row and kv head, or per part of one): rows at the edges of pages, pairs
 and parts against the oracle, and a captured launch whose rows have outgrown the parts it was laid out with."""
 import numpy as np
 import pytest
@@ -59,6 +59,45 @@ def test_rows_outgrow_a_captured_launch(gpu, oracle):  # noqa: F811
         torch.cuda.synchronize()
         rc_o, out_o = oracle.decode_attention(t.models[1], q, np.array(step, dtype=np.int32))
         assert rc_o == 0 and gpu.device_errors() == 0 and row_rel_err(out.cpu().numpy(), out_o) <= TOL[BF16]
+    t.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype", [(8, 1, 64, BF16), (4, 1, 128, E4M3), (4, 1, 128, BF16), (2, 1, 64, E4M3)])
+def test_long_walks_of_one_part(gpu, oracle, hq, hkv, d, dtype):  # noqa: F811
+    """A launch captured with rows in one part: later rows are walked by four waves, and a wave looks up 33 page pairs first and
+    then 32 at a time, so up to and past 33 and 65 pairs, a whole or half a pair or a token more or less."""
+    pages = [263, 264, 265, 272, 273, 513, 520, 522]
+    last = [16 * n - (s % 3) for s, n in enumerate(pages)]
+    n = len(last)
+    t = Twin(gpu, oracle, hq, hkv, d, dtype, last, max_blocks=540, poison=False)
+    m = t.models[0]
+    q = gen.queries((71, d), n, hq, d)
+    qd = torch.from_numpy(q.view(np.int16)).cuda()
+    ctx = torch.tensor(last, dtype=torch.int32, device="cuda")
+    out = torch.zeros((n, hq, d), dtype=torch.float32, device="cuda")
+    c = np.array(last, dtype=np.int32)
+    rc_o, out_o = oracle.decode_attention(t.models[1], q, c)
+    gpu.seq_release_batch(m, np.arange(n, dtype=np.int32))
+    assert gpu.seq_reserve_batch(m, list(range(n)), [40] * n) == 3 * n
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        gpu.use_current_stream()
+        graph.capture_begin()
+        assert gpu.decode_attention_dev(m, qd, ctx, out) == 0
+        graph.capture_end()
+    torch.cuda.synchronize()
+    gpu.use_current_stream()
+    assert gpu.last_kernel_form() == 2 and gpu.last_launch_items() == n * hkv
+    assert gpu.seq_reserve_batch(m, list(range(n)), last) >= 0
+    for s in range(n):
+        kv = gen.seq_kv((13, s), last[s], hkv, d, dtype, 16)
+        assert gpu.kv_write(m, s, 0, kv["k"], kv["v"], kv.get("k_scale"), kv.get("v_scale")) == last[s]
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert rc_o == 0 and gpu.device_errors() == 0 and row_rel_err(out.cpu().numpy(), out_o) <= TOL[dtype]
     t.close()
 
 
