@@ -193,9 +193,9 @@ __device__ __forceinline__ void blank_v(u32x4 *v, int live) {
     for (int j = 0; j < Tile<D, DT>::NL; ++j) v[j] &= DT == PKV_BF16 ? mk4(m01, m23, m01, m23) : mk4(m, m, m, m);
 }
 
-// The reference point, the sums and the probabilities of one online-softmax step over the 32 tokens of a page pair, whose
-// scaled and masked logits are s.  MAY_BE_EMPTY: logits of -inf may be all that a column has seen so far; they weigh nothing.
-template <int D, int DT, bool MAY_BE_EMPTY>
+// Small launches: the reference point, the sums and the probabilities of one online-softmax step, as process_pair below takes them,
+// from scaled and masked logits s; but logits of -inf may be all that a column has seen so far, and weigh nothing.
+template <int D, int DT>
 __device__ __forceinline__ void softmax_pair(State<D, DT> &st, const float *s, float sva, float svb, bf16x8 &phv, bf16x8 &plv) {
     using TL = Tile<D, DT>;
     float mx = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
@@ -204,14 +204,14 @@ __device__ __forceinline__ void softmax_pair(State<D, DT> &st, const float *s, f
     // wave-uniform: the reference point of the exponentials moves, and the sums are rescaled, only when some
     // column's maximum has run ahead of it by more than kRescaleSlack (probabilities stay below 2^kRescaleSlack)
     if (__any(m_new > st.m + kRescaleSlack)) {
-        const float alpha = MAY_BE_EMPTY && m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(st.m - m_new);
+        const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(st.m - m_new);
         st.l *= alpha;
 #pragma unroll
         for (int jt = 0; jt < TL::NV; ++jt) st.acc[jt] *= alpha;
         st.m = m_new;
     }
     float p[8];
-    const float m_ref = MAY_BE_EMPTY && st.m == -INFINITY ? 0.f : st.m;      // then every s is -inf and every p is 0
+    const float m_ref = st.m == -INFINITY ? 0.f : st.m;      // then every s is -inf and every p is 0
 #pragma unroll
     for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - m_ref);
     st.l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
@@ -254,8 +254,35 @@ __device__ __forceinline__ void process_pair(State<D, DT> &st, const PairRegs<D,
             if (4 * G + i >= valid_b) s[4 + i] = -INFINITY;
         }
     }
-    bf16x8 phv, plv;
-    softmax_pair<D, DT, false>(st, s, r.a.sv, r.b.sv, phv, plv);
+    float mx = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
+    mx = rows_max(mx);
+    const float m_new = fmaxf(st.m, mx);
+    // wave-uniform: the reference point of the exponentials moves, and the sums are rescaled, only when some
+    // column's maximum has run ahead of it by more than kRescaleSlack (probabilities stay below 2^kRescaleSlack)
+    if (__any(m_new > st.m + kRescaleSlack)) {
+        const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
+        st.l *= alpha;
+#pragma unroll
+        for (int jt = 0; jt < TL::NV; ++jt) st.acc[jt] *= alpha;
+        st.m = m_new;
+    }
+    float p[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(s[i] - st.m);
+    st.l += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+    if (DT == PKV_E4M3) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] *= r.a.sv;
+            p[4 + i] *= r.b.sv;
+        }
+    }
+    // B operand of the PV product: lane (G, head) holds P for tokens 4G..4G+3 of page a, then of page b
+    u32x2 ha, la, hb, lb;
+    split_p(p, ha, la);
+    split_p(p + 4, hb, lb);
+    u32x4 ph = mk4(ha.x, ha.y, hb.x, hb.y), pl = mk4(la.x, la.y, lb.x, lb.y);
+    const bf16x8 phv = *reinterpret_cast<bf16x8 *>(&ph), plv = *reinterpret_cast<bf16x8 *>(&pl);
     // tokens past the context length may hold anything (even NaN): blank their V
     uint32_t ma01 = 0xffffffffu, ma23 = 0xffffffffu, mb01 = 0xffffffffu, mb23 = 0xffffffffu;
     if (tail) {
@@ -1029,7 +1056,7 @@ __device__ __forceinline__ void attn_part(const AttnDesc &d, int wg, float *s_ac
             blank_v<D, DT>(r.b.v, valid_b - 4 * G);
         }
         bf16x8 phv, plv;
-        softmax_pair<D, DT, true>(st, s, r.a.sv, r.b.sv, phv, plv);
+        softmax_pair<D, DT>(st, s, r.a.sv, r.b.sv, phv, plv);
 #pragma unroll
         for (int jt = 0; jt < TL::NV; ++jt) {
             const u32x2 va = v_half<D, DT>(r.a, jt), vb = v_half<D, DT>(r.b, jt);
