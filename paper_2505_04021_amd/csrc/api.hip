@@ -616,12 +616,12 @@ static double lay_out_small(AttnGroup &grp, int size) {
 }
 
 // Lays a small launch out with the best of the part lengths.  False where the ordinary forms are the better ones, which
-// deal pages out evenly whatever the rows: a few long rows among many short ones, or very many rows.  Small kernel and
-// ordinary forms, us, 32/8/128 bf16: 63 rows of 128 tokens and one of 8192 75 uncut, 32 to 47 in parts, 25.5; 64 of 64 and one
-// of 17 600 50 to 154, 29; 30 of 256 and one of 8192 26, 24.4; 120 of 50 and one of 1500 20 to 24, 18; 500 of 16 27, 24; but
-// 60 of 100 and one of 2000 18.6, 20.3; 30 of 256 and one of 4096 20.6, 22.6; 20 of 300 and three of 4000 20.1, 29.6;
-// 127 of 16 and one of 1000 12.7, 15.7; 100 lognormal rows of 120 19.5, 23.  What the ordinary forms take grows with the
-// pages, and with the longest row, whose pieces are joined one after the other (one of 60 000, one kv head: 24, 67).
+// deal pages out evenly whatever the rows: very many rows, or a few long rows among so many short ones that most work-groups would
+// be without pages.  What the ordinary forms take grows with the pages, and with the longest row, whose pieces are joined
+// one after the other; the line is fitted, together with the estimate above, to both forms of 1550 random launches.  Small kernel and
+// ordinary forms, us: 60 rows of 50 tokens and one of 2000 of 32/8/128 15.1, 18.2; 30 of 50 and one of 4000 16.1, 20.0; 100 of 16 and one of
+// 6000 of 8/2/128 15.4, 18.2; 120 of 39 and one of 11 055 of 8/1/128 16.9, 30.7; of 8/8/64 30 of 256 and one of 4096 13.4, 19.9; 300 of 16
+// 13.9, 13.3; 500 of 16 more than 18.6; 63 of 128 and one of 8192 14.6 or 20.6 (the long row first or in the middle), 21.
 static bool plan_small(AttnGroup &grp) {
     if (!g_small_now) return false;
     int longest = 0, size = 0;
@@ -635,7 +635,7 @@ static bool plan_small(AttnGroup &grp) {
         }
         if (part >= longest) break;                       // longer parts change nothing
     }
-    if (size == 0 || best > fmax(12.0 + 0.5e-3 * g_small_pages, longest / 64.0)) return false;
+    if (size == 0 || best > 13.2 + 0.16e-3 * g_small_pages + longest / 160.0) return false;
     lay_out_small(grp, size);
     int begin = 0;
     for (int i = 0; i < grp.n; ++i) {
