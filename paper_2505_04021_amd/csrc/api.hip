@@ -290,13 +290,13 @@ constexpr double kDeepCapacity = 1.3;          // waves' own rate over the memor
 // Launches of fewer pages than kSmallMaxPages are bound by dependent memory trips and go to a kernel of their own
 // (k_attention_small: a work-group of four waves per part of a row and kv head), whichever form is in force, if plan_small
 // finds a part length that suits their rows.  Ordinary or second form -> small kernel, us:
-// 4 short sequences of 8/2/64 9.4 -> 4.7; 32/8/128 bf16: 4 x 256 tokens 9.9 -> 5.6, 64 x 190 18.4 -> 9.5, 4 x 2048
-// 17.3 -> 11.1, 1 x 8192 21.5 -> 12.7, lognormal 8 x 2048 (10 200 pages) 25.8 -> 22.1, 16 x 1024 (11 700) 24.0 -> 23.7,
-// 12 x 2048 (12 300) 25.2 -> 24.5, 16 x 2048 (27 100) 44.5 -> 45.4; e4m3 8 x 2048 22.2 -> 14.0 and, 64-wide, 21.6 -> 11.2.
-// The line lies on the safe side of where the two meet: lognormal rows of 11 200 to 12 600 pages still take 4 to 14 % less here.
+// 4 short sequences of 8/2/64 9.6 -> 3.8; 32/8/128 bf16: 4 x 256 tokens 10.1 -> 6.3, 64 x 190 18.6 -> 11.4, 4 x 2048
+// 17.3 -> 11.4, 1 x 8192 21.8 -> 13.7, lognormal 8 x 2048 (7500 pages) 21.7 -> 18.1, 16 x 1024 (11 000) 25.1 -> 25.6,
+// 40 x 460 (13 400) 27.3 -> 29.3, 16 x 2048 (24 300) 40.4 -> 42.6; e4m3 8 x 2048 19.8 -> 11.8 and, 64-wide, 19.9 -> 9.6.
+// The line lies where the two meet in bf16; e4m3 launches of some more pages (20 x 1000, 11 800: 20.1, 15.5) would still be faster here.
 constexpr double kSmallMaxPages = 11000.0;
 constexpr int kSmallPart[] = {24, 32, 40, 64, 96, 128, 256, PKV_MAX_ROW_BLOCKS}, kSmallMaxParts = 64;
-constexpr long kSmallWorkGroups = 512;         // that the chip holds at once
+constexpr long kSmallWorkGroups = 512, kSmallCUs = 256;         // work-groups that the chip holds at once, one to a CU
 // Smallest share of a wave, in pages.  It only binds in launches too small to give every wave slot a
 // share; there the last wave of a (sequence, kv head) merges one partial per piece, one after the
 // other, and many small pieces cost more than they gain in parallelism: an eighth of a mean row,
@@ -314,6 +314,7 @@ int g_last_prefill_parts = 0;         // most parts a context came in, in the mo
 int g_last_items = 0;                 // its work items, work-groups of a small launch
 bool g_small_now = false;             // the launch being prepared is a small one: a work-group per (sequence, kv head) or part of one
 double g_small_pages = 0.0;           // its pages
+int g_small_models = 0, g_small_rows[PKV_MAX_GROUP];    // pages of its models' rows, in the order of the group
 
 // Time (us) a wave of the second form, alone on its SIMD, spends on one page.
 double deep_page_us(const Model &m) {
@@ -364,6 +365,7 @@ void plan_launch(const LaunchLoad &l) {
     // (a caller that moves the split gets the kernel whose split it moves)
     g_small_now = g_deep_mode < 0 && g_items == 0 && g_min_share == 0 && g_seg_cost < 0 && l.pages < kSmallMaxPages;
     g_small_pages = l.pages;
+    g_small_models = 0;
     g_plan_items = g_items > 0 ? g_items : (g_deep_now ? n : kDefaultItems);
 }
 
@@ -407,10 +409,13 @@ void fill_desc_core(AttnDesc &d, Model &m, int batch, const void *q, const int32
     d.weighted = d.n_items % 8 == 0 ? 1 : 0;
     if (g_small_now) {
         d.max_pages = own ? 0 : row_stride;
-        for (int s = 0; s < batch; ++s) {
-            const int pages = own ? m.row_len[s] : row_stride;
+        int total = own ? 0 : batch * row_stride;
+        for (int s = 0; own && s < batch; ++s) {
+            const int pages = m.row_len[s];
             if (pages > d.max_pages) d.max_pages = pages;
+            total += pages;
         }
+        g_small_rows[g_small_models++] = total;
     }
 }
 
@@ -579,9 +584,12 @@ static int tune_setup() {
 // Lays a small launch out with parts of `size` pages: pages per part and parts per (sequence, kv head).  Returns an
 // estimate of what it takes (us) beside what any small launch takes, or a negative number if the partials of some model do
 // not fit.  Every row comes in as many parts as the longest one, so a long row among many short ones means work-groups
-// without pages.  The figures are fitted to 84 random launches of one to three models, each timed with parts of 16 to 256 pages: the
-// length chosen takes 4 % more than the best of them, and 7.5 % less than parts of at least 32 pages by the rule before (parts of 24
-// pages are three pairs a wave; 2 x 767 tokens of 16/4/128 bf16 9.3 us in parts of 32 pages, 7.4 in parts of 24).
+// without pages.  The figures are fitted, with the line below, to 1554 random launches of one to three models, each timed with parts of
+// 24 to 256 pages, uncut and in the ordinary forms: on 1193 others the choice takes 1.9 % more than the best of all in the geometric
+// mean, one in twenty 11 % or more.
+// Work-group i + 256 comes to the CU of work-group i, and if both have pages either takes longer.  Us, parts of 24 pages and of 32:
+// 7 x 1784 tokens of 64/8/128 16.6 (280 work-groups), 14.0 (224); 15 x 6984 of 2/1/128 18.6 (285), 15.9 (210).  Where both stay within
+// 256 the shorter parts win: 2 x 767 of 16/4/128 9.1, 10.1; 4 x 2048 of 32/8/128 11.5, 11.9.
 static double lay_out_small(AttnGroup &grp, int size) {
     const int grain = 8;                                  // a page pair for every wave of a work-group
     long grid = 0;
@@ -593,35 +601,45 @@ static double lay_out_small(AttnGroup &grp, int size) {
         d.parts = d.max_pages > part ? (d.max_pages + part - 1) / part : 1;
         grid += (long)d.batch * d.Hkv * d.parts;
     }
-    double walk = 0.0, empty = 0.0;
+    double walk = 0.0, live = 0.0, full = 0.0;            // us of the longest part; work-groups with pages; parts' worth of pages
     int most = 1;
+    const bool long_grid = grid > kSmallWorkGroups;
+    grid = 0;
     for (int i = 0; i < grp.n; ++i) {
         AttnDesc &d = grp.m[i];
         // Where the kv heads come fastest, the CUs of an XCD are dealt (row, part) in turn, and with an even number of parts
         // all first parts, which every row has, would fall on the same few CUs: 60 rows of 100 tokens and one of 2000 in
-        // four parts 26.5 us, in five 18.8; 32 lognormal rows of 512 33.4 and 24.6 in parts of 48.
-        if (d.parts > 1 && d.parts < kSmallMaxParts && grid > kSmallWorkGroups && d.Hkv % 8 == 0) d.parts |= 1;
+        // four parts 23.8 us, in five 17.5.
+        if (d.parts > 1 && d.parts < kSmallMaxParts && long_grid && d.Hkv % 8 == 0) d.parts |= 1;
         // partials: one per work-group, in a workspace made for two per work item
         const long wgs = (long)d.batch * d.Hkv * d.parts;
         if (wgs > 2L * kDefaultItems) return -1.0;
+        grid += wgs;
         most = d.parts > most ? d.parts : most;
         const double page_kib = d.D * (d.dtype == PKV_BF16 ? 4 : 2) / 64.0;      // K and V of 16 tokens
         const int pages = d.max_pages < d.part_pages ? d.max_pages : d.part_pages;
-        const double us = (double)((pages + grain - 1) / grain) * (0.3 + 0.085 * page_kib);
-        walk = us > walk ? us : walk;
-        empty += (double)wgs * (d.Hkv % 8 == 0 ? 0.003 : 0.002);
+        walk = fmax(walk, (pages + grain - 1) / grain * (0.41 + 0.128 * page_kib));
+        // a row's last part is half full on average
+        live += d.Hkv * fmax(d.batch, fmin((double)d.batch * d.parts, 0.5 * d.batch + (double)g_small_rows[i] / d.part_pages));
+        full += pages > 0 ? (double)d.Hkv * g_small_rows[i] / pages : 0.0;
     }
-    if (most == 1) return walk + (grid > kSmallWorkGroups ? 0.0035 * grid : 0.0);
-    return walk + 1.0 + empty + 0.4 * (most < 8 ? most - 1 : 7) + (most > 8 ? 0.1 * (most - 8) : 0.0);     // joined eight a trip
+    const double us = walk + 0.0051 * live + 0.0023 * (grid - live);
+    if (most == 1) return us;
+    // How likely two full parts meet on a CU.  Where parts come slowest and a multiple of the rows' work-groups is 256, a long row
+    // meets itself (16 rows of 16/2/128, one of 3689 tokens and the others of 23: 10.9 us in 256 work-groups, 13.6 in 320).
+    const AttnDesc &d = grp.m[0];
+    const double density = full / grid, pairs = grid > kSmallCUs ? (grid - kSmallCUs) * density * density : 0.0;
+    const bool same_row = grp.n == 1 && d.Hkv % 8 != 0 && grid > kSmallCUs && kSmallCUs % ((long)d.batch * d.Hkv) == 0;
+    const double shared = 0.33 * walk * (same_row ? 1.0 : 1.0 - exp(-0.125 * pairs));
+    return us + shared + 1.9 + 0.52 * (most < 8 ? most - 1 : 7) + (most > 8 ? 0.175 * (most - 8) : 0.0);     // joined eight a trip
 }
 
 // Lays a small launch out with the best of the part lengths.  False where the ordinary forms are the better ones, which
 // deal pages out evenly whatever the rows: very many rows, or a few long rows among so many short ones that most work-groups would
 // be without pages.  What the ordinary forms take grows with the pages, and with the longest row, whose pieces are joined
-// one after the other; the line is fitted, together with the estimate above, to both forms of 1550 random launches.  Small kernel and
-// ordinary forms, us: 60 rows of 50 tokens and one of 2000 of 32/8/128 15.1, 18.2; 30 of 50 and one of 4000 16.1, 20.0; 100 of 16 and one of
-// 6000 of 8/2/128 15.4, 18.2; 120 of 39 and one of 11 055 of 8/1/128 16.9, 30.7; of 8/8/64 30 of 256 and one of 4096 13.4, 19.9; 300 of 16
-// 13.9, 13.3; 500 of 16 more than 18.6; 63 of 128 and one of 8192 14.6 or 20.6 (the long row first or in the middle), 21.
+// one after the other.  Small kernel and ordinary forms, us, 32/8/128 bf16: 60 rows of 50 tokens and one of 2000 16.3, 17.2; 30 of 50 and
+// one of 4000 16.6, 20.0; 100 of 16 and one of 6000 of 8/2/128 15.5, 18.1; 120 of 39 and one of 11 055 of 8/1/128 16.9, 30.7; of 8/8/64 30 of
+// 256 and one of 4096 13.8, 20.0; 300 of 16 13.9, 13.3; 63 of 128 and one of 8192, by where the long row is, 14.6 to 20.6, 21.1.
 static bool plan_small(AttnGroup &grp) {
     if (!g_small_now) return false;
     int longest = 0, size = 0;
@@ -635,7 +653,7 @@ static bool plan_small(AttnGroup &grp) {
         }
         if (part >= longest) break;                       // longer parts change nothing
     }
-    if (size == 0 || best > 13.2 + 0.16e-3 * g_small_pages + longest / 160.0) return false;
+    if (size == 0 || best > 20.2 + 0.25e-3 * g_small_pages + longest / 136.0) return false;
     lay_out_small(grp, size);
     int begin = 0;
     for (int i = 0; i < grp.n; ++i) {

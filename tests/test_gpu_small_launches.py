@@ -161,3 +161,22 @@ def test_one_long_row_keeps_the_small_kernel(gpu, oracle, hq, hkv, d, dtype, ctx
         assert row_rel_err(out_g, out_o) <= TOL[dtype]
     finally:
         t.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d,dtype,ctx,items", [(64, 8, 128, BF16, [1784] * 7, 224), (2, 1, 128, BF16, [6984] * 15, 210), (32, 8, 128, BF16, [1024] * 4 + [512] * 8, 192),
+                                                      (32, 8, 128, BF16, [2048] * 4, 192), (16, 4, 128, BF16, [767] * 2, 16),
+                                                      (16, 2, 128, BF16, [3689] + [23] * 15, 256)])
+def test_parts_keep_a_cu_to_one_work_group(gpu, oracle, hq, hkv, d, dtype, ctx, items):  # noqa: F811
+    """Parts of 24 pages where that makes no more than 256 work-groups, and longer ones where it would take some more: two
+    work-groups on a CU take longer than the shorter parts save (a sixth of the first two launches)."""
+    t = Twin(gpu, oracle, hq, hkv, d, dtype, ctx, max_blocks=512, pool_bytes=128 << 20)
+    try:
+        q = gen.queries((79, len(ctx)), len(ctx), hq, d)
+        c = np.array(ctx, dtype=np.int32)
+        rc_o, out_o = oracle.decode_attention(t.models[1], q, c)
+        rc_g, out_g = gpu.decode_attention(t.models[0], q, c)
+        assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
+        assert gpu.last_kernel_form() == 2 and gpu.last_launch_items() == items
+        assert row_rel_err(out_g, out_o) <= TOL[dtype]
+    finally:
+        t.close()
