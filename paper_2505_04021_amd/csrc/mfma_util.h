@@ -60,13 +60,6 @@ __device__ __forceinline__ float halves_max(float x) {
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// The upper half of x (lanes 32 to 63) changes places with the lower half of y.
-__device__ __forceinline__ u32x2 halves_swap(float x, float y) {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
-    return mk2(r[0], r[1]);
-}
-
 // How far (in powers of two) a column's maximum may run ahead of the reference point of its
 // exponentials before a softmax step moves that point and rescales the column's sums.  The reference
 // point need not be the true maximum, only near it: results are the same up to rounding (probabilities

@@ -99,3 +99,16 @@ def test_prefill_steps_down_only_where_two_work_groups_share_a_cu():
             insn, _, _ = kernel_body(asm, f"9k_prefillILi{d}ELi{dtype}ELi{seqs}E")
             levels = {t.split()[1] for t in insn if t.startswith("s_setprio")}
             assert levels == ({"0", "1", "2", "3"} if d == 128 else set()), (d, dtype, levels)
+
+
+def test_prefill_sums_leave_their_lanes_in_order():
+    """A lane's sums are four output elements in a row, sixteen bytes a store, and no lane exchanges any with another."""
+    asm = device_assembly("prefill_kernels.hip")
+    for seqs in (127, 447):
+        for d, dtype in ((128, 0), (64, 0), (128, 1), (64, 1)):
+            name = f"9k_prefillILi{d}ELi{dtype}ELi{seqs}E"
+            insn, _, _ = kernel_body(asm, name)
+            stores = [i for i, t in enumerate(insn) if t.startswith("global_store_dwordx4")]
+            assert len(stores) == 2 * d // 8, name                  # a part's sums, and rows
+            for at in (stores[:len(stores) // 2], stores[len(stores) // 2:]):
+                assert not any("permlane" in t for t in insn[at[0]:at[-1]]), name
