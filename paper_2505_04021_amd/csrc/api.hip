@@ -1867,7 +1867,7 @@ int prefill_attention(int model, int batch, const void *q, const int32_t *q_lens
     d.batch = batch;
     d.cols = tile * m->g;
     d.scale_log2 = (float)(1.4426950408889634 / sqrt((double)m->D));
-    int split_groups = 0;
+    int split_groups = 0, longest_walk = 0;                // of the launch being put together; pairs of a work-group
     auto launch = [&](const ChunkPlan &plan) -> int {
         if (split_groups > 0) {
             const size_t need = (size_t)plan.s[plan.n_seqs].unit * m->Hkv * PKV_PREFILL_COLS * (size_t)(m->D + 4);
@@ -1881,8 +1881,8 @@ int prefill_attention(int model, int batch, const void *q, const int32_t *q_lens
             }
             d.ws = m->pf_ws;
         }
-        HIP_TRY(pkv_launch_prefill(d, plan, split_groups, g_stream));
-        split_groups = 0;
+        HIP_TRY(pkv_launch_prefill(d, plan, split_groups, longest_walk, g_stream));
+        split_groups = longest_walk = 0;
         return PKV_OK;
     };
     PlanBuilder plan(batch);
@@ -1898,6 +1898,8 @@ int prefill_attention(int model, int batch, const void *q, const int32_t *q_lens
         const int parts = prefill_parts(*m, s, part_pairs), groups = (q_lens[s] + group - 1) / group;
         plan.add((uint32_t)q_lens[s], (uint32_t)(groups * parts), (uint32_t)parts, (uint32_t)(m->row_len[s] / parts));
         if (parts > 1 && groups > split_groups) split_groups = groups;
+        const int walk = ((m->row_len[s] + 1) / 2 + parts - 1) / parts;
+        if (q_lens[s] > 0 && walk > longest_walk) longest_walk = walk;
         if (q_lens[s] > 0 && parts > g_last_prefill_parts) g_last_prefill_parts = parts;
     }
     return launch(plan.take(batch));

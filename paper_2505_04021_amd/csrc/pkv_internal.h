@@ -198,6 +198,7 @@ hipError_t pkv_launch_attention(const AttnGroup &grp, AttnForm form, hipStream_t
 hipError_t pkv_static_scratch(void **ptr);
 hipError_t pkv_launch_attention_static(const AttnGroup &grp, uint32_t *cnt, size_t n_cnt, hipStream_t s);
 // chunked prefill: a unit is a group of up to PKV_PREFILL_WAVES * (d.cols / d.g) query tokens, or one of the parts
-// of its context; split_groups: most groups of a sequence whose groups come in parts (0: none does)
-hipError_t pkv_launch_prefill(const AttnDesc &d, const ChunkPlan &plan, int split_groups, hipStream_t s);
+// of its context; split_groups: most groups of a sequence whose groups come in parts (0: none does);
+// longest_walk: page pairs that a unit walks at most, as far as the host knows
+hipError_t pkv_launch_prefill(const AttnDesc &d, const ChunkPlan &plan, int split_groups, int longest_walk, hipStream_t s);
 hipError_t pkv_launch_stream_read(const void *src, size_t bytes, size_t granule_bytes, uint32_t *sink, hipStream_t s);

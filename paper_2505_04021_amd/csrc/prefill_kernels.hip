@@ -102,14 +102,13 @@ __device__ __forceinline__ GroupInfo group_info(const AttnDesc &d, const PlanOf<
     return g;
 }
 
-template <int D, int DT, int SEQS>
+// The waves meet once in MEET pairs, and no wave runs further ahead than that.  An e4m3 cache leaves room in LDS for twice the
+// slots that bf16 has (two work-groups a CU, three with 64-wide heads).  Us a pass, met in two and in four pairs: 8 x (2048 + 512)
+// tokens of 32/8/128 179.3, 176.0; 8192 + 256 58.4, 56.5; ragged prompts 76.2, 75.1.  (Short walks: meets_often_in below.)
+template <int D, int DT, int SEQS, int MEET>
 __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, const PlanOf<SEQS> plan) {
     using TL = PfTile<D, DT>;
     constexpr int SLOT = 2 * TL::BYTES;                    // the K (or V) tiles of a pair
-    // The waves meet once in so many pairs, and no wave runs further ahead than that.  An e4m3 cache leaves room in LDS for twice the
-    // slots that bf16 has (two work-groups a CU, three with 64-wide heads).  Us a pass, met in two and in four pairs: 8 x (2048 + 512)
-    // tokens of 32/8/128 179.3, 176.0; 8192 + 256 58.4, 56.5; ragged prompts 76.2, 75.1.
-    constexpr int MEET = DT == PKV_BF16 ? 2 : 4;
     constexpr int PF_SLOTS = 2 * MEET;                     // page pairs per ring (K and V have a ring each)
     __shared__ __align__(16) uint8_t ring[2 * PF_SLOTS * SLOT];   // K slots, then V slots
     const PlanLanes<SEQS> lanes(plan);
@@ -605,14 +604,15 @@ __global__ __launch_bounds__(32 * MERGE_COLS) void k_prefill_merge(const AttnDes
 }
 
 template <int SEQS>
-void launch(const AttnDesc &d, const PlanOf<SEQS> &plan, int split_groups, hipStream_t s) {
+void launch(const AttnDesc &d, const PlanOf<SEQS> &plan, int split_groups, bool meets_often, hipStream_t s) {
     const dim3 grid(plan.s[plan.n_seqs].unit * (unsigned)d.Hkv), wg(64 * PF_WAVES);
     if (d.dtype == PKV_BF16) {
-        if (d.D == 128) hipLaunchKernelGGL((k_prefill<128, PKV_BF16, SEQS>), grid, wg, 0, s, d, plan);
-        else hipLaunchKernelGGL((k_prefill<64, PKV_BF16, SEQS>), grid, wg, 0, s, d, plan);
+        if (d.D == 128) hipLaunchKernelGGL((k_prefill<128, PKV_BF16, SEQS, 2>), grid, wg, 0, s, d, plan);
+        else hipLaunchKernelGGL((k_prefill<64, PKV_BF16, SEQS, 2>), grid, wg, 0, s, d, plan);
     } else {
-        if (d.D == 128) hipLaunchKernelGGL((k_prefill<128, PKV_E4M3, SEQS>), grid, wg, 0, s, d, plan);
-        else hipLaunchKernelGGL((k_prefill<64, PKV_E4M3, SEQS>), grid, wg, 0, s, d, plan);
+        if (d.D == 64) hipLaunchKernelGGL((k_prefill<64, PKV_E4M3, SEQS, 4>), grid, wg, 0, s, d, plan);
+        else if (meets_often) hipLaunchKernelGGL((k_prefill<128, PKV_E4M3, SEQS, 2>), grid, wg, 0, s, d, plan);
+        else hipLaunchKernelGGL((k_prefill<128, PKV_E4M3, SEQS, 4>), grid, wg, 0, s, d, plan);
     }
     if (split_groups > 0)
         hipLaunchKernelGGL(k_prefill_merge<SEQS>, dim3((unsigned)(split_groups * d.Hkv * (PKV_PREFILL_COLS / MERGE_COLS)), (unsigned)plan.n_seqs),
@@ -621,9 +621,20 @@ void launch(const AttnDesc &d, const PlanOf<SEQS> &plan, int split_groups, hipSt
 
 }  // namespace
 
-hipError_t pkv_launch_prefill(const AttnDesc &d, const ChunkPlan &plan, int split_groups, hipStream_t s) {
+// Whether the waves of an e4m3 launch with 128-wide heads meet once in two pairs.  A work-group's LDS is given back when its last wave
+// ends, its registers wave by wave: with the rings for four pairs (64 KiB) a third work-group of a CU waits for the LDS, with those for
+// two (32 KiB) it starts beside the last waves.  That counts where more work-groups come than two a CU and walks are short.  Us,
+// met in four and in two pairs: 92 x 5 new tokens of 32/8/128 (736 work-groups of one pair) 11.0, 10.2; 128 x (176 + 5) of 16/8/128 (1024 of
+// six) 22.5, 21.3.  180 launches of short chunks: one to two pairs 1.074 (513 to 768 work-groups), up to eight 1.007 to 1.026; but nine to
+// sixteen 0.97 to 0.99, and within 512 work-groups 0.95 to 1.00 of any length.  64-wide heads, three a CU: 0.99 to 1.01.
+static bool meets_often_in(const AttnDesc &d, const ChunkPlan &plan, int longest_walk) {
+    return longest_walk <= 8 && plan.s[plan.n_seqs].unit * (unsigned)d.Hkv > 512u;
+}
+
+hipError_t pkv_launch_prefill(const AttnDesc &d, const ChunkPlan &plan, int split_groups, int longest_walk, hipStream_t s) {
     if (plan.s[plan.n_seqs].unit == 0) return hipSuccess;
-    if (plan.n_seqs <= PKV_PLAN_FEW) launch(d, few_of(plan), split_groups, s);
-    else launch(d, plan, split_groups, s);
+    const bool meets_often = meets_often_in(d, plan, longest_walk);
+    if (plan.n_seqs <= PKV_PLAN_FEW) launch(d, few_of(plan), split_groups, meets_often, s);
+    else launch(d, plan, split_groups, meets_often, s);
     return hipGetLastError();
 }

@@ -161,3 +161,25 @@ def test_contexts_in_many_parts(gpu, oracle, ctx, parts, d, dtype):  # noqa: F81
             assert row_rel_err(out_g, out_o) <= TOL[dtype]
     finally:
         t.close()
+
+
+@pytest.mark.parametrize("g,hkv,longest", [(4, 8, 256), (4, 8, 257), (7, 8, 120), (16, 5, 255)])
+def test_short_walks_of_many_work_groups(gpu, oracle, g, hkv, longest):  # noqa: F811
+    """e4m3, more than 512 work-groups whose walks are of at most eight pairs, or just of more: such a launch, in which waves meet
+    more often, gives the same bits as launches of half of the sequences, in which they do not, and those of the oracle."""
+    n = 520 // hkv + 4
+    ctx = [max(1, longest - (37 * s) % longest) for s in range(n)]
+    qlen = [min(c, 1 + (3 * s) % 8) for s, c in enumerate(ctx)]
+    t = Twin(gpu, oracle, g * hkv, hkv, 128, E4M3, ctx, max_blocks=17, pool_bytes=128 << 20)
+    try:
+        q = gen.queries((83, g, longest), sum(qlen), g * hkv, 128)
+        rc_o, out_o = oracle.prefill_attention(t.models[1], q, qlen, ctx)
+        rc_g, out_g = gpu.prefill_attention(t.models[0], q, qlen, ctx)
+        assert rc_o == 0 and rc_g == 0 and gpu.device_errors() == 0
+        assert row_rel_err(out_g, out_o) <= TOL[E4M3]
+        at = sum(qlen[:n // 2])
+        for part, rows in ((qlen[:n // 2] + [0] * (n - n // 2), slice(0, at)), ([0] * (n // 2) + qlen[n // 2:], slice(at, None))):
+            rc_g, out_h = gpu.prefill_attention(t.models[0], q[rows], part, ctx)
+            assert rc_g == 0 and np.array_equal(out_h, out_g[rows])
+    finally:
+        t.close()

@@ -112,3 +112,18 @@ def test_prefill_sums_leave_their_lanes_in_order():
             assert len(stores) == 2 * d // 8, name                  # a part's sums, and rows
             for at in (stores[:len(stores) // 2], stores[len(stores) // 2:]):
                 assert not any("permlane" in t for t in insn[at[0]:at[-1]]), name
+
+
+def test_prefill_rings_of_short_walks_leave_room():
+    """The e4m3 kernel whose waves meet once in two pairs holds half the LDS of the other one, so that a third work-group fits on a
+    CU beside two; both keep to the registers of two."""
+    asm = device_assembly("prefill_kernels.hip")
+    for seqs in (127, 447):
+        lds = {}
+        for meet in (2, 4):
+            name = f"9k_prefillILi128ELi1ELi{seqs}ELi{meet}E"
+            found = re.findall(r"\.group_segment_fixed_size:\s+(\d+)(?:(?!\.group_segment_fixed_size)[\s\S])*?\.name:\s+\S*" + name, asm)
+            vg = re.findall(r"\.name:\s+\S*" + name + r"\S*\s*\n(?:.*\n){0,40}?\s+\.vgpr_count:\s+(\d+)", asm)
+            assert len(found) == 1 and len(vg) == 1 and int(vg[0]) <= 256, (name, found, vg)
+            lds[meet] = int(found[0])
+        assert 3 * lds[2] <= 160 * 1024 < 3 * lds[4], lds
