@@ -92,9 +92,7 @@ __device__ __forceinline__ void load_page(PageRegs<D, DT> &r, const AttnDesc &d,
         id = 0;
         live = false;                    // the page is skipped: frame 0 need not even be backed by memory
     }
-    const uint32_t f = fastdiv_div(id, d.slots_div);
-    const uint32_t s = id - f * d.slots_div.d;
-    const uint8_t *blk = d.pool_base + (uint64_t)f * d.frame_bytes + (uint64_t)s * d.block_bytes;
+    const uint8_t *blk = block_ptr(d, id);
     if (DT == PKV_E4M3) {
         // A dead page's id is whatever the table holds past the row's end: possibly a block of a
         // frame that was given back and, in an elastic pool, is no longer backed by memory.
@@ -897,10 +895,10 @@ __global__ __launch_bounds__(64, 2) void k_attention_static(const AttnGroup grp)
 // (plan_small); a context that has outgrown them (a launch replayed from a graph) gets longer parts here.
 //
 // A wave alone on its SIMD issues an instruction every four or five cycles, so once its pages are there it is bound by how many a
-// page pair costs: with the addresses of both pages worked out by scalar instructions and masks in every pair 560, so some
-// 230.  Stream of a row in parts of 32 pages, four pairs a wave, after the first pair 2.7 us, so 1.7; us a launch: 1 x 9735 tokens
-// of 4/1/128 bf16 9.9, 9.2; 3 x 1717 of 2/1/128 e4m3 8.6, 7.7; 7 x 573 of 16/8/64 e4m3 6.5, 5.2.  Eight waves a work-group instead of four
-// take longer everywhere (2 x 767 of 16/4/128 9.2, 9.9).
+// page pair costs: with the addresses of both pages worked out by scalar instructions and masks in every pair some 410 (bf16) and
+// 510 (e4m3, 128-wide heads), so 308 and 328 (cold branches included).  Us a launch, caches cold, with parts as they were and are
+// chosen: 1 x 9735 tokens of 4/1/128 bf16 12.4, 11.8; 3 x 1717 of 2/1/128 e4m3 9.2, 8.1; 7 x 573 of 16/8/64 e4m3 7.3, 6.1; rows in one part
+// 0.85 to 0.95 of the time before.  Eight waves a work-group instead of four take longer everywhere (2 x 767 of 16/4/128 9.2, 9.9).
 constexpr int SMALL_WAVES = 4;
 
 // Weight of a wave's sums with maximum m beside a joint maximum of M.  A wave that has seen nothing but logits of -inf has
@@ -933,15 +931,15 @@ __device__ __forceinline__ void attn_part(const AttnDesc &d, int wg, float *s_ac
     const int32_t *row = d.table + (size_t)seq * d.row_stride;
     bf16x8 qf[TL::NK];
     load_q<D>(qf, d, seq, kvh, lane);
-    // This wave's pairs: pages page0 + STEP k and the one behind it, k = 0, 1, ...  The ids of the first come by themselves, so that a
-    // row of one pair a wave pays for nothing else; those of the next 32 in one read, and lane i works out where page i & 1 of pair
-    // 1 + (i >> 1) is.  All are asked for with the context length and the queries.
+    // This wave's pairs: pages page0 + STEP k and the one behind it, k = 0, 1, ...  The ids of the first come by themselves, those of
+    // the next 32 in one read, for any row; lane i works out where page i & 1 of pair 1 + (i >> 1) is, if there is a second pair.
+    // All are asked for with the context length and the queries.
     constexpr int STEP = 2 * SMALL_WAVES;
     const int ahead = STEP * (lane >> 1) + (lane & 1);
     auto id_of = [&](int page) __attribute__((always_inline)) { return (uint32_t)row[page < d.row_stride ? page : d.row_stride - 1]; };
     int page0 = part * d.part_pages + 2 * w;
     PairIds ids = fetch_ids(d, row, page0);
-    uint32_t id = d.part_pages > STEP ? id_of(page0 + STEP + ahead) : 0u;
+    uint32_t id = id_of(page0 + STEP + ahead);
     const int L = __builtin_amdgcn_readfirstlane(ctx_clamped(d, seq));
     const int n_pages = (L + T - 1) / T;
     int size = d.part_pages;
@@ -970,8 +968,7 @@ __device__ __forceinline__ void attn_part(const AttnDesc &d, int wg, float *s_ac
     auto locate = [&](int page, uint32_t id) __attribute__((always_inline)) {
         const bool in_pool = id < d.max_block_id, live = page < pe;
         bad |= live && !in_pool;
-        const uint32_t f = fastdiv_div(id, d.slots_div);
-        const uint8_t *blk = d.pool_base + (uint64_t)f * d.frame_bytes + (uint64_t)(id - f * d.slots_div.d) * d.block_bytes;
+        const uint8_t *blk = block_ptr(d, id);
         if (DT == PKV_E4M3) {
             const float *hdr = reinterpret_cast<const float *>(live && in_pool ? blk : reinterpret_cast<const uint8_t *>(d.safe));
             page_sk = hdr[kvh];
@@ -994,8 +991,7 @@ __device__ __forceinline__ void attn_part(const AttnDesc &d, int wg, float *s_ac
         const bool in_pool = id < d.max_block_id;
         bad |= live && !in_pool;
         live = live && in_pool;
-        const uint32_t f = fastdiv_div(id, d.slots_div);
-        const uint8_t *blk = d.pool_base + (uint64_t)f * d.frame_bytes + (uint64_t)(id - f * d.slots_div.d) * d.block_bytes;
+        const uint8_t *blk = block_ptr(d, id);
         if (DT == PKV_E4M3) {
             const float *hdr = reinterpret_cast<const float *>(live ? blk : reinterpret_cast<const uint8_t *>(d.safe));
             sk = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(PKV_CONST(float, hdr)[kvh])));

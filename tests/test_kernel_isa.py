@@ -8,6 +8,7 @@ MFMA loops of k_attention there is no full wait on vector memory, no scratch tra
 the kernel keeps two waves per SIMD (at most 256 VGPRs).  The prefill kernel counts its
 requests into LDS by hand: the compiler may add no wait to its steps beside those for the
 block ids and scales of the next 64 page pairs."""
+import functools
 import os
 import re
 import subprocess
@@ -16,6 +17,7 @@ import tempfile
 from paper_2505_04021_amd import build as B
 
 
+@functools.lru_cache(maxsize=None)
 def device_assembly(source="attn_kernels.hip"):
     out = os.path.join(tempfile.mkdtemp(prefix="pkv_isa_"), "attn.s")
     flags = [f for f in B.FLAGS if f not in ("-fPIC", "-shared")]
@@ -70,6 +72,24 @@ def test_streaming_loops_keep_exact_load_counts():
             assert not any(t.startswith("scratch_") for t in seg), f"{name} loop {a}..{b} spills to scratch"
         vg = [int(x) for x in re.findall(r"\.name:\s+\S*" + name + r"\S*\s*\n(?:.*\n){0,40}?\s+\.vgpr_count:\s+(\d+)", asm)]
         assert vg and max(vg) <= max_vgpr, (name, vg)
+
+
+def test_small_launches_keep_exact_load_counts():
+    """The loops of k_attention_small, two page pairs a turn: nothing is read but the pages, no full wait, no scratch traffic; only a
+    turn that looks up the next 32 pairs, and then goes on in the loop, waits for them."""
+    asm = device_assembly()
+    for name in ("17k_attention_smallINS_7AttnOne", "17k_attention_smallI9AttnGroup"):
+        insn, labels, _ = kernel_body(asm, name)
+        loops = innermost_mfma_loops(insn, labels)
+        tight = [l for l in loops if not any(t.startswith("global_load") for t in insn[l[0]:l[1]])]
+        shapes = sorted((sum(t.startswith("v_mfma") for t in insn[a:b]), sum(t.startswith("buffer_load_dwordx4") for t in insn[a:b])) for a, b in tight)
+        assert shapes == [(24, 8), (24, 16), (48, 16), (48, 32)], (name, shapes)      # 64- and 128-wide heads, e4m3 and bf16
+        for a, b in loops:
+            full = [t for t in insn[a:b] if t.startswith("s_waitcnt") and re.search(r"vmcnt\(0\)", t)]
+            assert len(full) <= (0 if (a, b) in tight else 1), (name, a, b, full)
+            assert not any(t.startswith("scratch_") for t in insn[a:b]), f"{name} loop {a}..{b} spills to scratch"
+        vg = [int(x) for x in re.findall(r"\.name:\s+\S*" + name + r"\S*\s*\n(?:.*\n){0,40}?\s+\.vgpr_count:\s+(\d+)", asm)]
+        assert vg and max(vg) <= 256, (name, vg)
 
 
 def test_prefill_steps_wait_only_where_written():
