@@ -10,6 +10,7 @@
 #include <stdlib.h>
 #include <string.h>
 #include <algorithm>
+#include <functional>
 
 #include <condition_variable>
 #include <mutex>
@@ -1612,7 +1613,7 @@ struct PlanBuilder {
     uint32_t row = 0;
     int per_launch;
     uint32_t units[PKV_PLAN_SEQS];
-    uint64_t order[PKV_PLAN_SEQS];               // length, the last sequence's number first among equals
+    uint64_t order[PKV_PLAN_SEQS];               // length above; below, the earlier of equals first
     bool in_order = true;
     explicit PlanBuilder(int batch) {
         const int launches = (batch + PKV_PLAN_SEQS - 1) / PKV_PLAN_SEQS;

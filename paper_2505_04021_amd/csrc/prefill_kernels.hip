@@ -419,12 +419,15 @@ __global__ __launch_bounds__(64 * PF_WAVES, 2) void k_prefill(const AttnDesc d, 
     // on the last level is how long the other one is alone at the end: so each level is half as long as the one before (8, 4, 2 and 1
     // fifteenths of the walk).  With four equal levels the two of a CU ended 32 us apart.  Us a pass without and with equal levels:
     // that pass 361.1, 358.1; 8 x (2048 + 512) of 32/8/128 bf16 223.8, 222.3, e4m3 183.0, 181.2; 8 x (1024 + 512) 136.2, 133.8 and 118.3,
-    // 112.9; with halved ones, by the ratio to one older code: 0.6 % less, 2.0 %, 1.5 % (last levels of 1/24 or 1/8 instead of 1/15:
-    // 0.2 to 1.2 % more again).  Launches of few work-groups lose 1 to 2 %
-    // (2 x (768 + 256) 29.3, 29.9).  64-wide heads have three work-groups a CU, which even out by themselves: they go without
-    // (8 x (1024 + 512) of 32/8/64 bf16 86.5, 95.8, e4m3 80.3, 90.2).  A decode step of another model on a stream beside it takes as
-    // long either way (16 x 2048 beside 8 x (2048 + 512) 218.5, 217.0; 4 x 300 beside 1 x (3968 + 128) 15.9, 15.5).
-    // (the waves meet in every second or fourth step; a walk of less than 4 * MEET pairs may end above level 0)
+    // 112.9.  Without and with halved ones: 8 x (2048 + 512) bf16 218.4, 213.4, e4m3 174.2, 168.3; 8 x (1024 + 512) 131.6, 127.9 and 107.3,
+    // 104.2 (last levels of 1/24 or 1/8 of the walk instead of 1/15: 0.2 to 1.2 % more).  Within 256 work-groups, one a CU, bf16 launches lose
+    // 1 % to the code of the levels, whether they are taken or not (2 x (768 + 256) 27.4 without it, 27.8); fresh prompts of very many
+    // work-groups lose too (4 x 1024 66.0, 69.4, e4m3 56.8, 60.9).  64-wide heads have three work-groups a CU, which even out by
+    // themselves: they go without (8 x (1024 + 512) of 32/8/64 bf16 86.5, 95.8, e4m3 80.3, 90.2).  A decode step of another model on a stream
+    // beside it takes as long either way (16 x 2048 beside 8 x (2048 + 512) 218.5, 217.0; 4 x 300 beside 1 x (3968 + 128) 15.9, 15.5).
+    // (The waves meet in every second or fourth step, for the last time in step np - 2 or before.  Rounded to such a step the last one
+    // never comes in walks of up to 29 and odd numbers up to 43 pairs (bf16), of up to 17 and half of those up to 57 (e4m3): these end a level
+    // or two above 0.  Moved to the last meeting, so that all end on it, launches take as long or up to 1 % longer.)
     constexpr bool LEVELS = D == 128;
     const int first_step = (np / 2 + np / 32 + MEET / 2) & -MEET, second_step = (np - np / 5 + MEET / 2) & -MEET, third_step = (np - np / 15 + MEET / 2) & -MEET;
     if constexpr (LEVELS) __builtin_amdgcn_s_setprio(3);
