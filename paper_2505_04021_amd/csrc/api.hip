@@ -416,7 +416,7 @@ void fill_desc_core(AttnDesc &d, Model &m, int batch, const void *q, const int32
             if (pages > d.max_pages) d.max_pages = pages;
             total += pages;
         }
-        g_small_rows[g_small_models++] = total;
+        if (g_small_models < PKV_MAX_GROUP) g_small_rows[g_small_models++] = total;
     }
 }
 
