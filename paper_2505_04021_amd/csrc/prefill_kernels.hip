@@ -14,7 +14,7 @@
 // products (768 matrix cycles, a third of them the low half of the probabilities) and some 105 other vector
 // instructions (8 more with a maximum per step instead of the sum as the sign that the reference point has to move:
 // 228 -> 225 us a pass with its append, all shapes 0.7 to 1.3 % faster); by the counters of a launch a step takes a
-// wave 2210 cycles, 1000 of them waiting, and the matrix units are busy 59 % of the launch at 1.85 GHz; with all
+// wave 2250 cycles, 1000 of them waiting, and the matrix units are busy 58 % of the launch at 1.85 GHz; with all
 // operands zero the same kernel runs 25 % faster, and a plain 8192^3 matrix product loses as much to random data.  Why
 // this shape: 32x32x16 products read half as many operand registers and LDS bytes per flop as 16x16x32, need one lane
 // exchange instead of two per maximum (and that only when the reference point moves), and fill 32 columns better for
